@@ -1092,7 +1092,7 @@ static hipError_t launch_conv_thin_out(const ConvArgs& a, const ConvWeights& cw,
     return hipGetLastError();
 }
 
-static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scratch, hipStream_t st, const float* wino_u = nullptr) {
+static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scratch, hipStream_t st, const float* wino_u, const float* split_u) {
     const int taps_ = a.d.kt * a.d.kd * a.d.kh * a.d.kw;
     {   // two input channels and a wide output: HBM-bound kernels (matrix cores for 3x3x3 taps, vector ALUs otherwise)
         bool hit = false;
@@ -1103,6 +1103,15 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scrat
         bool hit = false;
         const hipError_t e = launch_conv_thin_out(a, cw, false, wt_scratch, &hit, st);
         if (hit || e != hipSuccess) return e;
+    }
+    if (wino_enabled() && conv_split_applies(a.d, a.K, a.Nn)) {   // 3x3 and 3x3x3: F(2, 3) on split operands
+        SplitConvArgs sa{};
+        sa.in = a.in; sa.out = a.out; sa.bias = a.bias; sa.mask_ref = a.mask_ref; sa.add = a.add;
+        sa.bits_in = a.bits_in; sa.bits_out = a.bits_out; sa.u = split_u;
+        sa.K = a.K; sa.Nn = a.Nn; sa.relu_out = a.relu_out; sa.mask_acc = a.mask_acc; sa.mask_add = a.mask_add;
+        char name[56];
+        snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
+        return launch_conv_split(sa, a.d, a.relu_in, name, st);
     }
     if (wino_enabled() && conv_wino_applies(a.d, a.K, a.Nn)) {   // 3x3 in the plane: Winograd F(2x2, 3x3)
         WinoArgs wa{};
@@ -1861,7 +1870,7 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
     plan.gz_off = off;
     off += align256(Q * 2 * sizeof(float));
     // ReLU masks as sign bits: where both the layer that produces t_l and the data gradient that flows back into
-    // it run on the Winograd kernel, the forward launch leaves one bit per value and the backward launch reads
+    // it run on the split-operand or the Winograd kernel, the forward launch leaves one bit per value and the backward launch reads
     // those (1/32 of the bytes of t_l)
     for (int l = 0; l <= kMaxLayers; ++l) plan.sign_off[l] = 0;
     if (p.dtype == 1)   // the same between two launches of the two-dimensional-tile bfloat16 kernel
@@ -1890,9 +1899,12 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
             db.Q = da.Q = plan.Q;
             db.kt = below.kt; db.kd = below.kd; db.kh = below.kh; db.kw = below.kw;
             da.kt = above.kt; da.kd = above.kd; da.kh = above.kh; da.kw = above.kw;
-            if (!conv_wino_applies(db, below.cin, below.cout) || !conv_wino_applies(da, above.cout, above.cin)) continue;
+            // the launch that writes the words and the one that reads them must be the same kernel (same tile geometry)
+            const bool split = conv_split_applies(db, below.cin, below.cout);
+            if (split != conv_split_applies(da, above.cout, above.cin)) continue;
+            if (split ? below.kd != above.kd : !conv_wino_applies(db, below.cin, below.cout) || !conv_wino_applies(da, above.cout, above.cin)) continue;
             plan.sign_off[l] = off;
-            off += align256(conv_wino_sign_words(db, below.cout) * sizeof(unsigned));
+            off += align256((split ? conv_split_sign_words(db, below.cout) : conv_wino_sign_words(db, below.cout)) * sizeof(unsigned));
         }
     plan.saved_bytes = off;
 
@@ -1958,8 +1970,9 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
             max_img = bb > max_img ? bb : max_img;
         }
     }
-    // behind the per-layer scratch: the transformed weights of all Winograd layers of one pass, made in one launch
-    size_t wino_floats = 0;
+    // behind the per-layer scratch: the transformed weights of all Winograd and of all split-operand layers of one pass, each
+    // made in one launch
+    size_t wino_floats = 0, split_floats = 0;
     if (p.dtype == 0)
         for (int l = 0; l < L; ++l) {
             const gleam_conv& c = p.layers[l];
@@ -1968,9 +1981,13 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
             dd.kt = c.kt; dd.kd = c.kd; dd.kh = c.kh; dd.kw = c.kw;
             if (conv_wino_applies(dd, c.cin, c.cout) || conv_wino_applies(dd, c.cout, c.cin))
                 wino_floats += (conv_wino_weight_floats(c.cin, c.cout) + 63) / 64 * 64;
+            const size_t f = conv_split_applies(dd, c.cin, c.cout) ? conv_split_weight_floats(c.cin, c.cout, c.kd) : 0;
+            const size_t b = conv_split_applies(dd, c.cout, c.cin) ? conv_split_weight_floats(c.cout, c.cin, c.kd) : 0;
+            split_floats += ((f > b ? f : b) + 63) / 64 * 64;
         }
     plan.wino_u_off = align256(max_img * sizeof(float));
-    const size_t img_bytes = plan.wino_u_off + align256(wino_floats * sizeof(float));
+    plan.split_u_off = plan.wino_u_off + align256(wino_floats * sizeof(float));
+    const size_t img_bytes = plan.split_u_off + align256(split_floats * sizeof(float));
     plan.wimg_off_bwd = w;
     w += img_bytes;
     const size_t bwd_ws = w;
@@ -1994,12 +2011,27 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
         float* up = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.wino_u_off);
         for (int l = 0; l < L; ++l) {
             const gleam_conv& c = p.layers[l];
-            if (!conv_wino_applies(pix_dims(g, c), c.cin, c.cout)) continue;
+            if (conv_split_applies(pix_dims(g, c), c.cin, c.cout) || !conv_wino_applies(pix_dims(g, c), c.cin, c.cout)) continue;
             wb.job[wb.n++] = WinoWeightJob{theta + plan.w_off[l], (long long)(9 * c.cin), (long long)c.cin, 1, 0, c.cin, c.cout, up};
             wino_u[l] = up;
             up += (conv_wino_weight_floats(c.cin, c.cout) + 63) / 64 * 64;
         }
         const hipError_t e = wino_weights_batch(wb, st);
+        if (e != hipSuccess) return e;
+    }
+    const float* split_u[kMaxLayers] = {};
+    if (p.dtype == 0 && wino_enabled()) {   // the same for the split-operand layers
+        SplitWeightBatch wb{};
+        float* up = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.split_u_off);
+        for (int l = 0; l < L; ++l) {
+            const gleam_conv& c = p.layers[l];
+            if (!conv_split_applies(pix_dims(g, c), c.cin, c.cout)) continue;
+            wb.job[wb.n++] = SplitWeightJob{theta + plan.w_off[l], (long long)(9 * c.kd * c.cin), (long long)c.cin, 1, 0, c.cin, c.cout, c.kd,
+                                            reinterpret_cast<unsigned short*>(up)};
+            split_u[l] = up;
+            up += (conv_split_weight_floats(c.cin, c.cout, c.kd) + 63) / 64 * 64;
+        }
+        const hipError_t e = split_weights_batch(wb, st);
         if (e != hipSuccess) return e;
     }
     for (int l = 0; l < L; ++l) {
@@ -2012,7 +2044,7 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
         a.bias = c.has_bias ? theta + plan.b_off[l] : nullptr;
         a.add = c.skip_src >= 0 ? reinterpret_cast<const float*>(act_base + plan.act_off[c.skip_src]) : nullptr;
         a.K = c.cin; a.Nn = c.cout;
-        if (wino_u[l] && l + 1 < L && plan.sign_off[l + 1]) a.bits_out = reinterpret_cast<unsigned*>(act_base + plan.sign_off[l + 1]);
+        if ((wino_u[l] || split_u[l]) && l + 1 < L && plan.sign_off[l + 1]) a.bits_out = reinterpret_cast<unsigned*>(act_base + plan.sign_off[l + 1]);
         a.relu_in = (c.relu_in && !plan.post_relu[l]) ? 1 : 0;
         a.relu_out = (c.relu_out || (l + 1 < L && plan.post_relu[l + 1])) ? 1 : 0;
         a.d = pix_dims(g, c);
@@ -2045,7 +2077,7 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
                                      reinterpret_cast<unsigned short*>((unsigned char*)ws + plan.wimg_off_fwd), st);
             }
         } else {
-            e = launch_conv(a, cw, reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd), st, wino_u[l]);
+            e = launch_conv(a, cw, reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd), st, wino_u[l], split_u[l]);
         }
         if (e != hipSuccess) return e;
     }
@@ -2244,12 +2276,28 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
         float* up = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.wino_u_off);
         for (int l = 2; l <= L; ++l) {   // the data gradient of layer l maps cout -> cin channels
             const gleam_conv& c = p.layers[l - 1];
-            if (!conv_wino_applies(pix_dims(g, c), c.cout, c.cin)) continue;
+            if (conv_split_applies(pix_dims(g, c), c.cout, c.cin) || !conv_wino_applies(pix_dims(g, c), c.cout, c.cin)) continue;
             wb.job[wb.n++] = WinoWeightJob{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(9 * c.cin), 1, c.cout, c.cin, up};
             wino_u[l - 1] = up;
             up += (conv_wino_weight_floats(c.cout, c.cin) + 63) / 64 * 64;
         }
         const hipError_t e = wino_weights_batch(wb, st);
+        if (e != hipSuccess) return e;
+    }
+
+    const float* split_u[kMaxLayers] = {};
+    if (p.dtype == 0 && wino_enabled()) {
+        SplitWeightBatch wb{};
+        float* up = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.split_u_off);
+        for (int l = 2; l <= L; ++l) {
+            const gleam_conv& c = p.layers[l - 1];
+            if (!conv_split_applies(pix_dims(g, c), c.cout, c.cin)) continue;
+            wb.job[wb.n++] = SplitWeightJob{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(9 * c.kd * c.cin), 1, c.cout, c.cin, c.kd,
+                                            reinterpret_cast<unsigned short*>(up)};
+            split_u[l - 1] = up;
+            up += (conv_split_weight_floats(c.cout, c.cin, c.kd) + 63) / 64 * 64;
+        }
+        const hipError_t e = split_weights_batch(wb, st);
         if (e != hipSuccess) return e;
     }
 
@@ -2404,7 +2452,7 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
                     e = launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 1, reinterpret_cast<unsigned short*>(scratch), st);
                 }
             } else {
-                e = launch_conv(a, cw, scratch, st);
+                e = launch_conv(a, cw, scratch, st, nullptr, nullptr);   // two output channels: neither kernel takes it
             }
             if (e != hipSuccess) return e;
             break;
@@ -2441,7 +2489,7 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
                 e = launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 1, reinterpret_cast<unsigned short*>(wsb + plan.wimg_off_bwd), st);
             }
         } else {
-            e = launch_conv(a, cw, reinterpret_cast<float*>(wsb + plan.wimg_off_bwd), st, wino_u[l - 1]);
+            e = launch_conv(a, cw, reinterpret_cast<float*>(wsb + plan.wimg_off_bwd), st, wino_u[l - 1], split_u[l - 1]);
         }
         if (e != hipSuccess) return e;
     }

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.h"
 #include "xcd.h"
 
@@ -151,8 +153,38 @@ __device__ __forceinline__ ChunkIter chunk_next(ChunkIter x, int n_kc, int nck, 
     return x;
 }
 
-// Launch arguments of the bf16 MFMA convolution (forward and data gradient): in/out/mask_ref/add are
-// bfloat16 [Q][channels] unless out_f32 (then out and add are float32).  wt: bf16 LDS images.
+// 3x3 and 3x3x3 convolution with operands split into bfloat16 parts, float32 (prox_split.hip).  Same fused epilogue as the
+// direct kernels.
+struct SplitConvArgs {
+    const float* in;        // [slices][H][W][K]
+    float* out;             // [slices][H][W][Nn]
+    const void* u;          // transformed and split weights made by split_weights_batch
+    const float* bias;      // [Nn] or null
+    const float* mask_ref;  // [Q][Nn] or null: ReLU mask source (value > 0 passes)
+    const float* add;       // [Q][Nn] or null
+    const unsigned* bits_in;   // or null: sign words of the mask source written by an earlier launch (replace mask_ref)
+    unsigned* bits_out;        // or null: sign words of this launch's output, conv_split_sign_words() of them
+    int K, Nn, relu_out, mask_acc, mask_add;
+    int H, W, D, bx_n, by_n;   // set by the launcher
+    long long n_blocks;
+};
+bool conv_split_applies(const PixDims& d, int K, int Nn);
+size_t conv_split_weight_floats(int K, int Nn, int kd);
+// 32-bit words of the sign-bit image of a [pixels][Nn] tensor as the kernel's threads write and read it
+size_t conv_split_sign_words(const PixDims& d, int Nn);
+hipError_t launch_conv_split(SplitConvArgs a, const PixDims& d, int relu_in, const char* name, hipStream_t stream);
+// Transformed weights of several layers in one launch (a launch costs more than the transform of one layer).
+struct SplitWeightJob {
+    const float* w;    // element (output n, tap t, input k) at w[n*sn + t*st + k*sk]; flip: taps mirrored
+    long long sn, st, sk;
+    int flip, K, Nn, kd;
+    unsigned short* u;   // conv_split_weight_floats(K, Nn, kd) floats
+};
+struct SplitWeightBatch {
+    int n;
+    SplitWeightJob job[kMaxLayers];
+};
+hipError_t split_weights_batch(const SplitWeightBatch& b, hipStream_t stream);
 // Winograd F(2x2, 3x3) convolution, float32 (prox_wino.hip).  Same fused epilogue as the direct kernels.
 struct WinoArgs {
     const float* in;        // [NI][H][W][K]
@@ -299,6 +331,8 @@ bool wgrad_thin_walk_applies(const PixDims& d, int WC, bool bf);
 hipError_t launch_wgrad_thin_walk(const WgradThinWalkArgs& a, size_t partial_floats, int* used_split, hipStream_t stream);
 hipError_t launch_conv_thin_in_mfma(const ThinInMfmaArgs& a, bool bf, hipStream_t stream);
 
+// Launch arguments of the bf16 MFMA convolution (forward and data gradient): in/out/mask_ref/add are
+// bfloat16 [Q][channels] unless out_f32 (then out and add are float32).  wt: bf16 LDS images.
 struct ConvBf16Args {
     const unsigned short* in;
     void* out;
