@@ -106,7 +106,7 @@ int gleam_theta_count(const gleam_prox_desc* prox, size_t* n_floats);
  * gleam_workspace_bytes must be asked under the policy the calls will run with.  Not synchronised with calls in
  * flight on other threads.  Unknown bits: GLEAM_E_DESC. */
 #define GLEAM_POLICY_NO_WINOGRAD      1u  /* 3x3 and 3x3x3 fp32 layers: direct fp32 MFMA kernels instead of the minimal-filtering
-                                          * ones (split bfloat16 operands up to 64 channels, fp32 MFMA above)          */
+                                          * ones (split bfloat16 operands; fp32 MFMA in MoDL modules and greedy iterations) */
 #define GLEAM_POLICY_NO_BF16_2D       2u  /* 3x3 bf16 layers: flattened-pixel kernel instead of the 2D-tile one        */
 #define GLEAM_POLICY_NO_THIN_MFMA     4u  /* 2-channel first / last layers: vector-ALU kernels instead of matrix-core   */
 #define GLEAM_POLICY_NO_WGRAD_BALANCE 8u  /* 27-tap weight gradient: nine 3-tap jobs instead of the balanced 8-wave split */

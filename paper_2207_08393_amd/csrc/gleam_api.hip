@@ -123,14 +123,14 @@ int check_prox(const gleam_prox_desc* p) {
 // Geometry, prox and buffer sizes of a plain module call, checked together so that callers which run several
 // modules can refuse bad arguments before the first launch.  `saved` may be null when need_saved is false.
 int check_module_buffers(const gleam_geom* geom, const gleam_prox_desc* prox, const void* ws, size_t ws_bytes,
-                         const void* saved, size_t saved_bytes, bool need_saved) {
+                         const void* saved, size_t saved_bytes, bool need_saved, bool split) {
     int rc = check_geom(geom);
     if (rc) return rc;
     rc = check_prox(prox);
     if (rc) return rc;
     if (!ws || (need_saved && !saved)) return GLEAM_E_NULL;
     ProxPlan plan;
-    plan_prox(*geom, *prox, plan);
+    plan_prox(*geom, *prox, split, plan);
     if (!aligned(ws) || ws_bytes < plan.ws_bytes) return GLEAM_E_WORKSPACE;
     if (saved && (!aligned(saved) || saved_bytes < plan.saved_bytes)) return GLEAM_E_WORKSPACE;
     return GLEAM_OK;
@@ -220,7 +220,7 @@ int gleam_workspace_bytes(const gleam_geom* geom, const gleam_prox_desc* prox, s
         rc = check_prox(prox);
         if (rc) return rc;
         ProxPlan plan;
-        plan_prox(*geom, *prox, plan);
+        plan_prox(*geom, *prox, true, plan);
         if (plan.ws_bytes > ws) ws = plan.ws_bytes;
         saved = plan.saved_bytes;
     }
@@ -255,7 +255,7 @@ int gleam_sense_normal_static(const gleam_geom* geom, const gleam_c64* x, const 
     return e == hipSuccess ? GLEAM_OK : GLEAM_E_LAUNCH;
 }
 
-int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, const gleam_c64* x_in,
+static int module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, bool split, const gleam_c64* x_in,
                      const gleam_c64* S, const uint8_t* M, const gleam_c64* y, float alpha, const float* theta,
                      const gleam_c64* x_ref, gleam_c64* x_out, float* loss, void* saved, size_t saved_bytes,
                      void* ws, size_t ws_bytes, void* stream) {
@@ -266,7 +266,7 @@ int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, const 
     if (!x_in || !S || !M || !y || !theta || !x_out || !ws) return GLEAM_E_NULL;
     if (x_ref && (!loss || !saved)) return GLEAM_E_NULL;
     ProxPlan plan;
-    plan_prox(*geom, *prox, plan);
+    plan_prox(*geom, *prox, split, plan);
     if (!aligned(ws) || ws_bytes < plan.ws_bytes) return GLEAM_E_WORKSPACE;
     if (saved && (!aligned(saved) || saved_bytes < plan.saved_bytes)) return GLEAM_E_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
@@ -280,7 +280,14 @@ int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, const 
     return e == hipSuccess ? GLEAM_OK : GLEAM_E_LAUNCH;
 }
 
-int gleam_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, const float* theta, const void* saved,
+int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, const gleam_c64* x_in,
+                     const gleam_c64* S, const uint8_t* M, const gleam_c64* y, float alpha, const float* theta,
+                     const gleam_c64* x_ref, gleam_c64* x_out, float* loss, void* saved, size_t saved_bytes,
+                     void* ws, size_t ws_bytes, void* stream) {
+    return module_fwd(geom, prox, true, x_in, S, M, y, alpha, theta, x_ref, x_out, loss, saved, saved_bytes, ws, ws_bytes, stream);
+}
+
+static int module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, bool split, const float* theta, const void* saved,
                      size_t saved_bytes, float* grad_theta, void* ws, size_t ws_bytes, void* stream) {
     int rc = check_geom(geom);
     if (rc) return rc;
@@ -288,12 +295,17 @@ int gleam_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, const 
     if (rc) return rc;
     if (!theta || !saved || !grad_theta || !ws) return GLEAM_E_NULL;
     ProxPlan plan;
-    plan_prox(*geom, *prox, plan);
+    plan_prox(*geom, *prox, split, plan);
     if (!aligned(ws) || ws_bytes < plan.ws_bytes) return GLEAM_E_WORKSPACE;
     if (!aligned(saved) || saved_bytes < plan.saved_bytes) return GLEAM_E_WORKSPACE;
     hipError_t e = prox_backward(*geom, *prox, plan, theta, (const unsigned char*)saved, grad_theta, nullptr, ws,
                                  (hipStream_t)stream);
     return e == hipSuccess ? GLEAM_OK : GLEAM_E_LAUNCH;
+}
+
+int gleam_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, const float* theta, const void* saved,
+                     size_t saved_bytes, float* grad_theta, void* ws, size_t ws_bytes, void* stream) {
+    return module_bwd(geom, prox, true, theta, saved, saved_bytes, grad_theta, ws, ws_bytes, stream);
 }
 
 static int check_deep(const gleam_prox_desc* prox, int n_iter);
@@ -309,7 +321,7 @@ int gleam_module_bwd_alpha(const gleam_geom* geom, const gleam_prox_desc* prox, 
     if (rc) return rc;
     if (!x_in || !S || !M || !y || !theta || !saved || !grad_theta || !grad_alpha || !ws) return GLEAM_E_NULL;
     ProxPlan plan;
-    plan_prox(*geom, *prox, plan);
+    plan_prox(*geom, *prox, true, plan);
     if (!aligned(ws) || ws_bytes < plan.ws_bytes) return GLEAM_E_WORKSPACE;
     if (!aligned(saved) || saved_bytes < plan.saved_bytes) return GLEAM_E_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
@@ -384,7 +396,7 @@ int gleam_deep_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, i
     rc = gleam_theta_count(prox, &n_theta);
     if (rc) return rc;
     ProxPlan plan;
-    plan_prox(*geom, *prox, plan);
+    plan_prox(*geom, *prox, true, plan);
     const size_t block = saved_need / (size_t)n_iter;
     hipStream_t st = (hipStream_t)stream;
     for (int j = n_iter - 1; j >= 0; --j) {
@@ -492,7 +504,7 @@ int gleam_modl_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, c
     if (!aligned(ws) || ws_bytes < ws_need) return GLEAM_E_WORKSPACE;
     if (saved && (!aligned(saved) || saved_bytes < saved_need)) return GLEAM_E_WORKSPACE;
     ProxPlan plan;
-    plan_prox(*geom, *prox, plan);
+    plan_prox(*geom, *prox, false, plan);
     hipStream_t st = (hipStream_t)stream;
     unsigned char* act_base = saved ? (unsigned char*)saved : (unsigned char*)ws + plan.k_bytes;
     unsigned char* scratch = (unsigned char*)ws + (ws_need - cg_scratch_bytes(*geom));
@@ -526,7 +538,7 @@ int gleam_modl_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, c
     if (!aligned(ws) || ws_bytes < ws_need) return GLEAM_E_WORKSPACE;
     if (!aligned(saved) || saved_bytes < saved_need) return GLEAM_E_WORKSPACE;
     ProxPlan plan;
-    plan_prox(*geom, *prox, plan);
+    plan_prox(*geom, *prox, false, plan);
     hipStream_t st = (hipStream_t)stream;
     unsigned char* scratch = (unsigned char*)ws + (ws_need - cg_scratch_bytes(*geom));
     // dL/dz = mu Q^-1 dL/dx_out, solved in place: the solve is linear in its right-hand side, so the factor mu
@@ -557,7 +569,7 @@ int gleam_greedy_iteration(const gleam_geom* geom, const gleam_prox_desc* prox, 
     if (x_out == x0 || x_tmp == x0 || x_out == x_tmp) return GLEAM_E_DIMS;
     // everything any of the per-module calls below would refuse is refused here, before the first launch
     if (!S || !M || !y) return GLEAM_E_NULL;
-    int rc = check_module_buffers(geom, prox, ws, ws_bytes, saved, saved_bytes, true);
+    int rc = check_module_buffers(geom, prox, ws, ws_bytes, saved, saved_bytes, true, false);
     if (rc) return rc;
     if (!adam_args_ok(hyper, t)) return GLEAM_E_DESC;
     size_t n_theta = 0;
@@ -568,10 +580,10 @@ int gleam_greedy_iteration(const gleam_geom* geom, const gleam_prox_desc* prox, 
         // alternate the two image buffers so that the last module writes x_out
         gleam_c64* xo = ((n_modules - 1 - i) % 2 == 0) ? x_out : x_tmp;
         float* th = theta + (size_t)i * n_theta;
-        rc = gleam_module_fwd(geom, prox, x_in, S, M, y, alpha, th, x_ref, xo, losses + i, saved, saved_bytes, ws, ws_bytes,
+        rc = module_fwd(geom, prox, false, x_in, S, M, y, alpha, th, x_ref, xo, losses + i, saved, saved_bytes, ws, ws_bytes,
                               stream);
         if (rc) return rc;
-        rc = gleam_module_bwd(geom, prox, th, saved, saved_bytes, grad, ws, ws_bytes, stream);
+        rc = module_bwd(geom, prox, false, th, saved, saved_bytes, grad, ws, ws_bytes, stream);
         if (rc) return rc;
         rc = gleam_adam_step(hyper, t, n_theta, th, grad, adam_m + (size_t)i * n_theta, adam_v + (size_t)i * n_theta, stream);
         if (rc) return rc;
@@ -586,7 +598,7 @@ int gleam_unrolled_infer(const gleam_geom* geom, const gleam_prox_desc* prox, in
     if (n_modules < 1) return GLEAM_E_DIMS;
     if (!x0 || !theta || !x_out || !x_tmp || !S || !M || !y) return GLEAM_E_NULL;
     if (x_out == x0 || x_tmp == x0 || x_out == x_tmp) return GLEAM_E_DIMS;
-    int rc = check_module_buffers(geom, prox, ws, ws_bytes, nullptr, 0, false);   // before the first launch
+    int rc = check_module_buffers(geom, prox, ws, ws_bytes, nullptr, 0, false, true);   // before the first launch
     if (rc) return rc;
     size_t n_theta = 0;
     rc = gleam_theta_count(prox, &n_theta);

@@ -49,6 +49,14 @@ hipError_t kspace_to_hybrid(const gleam_geom& g, float2* y, hipStream_t st);
 //           [G_1 .. G_{L-1} | split-K partials | loss partials] for backward
 struct ProxPlan {
     int L;
+    // Whether 3x3 and 3x3x3 float32 layers run on split bfloat16 operands (conv_split_applies, wgrad_split_applies).  The MoDL
+    // module and the greedy iteration keep the float32 matrix cores.  Not for speed (100 -> 100 channels at 4 x 320 x 256: 771 us
+    // forward and 1370 us weight gradient there, 280 and 340 us here) and not for accuracy (the split kernels' error against
+    // 64 bits is the smaller one): both magnify any other order of rounding.  The first Adam step moves a parameter by
+    // lr * sign(g), so one whose gradient is near zero moves by 2 lr; the gradient of a MoDL module with the complex-l1 loss
+    // takes d / |d| of residuals that the solve drives to zero, and varies by 1e-6 .. 5e-4 between equally exact results.
+    // Both stay on the arithmetic their results have been compared with.
+    bool split;
     long long Q;                      // pixels B*T*D*H*W
     size_t act_off[kMaxLayers + 1];   // t_l inside saved, l < L
     size_t gz_off;
@@ -77,7 +85,7 @@ size_t wgrad_lds_bytes(const gleam_conv& c);
 // Whether prox dtype 1 (bfloat16 operands) has kernels for this network.
 bool prox_bf16_supported(const gleam_prox_desc& p);
 
-void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan);
+void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, bool split, ProxPlan& plan);
 
 // z = f_theta(u) with u = t_0 already stored at act_base + act_off[0]; writes t_1..t_{L-1} next to it
 // and z to x_out.  With x_ref: loss (device scalar) and g_z are produced as well.

@@ -1104,7 +1104,7 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scrat
         const hipError_t e = launch_conv_thin_out(a, cw, false, wt_scratch, &hit, st);
         if (hit || e != hipSuccess) return e;
     }
-    if (wino_enabled() && conv_split_applies(a.d, a.K, a.Nn)) {   // 3x3 and 3x3x3: F(2, 3) on split operands
+    if (split_u) {   // 3x3 and 3x3x3: F(2, 3) on split operands
         SplitConvArgs sa{};
         sa.in = a.in; sa.out = a.out; sa.bias = a.bias; sa.mask_ref = a.mask_ref; sa.add = a.add;
         sa.bits_in = a.bits_in; sa.bits_out = a.bits_out; sa.u = split_u;
@@ -1843,7 +1843,8 @@ bool prox_bf16_supported(const gleam_prox_desc& p) {
     return true;
 }
 
-void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
+static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, ProxPlan& plan) {
+    plan.split = split;
     for (int t = 0; t <= kMaxLayers; ++t) plan.post_relu[t] = false;
     for (int t = 1; t < p.n_layers; ++t) {
         bool ok = p.layers[t].relu_in != 0 && p.layers[t - 1].skip_src < 0;
@@ -1900,11 +1901,11 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
             db.kt = below.kt; db.kd = below.kd; db.kh = below.kh; db.kw = below.kw;
             da.kt = above.kt; da.kd = above.kd; da.kh = above.kh; da.kw = above.kw;
             // the launch that writes the words and the one that reads them must be the same kernel (same tile geometry)
-            const bool split = conv_split_applies(db, below.cin, below.cout);
-            if (split != conv_split_applies(da, above.cout, above.cin)) continue;
-            if (split ? below.kd != above.kd : !conv_wino_applies(db, below.cin, below.cout) || !conv_wino_applies(da, above.cout, above.cin)) continue;
+            const bool on_split = split && conv_split_applies(db, below.cin, below.cout);
+            if (on_split != (split && conv_split_applies(da, above.cout, above.cin))) continue;
+            if (on_split ? below.kd != above.kd : !conv_wino_applies(db, below.cin, below.cout) || !conv_wino_applies(da, above.cout, above.cin)) continue;
             plan.sign_off[l] = off;
-            off += align256((split ? conv_split_sign_words(db, below.cout) : conv_wino_sign_words(db, below.cout)) * sizeof(unsigned));
+            off += align256((on_split ? conv_split_sign_words(db, below.cout) : conv_wino_sign_words(db, below.cout)) * sizeof(unsigned));
         }
     plan.saved_bytes = off;
 
@@ -1928,6 +1929,11 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
         dd.kt = c.kt; dd.kd = c.kd; dd.kh = c.kh; dd.kw = c.kw;
         if (p.dtype == 0 && wgrad_wino_applies(dd, c.cin, c.cout)) {
             const size_t need = align256(wgrad_wino_partial_floats(c.cin, c.cout, plan.n_split) * sizeof(float));
+            if (need > plan.partial_bytes) plan.partial_bytes = need;
+        }
+        if (p.dtype == 0 && split && wgrad_split_applies(dd, c.cin, c.cout)) {
+            dd.Q = plan.Q;
+            const size_t need = align256(wgrad_split_partial_floats(dd, c.cin, c.cout) * sizeof(float));
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }
         if (p.dtype == 0 && wgrad_time_applies(dd, c.cin, c.cout)) {
@@ -1981,8 +1987,8 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
             dd.kt = c.kt; dd.kd = c.kd; dd.kh = c.kh; dd.kw = c.kw;
             if (conv_wino_applies(dd, c.cin, c.cout) || conv_wino_applies(dd, c.cout, c.cin))
                 wino_floats += (conv_wino_weight_floats(c.cin, c.cout) + 63) / 64 * 64;
-            const size_t f = conv_split_applies(dd, c.cin, c.cout) ? conv_split_weight_floats(c.cin, c.cout, c.kd) : 0;
-            const size_t b = conv_split_applies(dd, c.cout, c.cin) ? conv_split_weight_floats(c.cout, c.cin, c.kd) : 0;
+            const size_t f = split && conv_split_applies(dd, c.cin, c.cout) ? conv_split_weight_floats(c.cin, c.cout, c.kd) : 0;
+            const size_t b = split && conv_split_applies(dd, c.cout, c.cin) ? conv_split_weight_floats(c.cout, c.cin, c.kd) : 0;
             split_floats += ((f > b ? f : b) + 63) / 64 * 64;
         }
     plan.wino_u_off = align256(max_img * sizeof(float));
@@ -2001,6 +2007,15 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
     plan.ws_bytes = fwd_ws > bwd_ws ? fwd_ws : bwd_ws;
 }
 
+void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, bool split, ProxPlan& plan) {
+    ProxPlan other;
+    plan_one(g, p, !split, other);
+    plan_one(g, p, split, plan);
+    // one pair of buffer sizes for every entry point
+    if (other.ws_bytes > plan.ws_bytes) plan.ws_bytes = other.ws_bytes;
+    if (other.saved_bytes > plan.saved_bytes) plan.saved_bytes = other.saved_bytes;
+}
+
 hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const ProxPlan& plan, const float* theta,
                         unsigned char* act_base, const float2* x_ref, float2* x_out, float* loss, void* ws,
                         hipStream_t st) {
@@ -2011,7 +2026,7 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
         float* up = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.wino_u_off);
         for (int l = 0; l < L; ++l) {
             const gleam_conv& c = p.layers[l];
-            if (conv_split_applies(pix_dims(g, c), c.cin, c.cout) || !conv_wino_applies(pix_dims(g, c), c.cin, c.cout)) continue;
+            if ((plan.split && conv_split_applies(pix_dims(g, c), c.cin, c.cout)) || !conv_wino_applies(pix_dims(g, c), c.cin, c.cout)) continue;
             wb.job[wb.n++] = WinoWeightJob{theta + plan.w_off[l], (long long)(9 * c.cin), (long long)c.cin, 1, 0, c.cin, c.cout, up};
             wino_u[l] = up;
             up += (conv_wino_weight_floats(c.cin, c.cout) + 63) / 64 * 64;
@@ -2020,7 +2035,7 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
         if (e != hipSuccess) return e;
     }
     const float* split_u[kMaxLayers] = {};
-    if (p.dtype == 0 && wino_enabled()) {   // the same for the split-operand layers
+    if (p.dtype == 0 && plan.split && wino_enabled()) {   // the same for the split-operand layers
         SplitWeightBatch wb{};
         float* up = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.split_u_off);
         for (int l = 0; l < L; ++l) {
@@ -2276,7 +2291,7 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
         float* up = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.wino_u_off);
         for (int l = 2; l <= L; ++l) {   // the data gradient of layer l maps cout -> cin channels
             const gleam_conv& c = p.layers[l - 1];
-            if (conv_split_applies(pix_dims(g, c), c.cout, c.cin) || !conv_wino_applies(pix_dims(g, c), c.cout, c.cin)) continue;
+            if ((plan.split && conv_split_applies(pix_dims(g, c), c.cout, c.cin)) || !conv_wino_applies(pix_dims(g, c), c.cout, c.cin)) continue;
             wb.job[wb.n++] = WinoWeightJob{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(9 * c.cin), 1, c.cout, c.cin, up};
             wino_u[l - 1] = up;
             up += (conv_wino_weight_floats(c.cout, c.cin) + 63) / 64 * 64;
@@ -2286,7 +2301,7 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
     }
 
     const float* split_u[kMaxLayers] = {};
-    if (p.dtype == 0 && wino_enabled()) {
+    if (p.dtype == 0 && plan.split && wino_enabled()) {
         SplitWeightBatch wb{};
         float* up = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.split_u_off);
         for (int l = 2; l <= L; ++l) {
@@ -2344,6 +2359,17 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
                 }
                 bias_done = c.has_bias;
             }
+        } else if (plan.split && wino_enabled() && wgrad_split_applies(d, c.cin, c.cout)) {   // 3x3 and 3x3x3: F(2, 3) on split operands
+            SplitWgradArgs sw{};
+            sw.g = wa.g; sw.a = wa.a; sw.partial = partial; sw.bias_partial = c.has_bias ? bpart : nullptr;
+            sw.Co = c.cout; sw.Ci = c.cin;
+            char name[56];
+            snprintf(name, sizeof(name), "conv_wgrad_%dto%d_t%d", c.cin, c.cout, (int)taps);
+            const double direct = 2.0 * (double)d.Q * c.cin * c.cout * taps;
+            KernelScope ks(name, direct, 4.0 * (double)d.Q * (c.cin + c.cout), st, direct * 4.0);
+            e = launch_wgrad_split(sw, d, wa.relu_in, st);
+            used_split = wgrad_split_splits(d, c.cin, c.cout);
+            bias_done = c.has_bias;
         } else if (wino_enabled() && wgrad_wino_applies(d, c.cin, c.cout)) {
             // Winograd F(2x2, 3x3): partial sums of the 16 transformed products, fixed-order reduction, back-transform
             WinoWgradArgs ww{};

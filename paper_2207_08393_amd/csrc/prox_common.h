@@ -331,6 +331,21 @@ bool wgrad_thin_walk_applies(const PixDims& d, int WC, bool bf);
 hipError_t launch_wgrad_thin_walk(const WgradThinWalkArgs& a, size_t partial_floats, int* used_split, hipStream_t stream);
 hipError_t launch_conv_thin_in_mfma(const ThinInMfmaArgs& a, bool bf, hipStream_t stream);
 
+// Weight gradient of a 3x3 or 3x3x3 layer with split operands, float32 (prox_splitw.hip): partial sums
+// [gridDim.x][Co][taps][Ci] for reduce_partials_kernel.
+struct SplitWgradArgs {
+    const float* g;         // [slices][H][W][Co]  gradient at the conv output (already ReLU-masked)
+    const float* a;         // [slices][H][W][Ci]  conv input before its optional ReLU
+    float* partial;
+    float* bias_partial;    // [gridDim.x][Co] or null
+    int Co, Ci;
+    int H, W, D, bx_n;      // set by the launcher
+    long long n_rows;
+};
+bool wgrad_split_applies(const PixDims& d, int Ci, int Co);
+int wgrad_split_splits(const PixDims& d, int Ci, int Co);   // workgroups along x = partial sums written
+size_t wgrad_split_partial_floats(const PixDims& d, int Ci, int Co);
+hipError_t launch_wgrad_split(SplitWgradArgs a, const PixDims& d, int relu_in, hipStream_t stream);
 // Launch arguments of the bf16 MFMA convolution (forward and data gradient): in/out/mask_ref/add are
 // bfloat16 [Q][channels] unless out_f32 (then out and add are float32).  wt: bf16 LDS images.
 struct ConvBf16Args {

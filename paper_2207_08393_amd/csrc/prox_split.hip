@@ -425,11 +425,7 @@ __global__ __launch_bounds__(256) void split_weights_kernel(SplitWeightBatch b) 
 }
 
 bool conv_split_applies(const PixDims& d, int K, int Nn) {
-    // Layers wider than 64 channels stay on the float32 matrix cores.  Not for speed (100 -> 100 channels at 4 x 320 x 256
-    // measured 771 us there and 262 us here): the first Adam step of a training run moves a parameter by lr * sign(g), so
-    // another order of rounding moves single parameters with gradients near zero by 2 lr, and in the wide layers, whose
-    // weights are small, that is more than the stated tolerance of a training iteration allows.
-    return d.kt == 1 && (d.kd == 1 || d.kd == 3) && d.kh == 3 && d.kw == 3 && K % 4 == 0 && Nn % 4 == 0 && K <= 64 && Nn <= 64 &&
+    return d.kt == 1 && (d.kd == 1 || d.kd == 3) && d.kh == 3 && d.kw == 3 && K % 4 == 0 && Nn % 4 == 0 &&
            4.0 * d.H * d.W * (K > Nn ? K : Nn) < 2.0e9;   // byte offsets inside a slice stay below the out-of-image marker
 }
 

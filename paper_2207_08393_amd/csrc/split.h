@@ -36,6 +36,13 @@ __device__ __forceinline__ Split split8(const float* v) {
     return s.done();
 }
 
+// Keeps the operand's instructions where they are written: without it the compiler sinks them to their first use, behind the
+// next barrier.
+__device__ __forceinline__ void pin(Split& s) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(s.p[k]));
+}
+
 // The six partial products of a product of split numbers that count, small ones first.
 constexpr int kProducts = 6;
 __device__ constexpr int kPartA[kProducts] = {2, 1, 0, 1, 0, 0}, kPartB[kProducts] = {0, 1, 2, 0, 1, 0};

@@ -16,8 +16,8 @@ def cases():
     yield "odd_rows_batched", synth.Geom(1, 1, 2, 1, 3, 9, 64), synth.resblock_prox(16, 1)
     yield "ragged_channels", synth.Geom(2, 1, 2, 1, 1, 12, 20), synth.chain_prox([2, 36, 12, 60, 2], [K2] * 4)
     yield "ragged_chunk_many_blocks", synth.Geom(2, 2, 2, 3, 1, 32, 96), synth.resblock_prox(20, 2)
-    yield "widest", synth.Geom(2, 1, 2, 1, 1, 20, 46), synth.chain_prox([2, 64, 4, 64, 2], [K2] * 4)
-    yield "just_past_the_widest", synth.Geom(2, 1, 2, 1, 1, 10, 20), synth.chain_prox([2, 64, 68, 64, 2], [K2] * 4)
+    yield "narrow_between_wide", synth.Geom(2, 1, 2, 1, 1, 20, 46), synth.chain_prox([2, 64, 4, 64, 2], [K2] * 4)
+    yield "wide_and_ragged", synth.Geom(2, 1, 2, 1, 1, 10, 46), synth.chain_prox([2, 100, 128, 68, 2], [K2] * 4)
     yield "one_slice", synth.Geom(2, 1, 2, 1, 1, 10, 46), synth.chain_prox([2, 32, 32, 2], [K3] * 3)
     yield "slices_ragged_channels", synth.Geom(3, 2, 2, 1, 4, 10, 46), synth.chain_prox([2, 20, 36, 2], [K3] * 3)
     yield "plane_then_volume", synth.Geom(3, 1, 2, 1, 6, 12, 20), synth.chain_prox([2, 32, 32, 32, 2], [K2, K3, K2, K3])
