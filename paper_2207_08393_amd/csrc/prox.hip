@@ -1297,8 +1297,7 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
 
     // Per-thread staging descriptors: the float4 slots this thread moves are the same for every chunk.
     int g_lds[PG], g_dq[PG], g_c[PG];
-    int a_lds[PA], a_dq[PA], a_c[PA], a_px[PA];
-    unsigned a_rt[PA];
+    int a_lds[PA], a_c[PA], a_pr[PA];   // a_pr: row tap (31: none) << 8 | pixel offset + 128
 #pragma unroll
     for (int i = 0; i < PG; ++i) {
         const int v = tid + i * NT;
@@ -1313,10 +1312,8 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         const int rt = v / (n_pa * Ci4), r = v % (n_pa * Ci4);
         const int p = r / Ci4, c4 = r % Ci4;
         a_lds[i] = v < n_a4 ? (rt * n_pa + p) * RSa + 4 * c4 : -1;
-        a_dq[i] = v < n_a4 ? (int)rowtap_offset(rt, d) - d.kw / 2 + p : 0;
-        a_c[i] = a_dq[i] * a.Ci + 4 * c4;   // element offset from the chunk's first pixel (may be negative)
-        a_px[i] = p - d.kw / 2;
-        a_rt[i] = v < n_a4 ? 1u << rt : 0u;
+        a_c[i] = (v < n_a4 ? (int)rowtap_offset(rt, d) - d.kw / 2 + p : 0) * a.Ci + 4 * c4;   // element offset from the chunk's first pixel (may be negative)
+        a_pr[i] = (v < n_a4 ? rt : 31) << 8 | (p - d.kw / 2 + 128);   // (extents are odd: at most 27 row taps)
     }
     float4 rg[PG], ra[PA], bsum[PG];
 #pragma unroll
@@ -1364,7 +1361,7 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         }
 #pragma unroll
         for (int i = 0; i < PA; ++i) {
-            const bool ok = (rows_ok & a_rt[i]) != 0u && (unsigned)(w0 + a_px[i]) < (unsigned)d.W;
+            const bool ok = ((rows_ok >> (a_pr[i] >> 8)) & 1u) != 0u && (unsigned)(w0 + (a_pr[i] & 255) - 128) < (unsigned)d.W;
             ra[i] = *reinterpret_cast<const float4*>(ok ? abase + a_c[i] : a.a);
             a_okb |= (ok ? 1u : 0u) << i;
         }
@@ -2224,6 +2221,12 @@ static hipError_t launch_wgrad(const WgradArgs& a, float* bias_partial, bool* bi
                 hit_none = false;
             } else if (jobs1 >= 7 && jobs1 <= 12 && pg12 <= 1 && pa12 <= 3) {
                 launch_wgrad_pipe_t<1, 1, 3, 12>(pa, g12, lds, st);
+                hit_none = false;
+            } else if (taps == 9 && blocks > 4 && (blocks + 7) / 8 * 8 <= (blocks + 3) / 4 * 4 && pg8b <= 2 && pa8b <= 5) {
+                // more than 64 channels on a side: eight waves of nine taps share one staged chunk, two per SIMD (four waves with
+                // twice the staging registers each left a SIMD one wave; 100 -> 100 channels, 4 x 320 x 256: 1370 -> 970 us).  The
+                // order of every sum is the same.
+                launch_wgrad_pipe_t<9, 2, 5, 8>(pa, dim3(n_split, (blocks + 7) / 8), lds, st);
                 hit_none = false;
             } else if (taps == 9 && blocks == 4) {   // wider layers: eight waves, 5 + 4 taps per wave pair
                 const int pg8 = (kWgTM * (a.Co / 4) + 511) / 512, pa8 = (rowtaps * n_pa * (a.Ci / 4) + 511) / 512;
