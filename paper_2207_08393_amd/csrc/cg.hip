@@ -1,7 +1,7 @@
 // Conjugate-gradient vector kernels of the MoDL module (MoDL section, Eq. 6-8): the solve of
 // (A^H A + mu I) x = b by a fixed number of CG steps from zero, one system per batch sample.  The operator
-// itself is the fused SENSE sweep (sense_dc with xs = mu, gs = 1, y = 0); the kernels here are the three
-// HBM-bound vector updates between two applications.  Every scalar of the recurrence stays on the device:
+// itself is the fused SENSE sweep (xs = mu, gs = 1, y = 0), which also takes over the inner product and the update of the search
+// direction where it can (sense_cg); the kernels here are the vector updates between two applications.  Every scalar of the recurrence stays on the device:
 // a workgroup writes its partial inner product, and each consumer sums the partials of its sample in a fixed
 // order, so a solve is a plain sequence of launches with no host synchronisation and a reproducible result.
 #include "internal.h"
@@ -76,11 +76,12 @@ __global__ __launch_bounds__(kCgThreads) void cg_dot_kernel(const float2* __rest
 __global__ __launch_bounds__(kCgThreads) void cg_update_xr_kernel(float2* __restrict__ x, float2* __restrict__ r,
                                                                   const float2* __restrict__ p, const float2* __restrict__ q,
                                                                   long long n, const double* __restrict__ rr_old,
-                                                                  const double* __restrict__ pq, double* __restrict__ rr_new) {
+                                                                  const double* __restrict__ pq, int n_pq,
+                                                                  double* __restrict__ rr_new) {
     __shared__ double red[kCgThreads];
     const int nb = gridDim.x;
     const double num = sum_partials(rr_old + (size_t)blockIdx.y * nb, nb, red);
-    const double den = sum_partials(pq + (size_t)blockIdx.y * nb, nb, red);
+    const double den = sum_partials(pq + (size_t)blockIdx.y * n_pq, n_pq, red);
     const float a = den > 0.0 ? (float)(num / den) : 0.f;
     const long long base = (long long)blockIdx.y * n;
     double s = 0.0;
@@ -159,21 +160,33 @@ hipError_t cg_solve(const gleam_geom& g, const float2* S, const unsigned char* M
         KernelScope ks("cg_init", 0.0, (v ? 5.0 : 4.0) * vec_bytes, st);
         hipLaunchKernelGGL(cg_init_kernel, grid, block, 0, st, u, v, c1, c2, n, x, r, p, rr[0]);
     }
+    // Where the tiles of the operator's row sweeps allow it, the inner product rides on the last sweep and the update of the
+    // search direction on the first sweep of the next application: four launches per step instead of six, and p and q are not read
+    // again.  At 2 x 320 x 256 with 8 coils a step is bound by its launches (the module 1717 -> 1602 us); the products are summed in
+    // double as before, in another order.  The partial sums take what is left of the room for three sets.
+    const int n_dot = cg_fused_dot_partials(g, 3 * kCgBlocksMax - 2 * nb), n_pq = n_dot ? n_dot : nb;
+    const bool fuse_p = cg_fused_update(g);
     for (int k = 0; k < n_cg; ++k) {
-        hipError_t e = sense_dc(g, p, S, M, nullptr, mu, 1.f, q, kbuf, st);   // q = (A^H A + mu I) p
-        if (e != hipSuccess) return e;
         double* cur = rr[k & 1];
         double* nxt = rr[(k + 1) & 1];
-        {
+        CgFusion f{};
+        f.dot = n_dot ? pq : nullptr;
+        f.dot_per = n_dot;
+        if (fuse_p && k > 0) {   // p = r + beta p with the sums of the step before: nxt holds the older one
+            f.x_rw = p; f.r = r; f.rr_old = nxt; f.rr_new = cur; f.nb = nb;
+        }
+        const hipError_t e = sense_cg(g, p, S, M, mu, 1.f, q, kbuf, f, st);   // q = (A^H A + mu I) p
+        if (e != hipSuccess) return e;
+        if (!n_dot) {
             KernelScope ks("cg_dot", 0.0, 2.0 * vec_bytes, st);
             hipLaunchKernelGGL(cg_dot_kernel, grid, block, 0, st, (const float2*)p, (const float2*)q, n, pq);
         }
         {
             KernelScope ks("cg_update_xr", 0.0, 6.0 * vec_bytes, st);
             hipLaunchKernelGGL(cg_update_xr_kernel, grid, block, 0, st, x, r, (const float2*)p, (const float2*)q, n,
-                               (const double*)cur, (const double*)pq, nxt);
+                               (const double*)cur, (const double*)pq, n_pq, nxt);
         }
-        if (k + 1 < n_cg) {   // the search direction of a step that is never taken is not needed
+        if (!fuse_p && k + 1 < n_cg) {   // the search direction of a step that is never taken is not needed
             KernelScope ks("cg_update_p", 0.0, 3.0 * vec_bytes, st);
             hipLaunchKernelGGL(cg_update_p_kernel, grid, block, 0, st, (const float2*)r, p, n, (const double*)cur,
                                (const double*)nxt);

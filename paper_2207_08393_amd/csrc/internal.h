@@ -40,6 +40,28 @@ struct KernelScope {
 hipError_t sense_dc(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M,
                     const float2* y, float xs, float gs, float2* out, float2* kbuf, hipStream_t st);
 
+constexpr int kCgBlocksMax = 512;  // workgroups (= partial sums) per batch sample
+
+// What the conjugate-gradient solver has the two row sweeps of an operator application do on the side.  One system per
+// batch sample; every scalar stays on the device.
+struct CgFusion {
+    // first sweep: x <- r + beta x (written back), beta = <r,r>_new / <r,r>_old of the row's sample (0 when the old one is not
+    // positive); r null: x is taken as it is
+    float2* x_rw;
+    const float2* r;
+    const double *rr_old, *rr_new;   // [B][nb] partial sums
+    int nb;
+    // last sweep: dot[b][dot_per] = partial Re <x, out>; null: none
+    double* dot;
+    int dot_per;
+};
+// Partial sums per sample the last sweep would write (0: it cannot, tiles straddle samples or there are more than max_partials),
+// and whether the first sweep can update x (all coils of a row in one tile, so that nothing reads x after it was written).
+int cg_fused_dot_partials(const gleam_geom& g, int max_partials);
+bool cg_fused_update(const gleam_geom& g);
+hipError_t sense_cg(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M, float xs, float gs, float2* out,
+                    float2* kbuf, const CgFusion& f, hipStream_t st);
+
 // y: measured k-space, inverse-transformed in place along the outermost transformed axis (ndim_fft 2 or 3).
 hipError_t kspace_to_hybrid(const gleam_geom& g, float2* y, hipStream_t st);
 
@@ -108,7 +130,6 @@ hipError_t loss_and_grad(const float2* x, const float2* x_ref, float2* g, long l
 
 // n_cg conjugate-gradient steps from zero on (A^H A + mu I) x = c1*u + c2*v (v may be null), one system per
 // batch sample.  x may alias u.  kbuf: coil k-space buffer of sense_dc; scratch: cg_scratch_bytes(g) bytes.
-constexpr int kCgBlocksMax = 512;  // workgroups (= partial sums) per batch sample
 size_t cg_scratch_bytes(const gleam_geom& g);
 hipError_t cg_solve(const gleam_geom& g, const float2* S, const unsigned char* M, float mu, int n_cg, const float2* u,
                     const float2* v, float c1, float c2, float2* x, float2* kbuf, void* scratch, hipStream_t st);

@@ -8,6 +8,8 @@
 //   rows_reduce  : inverse transform along W with conj(S) multiply, coil sum and the DC update fused
 //                  into the store (the per-coil images are never written).
 #include <hip/hip_runtime.h>
+#include <type_traits>
+
 
 #include "fft_core.h"
 #include "internal.h"
@@ -50,6 +52,10 @@ struct RowsArgs {
     int cen, par_h, par_d, ysign_bit;
     long long Hh;
 };
+struct RowsCgArgs : RowsArgs {   // (apart, so that the plain sweeps' argument block stays as short as it was: + 0.4 us a call with it)
+    CgFusion cg;
+};
+template <bool CG> using RowsArgsOf = typename std::conditional<CG, RowsCgArgs, RowsArgs>::type;
 
 // v with its sign flipped when bit is 1 (bit is 0 or 1)
 __device__ __forceinline__ float2 flip_sign(float2 v, unsigned bit) {
@@ -66,13 +72,21 @@ __device__ __forceinline__ unsigned row_parity(const RowsArgs& a, long long dh) 
 // is fetched from memory once and reused from cache for all of its coils (tiles of consecutive k-space rows would
 // come back to the same image row once per coil, megabytes later); coil multiply fused into the load, two complex
 // values (16 bytes) per global access.
-template <int N>
-__global__ __launch_bounds__(rows_threads<N>()) void rows_expand_kernel(RowsArgs a) {
+__device__ __forceinline__ float4 cg_direction(const RowsCgArgs& a, float4 x, long long at, float beta) {   // r + beta x
+    const float4 r = *reinterpret_cast<const float4*>(a.cg.r + at);
+    return make_float4(fmaf(beta, x.x, r.x), fmaf(beta, x.y, r.y), fmaf(beta, x.z, r.z), fmaf(beta, x.w, r.w));
+}
+
+// UPD: the image is first updated from the solver's residual (CgFusion): every coil line forms the new value for itself, the
+// first one writes it back behind the transform, when no line of the tile reads the old one any more (one coil group only).
+template <int N, bool UPD>
+__global__ __launch_bounds__(rows_threads<N>()) void rows_expand_kernel(RowsArgsOf<UPD> a) {
     constexpr int L = rows_lines<N>(), NT = rows_threads<N>(), H2 = N / 2;
     using Lay = Layout<N, L, 1>;
     __shared__ float2 buf[Lay::kElems], tw[N];
     __shared__ long long xoff[L], soff[L], koff[L];   // per image row of the tile: image, coil map (coil 0), k-space (coil 0)
     __shared__ unsigned lpar[L];
+    __shared__ float lbeta[UPD ? L : 1];
     fill_twiddles<N, NT>(tw);
     const int CG = a.C < L ? (int)a.C : L;        // coils transformed together
     const int LR = L / CG;                        // image rows per tile
@@ -98,6 +112,25 @@ __global__ __launch_bounds__(rows_threads<N>()) void rows_expand_kernel(RowsArgs
             koff[threadIdx.x] = ko;
             lpar[threadIdx.x] = par;
         }
+        if constexpr (UPD) {
+            if (threadIdx.x < 64) {   // one wave adds up the partial sums of every sample that has a row in the tile
+                const long long per = a.T * a.DH, r0 = tile * LR, r1 = (r0 + LR < a.n_rows ? r0 + LR : a.n_rows) - 1;
+                for (long long b = r0 / per; b <= r1 / per; ++b) {
+                    double den = 0.0, num = 0.0;
+                    for (int i = threadIdx.x; i < a.cg.nb; i += 64) {
+                        den += a.cg.rr_old[b * a.cg.nb + i];
+                        num += a.cg.rr_new[b * a.cg.nb + i];
+                    }
+                    for (int o = 32; o > 0; o >>= 1) {
+                        den += __shfl_xor(den, o);
+                        num += __shfl_xor(num, o);
+                    }
+                    const float beta = den > 0.0 ? (float)(num / den) : 0.f;
+                    for (int r = threadIdx.x; r < LR; r += 64)
+                        if ((r0 + r) / per == b) lbeta[r] = beta;
+                }
+            }
+        }
         __syncthreads();
         for (int c0 = 0; c0 < a.C; c0 += CG) {
             const int ncg = a.C - c0 < CG ? (int)(a.C - c0) : CG;
@@ -108,7 +141,8 @@ __global__ __launch_bounds__(rows_threads<N>()) void rows_expand_kernel(RowsArgs
                 float2 v0 = make_float2(0.f, 0.f), v1 = v0;
                 if (r < LR && c < ncg && xoff[r] >= 0) {
                     const float4 sv = *reinterpret_cast<const float4*>(a.S + soff[r] + (c0 + c) * sstride + p);
-                    const float4 xv = *reinterpret_cast<const float4*>(a.x + xoff[r] + p);
+                    float4 xv = *reinterpret_cast<const float4*>(a.x + xoff[r] + p);
+                    if constexpr (UPD) xv = cg_direction(a, xv, xoff[r] + p, lbeta[r]);
                     v0 = cmul(make_float2(sv.x, sv.y), make_float2(xv.x, xv.y));
                     v1 = cmul(make_float2(sv.z, sv.w), make_float2(xv.z, xv.w));
                     if (a.cen) {   // D x: p is even, so the pair's signs are the row's parity and its opposite
@@ -128,6 +162,12 @@ __global__ __launch_bounds__(rows_threads<N>()) void rows_expand_kernel(RowsArgs
                     const float2 v0 = buf[Lay::at(line, p)], v1 = buf[Lay::at(line, p + 1)];
                     *reinterpret_cast<float4*>(a.k + koff[r] + (c0 + c) * kstride + p) =
                         make_float4(v0.x * a.scale, v0.y * a.scale, v1.x * a.scale, v1.y * a.scale);
+                    if constexpr (UPD) {
+                        if (c == 0) {
+                            float4* x = reinterpret_cast<float4*>(a.cg.x_rw + xoff[r] + p);
+                            *x = cg_direction(a, *x, xoff[r] + p, lbeta[r]);
+                        }
+                    }
                 }
             }
             if (c0 + CG < a.C) __syncthreads();   // the next coil group overwrites the tile
@@ -150,8 +190,9 @@ static inline int reduce_rows_per_tile(int L, int LRmax, long long C) {
     return lr < LRmax ? lr : LRmax;
 }
 
-template <int N>
-__global__ __launch_bounds__(reduce_threads<N>()) void rows_reduce_kernel(RowsArgs a) {
+// DOT: every tile also writes its part of Re <x, out> (CgFusion), summed in double.
+template <int N, bool DOT>
+__global__ __launch_bounds__(reduce_threads<N>()) void rows_reduce_kernel(RowsArgsOf<DOT> a) {
     constexpr int L = reduce_lines<N>(), NT = reduce_threads<N>(), H2 = N / 2;
     constexpr int PER = kRedAcc;
     static_assert(H2 <= PER * NT, "one image row must fit the accumulators");
@@ -159,6 +200,7 @@ __global__ __launch_bounds__(reduce_threads<N>()) void rows_reduce_kernel(RowsAr
     __shared__ float2 buf[Lay::kElems], tw[N];
     __shared__ long long koff[L], soff[L];        // per image row of the tile, coil 0
     __shared__ unsigned lpar[L];
+    __shared__ double red[DOT ? NT / 64 : 1];
     fill_twiddles<N, NT>(tw);
     const int CG = a.C < L ? (int)a.C : L;        // coils transformed together
     const int LR = (L / CG) < reduce_rows_max<N>() ? (L / CG) : reduce_rows_max<N>();   // image rows per tile
@@ -229,6 +271,7 @@ __global__ __launch_bounds__(reduce_threads<N>()) void rows_reduce_kernel(RowsAr
             __syncthreads();
         }
         const float gsc = a.gs * a.scale;
+        double dot = 0.0;
 #pragma unroll
         for (int m = 0; m < PER; ++m) {
             const int e = threadIdx.x + m * NT;
@@ -244,7 +287,20 @@ __global__ __launch_bounds__(reduce_threads<N>()) void rows_reduce_kernel(RowsAr
                         res.z = fmaf(a.xs, xv.z, res.z); res.w = fmaf(a.xs, xv.w, res.w);
                     }
                     *reinterpret_cast<float4*>(a.out + o) = res;
+                    if constexpr (DOT) {
+                        const float4 xv = *reinterpret_cast<const float4*>(a.x + o);
+                        dot += ((double)xv.x * res.x + (double)xv.y * res.y) + ((double)xv.z * res.z + (double)xv.w * res.w);
+                    }
                 }
+            }
+        }
+        if constexpr (DOT) {   // a tile's rows belong to one sample (cg_fused_dot_partials)
+            for (int o = 32; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dot;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                for (int w = 1; w < NT / 64; ++w) dot += red[w];
+                a.cg.dot[tile] = dot;
             }
         }
     }
@@ -543,7 +599,7 @@ static int grid_for(long long n_tiles) {
     return (int)((g + 7) / 8 * 8);   // multiple of 8 for the XCD-aware split of the column kernels
 }
 
-static hipError_t launch_rows(bool reduce, int N, const RowsArgs& a, hipStream_t st) {
+static hipError_t launch_rows(bool reduce, int N, const RowsCgArgs& a, hipStream_t st) {
     switch (N) {
 #define X(NN)                                                                                          \
     case NN: {                                                                                         \
@@ -551,8 +607,11 @@ static hipError_t launch_rows(bool reduce, int N, const RowsArgs& a, hipStream_t
         const long long per = reduce ? reduce_rows_per_tile(LR_, reduce_rows_max<NN>(), a.C)           \
                                      : reduce_rows_per_tile(L_, L_, a.C);                              \
         const long long tiles = (a.n_rows + per - 1) / per;                                            \
-        if (reduce) hipLaunchKernelGGL(rows_reduce_kernel<NN>, dim3(grid_for(tiles)), dim3(reduce_threads<NN>()), 0, st, a); \
-        else hipLaunchKernelGGL(rows_expand_kernel<NN>, dim3(grid_for(tiles)), dim3(rows_threads<NN>()), 0, st, a);   \
+        const dim3 grid(grid_for(tiles)), block(reduce ? reduce_threads<NN>() : rows_threads<NN>());   \
+        if (reduce && a.cg.dot) hipLaunchKernelGGL((rows_reduce_kernel<NN, true>), grid, block, 0, st, a);             \
+        else if (reduce) hipLaunchKernelGGL((rows_reduce_kernel<NN, false>), grid, block, 0, st, (const RowsArgs&)a);  \
+        else if (a.cg.r) hipLaunchKernelGGL((rows_expand_kernel<NN, true>), grid, block, 0, st, a);                    \
+        else hipLaunchKernelGGL((rows_expand_kernel<NN, false>), grid, block, 0, st, (const RowsArgs&)a);              \
         break;                                                                                         \
     }
         GLEAM_FFT_SIZES(X)
@@ -598,10 +657,11 @@ static hipError_t launch_cols(int mode, int N, const ColsArgs& a, hipStream_t st
     return hipGetLastError();
 }
 
-hipError_t sense_dc(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M,
-                    const float2* y, float xs, float gs, float2* out, float2* kbuf, hipStream_t st) {
+static hipError_t sense_sweeps(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M, const float2* y, float xs,
+                               float gs, float2* out, float2* kbuf, const CgFusion& cg, hipStream_t st) {
     const long long DH = g.D * g.H;
-    RowsArgs ra{};
+    RowsCgArgs ra{};
+    ra.cg = cg;
     ra.x = x; ra.S = S; ra.k = kbuf; ra.out = out;
     ra.C = g.C; ra.T = g.T; ra.DH = DH;
     ra.scale = 1.0f / sqrtf((float)g.W);
@@ -666,6 +726,41 @@ hipError_t sense_dc(const gleam_geom& g, const float2* x, const float2* S, const
     KernelScope ks("sense_rows_reduce", 0.0, E8 + S8 + P8 + (xs != 0.f ? P8 : 0.0), st);
     return launch_rows(true, (int)g.W, ra, st);
 }
+
+hipError_t sense_dc(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M,
+                    const float2* y, float xs, float gs, float2* out, float2* kbuf, hipStream_t st) {
+    return sense_sweeps(g, x, S, M, y, xs, gs, out, kbuf, CgFusion{}, st);
+}
+
+hipError_t sense_cg(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M, float xs, float gs, float2* out,
+                    float2* kbuf, const CgFusion& f, hipStream_t st) {
+    return sense_sweeps(g, x, S, M, nullptr, xs, gs, out, kbuf, f, st);
+}
+
+static int rows_lines_of(long long N) {
+    switch (N) {
+#define X(NN) case NN: return rows_lines<NN>();
+        GLEAM_FFT_SIZES(X)
+#undef X
+        default: return 0;
+    }
+}
+static int reduce_rows_of(long long N, long long C) {
+    switch (N) {
+#define X(NN) case NN: return reduce_rows_per_tile(reduce_lines<NN>(), reduce_rows_max<NN>(), C);
+        GLEAM_FFT_SIZES(X)
+#undef X
+        default: return 1;
+    }
+}
+
+int cg_fused_dot_partials(const gleam_geom& g, int max_partials) {
+    const long long rows = g.T * g.D * g.H, per = reduce_rows_of(g.W, g.C);
+    if (g.ndim_fft == 1 || rows % per != 0 || rows / per > max_partials) return 0;
+    return (int)(rows / per);
+}
+
+bool cg_fused_update(const gleam_geom& g) { return g.ndim_fft > 1 && g.C <= rows_lines_of(g.W); }
 
 // Measured k-space to hybrid space: the inverse transform (centred when the geometry says so) along the outermost
 // transformed axis, in place: H for two transformed axes, D for three.

@@ -570,6 +570,30 @@ def test_modl_module_survives_an_exactly_converged_solve():
 
 
 
+@pytest.mark.parametrize("geom", [synth.Geom(2, 3, 2, 1, 1, 6, 10),        # several samples in one tile of the row sweeps
+                                  synth.Geom(2, 2, 8, 1, 1, 24, 32),       # whole tiles: inner product inside the sweep
+                                  synth.Geom(2, 2, 64, 1, 1, 6, 10),       # one row per tile
+                                  synth.Geom(2, 2, 65, 1, 1, 6, 10),       # more coils than a tile holds: no update inside
+                                  synth.Geom(2, 1, 64, 50, 1, 32, 10),     # more tiles than room for partial sums
+                                  synth.Geom(2, 2, 8, 2, 1, 12, 32), synth.Geom(3, 1, 8, 1, 4, 8, 32),
+                                  synth.Geom(1, 2, 3, 1, 2, 5, 46)])
+def test_modl_solver_inside_the_row_sweeps(geom):
+    """The solver's inner product and direction update inside the operator's sweeps, where the tiles allow it and where they
+    do not: against the oracle."""
+    from paper_2207_08393_amd.runner import ModlRunner
+    prox = synth.chain_prox([2, 8, 2], [K2] * 2)
+    c = synth.make_custom(67, geom, prox, accel=2.0, centre=2, bias_std=0.1)
+    nd, mu = geom.ndim_fft, 0.5
+    aty_o = og.sense_adjoint(c.y.astype(np.complex128), c.S, c.M, nd)
+    for n_cg in (1, 4):
+        print("case modl row sweeps", geom, n_cg, flush=True)
+        r = ModlRunner(c, mu, n_cg)
+        r.step()
+        x, loss, grad, aty = r.results()
+        f = og.modl_module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, aty_o, mu, n_cg, c.theta, c.x_true)
+        g = og.modl_module_bwd(c.geom, c.prox, c.S, c.M, mu, n_cg, c.theta, f)
+        assert rel_l2(x, f["x_out"]) <= TOL and rel_l2(grad, g) <= TOL
+
 
 @pytest.mark.timeout(900)
 def test_modl_module_knee2d_full_size():
