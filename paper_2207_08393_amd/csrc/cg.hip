@@ -12,24 +12,28 @@ constexpr int kCgThreads = 256;
 
 namespace {
 
+// Sum over the workgroup, in thread 0.
 __device__ inline double block_sum(double v, double* red) {
-    red[threadIdx.x] = v;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int o = kCgThreads / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    return red[0];
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kCgThreads / 64; ++w) v += red[w];
+    return v;
 }
 
-// Sum of a sample's nb partials, the same value in every thread: strided per-thread sums in a fixed order, then
-// the block tree.  Ends with a barrier so that red can be used again at once.
-__device__ inline double sum_partials(const double* __restrict__ part, int nb, double* red) {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < nb; i += kCgThreads) s += part[i];
-    const double total = block_sum(s, red);
-    __syncthreads();
-    return total;
+// Sums of two sets of a sample's partials, the same values in every thread: each wave adds up both sets by itself, strided per
+// lane in a fixed order and then across the lanes, so that no barrier stands between the launch and the first update.
+__device__ inline double2 sum_partials(const double* __restrict__ u, int nu, const double* __restrict__ v, int nv) {
+    const int lane = threadIdx.x & 63;
+    double a = 0.0, b = 0.0;
+    for (int i = lane; i < nu; i += 64) a += u[i];
+    for (int i = lane; i < nv; i += 64) b += v[i];
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+    }
+    return make_double2(a, b);
 }
 
 }  // namespace
@@ -39,7 +43,7 @@ __device__ inline double sum_partials(const double* __restrict__ part, int nb, d
 __global__ __launch_bounds__(kCgThreads) void cg_init_kernel(const float2* u, const float2* __restrict__ v, float c1, float c2,
                                                              long long n, float2* x, float2* __restrict__ r,
                                                              float2* __restrict__ p, double* __restrict__ rr) {
-    __shared__ double red[kCgThreads];
+    __shared__ double red[kCgThreads / 64];
     const long long base = (long long)blockIdx.y * n;
     double s = 0.0;
     for (long long i = (long long)blockIdx.x * kCgThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kCgThreads) {
@@ -61,7 +65,7 @@ __global__ __launch_bounds__(kCgThreads) void cg_init_kernel(const float2* u, co
 // pq[b][blk] = partial Re <p, q>
 __global__ __launch_bounds__(kCgThreads) void cg_dot_kernel(const float2* __restrict__ p, const float2* __restrict__ q, long long n,
                                                             double* __restrict__ pq) {
-    __shared__ double red[kCgThreads];
+    __shared__ double red[kCgThreads / 64];
     const long long base = (long long)blockIdx.y * n;
     double s = 0.0;
     for (long long i = (long long)blockIdx.x * kCgThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kCgThreads) {
@@ -78,21 +82,37 @@ __global__ __launch_bounds__(kCgThreads) void cg_update_xr_kernel(float2* __rest
                                                                   long long n, const double* __restrict__ rr_old,
                                                                   const double* __restrict__ pq, int n_pq,
                                                                   double* __restrict__ rr_new) {
-    __shared__ double red[kCgThreads];
+    __shared__ double red[kCgThreads / 64];
     const int nb = gridDim.x;
-    const double num = sum_partials(rr_old + (size_t)blockIdx.y * nb, nb, red);
-    const double den = sum_partials(pq + (size_t)blockIdx.y * n_pq, n_pq, red);
-    const float a = den > 0.0 ? (float)(num / den) : 0.f;
-    const long long base = (long long)blockIdx.y * n;
+    const long long base = (long long)blockIdx.y * n, step = (long long)gridDim.x * kCgThreads;
+    constexpr int U = 4;   // elements in flight per lane; the first ones are fetched while the scalars are summed
+    float2 pv[U], qv[U], xv[U], rv[U];
+    long long i = (long long)blockIdx.x * kCgThreads + threadIdx.x;
+    const auto fetch = [&]() {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * step < n) {
+                const long long at = base + i + u * step;
+                pv[u] = p[at]; qv[u] = q[at]; xv[u] = x[at]; rv[u] = r[at];
+            }
+    };
+    fetch();
+    const double2 nd = sum_partials(rr_old + (size_t)blockIdx.y * nb, nb, pq + (size_t)blockIdx.y * n_pq, n_pq);
+    const float a = nd.y > 0.0 ? (float)(nd.x / nd.y) : 0.f;
     double s = 0.0;
-    for (long long i = (long long)blockIdx.x * kCgThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kCgThreads) {
-        const float2 pv = p[base + i], qv = q[base + i];
-        float2 xv = x[base + i], rv = r[base + i];
-        xv.x += a * pv.x; xv.y += a * pv.y;
-        rv.x -= a * qv.x; rv.y -= a * qv.y;
-        x[base + i] = xv;
-        r[base + i] = rv;
-        s += (double)rv.x * rv.x + (double)rv.y * rv.y;
+    while (i < n) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * step < n) {
+                const long long at = base + i + u * step;
+                xv[u].x += a * pv[u].x; xv[u].y += a * pv[u].y;
+                rv[u].x -= a * qv[u].x; rv[u].y -= a * qv[u].y;
+                x[at] = xv[u];
+                r[at] = rv[u];
+                s += (double)rv[u].x * rv[u].x + (double)rv[u].y * rv[u].y;
+            }
+        i += U * step;
+        fetch();
     }
     s = block_sum(s, red);
     if (threadIdx.x == 0) rr_new[(size_t)blockIdx.y * nb + blockIdx.x] = s;
@@ -103,10 +123,8 @@ __global__ __launch_bounds__(kCgThreads) void cg_update_p_kernel(const float2* _
                                                                  const double* __restrict__ rr_old,
                                                                  const double* __restrict__ rr_new) {
     const int nb = gridDim.x;
-    __shared__ double red[kCgThreads];
-    const double den = sum_partials(rr_old + (size_t)blockIdx.y * nb, nb, red);
-    const double num = sum_partials(rr_new + (size_t)blockIdx.y * nb, nb, red);
-    const float beta = den > 0.0 ? (float)(num / den) : 0.f;
+    const double2 s = sum_partials(rr_old + (size_t)blockIdx.y * nb, nb, rr_new + (size_t)blockIdx.y * nb, nb);
+    const float beta = s.x > 0.0 ? (float)(s.y / s.x) : 0.f;
     const long long base = (long long)blockIdx.y * n;
     for (long long i = (long long)blockIdx.x * kCgThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kCgThreads) {
         const float2 rv = r[base + i];
@@ -162,7 +180,7 @@ hipError_t cg_solve(const gleam_geom& g, const float2* S, const unsigned char* M
     }
     // Where the tiles of the operator's row sweeps allow it, the inner product rides on the last sweep and the update of the
     // search direction on the first sweep of the next application: four launches per step instead of six, and p and q are not read
-    // again.  At 2 x 320 x 256 with 8 coils a step is bound by its launches (the module 1717 -> 1602 us); the products are summed in
+    // again.  At 2 x 320 x 256 with 8 coils a step is bound by its launches (the module 1717 -> 1602 us; 1595 with the scalars summed by each wave for itself, the first elements in flight meanwhile); the products are summed in
     // double as before, in another order.  The partial sums take what is left of the room for three sets.
     const int n_dot = cg_fused_dot_partials(g, 3 * kCgBlocksMax - 2 * nb), n_pq = n_dot ? n_dot : nb;
     const bool fuse_p = cg_fused_update(g);
