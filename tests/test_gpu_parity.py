@@ -696,14 +696,16 @@ def test_fallback_kernels_of_the_two_channel_layers_and_the_27_tap_gradient(kern
         check_module(c, tol=tol)
 
 
-@pytest.mark.parametrize("chans", [[2, 96, 64, 2], [2, 100, 100, 2], [2, 64, 128, 100, 2]], ids=["6_blocks", "16_ragged", "8_and_16"])
-def test_direct_weight_gradient_of_wide_layers(chans, kernel_policy):
+@pytest.mark.parametrize("chans", [[2, 96, 64, 2], [2, 100, 100, 2], [2, 64, 128, 100, 2], [2, 28, 24, 20, 2]],
+                         ids=["6_blocks", "16_ragged", "8_and_16", "last_chunks_of_12_8_4"])
+def test_direct_kernels_of_wide_and_ragged_layers(chans, kernel_policy):
     """Nine taps on five to eight (or thirteen to sixteen) 32 x 32 channel blocks without a transform: the eight-wave
-    weight-gradient kernel, whole and ragged blocks, one and two workgroups of channel blocks."""
+    weight-gradient kernel, whole and ragged blocks, one and two workgroups of channel blocks; convolutions whose last
+    chunk of input channels is ragged, with half of it skipped (4, 8) or not (12)."""
     c = synth.make_custom(39, synth.Geom(2, 2, 2, 1, 1, 10, 46), synth.chain_prox(chans, [K2] * (len(chans) - 1)), accel=2.0,
                           centre=2, bias_std=0.1, alpha=0.8)
     kernel_policy(gb.POLICY_NO_WINOGRAD)
-    print("case wide direct weight gradient", chans, flush=True)
+    print("case wide and ragged direct layers", chans, flush=True)
     check_module(c)
 
 
