@@ -286,7 +286,10 @@ __global__ __launch_bounds__(kConvThreads) void conv_mfma_kernel(ConvArgs a) {
 // Requires K % 4 == 0 (16-byte alignment of every quad).
 // KW > 0 fixes the kernel extent along W at compile time (all LDS operand offsets become immediates);
 // KW == 0 reads it from the arguments.
-template <int NB, int CK, int PJ, int NW, int KW, bool RELU>
+// HALF: the last chunk of channels holds at most half of CK, the other half is zero weights and not multiplied (100 channels,
+// 4 x 320 x 256: 743 -> 713 us).  An instance of its own: the second copy of the loop costs 40 registers, and with them
+// 3 % of a greedy iteration between whole chunks of 32 channels.
+template <int NB, int CK, int PJ, int NW, int KW, bool RELU, bool HALF>
 __global__ __launch_bounds__(NW * 64, 2) void conv_dlds_kernel(ConvArgs a) {
     constexpr int TM = NW * 32 * PJ, G = CK / 8, NJ = NB / 32, Q4 = CK / 4;
     // Swizzle period: LDS serves 128-bit accesses 16 lanes at a time out of 64 banks (256 bytes), so 16 consecutive
@@ -471,9 +474,12 @@ __global__ __launch_bounds__(NW * 64, 2) void conv_dlds_kernel(ConvArgs a) {
                     }
                 }
                 };
-                // a last chunk of at most eight channels: the second half is zero weights (100 channels: 743 -> 713 us)
-                if (G == 2 && a.K - ci.kc * CK <= 8) taps(std::integral_constant<int, 1>{});
-                else taps(std::integral_constant<int, G>{});
+                if constexpr (HALF) {
+                    if (ci.kc == n_kc - 1) taps(std::integral_constant<int, 1>{});
+                    else taps(std::integral_constant<int, G>{});
+                } else {
+                    taps(std::integral_constant<int, G>{});
+                }
             } else {
 #pragma unroll
                 for (int dw = 0; dw < KWM; ++dw) {
@@ -932,8 +938,15 @@ static void launch_conv_dlds_k(const ConvArgs& a, hipStream_t st) {
     const long long cap = 256LL * per_cu;
     const long long gx = ((n_tiles < cap ? n_tiles : cap) + 7) / 8 * 8;   // XCD-aware split needs a multiple of 8
     dim3 grid((unsigned)gx, (a.Nn + NB - 1) / NB);
-    if (a.relu_in) hipLaunchKernelGGL((conv_dlds_kernel<NB, CK, PJ, NW, KW, true>), grid, dim3(NW * 64), 0, st, a);
-    else hipLaunchKernelGGL((conv_dlds_kernel<NB, CK, PJ, NW, KW, false>), grid, dim3(NW * 64), 0, st, a);
+    if constexpr (CK == 16 && KW > 0) {
+        if (a.K % CK != 0 && a.K % CK <= CK / 2) {
+            if (a.relu_in) hipLaunchKernelGGL((conv_dlds_kernel<NB, CK, PJ, NW, KW, true, true>), grid, dim3(NW * 64), 0, st, a);
+            else hipLaunchKernelGGL((conv_dlds_kernel<NB, CK, PJ, NW, KW, false, true>), grid, dim3(NW * 64), 0, st, a);
+            return;
+        }
+    }
+    if (a.relu_in) hipLaunchKernelGGL((conv_dlds_kernel<NB, CK, PJ, NW, KW, true, false>), grid, dim3(NW * 64), 0, st, a);
+    else hipLaunchKernelGGL((conv_dlds_kernel<NB, CK, PJ, NW, KW, false, false>), grid, dim3(NW * 64), 0, st, a);
 }
 
 template <int NB, int CK, int PJ, int NW>
