@@ -180,10 +180,15 @@ hipError_t cg_solve(const gleam_geom& g, const float2* S, const unsigned char* M
     }
     // Where the tiles of the operator's row sweeps allow it, the inner product rides on the last sweep and the update of the
     // search direction on the first sweep of the next application: four launches per step instead of six, and p and q are not read
-    // again.  At 2 x 320 x 256 with 8 coils a step is bound by its launches (the module 1717 -> 1602 us; 1595 with the scalars summed by each wave for itself, the first elements in flight meanwhile); the products are summed in
-    // double as before, in another order.  The partial sums take what is left of the room for three sets.
-    const int n_dot = cg_fused_dot_partials(g, 3 * kCgBlocksMax - 2 * nb), n_pq = n_dot ? n_dot : nb;
-    const bool fuse_p = cg_fused_update(g);
+    // again.  At 2 x 320 x 256 with 8 coils a step is bound by its launches (the module 1717 -> 1602 us; 1595 with the scalars
+    // summed by each wave for itself, the first elements in flight meanwhile).  The products are summed in double as before, in
+    // another order.
+    // Every workgroup sums the partials for itself, so many of them cost more than the launch they save: 1 x 256 x 24 x 160 with 5
+    // coils and 512 partials was 4589 us apart and 4627 us fused.
+    constexpr int kFusedPartials = 256, kFusedSums = 128;
+    const int room = 3 * kCgBlocksMax - 2 * nb, n_dot = cg_fused_dot_partials(g, room < kFusedPartials ? room : kFusedPartials);
+    const int n_pq = n_dot ? n_dot : nb;
+    const bool fuse_p = nb <= kFusedSums && cg_fused_update(g);
     for (int k = 0; k < n_cg; ++k) {
         double* cur = rr[k & 1];
         double* nxt = rr[(k + 1) & 1];
