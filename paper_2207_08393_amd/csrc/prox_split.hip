@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
         s.rs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.in + (in && KD == 3 ? b.img + kd - 1 : b.img) * (long long)a.H * a.W * a.K), 0,
                                                  in ? slice_bytes : 0u, 0x00020000);
         s.skip = kc == n_kc - 1 ? ragged : 0u;
-        s.off = kc * kChunk * 4;
+        s.off = in ? kc * kChunk * 4 : 0;   // (no more than the size of the resource: the range check subtracts it from that)
         return s;
     };
     auto request = [&](const Source& s, int i, float* dst) {
@@ -299,12 +299,15 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             float* const ex = (g & 1) ? ex2 : free_raw;
+            // An image of fewer rows than g has none of these rows: an offset of the whole slice puts every lane outside.  (The
+            // range check subtracts it from the size of the slice, so it must not be larger.)
+            const unsigned row_off = (g < a.H ? g : a.H) * row_bytes;
             uint4v refv[2], addv[2];
             if constexpr (EPI != 0) {
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj) {
-                    if constexpr (EPI == 1) refv[jj] = load16(r_ref, off_px[jj], g * row_bytes);
-                    addv[jj] = load16(r_add, off_px[jj], g * row_bytes);
+                    if constexpr (EPI == 1) refv[jj] = load16(r_ref, off_px[jj], row_off);
+                    addv[jj] = load16(r_add, off_px[jj], row_off);
                 }
             }
 #pragma unroll
@@ -335,7 +338,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
                     if (a.bits_out) sign_out = sign_out + sign_out + (v > 0.f ? 1u : 0u);   // value 0 ends up in bit 31
                     o[e] = __float_as_uint(v);
                 }
-                store16(r_out, o, off_px[jj], g * row_bytes);
+                store16(r_out, o, off_px[jj], row_off);
             }
         }
         if (a.bits_out) a.bits_out[word_idx] = sign_out;

@@ -14,6 +14,9 @@ def cases():
     yield "narrower_and_lower_than_a_block", synth.Geom(2, 1, 2, 1, 1, 4, 6), synth.resblock_prox(64, 1)
     yield "whole_blocks_only", synth.Geom(2, 1, 2, 1, 1, 16, 32), synth.resblock_prox(32, 2)
     yield "odd_rows_batched", synth.Geom(1, 1, 2, 1, 3, 9, 64), synth.resblock_prox(16, 1)
+    for h in (1, 2, 3):   # fewer rows than a thread's four, between slices that must stay as they are
+        yield f"{h}_rows_many_slices", synth.Geom(1, 2, 2, 1, 5, h, 46), synth.resblock_prox(36, 1)
+    yield "2_rows_sign_words", synth.Geom(1, 1, 2, 1, 6, 2, 64), synth.chain_prox([2, 32, 64, 32, 2], [K2] * 4)
     yield "ragged_channels", synth.Geom(2, 1, 2, 1, 1, 12, 20), synth.chain_prox([2, 36, 12, 60, 2], [K2] * 4)
     yield "ragged_chunk_many_blocks", synth.Geom(2, 2, 2, 3, 1, 32, 96), synth.resblock_prox(20, 2)
     yield "narrow_between_wide", synth.Geom(2, 1, 2, 1, 1, 20, 46), synth.chain_prox([2, 64, 4, 64, 2], [K2] * 4)
