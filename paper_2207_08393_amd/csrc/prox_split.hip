@@ -292,6 +292,11 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
             off_px[jj] = xx < a.W && n_ok ? ((unsigned)(yy * a.W + xx) * (unsigned)a.Nn + n0 + 4 * e_cq) * 4u : 0x80000000u;
         }
         const int no_acc = EPI == 0 || a.mask_acc ? 0 : -1, no_add = EPI == 0 || a.mask_add ? 0 : -1;
+        // The transform and the split turn an overflow into NaN.  A ReLU at the output takes what is below zero and lets NaN
+        // pass; without one, NaN leaves as +infinity, because a ReLU at the input of the next layer may make 0 of NaN (fmaxf
+        // does, and a maximum of bit patterns where the sign is set).  Two instructions per value, as a plain ReLU was.
+        const int out_class = a.relu_out ? 0x3c : 0x3;   // negative numbers and -0, or NaN
+        const float out_instead = a.relu_out ? 0.f : __builtin_huge_valf();
         const long long word_idx = ((long long)blockIdx.y * a.n_blocks + item) * 256 + t;
         const unsigned sign_in = EPI == 2 ? a.bits_in[word_idx] : 0u;   // one bit per value of this thread
         unsigned sign_out = 0u;
@@ -328,7 +333,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float v = (jj == 0 ? q[0][e] + (q[1][e] + q[2][e]) : (q[1][e] - q[2][e]) - q[3][e]) + bb[e];
-                    if (a.relu_out) v = fmaxf(v, 0.f);
+                    v = __builtin_amdgcn_classf(v, out_class) ? out_instead : v;
                     if constexpr (EPI != 0) {
                         const int idx = 8 * g + 4 * jj + e;
                         const int pass = EPI == 2 ? __builtin_amdgcn_sbfe(sign_in, 31 - idx, 1) : (__uint_as_float(refv[jj][e]) > 0.f ? -1 : 0);
@@ -418,7 +423,7 @@ __global__ __launch_bounds__(256) void split_weights_kernel(SplitWeightBatch b) 
                 float r = uu[nu];
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
-                    const unsigned short s = f32_to_bf16(r);
+                    const unsigned short s = (unsigned short)pack_bf16x2(r, 0.f);   // (keeps every NaN, unlike f32_to_bf16)
                     dst[((ky * 4 + nu) * 3 + p) * kOperand] = s;
                     r -= bf16_to_f32(s);
                 }
