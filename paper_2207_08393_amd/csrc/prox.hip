@@ -319,6 +319,10 @@ __global__ __launch_bounds__(NW * 64, 2) void conv_dlds_kernel(ConvArgs a) {
     const long long n_tiles = (d.Q + TM - 1) / TM;
     const bool vec_out = (a.Nn % 4) == 0;
     const long long last_quad = d.Q * a.K - 4;            // highest legal quad start
+    // Last first pixel of a slab of which no quad of any chunk starts outside the tensor.  (The last chunk of a ragged K runs
+    // into the next pixels: those channels meet zero weights.)  With K % CK == 0 as the condition, 100 -> 100 channels took the
+    // clamped 64-bit addresses everywhere: 770 us at 4 x 320 x 256, 743 us so.
+    const long long last_start = d.Q - (n_kc * CK + a.K - 1) / a.K - slab_ops * 64 / Q4 + 1;
 
     // Per-lane constants of the direct loads: element offset of this lane's quad from the slab origin
     // (pixel qs, channel kc*CK) and float offset of its weight quad inside an image.
@@ -340,10 +344,7 @@ __global__ __launch_bounds__(NW * 64, 2) void conv_dlds_kernel(ConvArgs a) {
     auto issue = [&](long long tile, const ChunkIter& ci, float* dst) {
         const int rt = ci.rt, kc = ci.kc;
         const long long qs = tile * TM + ci.off - kw / 2;
-        // No quad of any chunk starts outside the tensor.  (The last chunk of a ragged K runs into the next pixel: those
-        // channels meet zero weights.)  With K % CK == 0 as the condition, 100 -> 100 channels took the clamped 64-bit
-        // addresses everywhere: 770 us at 4 x 320 x 256, 743 us so.
-        const bool interior = qs >= 0 && (qs + (long long)slab_ops * 64 / Q4 - 1) * a.K + n_kc * CK - 4 <= last_quad;   // uniform
+        const bool interior = qs >= 0 && qs <= last_start;   // uniform
         if (interior) {
             const float* base = a.in + qs * a.K + kc * CK;                                       // uniform
 #pragma unroll
@@ -547,7 +548,9 @@ __global__ __launch_bounds__(NW * 64, 2) void conv_dlds_kernel(ConvArgs a) {
                                     for (int i = 0; i < 4; ++i) v[i] = rr[i] > 0.f ? v[i] : 0.f;
                                 }
                                 if (a.add) {
-                                    const float4 av = *reinterpret_cast<const float4*>(a.add + o);
+                                    float4 av = *reinterpret_cast<const float4*>(a.add + o);
+                                    // (keeps it one load of 16 bytes: the compiler may move the one of .x to where it is needed)
+                                    asm volatile("" : "+v"(av.x), "+v"(av.y), "+v"(av.z), "+v"(av.w));
                                     const float aa[4] = {av.x, av.y, av.z, av.w};
 #pragma unroll
                                     for (int i = 0; i < 4; ++i) v[i] += (a.mask_add && !(rr[i] > 0.f)) ? 0.f : aa[i];
