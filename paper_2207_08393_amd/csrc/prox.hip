@@ -1321,7 +1321,12 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
 
     // Per-thread staging descriptors: the float4 slots this thread moves are the same for every chunk.
     int g_lds[PG], g_dq[PG], g_c[PG];
-    int a_lds[PA], a_c[PA], a_pr[PA];   // a_pr: row tap (31: none) << 8 | pixel offset + 128
+    // Row tap and pixel offset of a slot: apart, or as one word (row tap << 8 | pixel offset + 128, row tap 31: none) in the
+    // eight waves of nine taps, which have no registers for two.  (One word everywhere: two more instructions per slot and
+    // chunk; 16 -> 16 channels 59.7 -> 60.4 us at 555 x 256, 96 -> 96 230.1 -> 232.3 us at 3 x 128 x 160.)
+    constexpr bool kOneWord = JT == 9 && NW == 8;
+    int a_lds[PA], a_c[PA], a_px[PA];
+    unsigned a_rt[PA];
 #pragma unroll
     for (int i = 0; i < PG; ++i) {
         const int v = tid + i * NT;
@@ -1337,7 +1342,9 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         const int p = r / Ci4, c4 = r % Ci4;
         a_lds[i] = v < n_a4 ? (rt * n_pa + p) * RSa + 4 * c4 : -1;
         a_c[i] = (v < n_a4 ? (int)rowtap_offset(rt, d) - d.kw / 2 + p : 0) * a.Ci + 4 * c4;   // element offset from the chunk's first pixel (may be negative)
-        a_pr[i] = (v < n_a4 ? rt : 31) << 8 | (p - d.kw / 2 + 128);   // (extents are odd: at most 27 row taps)
+        a_px[i] = p - d.kw / 2;
+        a_rt[i] = v < n_a4 ? 1u << rt : 0u;
+        if constexpr (kOneWord) a_px[i] = (v < n_a4 ? rt : 31) << 8 | (a_px[i] + 128);   // (extents are odd: at most 27 row taps)
     }
     float4 rg[PG], ra[PA], bsum[PG];
 #pragma unroll
@@ -1385,7 +1392,9 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         }
 #pragma unroll
         for (int i = 0; i < PA; ++i) {
-            const bool ok = ((rows_ok >> (a_pr[i] >> 8)) & 1u) != 0u && (unsigned)(w0 + (a_pr[i] & 255) - 128) < (unsigned)d.W;
+            bool ok;
+            if constexpr (kOneWord) ok = ((rows_ok >> (a_px[i] >> 8)) & 1u) != 0u && (unsigned)(w0 + (a_px[i] & 255) - 128) < (unsigned)d.W;
+            else ok = (rows_ok & a_rt[i]) != 0u && (unsigned)(w0 + a_px[i]) < (unsigned)d.W;
             ra[i] = *reinterpret_cast<const float4*>(ok ? abase + a_c[i] : a.a);
             a_okb |= (ok ? 1u : 0u) << i;
         }
