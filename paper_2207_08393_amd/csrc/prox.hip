@@ -19,7 +19,6 @@
 #include <cstdint>
 #include <cstdio>
 #include <type_traits>
-#include <type_traits>
 
 #include "prox_common.h"
 

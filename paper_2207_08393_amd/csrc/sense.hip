@@ -10,7 +10,6 @@
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
-
 #include "fft_core.h"
 #include "internal.h"
 #include "xcd.h"
