@@ -22,13 +22,27 @@ __device__ inline double block_sum(double v, double* red) {
     return v;
 }
 
-// Sums of two sets of a sample's partials, the same values in every thread: each wave adds up both sets by itself, strided per
-// lane in a fixed order and then across the lanes, so that no barrier stands between the launch and the first update.
+// Sums of two sets of a sample's partials (kCgBlocksMax at most), the same values in every thread: each wave adds up both sets
+// by itself, strided per lane in a fixed order and then across the lanes, so that no barrier stands between the launch and the
+// first update.  All loads of a lane are in flight together: one after the other, 512 partials cost the updates 1.3 us each
+// (1 x 256 x 24 x 160: 13.1 and 9.5 us).
 __device__ inline double2 sum_partials(const double* __restrict__ u, int nu, const double* __restrict__ v, int nv) {
+    constexpr int N = kCgBlocksMax / 64;
     const int lane = threadIdx.x & 63;
-    double a = 0.0, b = 0.0;
-    for (int i = lane; i < nu; i += 64) a += u[i];
-    for (int i = lane; i < nv; i += 64) b += v[i];
+    double x[N], y[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int i = lane + 64 * k;
+        x[k] = y[k] = 0.0;
+        if (i < nu) x[k] = u[i];
+        if (i < nv) y[k] = v[i];
+    }
+    double a = x[0], b = y[0];
+#pragma unroll
+    for (int k = 1; k < N; ++k) {
+        a += x[k];
+        b += y[k];
+    }
     for (int o = 32; o > 0; o >>= 1) {
         a += __shfl_xor(a, o);
         b += __shfl_xor(b, o);
@@ -183,9 +197,16 @@ hipError_t cg_solve(const gleam_geom& g, const float2* S, const unsigned char* M
     // again.  At 2 x 320 x 256 with 8 coils a step is bound by its launches (the module 1717 -> 1602 us; 1595 with the scalars
     // summed by each wave for itself, the first elements in flight meanwhile).  The products are summed in double as before, in
     // another order.
-    // Every workgroup sums the partials for itself, so many of them cost more than the launch they save: 1 x 256 x 24 x 160 with 5
-    // coils and 512 partials was 4589 us apart and 4627 us fused.
+    // Every tile of the first sweep sums the partials of its samples for itself, and every workgroup of the update those of the
+    // inner product, so many of them cost more than the launches they save.  A module of 10 steps, all apart / by the rule below /
+    // with both limits at 512 (samples x coils x size: sums, partials of the inner product; us):
+    //     2 x 8 x 320 x 256         80,  160   1130 / 1036 / 1029     1 x 5 x 4 x 128 x 256    128, none    937 /  902 /  901
+    //     4 x 12 x 320 x 368       115,  320   2786 / 2792 / 2779     1 x 15 x 320 x 368       115,  320   1456 / 1415 / 1370
+    //     1 x 8 x 640 x 320        200,  320   1270 / 1271 / 1187     2 x 15 x 640 x 368       230,  640   2787 / 2787 / 2813
+    //     1 x 5 x 256 x 24 x 160   512, 1024   4245 / 4243 / 4279     1 x 8 x 20 x 192 x 160   512,  960   2114 / 2114 / 2147
+    // What the rule takes in has never cost more than 0.2 %; above it, it depends on how many tiles a workgroup has.
     constexpr int kFusedPartials = 256, kFusedSums = 128;
+    static_assert(kFusedPartials <= kCgBlocksMax, "what sum_partials takes");
     const int room = 3 * kCgBlocksMax - 2 * nb, n_dot = cg_fused_dot_partials(g, room < kFusedPartials ? room : kFusedPartials);
     const int n_pq = n_dot ? n_dot : nb;
     const bool fuse_p = nb <= kFusedSums && cg_fused_update(g);
