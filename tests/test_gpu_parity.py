@@ -595,6 +595,31 @@ def test_modl_solver_inside_the_row_sweeps(geom):
         assert rel_l2(x, f["x_out"]) <= TOL and rel_l2(grad, g) <= TOL
 
 
+@pytest.mark.parametrize("geom,dots,updates", [
+    (synth.Geom(2, 1, 8, 1, 1, 24, 32), 0, 0),        # 1 sum, 3 tiles: both inside the sweeps
+    (synth.Geom(2, 1, 2, 1, 2, 192, 368), 0, 6),      # 138 sums, 192 tiles: the inner product only
+    (synth.Geom(2, 1, 64, 9, 1, 32, 10), 8, 0),       # 3 sums, 288 tiles: the update only
+    (synth.Geom(2, 1, 12, 1, 2, 192, 368), 8, 6),     # 138 sums, 384 tiles: neither
+], ids=["both", "inner_product", "update", "neither"])
+def test_modl_solver_launches_what_the_sweeps_do_not_take_in(geom, dots, updates):
+    """Which of its launches the solver makes by itself, from the library's own records (two solves of four steps each), and
+    the results of every mixture against the oracle."""
+    from paper_2207_08393_amd.runner import ModlRunner
+    c = synth.make_custom(68, geom, synth.chain_prox([2, 8, 2], [K2] * 2), accel=2.0, centre=2, bias_std=0.1)
+    mu, n_cg = 0.5, 4
+    print("case modl launches", geom, flush=True)
+    r = ModlRunner(c, mu, n_cg)
+    gb.gleam_profile_begin()
+    r.step()
+    names = [rec[0] for rec in gb.gleam_profile_end()]
+    assert (names.count("cg_dot"), names.count("cg_update_p")) == (dots, updates)
+    x, loss, grad, aty = r.results()
+    aty_o = og.sense_adjoint(c.y.astype(np.complex128), c.S, c.M, 2)
+    f = og.modl_module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, aty_o, mu, n_cg, c.theta, c.x_true)
+    g = og.modl_module_bwd(c.geom, c.prox, c.S, c.M, mu, n_cg, c.theta, f)
+    assert rel_l2(x, f["x_out"]) <= TOL and rel_l2(grad, g) <= TOL
+
+
 @pytest.mark.timeout(900)
 def test_modl_module_knee2d_full_size():
     """One MoDL module (prox, then 10 CG steps on A^H A + mu I, both ways) at the knee workload's full size."""
