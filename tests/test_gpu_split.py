@@ -4,9 +4,11 @@ import numpy as np
 import pytest
 
 from oracle import gleam_oracle as og
+from paper_2207_08393_amd import binding as gb
 from paper_2207_08393_amd import synth
-from tests.gpu_util import ModuleRunner, rel_l2, theta_slices
-from tests.test_gpu_parity import K2, K3, TOL, check_module
+from tests.gpu_util import ModuleRunner, assert_grad_close, assert_image_close, rel_l2, theta_slices
+from tests.test_gpu_parity import K2, K3, TOL, check_module, kernel_policy  # noqa: F401
+from tests.test_split_arithmetic import BOUND
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +78,126 @@ def test_a_nan_weight_stays_visible():
         r.step()
         x_out, loss, grad = r.results()
         assert not np.isfinite(x_out).any() and not np.isfinite(loss) and np.isnan(grad).any()
+
+
+def linear_prox(chans, k):
+    """Convolutions only: no ReLU that a rounding could decide the other way, no skip that dilutes the error."""
+    return synth.ProxDesc([synth.ConvLayer(a, b, *k, 0, 0, 1, -1) for a, b in zip(chans, chans[1:])])
+
+
+@pytest.mark.parametrize("chans,k", [([2, 32, 32, 32, 2], K2), ([2, 36, 60, 20, 2], K2), ([2, 100, 100, 2], K2), ([2, 64, 64, 64, 2], K2),
+                                     ([2, 20, 36, 2], K3), ([2, 32, 32, 2], K3)], ids=["32", "ragged", "100", "64", "volume_ragged", "volume_32"])
+def test_split_operands_keep_the_precision_of_float32(chans, k):
+    """Output and the gradients of every layer within 1e-6 of the 64-bit oracle: a float32 sum of these lengths is off by 1e-7 to
+    7e-7 (the direct float32 kernels on such networks: 5e-8 to 6.8e-7), and a product that has lost one of its six parts by 3e-6
+    in a single layer (tests/test_split_arithmetic.py)."""
+    geom = synth.Geom(3, 1, 2, 1, 6, 12, 20) if k == K3 else synth.Geom(2, 2, 2, 1, 1, 20, 46)
+    for seed in (1, 2):
+        c = synth.make_custom(seed, geom, linear_prox(chans, k), accel=2.0, centre=2, bias_std=0.1, alpha=0.8)
+        print("case split precision", chans, seed, flush=True)
+        r = ModuleRunner(c)
+        r.step()
+        x_out, loss, grad = r.results()
+        f = og.module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, c.y, c.alpha, c.theta, c.x_true)
+        g = og.module_bwd(c.prox, c.theta, f)
+        errs = {"x_out": rel_l2(x_out, f["x_out"]), "loss": abs(loss / f["loss"] - 1)}
+        errs.update({f"{layer}{kind}": rel_l2(grad[part], g[part]) for layer, kind, part in theta_slices(c.prox)})
+        print({name: float(f"{e:.1e}") for name, e in errs.items()}, flush=True)
+        assert max(errs.values()) <= BOUND, errs
+
+
+def wide_convolutions(records):
+    """Matrix-core flops issued per flop of the direct convolution, of every convolution between wide layers."""
+    return {n: round(m / f, 3) for n, f, _, _, m in records if n.startswith("conv_") and "_2to" not in n and "to2_" not in n}
+
+
+def winograd_cases():
+    # (name, geometry, prox, Winograd): networks as greedy iterations and MoDL modules run them.  64-multiples of channels (3x3)
+    # and 32-multiples (3x3x3) take the Winograd kernels there: sizes that their 4 x 32, 2 x 32 and 8 x 32 pixel blocks do not
+    # divide, several images, two channel blocks on either side, one and two slices, no bias
+    yield "ragged", synth.Geom(2, 2, 2, 1, 1, 10, 46), synth.resblock_prox(64, 1), True
+    yield "two_blocks", synth.Geom(2, 1, 2, 1, 1, 6, 96), synth.chain_prox([2, 64, 128, 64, 2], [K2] * 4), True
+    yield "nobias_l1", synth.Geom(2, 1, 2, 3, 1, 6, 46), synth.chain_prox([2, 64, 64, 2], [K2] * 3, has_bias=0, loss_kind=1), True
+    yield "volume_ragged", synth.Geom(3, 2, 2, 1, 6, 6, 46), synth.chain_prox([2, 32, 64, 32, 2], [K3] * 4), True
+    yield "two_slices_l1", synth.Geom(2, 1, 2, 1, 2, 10, 12), synth.chain_prox([2, 32, 32, 2], [K3] * 3, has_bias=0, loss_kind=1), True
+    yield "one_slice", synth.Geom(2, 1, 2, 1, 1, 10, 46), synth.chain_prox([2, 32, 32, 2], [K3] * 3), True
+    yield "direct_100", synth.Geom(2, 1, 2, 1, 1, 10, 46), synth.resblock_prox(100, 1), False
+    yield "direct_ragged", synth.Geom(2, 1, 2, 1, 1, 12, 20), synth.chain_prox([2, 36, 12, 60, 2], [K2] * 4), False
+
+
+@pytest.mark.parametrize("name,geom,prox,winograd", list(winograd_cases()), ids=[c[0] for c in winograd_cases()])
+def test_float32_matrix_core_kernels_of_greedy_and_modl_calls(name, geom, prox, winograd):
+    """The float32 Winograd and direct kernels, which these calls keep, against the oracle: a greedy iteration of one module
+    (Adam's first moment is a tenth of the gradient) and a MoDL module.  The library's own records tell that they ran."""
+    from paper_2207_08393_amd.runner import GreedyRunner, ModlRunner
+    c = synth.make_custom(31, geom, prox, accel=2.0, centre=2, bias_std=0.1, alpha=0.8)
+    print("case float32 kernels", name, flush=True)
+    r = GreedyRunner(c, [c.theta], 1e-3)
+    gb.gleam_profile_begin()
+    r.iteration(1)
+    ran = wide_convolutions(gb.gleam_profile_end())
+    assert len(ran) >= 3 and set(ran.values()) == {0.444 if winograd else 1.0}, ran
+    x, losses, _, m, _ = r.results()
+    f = og.module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, c.y, c.alpha, c.theta, c.x_true)
+    assert_image_close(x, f["x_out"], TOL)
+    assert abs(losses[0] - f["loss"]) <= TOL * abs(f["loss"])
+    assert_grad_close(c.prox, m[0], 0.1 * og.module_bwd(c.prox, c.theta, f), TOL, "Adam m")
+
+    mu, n_cg = 0.5, 3
+    r = ModlRunner(c, mu, n_cg)
+    gb.gleam_profile_begin()
+    r.step()
+    ran = wide_convolutions(gb.gleam_profile_end())
+    assert len(ran) >= 3 and set(ran.values()) == {0.444 if winograd else 1.0}, ran
+    x, loss, grad, _ = r.results()
+    aty = og.sense_adjoint(c.y.astype(np.complex128), c.S, c.M, geom.ndim_fft)
+    f = og.modl_module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, aty, mu, n_cg, c.theta, c.x_true)
+    g = og.modl_module_bwd(c.geom, c.prox, c.S, c.M, mu, n_cg, c.theta, f)
+    assert_image_close(x, f["x_out"], TOL)
+    assert rel_l2(grad, g) <= TOL
+
+    # a plain module of the same network runs on split operands (the weight gradient of whole 3x3x3 blocks excepted)
+    r = ModuleRunner(c)
+    gb.gleam_profile_begin()
+    r.step()
+    ran = wide_convolutions(gb.gleam_profile_end())
+    assert {v for n, v in ran.items() if "wgrad" not in n} == {4.0}, ran
+    assert {v for n, v in ran.items() if "wgrad" in n} == {0.444 if prox.layers[1].kd == 3 else 4.0}, ran
+
+
+def modules_by_hand(c, thetas, lr):
+    """What gleam_greedy_iteration does, call by call: x, losses, theta, m, v."""
+    from paper_2207_08393_amd.runner import GreedyRunner
+    r = GreedyRunner(c, thetas, lr)
+    x_in = r.x0
+    for i in range(len(thetas)):
+        x = r.x_out if (len(thetas) - 1 - i) % 2 == 0 else r.x_tmp
+        gb.gleam_module_fwd(r.geom, r.prox, x_in, r.S, r.M, r.y, r.alpha, r.theta[i], r.x_ref, x, r.losses[i:], r.saved, r.ws)
+        gb.gleam_module_bwd(r.geom, r.prox, r.theta[i], r.saved, r.grad, r.ws)
+        gb.gleam_adam_step(r.hyper, 1, r.theta[i], r.grad, r.m[i], r.v[i])
+        x_in = x
+    return r.results()
+
+
+@pytest.mark.parametrize("nf", [64, 36, 6])
+def test_greedy_iteration_and_the_same_calls_by_hand(nf, kernel_policy):
+    """Bit for bit the same where a layer has one kernel for both (6 channels, or GLEAM_POLICY_NO_WINOGRAD).  Otherwise the
+    modules by hand run on split operands and the iteration does not: each is within 1e-6 of the 64-bit results in its first
+    module (test above, and TOL for the iteration), a second module starts from an input that differs by that much; no further
+    apart than 1e-5 in the outputs and the first moments, where no ReLU of these networks is decided the other way."""
+    from paper_2207_08393_amd.runner import GreedyRunner
+    c = synth.make_custom(21, synth.Geom(2, 2, 3, 1, 1, 12, 46), synth.resblock_prox(nf, 1), accel=2.0, centre=2, bias_std=0.1, alpha=0.8)
+    thetas = [c.theta, c.theta + np.float32(0.03) * np.random.default_rng(2).standard_normal(c.theta.size).astype(np.float32)]
+    for policy in (0, gb.POLICY_NO_WINOGRAD):
+        kernel_policy(policy)
+        print("case greedy by hand", nf, policy, flush=True)
+        r = GreedyRunner(c, thetas, 1e-3)
+        r.iteration(1)
+        whole, parts = r.results(), modules_by_hand(c, thetas, 1e-3)
+        if policy or nf == 6:
+            assert all(np.array_equal(a, b) for a, b in zip(whole, parts))
+            continue
+        x, losses, _, m, _ = whole
+        errs = [rel_l2(parts[0], x), rel_l2(parts[1], losses)] + [rel_l2(parts[3][i], m[i]) for i in range(2)]
+        print("apart", errs, flush=True)
+        assert 0 < max(errs) <= 1e-5
