@@ -146,7 +146,9 @@ int gleam_sense_normal_static(const gleam_geom* geom, const gleam_c64* x, const 
  *            and no backward pass may follow).
  *   loss   : device float32 scalar, overwritten with L(x_out, x_ref) (Eq. 10).
  *   x_out  : image, overwritten; must not alias x_in.  Passing it as the next module's x_in is the
- *            detached hand-off between modules. */
+ *            detached hand-off between modules.
+ * Range: float32 3x3 and 3x3x3 layers whose widths are multiples of 4 take inputs of up to 1.69e38, half the float32 range.
+ * An input beyond it, infinity or NaN makes infinity or NaN of the outputs it reaches (and of a few more beside them). */
 int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox,
                      const gleam_c64* x_in, const gleam_c64* S, const uint8_t* M, const gleam_c64* y,
                      float alpha, const float* theta, const gleam_c64* x_ref,
@@ -263,7 +265,13 @@ int gleam_adam_step(const gleam_adam* hyper, int64_t t, size_t n, float* theta, 
  *   losses    : device float32 [n_modules], loss of every module before its update.
  *   grad      : device scratch of n_theta floats.
  * Every module's output is computed with its parameters BEFORE the update.  All modules share the
- * architecture `prox`.  Other arguments as in gleam_module_fwd. */
+ * architecture `prox`.  Other arguments as in gleam_module_fwd.
+ * The iteration does what gleam_module_fwd, gleam_module_bwd and gleam_adam_step do in turn, to the same bits where a layer
+ * has one kernel for both.  Float32 3x3 and 3x3x3 layers whose widths are multiples of 4 have two: the module calls and
+ * gleam_unrolled_infer run them on split operands, this call (like a MoDL module) on the float32 matrix cores.  Outputs,
+ * losses and first moments then differ by rounding (6e-7 over two modules of 64 channels); a parameter whose gradient is that
+ * close to zero can differ by twice the learning rate after Adam's first step.  Under GLEAM_POLICY_NO_WINOGRAD all of it is
+ * the same bit for bit, at the speed of the direct kernels. */
 int gleam_greedy_iteration(const gleam_geom* geom, const gleam_prox_desc* prox, int n_modules,
                            const gleam_c64* x0, const gleam_c64* S, const uint8_t* M, const gleam_c64* y,
                            float alpha, float* theta, float* adam_m, float* adam_v, const gleam_adam* hyper,
@@ -272,7 +280,8 @@ int gleam_greedy_iteration(const gleam_geom* geom, const gleam_prox_desc* prox, 
                            size_t ws_bytes, void* stream);
 
 /* Inference through the first n_modules modules (all of them, or fewer: early exit at depth N_inf),
- * x_i = f_theta_i(DC(x_{i-1})); nothing is saved.  theta: [n_modules][n_theta]; x_out, x_tmp as above. */
+ * x_i = f_theta_i(DC(x_{i-1})); nothing is saved.  theta: [n_modules][n_theta]; x_out, x_tmp as above.  The kernels are
+ * those of gleam_module_fwd. */
 int gleam_unrolled_infer(const gleam_geom* geom, const gleam_prox_desc* prox, int n_modules,
                          const gleam_c64* x0, const gleam_c64* S, const uint8_t* M, const gleam_c64* y,
                          float alpha, const float* theta, gleam_c64* x_out, gleam_c64* x_tmp,
@@ -284,7 +293,9 @@ int gleam_unrolled_infer(const gleam_geom* geom, const gleam_prox_desc* prox, in
  * *n_records receives the number of launches seen.  `flops` / `bytes` are the algorithmic work of the launch
  * (padding and re-reads not counted; a convolution counts 2 * taps * cin * cout per pixel whatever the kernel);
  * `mfma_flops` is what the launch issues on the matrix cores: equal to `flops` for the direct kernels, 4/9 of it
- * for the Winograd F(2x2,3x3) kernels, so mfma_flops / time never exceeds the matrix-core peak.
+ * for the Winograd F(2x2,3x3) kernels, 4 times it for the split-operand kernels (2/3 of the multiplications, six bfloat16
+ * products each).  mfma_flops / time never exceeds the peak of the matrix cores it is issued on: the bfloat16 ones for the
+ * split-operand kernels and for dtype 1, the float32 ones for the others.
  * Not thread-safe; leave it off in production. */
 typedef struct {
     char name[56];

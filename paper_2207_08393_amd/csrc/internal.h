@@ -72,12 +72,12 @@ hipError_t kspace_to_hybrid(const gleam_geom& g, float2* y, hipStream_t st);
 struct ProxPlan {
     int L;
     // Whether 3x3 and 3x3x3 float32 layers run on split bfloat16 operands (conv_split_applies, wgrad_split_applies).  The MoDL
-    // module and the greedy iteration keep the float32 matrix cores.  Not for speed (100 -> 100 channels at 4 x 320 x 256: 771 us
-    // forward and 1370 us weight gradient there, 280 and 340 us here) and not for accuracy (the split kernels' error against
-    // 64 bits is the smaller one): both magnify any other order of rounding.  The first Adam step moves a parameter by
-    // lr * sign(g), so one whose gradient is near zero moves by 2 lr; the gradient of a MoDL module with the complex-l1 loss
-    // takes d / |d| of residuals that the solve drives to zero, and varies by 1e-6 .. 5e-4 between equally exact results.
-    // Both stay on the arithmetic their results have been compared with.
+    // module and the greedy iteration keep the float32 matrix cores, so that their results stay what they were.  It is not for
+    // speed (100 -> 100 channels at 4 x 320 x 256: 713 us forward and 970 us weight gradient there, 280 and 340 us here) and not
+    // for accuracy (the split kernels are the nearer ones to 64 bits): any other order of rounding shows in them.  The first
+    // Adam step moves a parameter by lr * sign(g), so one whose gradient is near zero moves by 2 lr; the gradient of a MoDL
+    // module with the complex-l1 loss takes d / |d| of residuals that the solve drives to zero, and is 1e-6 .. 5e-4 from the
+    // 64-bit result by input, with either arithmetic.
     bool split;
     long long Q;                      // pixels B*T*D*H*W
     size_t act_off[kMaxLayers + 1];   // t_l inside saved, l < L

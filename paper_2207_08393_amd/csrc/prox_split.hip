@@ -33,10 +33,11 @@
 //
 // What bounds it: power.  A loop of nothing but these matrix instructions sustains 1.8 PFLOP/s on random operands (2.3 on
 // constant ones), 1.5 with the four vector instructions per matrix instruction that the transform and the split need; a
-// library product of two 8192 x 8192 bfloat16 matrices reaches 1.23.  64 -> 64 channels, 2 x 640 x 368: 181 us forward and
-// 189 us data gradient with F(2x2, 3x3) on the float32 matrix cores, 140 us both here (1.0 PFLOP/s issued); 32 -> 32 channels,
-// 256 x 160 x 160, 27 taps: 1640 / 1850 us before, 1200 / 1220 us here; without the epilogue 10 % less, without the direct
-// loads 8 - 15 % less, matrix and vector work alone 1.4 PFLOP/s.  Tried and taken out: 16-row blocks with one accumulator per
+// library product of two 8192 x 8192 bfloat16 matrices reaches 1.23.  64 -> 64 channels, 2 x 640 x 368, inside a step: 182 us
+// forward and 189 us data gradient with F(2x2, 3x3) on the float32 matrix cores, 148 - 156 us both here, by card and by how long
+// it has been busy (0.89 - 0.94 PFLOP/s issued; 140 us by itself); 32 -> 32 channels, 256 x 160 x 160, 27 taps: 1640 / 1850 us
+// before, 1.30 - 1.33 ms both here (1.20 by itself); without the epilogue 10 % less, without the direct loads 8 - 15 % less,
+// matrix and vector work alone 1.4 PFLOP/s.  Tried and taken out: 16-row blocks with one accumulator per
 // product (6 - 8 % faster, less exact); all direct loads of a chunk at its start (each wave then waits for the address unit
 // before its first matrix instruction: 10 % slower).
 #include "split.h"

@@ -15,8 +15,8 @@
 // The pixel rows of the image are dealt to the workgroups in equal contiguous runs; at the end the four positions meet in
 // LDS, G^T is applied and every workgroup writes one partial sum in the layout of the weights.
 //
-// What bounds it: 64 -> 64 channels at 2 x 640 x 368 takes 135 us (1.0 PFLOP/s issued; 171 us with F(2x2, 3x3) on the float32
-// matrix cores); 117 us without the splits and the direct loads, 110 us with a sixth of the matrix instructions: a barrier per
+// What bounds it: 64 -> 64 channels at 2 x 640 x 368 takes 139 - 150 us inside a step, by card and by how long it has been busy
+// (171 us with F(2x2, 3x3) on the float32 matrix cores), and 135 us by itself (1.0 PFLOP/s issued); 117 us without the splits and the direct loads, 110 us with a sixth of the matrix instructions: a barrier per
 // 18 matrix instructions and wave, and 113 vector instructions and 18 LDS reads between two of them.  16 -> 16 at 64 x 64:
 // 31 -> 13 us.  Tried and taken out: 64 input channels per workgroup, three waves per SIMD (both spill: 2 - 4 times slower),
 // one wave per SIMD with 64 x 64 channels (225 us, moves between the register files) or with all three slice taps of a
@@ -306,9 +306,10 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradArgs a) {
 }
 
 bool wgrad_split_applies(const PixDims& d, int Ci, int Co) {
-    // 3x3x3 layers between multiples of 32 channels have a kernel that forms every operand once for three slice taps and is as
-    // fast on the float32 matrix cores (32 -> 32, 256 x 160 x 160: 1.49 against 1.51 ms here); the other widths would go to the
-    // direct kernel.
+    // 3x3x3 layers between multiples of 32 channels have a kernel on the float32 matrix cores that forms every operand once for
+    // three slice taps, and keep it.  32 -> 32 at 256 x 160 x 160 by itself: 1.49 ms there, 1.51 here, which is where this line
+    // was drawn; between the other launches of a step it is 1.60 - 1.65 ms there and 1.41 here (11.55 and 11.25 ms the step).  The
+    // other widths would go to the direct kernel.
     return d.kt == 1 && (d.kd == 1 || d.kd == 3) && d.kh == 3 && d.kw == 3 && Ci % 4 == 0 && Co % 4 == 0 &&
            (d.kd == 1 || Ci % 32 != 0 || Co % 32 != 0) &&
            4.0 * d.W * (Ci > Co ? Ci : Co) < 2.0e9;   // byte offsets inside an image row stay below the out-of-row marker

@@ -87,9 +87,9 @@ def module_cases():
     yield "vol32", synth.Geom(3, 1, 2, 1, 8, 10, 12), synth.chain_prox([2, 32, 32, 2], [K3] * 3), 0
     yield "cine64", synth.Geom(2, 1, 2, 6, 1, 12, 16), synth.chain_prox([2, 64, 64, 64, 2], [KS, KT, KS, KT]), 0
     yield "k5", synth.Geom(2, 1, 2, 1, 1, 10, 12), synth.chain_prox([2, 6, 2], [(1, 1, 5, 5), (1, 1, 1, 5)]), 0
-    # 3x3 layers with 64-multiples of channels take the Winograd kernels: image sizes that the 4 x 32 and 2 x 32
-    # pixel blocks do not divide (transform lengths are even, so odd sizes cannot occur), several images, two
-    # channel blocks on either side, no bias
+    # 3x3 layers with 64-multiples of channels (the Winograd kernels' widths; a plain module runs them on split operands, greedy
+    # and MoDL calls of these networks are in test_gpu_split.py): image sizes that no kernel's pixel blocks divide (transform
+    # lengths are even, so odd sizes cannot occur), several images, two channel blocks on either side, no bias
     yield "wino_ragged", synth.Geom(2, 2, 2, 1, 1, 10, 46), synth.resblock_prox(64, 1), 0
     yield "wino_128", synth.Geom(2, 1, 2, 1, 1, 6, 96), synth.chain_prox([2, 64, 128, 64, 2], [K2] * 4), 0
     yield "wino_nobias_l1", synth.Geom(2, 1, 2, 3, 1, 6, 46), synth.chain_prox([2, 64, 64, 2], [K2] * 3, has_bias=0), 1
@@ -101,8 +101,8 @@ def module_cases():
     yield "thin_time32", synth.Geom(2, 2, 2, 5, 1, 6, 10), synth.chain_prox([2, 32, 2], [KS, KT]), 0
     yield "thin_time64_l1", synth.Geom(2, 1, 2, 3, 1, 6, 46), synth.chain_prox([2, 64, 2], [KS, KT], has_bias=0), 1
     yield "thin_vol128_flat", synth.Geom(3, 1, 2, 1, 4, 6, 46), synth.chain_prox([2, 128, 32, 2], [K3, (1, 1, 1, 1), K3], has_bias=0), 1
-    # 3x3x3 layers with 32-multiples of channels (Winograd inside the slices, runs along the depth): volumes that the
-    # 8 x 32 and 2 x 32 pixel blocks do not divide, one and two slices, two samples, two channel blocks, no bias
+    # 3x3x3 layers with 32-multiples of channels (forward and data gradient on split operands, weight gradient Winograd inside
+    # the slices): volumes that the pixel blocks do not divide, one and two slices, two samples, two channel blocks, no bias
     yield "vol_wino_ragged", synth.Geom(3, 2, 2, 1, 6, 6, 46), synth.chain_prox([2, 32, 64, 32, 2], [K3] * 4), 0
     yield "vol_16_to_32_direct", synth.Geom(3, 1, 2, 1, 4, 6, 12), synth.chain_prox([2, 16, 32, 2], [K3] * 3), 0
     yield "vol_wino_two_slices_l1", synth.Geom(2, 1, 2, 1, 2, 10, 12), synth.chain_prox([2, 32, 32, 2], [K3] * 3, has_bias=0), 1
@@ -207,7 +207,7 @@ def test_backward_is_deterministic_and_decoupled():
     r.step()
     assert np.array_equal(r.results()[2], g1)                 # bit-identical split-K reduction
     assert torch.equal(r.x_in, x_in_before)                   # inputs are never written
-    # the same for the Winograd kernels (64-channel 3x3 layers): partial sums are reduced in a fixed order
+    # the same for 64-channel 3x3 layers: partial sums are reduced in a fixed order
     cw = synth.make_custom(4, synth.Geom(2, 2, 2, 1, 1, 20, 46), synth.resblock_prox(64, 1), accel=2.0, centre=2)
     rw = ModuleRunner(cw)
     rw.step()
@@ -681,7 +681,7 @@ def kernel_policy():
 
 def test_direct_kernels_still_cover_the_winograd_shapes(kernel_policy):
     """GLEAM_POLICY_NO_WINOGRAD routes the 64-channel 3x3 layers through the direct MFMA kernels: one module step
-    that way against the oracle, and the default (Winograd) step on the same inputs beside it."""
+    that way against the oracle, and the default step (split operands) on the same inputs beside it."""
     c = synth.make_custom(31, synth.Geom(2, 1, 2, 1, 1, 24, 46), synth.resblock_prox(64, 1), accel=2.0, centre=2,
                           bias_std=0.1, alpha=0.8)
     kernel_policy(gb.POLICY_NO_WINOGRAD)
@@ -689,8 +689,8 @@ def test_direct_kernels_still_cover_the_winograd_shapes(kernel_policy):
     r_direct, _ = check_module(c)
     gd = r_direct.results()[2].copy()
     kernel_policy(0)
-    r_wino, _ = check_module(c)
-    assert not np.array_equal(r_wino.results()[2], gd)            # two different kernels did run
+    r_split, _ = check_module(c)
+    assert not np.array_equal(r_split.results()[2], gd)            # two different kernels did run
     # the same for a 3x3x3 layer between 32 channels
     c = synth.make_custom(33, synth.Geom(3, 1, 2, 1, 4, 10, 12), synth.chain_prox([2, 32, 32, 2], [K3] * 3), accel=2.0, centre=2,
                           bias_std=0.1, alpha=0.8)
@@ -699,8 +699,8 @@ def test_direct_kernels_still_cover_the_winograd_shapes(kernel_policy):
     r_direct, _ = check_module(c)
     gd = r_direct.results()[2].copy()
     kernel_policy(0)
-    r_wino, _ = check_module(c)
-    assert not np.array_equal(r_wino.results()[2], gd)
+    r_split, _ = check_module(c)
+    assert not np.array_equal(r_split.results()[2], gd)
 
 
 def test_fallback_kernels_of_the_two_channel_layers_and_the_27_tap_gradient(kernel_policy):
