@@ -148,7 +148,8 @@ int gleam_sense_normal_static(const gleam_geom* geom, const gleam_c64* x, const 
  *   x_out  : image, overwritten; must not alias x_in.  Passing it as the next module's x_in is the
  *            detached hand-off between modules.
  * Range: float32 3x3 and 3x3x3 layers whose widths are multiples of 4 take inputs of up to 1.69e38, half the float32 range.
- * An input beyond it, infinity or NaN makes infinity or NaN of the outputs it reaches (and of a few more beside them). */
+ * What overflows there, and an infinity that gets through the layer's own ReLU, comes out as infinity or NaN (also in the pixel
+ * beside the ones it reaches) and passes the ReLUs behind it. */
 int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox,
                      const gleam_c64* x_in, const gleam_c64* S, const uint8_t* M, const gleam_c64* y,
                      float alpha, const float* theta, const gleam_c64* x_ref,
