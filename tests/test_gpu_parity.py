@@ -600,7 +600,8 @@ def test_modl_solver_inside_the_row_sweeps(geom):
     (synth.Geom(2, 1, 2, 1, 2, 192, 368), 0, 6),      # 138 sums, 192 tiles: the inner product only
     (synth.Geom(2, 1, 64, 9, 1, 32, 10), 8, 0),       # 3 sums, 288 tiles: the update only
     (synth.Geom(2, 1, 12, 1, 2, 192, 368), 8, 6),     # 138 sums, 384 tiles: neither
-], ids=["both", "inner_product", "update", "neither"])
+    (synth.Geom(2, 1, 2, 1, 6, 256, 368), 8, 6),      # 512 sums, as many as there are (eight per lane): neither
+], ids=["both", "inner_product", "update", "neither", "most_sums"])
 def test_modl_solver_launches_what_the_sweeps_do_not_take_in(geom, dots, updates):
     """Which of its launches the solver makes by itself, from the library's own records (two solves of four steps each), and
     the results of every mixture against the oracle."""
