@@ -205,11 +205,11 @@ hipError_t cg_solve(const gleam_geom& g, const float2* S, const unsigned char* M
     //     1 x 8 x 640 x 320        200,  320   1270 / 1271 / 1187     2 x 15 x 640 x 368       230,  640   2787 / 2787 / 2813
     //     1 x 5 x 256 x 24 x 160   512, 1024   4245 / 4243 / 4279     1 x 8 x 20 x 192 x 160   512,  960   2114 / 2114 / 2147
     // What the rule takes in has never cost more than 0.2 %; above it, it depends on how many tiles a workgroup has.
-    constexpr int kFusedPartials = 256, kFusedSums = 128;
+    constexpr int kFusedPartials = 256;
     static_assert(kFusedPartials <= kCgBlocksMax, "what sum_partials takes");
     const int room = 3 * kCgBlocksMax - 2 * nb, n_dot = cg_fused_dot_partials(g, room < kFusedPartials ? room : kFusedPartials);
     const int n_pq = n_dot ? n_dot : nb;
-    const bool fuse_p = nb <= kFusedSums && cg_fused_update(g);
+    const bool fuse_p = nb <= kCgFusedSums && cg_fused_update(g);
     for (int k = 0; k < n_cg; ++k) {
         double* cur = rr[k & 1];
         double* nxt = rr[(k + 1) & 1];

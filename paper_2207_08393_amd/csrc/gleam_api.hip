@@ -273,8 +273,8 @@ static int module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, bool 
     // Without a saved buffer (inference) the activations live in the workspace, after the k-space buffer.
     unsigned char* act_base = saved ? (unsigned char*)saved : (unsigned char*)ws + plan.k_bytes;
     float2* u = (float2*)(act_base + plan.act_off[0]);
-    hipError_t e = sense_dc(*geom, (const float2*)x_in, (const float2*)S, M, (const float2*)y, 1.f, -alpha, u,
-                            (float2*)ws, st);
+    hipError_t e = (plan.staged ? sense_dc_staged : sense_dc)(*geom, (const float2*)x_in, (const float2*)S, M, (const float2*)y,
+                                                              1.f, -alpha, u, (float2*)ws, st);
     if (e != hipSuccess) return GLEAM_E_LAUNCH;
     e = prox_forward(*geom, *prox, plan, theta, act_base, (const float2*)x_ref, (float2*)x_out, loss, ws, st);
     return e == hipSuccess ? GLEAM_OK : GLEAM_E_LAUNCH;

@@ -40,7 +40,12 @@ struct KernelScope {
 hipError_t sense_dc(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M,
                     const float2* y, float xs, float gs, float2* out, float2* kbuf, hipStream_t st);
 
+// The same by the kernels staged through LDS (ProxPlan::staged); y may be null for one transformed axis only.
+hipError_t sense_dc_staged(const gleam_geom& g, const float2* x, const float2* S, const unsigned char* M, const float2* y, float xs,
+                           float gs, float2* out, float2* kbuf, hipStream_t st);
+
 constexpr int kCgBlocksMax = 512;  // workgroups (= partial sums) per batch sample
+constexpr int kCgFusedSums = 128;  // at most so many where the first sweep updates the search direction
 
 // What the conjugate-gradient solver has the two row sweeps of an operator application do on the side.  One system per
 // batch sample; every scalar stays on the device.
@@ -79,6 +84,9 @@ struct ProxPlan {
     // module with the complex-l1 loss takes d / |d| of residuals that the solve drives to zero, and is 1e-6 .. 5e-4 from the
     // 64-bit result by input, with either arithmetic.
     bool split;
+    // Whether the data-consistency step takes the sweeps staged through LDS: where float32 layers that have split kernels are kept
+    // from them, and for the same reason.
+    bool staged;
     long long Q;                      // pixels B*T*D*H*W
     size_t act_off[kMaxLayers + 1];   // t_l inside saved, l < L
     size_t gz_off;

@@ -2040,6 +2040,9 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, bool split, ProxPl
     ProxPlan other;
     plan_one(g, p, !split, other);
     plan_one(g, p, split, plan);
+    plan.staged = false;
+    if (p.dtype == 0 && !(split && wino_enabled()))
+        for (int l = 0; l < p.n_layers; ++l) plan.staged |= conv_split_applies(pix_dims(g, p.layers[l]), p.layers[l].cin, p.layers[l].cout);
     // one pair of buffer sizes for every entry point
     if (other.ws_bytes > plan.ws_bytes) plan.ws_bytes = other.ws_bytes;
     if (other.saved_bytes > plan.saved_bytes) plan.saved_bytes = other.saved_bytes;

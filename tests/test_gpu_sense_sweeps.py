@@ -1,0 +1,76 @@
+"""The operator's sweeps at the edges of their tiles, against the oracle's explicit transforms.
+
+A value passes 2 d transforms of at most two butterflies each; a butterfly of R <= 32 points is at most log2(R) + 2 roundings
+deep, its twiddles one more.  With roundings of 2^-24 / sqrt(3) that are independent of one another, three transformed axes give
+sqrt(6 * 2 * 8) * 3.4e-8 = 3.4e-7; the bound is three times that (measured 1.0e-7 to 1.8e-7)."""
+import numpy as np
+import pytest
+
+from oracle import gleam_oracle as og
+from paper_2207_08393_amd import binding as gb
+from paper_2207_08393_amd import synth
+from tests.gpu_util import assert_image_close, run_sense_normal
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-6
+LENGTHS = (4, 6, 8, 10, 12, 16, 20, 24, 32, 46, 64, 96, 128, 160, 192, 256, 320, 368, 640)
+
+
+def inputs(nd, B, C, T, D, H, W, centred, seed):
+    r = np.random.default_rng(seed)
+    z = lambda *s: (r.standard_normal(s) + 1j * r.standard_normal(s)).astype(np.complex64)  # noqa: E731
+    return (synth.Geom(nd, B, C, T, D, H, W, centred=centred), z(B, T, D, H, W), z(B, C, D, H, W),
+            (r.random((B, T, D, H, W)) < 0.4).astype(np.uint8), z(B, C, T, D, H, W))
+
+
+def check(geom, x, S, M, y):
+    import torch
+    print("case", geom, flush=True)
+    cen = bool(geom.centred)
+    got = run_sense_normal(geom, x, S, M)
+    assert_image_close(got, og.sense_normal(x, S, M, geom.ndim_fft, centred=cen), TOL, "A^H A x")
+    g = gb.gleam_geom(geom.ndim_fft, geom.centred, *(x.shape[:1] + S.shape[1:2] + x.shape[1:]))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    real = lambda a: torch.view_as_real(dev(a)).contiguous()  # noqa: E731
+    out, ws = torch.empty(x.shape + (2,), device="cuda"), torch.empty(
+        int(gb.gleam_workspace_bytes(g, None)[0]) + x.nbytes + 512, dtype=torch.uint8, device="cuda")
+    gb.gleam_sense_adjoint(g, real(S), dev(M), real(y), out, ws)
+    got = torch.view_as_complex(out).cpu().numpy()
+    ref = og.sense_adjoint(y.astype(np.complex128) * M[:, None], S, M, geom.ndim_fft, centred=cen)
+    assert_image_close(got, ref, TOL, "A^H y")
+
+
+# coils and rows that leave a tile of 16, 8 or 64 lines ragged: one coil, a full tile, one more, more than 64
+@pytest.mark.parametrize("coils", [1, 3, 16, 17, 65])
+@pytest.mark.parametrize("W", [20, 32, 46, 64, 160, 368, 640])
+def test_rows_and_coils_that_do_not_fill_a_tile(W, coils):
+    for nd, H in ((2, 6), (1, 19)):
+        check(*inputs(nd, 1, coils, 2, 1, H, W, coils % 2, W + coils))
+
+
+# every length along both strided axes; W = 20 and 46 leave the column tiles ragged, and the mask's rows unaligned
+@pytest.mark.parametrize("N", LENGTHS)
+def test_every_length_along_the_strided_axes(N):
+    for nd, D, H, W in ((2, 2, N, 20), (3, N, 4, 46), (3, 4, N, 16)):
+        check(*inputs(nd, 1, 2, 1, D, H, W, N % 4 == 0, N + D))
+
+
+# so many tiles that the columns go 32 at a time and a workgroup of the first sweep takes several coils
+@pytest.mark.parametrize("H, W", [(96, 32), (256, 20)])
+def test_many_tiles(H, W):
+    check(*inputs(2, 1, 8, 1, 256 * 96 // H, H, W, 0, H))
+
+
+# the solver's sweeps: rows that do not divide into tiles, the update of the search direction, one sample and three
+@pytest.mark.parametrize("B, C, H, W", [(1, 5, 46, 20), (3, 3, 6, 46), (2, 8, 10, 160), (1, 16, 20, 368), (2, 7, 24, 640)])
+def test_solver(B, C, H, W):
+    from paper_2207_08393_amd.runner import ModlRunner
+    geom = synth.Geom(2, B, C, 1, 1, H, W)
+    c = synth.make_custom(H + W, geom, synth.chain_prox([2, 8, 2], [(1, 1, 3, 3)] * 2), accel=3.0, centre=2)
+    print("case", geom, flush=True)
+    r = ModlRunner(c, 0.5, 4)
+    r.step()
+    x = r.results()[0]
+    aty = og.sense_adjoint(c.y.astype(np.complex128), c.S, c.M, 2)
+    f = og.modl_module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, aty, 0.5, 4, c.theta, c.x_true)
+    assert_image_close(x, f["x_out"], 4 * TOL, "MoDL x_out")   # four steps, each with an operator of its own in float32
