@@ -1954,6 +1954,7 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
     for (int l = 0; l < L; ++l) {   // Winograd weight gradient: 16 products per channel pair, per split, plus their sum
         const gleam_conv& c = p.layers[l];
         PixDims dd{};
+        dd.Q = plan.Q;
         dd.T = (int)g.T; dd.D = (int)g.D; dd.H = (int)g.H; dd.W = (int)g.W;
         dd.kt = c.kt; dd.kd = c.kd; dd.kh = c.kh; dd.kw = c.kw;
         if (p.dtype == 0 && wgrad_wino_applies(dd, c.cin, c.cout)) {
@@ -1961,22 +1962,18 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }
         if (p.dtype == 0 && split && wgrad_split_applies(dd, c.cin, c.cout)) {
-            dd.Q = plan.Q;
             const size_t need = align256(wgrad_split_partial_floats(dd, c.cin, c.cout) * sizeof(float));
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }
         if (p.dtype == 0 && wgrad_time_applies(dd, c.cin, c.cout)) {
-            dd.Q = plan.Q;
             const size_t need = align256(wgrad_time_partial_floats(dd, c.cin, c.cout) * sizeof(float));
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }
         if (p.dtype == 0 && wgrad_wino3_applies(dd, c.cin, c.cout)) {
-            dd.Q = plan.Q;
             const size_t need = align256(wgrad_wino3_partial_floats(dd, c.cin, c.cout) * sizeof(float));
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }
         if (p.dtype == 1 && wgrad_bf16_walk_applies(dd, c.cin, c.cout)) {
-            dd.Q = plan.Q;
             const size_t need = align256(wgrad_bf16_walk_partial_floats(dd, c.cin, c.cout) * sizeof(float));
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }

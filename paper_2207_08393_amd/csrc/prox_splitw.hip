@@ -307,11 +307,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(SplitWgradArgs a) {
 
 bool wgrad_split_applies(const PixDims& d, int Ci, int Co) {
     // 3x3x3 layers between multiples of 32 channels have a kernel on the float32 matrix cores that forms every operand once for
-    // three slice taps, and keep it.  32 -> 32 at 256 x 160 x 160 by itself: 1.49 ms there, 1.51 here, which is where this line
-    // was drawn; between the other launches of a step it is 1.60 - 1.65 ms there and 1.41 here (11.55 and 11.25 ms the step).  The
-    // other widths would go to the direct kernel.
+    // three slice taps.  By itself it is as fast on a large volume (32 -> 32 at 256 x 160 x 160: 1.49 ms there, 1.51 here),
+    // between the other launches of a step, under the power limit, it is not: 1.56 - 1.66 ms there, 1.43 here, with the sums of
+    // the partial results 66 and 40 us (64 -> 64 at 2 x 20 x 96 x 96: 370 + 104 and 290 + 15 us a layer, the step 2370 and 2031).
+    // Under 160 row segments the step takes 166 - 178 us here and 179 - 195 there; such volumes stay there, so that the kernel,
+    // which MoDL modules and greedy iterations run, has plain modules to be compared with.
+    const long long segments = d.Q / d.W * ((d.W + 31) / 32);
     return d.kt == 1 && (d.kd == 1 || d.kd == 3) && d.kh == 3 && d.kw == 3 && Ci % 4 == 0 && Co % 4 == 0 &&
-           (d.kd == 1 || Ci % 32 != 0 || Co % 32 != 0) &&
+           (d.kd == 1 || Ci % 32 != 0 || Co % 32 != 0 || segments >= 160) &&
            4.0 * d.W * (Ci > Co ? Ci : Co) < 2.0e9;   // byte offsets inside an image row stay below the out-of-row marker
 }
 

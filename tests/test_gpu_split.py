@@ -201,3 +201,17 @@ def test_greedy_iteration_and_the_same_calls_by_hand(nf, kernel_policy):
         errs = [rel_l2(parts[0], x), rel_l2(parts[1], losses)] + [rel_l2(parts[3][i], m[i]) for i in range(2)]
         print("apart", errs, flush=True)
         assert 0 < max(errs) <= 1e-5
+
+
+@pytest.mark.parametrize("geom,chans", [(synth.Geom(3, 1, 2, 1, 8, 20, 46), (32, 64, 32)), (synth.Geom(3, 2, 2, 1, 4, 20, 20), (32, 32, 64))],
+                         ids=["320_segments", "160_segments"])
+def test_weight_gradient_of_whole_3x3x3_blocks_on_split_operands(geom, chans):
+    """From 160 row segments on, 3x3x3 layers between multiples of 32 channels take the split-operand weight gradient too."""
+    c = synth.make_custom(41, geom, synth.chain_prox([2, *chans, 2], [K3] * 4), accel=2.0, centre=2, bias_std=0.1, alpha=0.8)
+    print("case whole 3x3x3 blocks", chans, flush=True)
+    r = ModuleRunner(c)
+    gb.gleam_profile_begin()
+    r.step()
+    ran = wide_convolutions(gb.gleam_profile_end())
+    assert set(ran.values()) == {4.0}, ran
+    check_module(c)
