@@ -22,8 +22,8 @@
 // two-dimensional F(2x2, 3x3) needs a third less matrix work again but twice the accumulators per pixel: half the pixels per
 // pass over the transformed weights, whose traffic out of L2 would then bound the kernel.
 //
-// Work split.  A workgroup of 4 waves owns 8 x 32 output pixels x 32 output channels, two workgroups share a CU.  Wave nu
-// owns transform position nu: accumulators r = 0..3 of 32 channels x 32 tiles, where accumulator r holds the 16 tiles (pixel
+// Work split.  A workgroup of 4 waves owns 8 x 32 output pixels x 32 output channels (4 x 32 on small grids: two accumulators
+// instead of the four below), two workgroups share a CU.  Wave nu owns transform position nu: accumulators r = 0..3 of 32 channels x 32 tiles, where accumulator r holds the 16 tiles (pixel
 // pairs) of output row r and those of row r + 4.  The operand made from input rows (j, j + 4) then serves output rows
 // (j - ky, j + 4 - ky) of all three row taps ky: 6 operands for 12 products.  A chunk is 16 input channels of one slice: the
 // raw region (10 rows x 34 columns, zeros outside the image through the bounds of a buffer resource) is loaded straight into
@@ -50,12 +50,12 @@ constexpr int kChunk = 16;                 // input channels per chunk: the dept
 constexpr int kOperand = 64 * 8;           // bfloat16 values of one weight operand (64 lanes x 8)
 constexpr int kExFloats = 4 * 32 * 32;     // exchange of one pass: 4 positions x 32 tiles x 32 channels
 
-constexpr int G = 4;                       // a block has 2G rows
-constexpr int kRows = 2 * G + 2;
-constexpr int kSlots = kRows * 34 * 4;     // 16-byte quads of a raw region
-constexpr int kWaveLoads = (kSlots + 63) / 64, kLoads = (kWaveLoads + 3) / 4;   // wave-wide direct loads, and per wave
-constexpr int kRawFloats = kWaveLoads * 256;
-static_assert(kExFloats <= kRawFloats, "the exchange reuses a region");
+template <int G> struct Region {             // a block has 2G rows
+    static constexpr int kRows = 2 * G + 2;
+    static constexpr int kSlots = kRows * 34 * 4;     // 16-byte quads of a raw region
+    static constexpr int kWaveLoads = (kSlots + 63) / 64, kLoads = (kWaveLoads + 3) / 4;   // wave-wide direct loads, and per wave
+    static constexpr int kRawFloats = kWaveLoads * 256 > kExFloats ? kWaveLoads * 256 : kExFloats;   // the exchange reuses a region
+};
 
 // exchange element (position, tile, channel quad): the quad index is XOR-ed with bits of the tile index so that the 16
 // lanes LDS serves together touch 16 different 16-byte bank groups on both sides
@@ -64,8 +64,9 @@ __device__ __forceinline__ int ex_off(int pos, int tile, int cq) { return ((pos 
 }  // namespace
 
 // EPI: the call has a ReLU mask or a tensor to add (1: the mask, if any, is a tensor; 2: it is sign words); 0: neither
-template <int KD, bool RELU, int EPI>
+template <int KD, bool RELU, int EPI, int G>
 __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
+    constexpr int kRows = Region<G>::kRows, kWaveLoads = Region<G>::kWaveLoads, kLoads = Region<G>::kLoads, kRawFloats = Region<G>::kRawFloats;
     // Separate LDS objects: reads of one region then do not wait for direct loads into the other.
     __shared__ __attribute__((aligned(16))) float rawA[kRawFloats];
     __shared__ __attribute__((aligned(16))) float rawB[kRawFloats];
@@ -337,11 +338,11 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
                     v = __builtin_amdgcn_classf(v, out_class) ? out_instead : v;
                     if constexpr (EPI != 0) {
                         const int idx = 8 * g + 4 * jj + e;
-                        const int pass = EPI == 2 ? __builtin_amdgcn_sbfe(sign_in, 31 - idx, 1) : (__uint_as_float(refv[jj][e]) > 0.f ? -1 : 0);
+                        const int pass = EPI == 2 ? __builtin_amdgcn_sbfe(sign_in, 8 * G - 1 - idx, 1) : (__uint_as_float(refv[jj][e]) > 0.f ? -1 : 0);
                         v = __int_as_float(__float_as_int(v) & (pass | no_acc));
                         v += __int_as_float((int)addv[jj][e] & (pass | no_add));
                     }
-                    if (a.bits_out) sign_out = sign_out + sign_out + (v > 0.f ? 1u : 0u);   // value 0 ends up in bit 31
+                    if (a.bits_out) sign_out = sign_out + sign_out + (v > 0.f ? 1u : 0u);   // value 0 ends up in the highest bit
                     o[e] = __float_as_uint(v);
                 }
                 store16(r_out, o, off_px[jj], row_off);
@@ -442,9 +443,18 @@ size_t conv_split_weight_floats(int K, int Nn, int kd) {
     return (size_t)((Nn + 31) / 32) * ((K + kChunk - 1) / kChunk) * kd * 36 * kOperand / 2;
 }
 
-size_t conv_split_sign_words(const PixDims& d, int Nn) {
-    const size_t ni = (size_t)(d.Q / ((long long)d.H * d.W));   // one word per thread, block and group of 32 channels
-    return ni * ((d.W + 31) / 32) * ((d.H + 2 * G - 1) / (2 * G)) * 256 * (size_t)((Nn + 31) / 32);
+// Rows of a block: 8, and 4 where blocks of 8 would leave CUs without one (half of them, with the longer chunk sequence of 27
+// taps: a block of 4 rows forms four operands for 36 matrix instructions, one of 8 six for 72).  A residual block's layers, us
+// with blocks of 8 and of 4 (workgroups of 8): 64 x 64, 16 channels (16) 9.4 / 7.6, 64 channels (32) 14.8 / 11.2; 160 x 128, 32
+// channels (80) 13.0 / 10.3; 2 x 128 x 160, 32 channels (160) 13.0 / 11.6; 256 x 256, 32 channels (256) 14.0 / 12.9; 128 x 128,
+// 128 channels (256) 25.1 / 25.6; 27 taps, 10 x 96 x 32, 64 channels (240) 31.0 / 31.9, 8 x 20 x 24, 32 channels (24) 17.2 / 12.9.
+static long long split_blocks(const PixDims& d, int rows) {
+    return d.Q / ((long long)d.H * d.W) * ((d.W + 31) / 32) * ((d.H + rows - 1) / rows);
+}
+static int split_rows(const PixDims& d, int Nn) { return split_blocks(d, 8) * ((Nn + 31) / 32) <= (d.kd == 3 ? 128 : 256) ? 4 : 8; }
+
+size_t conv_split_sign_words(const PixDims& d, int Nn) {   // one word per thread, block and group of 32 channels
+    return (size_t)split_blocks(d, split_rows(d, Nn)) * 256 * (size_t)((Nn + 31) / 32);
 }
 
 hipError_t split_weights_batch(const SplitWeightBatch& b, hipStream_t st) {
@@ -462,16 +472,16 @@ hipError_t split_weights_batch(const SplitWeightBatch& b, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int KD>
+template <int KD, int G>
 static void launch_conv_split_t(const SplitConvArgs& a, dim3 grid, int relu_in, hipStream_t st) {
     const int epi = a.bits_in ? 2 : a.mask_ref || a.add ? 1 : 0;
     if (relu_in) {   // a forward launch: no mask
-        if (epi) hipLaunchKernelGGL((conv_split_kernel<KD, true, 1>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((conv_split_kernel<KD, true, 0>), grid, dim3(256), 0, st, a);
+        if (epi) hipLaunchKernelGGL((conv_split_kernel<KD, true, 1, G>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((conv_split_kernel<KD, true, 0, G>), grid, dim3(256), 0, st, a);
     } else {
-        if (epi == 2) hipLaunchKernelGGL((conv_split_kernel<KD, false, 2>), grid, dim3(256), 0, st, a);
-        else if (epi) hipLaunchKernelGGL((conv_split_kernel<KD, false, 1>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((conv_split_kernel<KD, false, 0>), grid, dim3(256), 0, st, a);
+        if (epi == 2) hipLaunchKernelGGL((conv_split_kernel<KD, false, 2, G>), grid, dim3(256), 0, st, a);
+        else if (epi) hipLaunchKernelGGL((conv_split_kernel<KD, false, 1, G>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((conv_split_kernel<KD, false, 0, G>), grid, dim3(256), 0, st, a);
     }
 }
 
@@ -479,15 +489,21 @@ hipError_t launch_conv_split(SplitConvArgs a, const PixDims& d, int relu_in, con
     const int nb = (a.Nn + 31) / 32;
     a.H = d.H; a.W = d.W; a.D = d.D;
     a.bx_n = (a.W + 31) / 32;
-    a.by_n = (a.H + 2 * G - 1) / (2 * G);
-    a.n_blocks = d.Q / ((long long)d.H * d.W) * a.bx_n * a.by_n;
+    const int rows = split_rows(d, a.Nn);
+    a.by_n = (a.H + rows - 1) / rows;
+    a.n_blocks = split_blocks(d, rows);
     const long long cap = 512 / nb > 8 ? 512 / nb : 8;   // two workgroups per CU in total
     const dim3 grid((unsigned)(((a.n_blocks < cap ? a.n_blocks : cap) + 7) / 8 * 8), (unsigned)nb);
     const double direct = 2.0 * (double)d.Q * a.K * a.Nn * 9 * d.kd;
     // F(2, 3) along the rows: 4 multiplications of 6; six bfloat16 products per multiplication
     KernelScope ks(name, direct, 4.0 * (double)d.Q * (a.K + a.Nn), st, direct * 4.0);
-    if (d.kd == 3) launch_conv_split_t<3>(a, grid, relu_in, st);
-    else launch_conv_split_t<1>(a, grid, relu_in, st);
+    if (rows == 8) {
+        if (d.kd == 3) launch_conv_split_t<3, 4>(a, grid, relu_in, st);
+        else launch_conv_split_t<1, 4>(a, grid, relu_in, st);
+    } else {
+        if (d.kd == 3) launch_conv_split_t<3, 2>(a, grid, relu_in, st);
+        else launch_conv_split_t<1, 2>(a, grid, relu_in, st);
+    }
     return hipGetLastError();
 }
 

@@ -215,3 +215,17 @@ def test_weight_gradient_of_whole_3x3x3_blocks_on_split_operands(geom, chans):
     ran = wide_convolutions(gb.gleam_profile_end())
     assert set(ran.values()) == {4.0}, ran
     check_module(c)
+
+
+# the last grid of 4-row blocks and the first of 8-row ones (256 workgroups, 128 with 27 taps), with sign words between two launches;
+# heights that leave a 4-row block ragged
+@pytest.mark.parametrize("H", [253, 256, 257])
+def test_blocks_of_four_and_eight_rows_2d(H):
+    check_module(synth.make_custom(51, synth.Geom(1, 1, 2, 1, 4, H, 46), synth.chain_prox([2, 20, 32, 2], [K2] * 3), accel=2.0, centre=2,
+                                   bias_std=0.1, alpha=0.8))
+
+
+@pytest.mark.parametrize("D", [64, 96])
+def test_blocks_of_four_and_eight_rows_3d(D):
+    check_module(synth.make_custom(52, synth.Geom(3, 1, 2, 1, D, 10, 20), synth.chain_prox([2, 20, 32, 20, 2], [K3] * 4), accel=2.0,
+                                   centre=2, bias_std=0.1, alpha=0.8))
