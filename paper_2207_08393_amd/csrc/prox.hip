@@ -11,8 +11,9 @@
 // Zero padding is a per-pixel 32-bit tap-validity mask, so pixel tiles are plain runs of the flattened
 // index and never ragged except at the very end of the tensor.
 // 3x3 layers in the plane whose channel counts are multiples of 64 take the Winograd F(2x2, 3x3) kernels of
-// prox_wino.hip instead (forward, data gradient and weight gradient); this file keeps the direct kernels for
-// every other shape, the two-channel first / last layers, the loss, the reductions and the host side.
+// prox_wino.hip instead (forward, data gradient and weight gradient), direct layers of 36 to 104 output channels on many
+// pixels the kernel of prox_cover.hip; this file keeps the direct kernels for every other shape, the two-channel first / last
+// layers, the loss, the reductions and the host side.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -25,21 +26,6 @@
 namespace gleam {
 
 // ------------------------------------------------------------------ forward / data-gradient conv
-struct ConvArgs {
-    const float* in;        // [Q][K]
-    float* out;             // [Q][Nn]
-    const float* wt;        // weights re-laid as LDS images, see weights_image_kernel
-    const float* bias;      // [Nn] or null
-    const float* mask_ref;  // [Q][Nn] or null: ReLU mask source (value > 0 passes)
-    const float* add;       // [Q][Nn] or null: added to the result
-    const unsigned* bits_in;   // Winograd launches only, or null: sign words that stand in for mask_ref
-    unsigned* bits_out;        // Winograd launches only, or null: sign words of the output
-    int K, Nn;              // input / output channels of this GEMM
-    int flip;               // 1: data gradient (only used for naming)
-    int relu_in, relu_out, mask_acc, mask_add;
-    PixDims d;
-};
-
 // Software pipeline: while the MFMAs of chunk i (one row-tap x CK input channels) run out of LDS, the
 // pixel slab and the weight image of chunk i+1 - of the next tile when the tile ends - are already in
 // flight into registers; they are written to LDS between two barriers once the MFMAs are issued.
@@ -1165,13 +1151,14 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scrat
         KernelScope ks(name, 2.0 * (double)a.d.Q * a.K * a.Nn * taps_, 4.0 * (double)a.d.Q * (a.K + a.Nn), st);
         return launch_conv_time(t, a.d, st);
     }
-    const int ck = conv_ck(a.K), nb = conv_nb(a.Nn);
+    const int cover = conv_cover_channels(a.d, a.K, a.Nn);
+    const int ck = conv_ck(a.K), nb = cover ? cover : conv_nb(a.Nn);
     {
         WimgArgs t{};
         t.w = cw.w; t.wt = wt_scratch; t.sn = cw.sn; t.st = cw.st; t.sk = cw.sk;
         t.K = a.K; t.Nn = a.Nn; t.flip = a.flip; t.taps = taps_; t.kw = a.d.kw; t.CK = ck; t.NB = nb;
         t.n_kc = (a.K + ck - 1) / ck; t.n_nb = (a.Nn + nb - 1) / nb;
-        t.total = (long long)conv_wimg_floats(a.K, a.Nn, taps_);
+        t.total = (long long)taps_ * t.n_kc * ck * t.n_nb * nb;
         KernelScope ks("weights_image", 0.0, 8.0 * (double)t.total, st);
         hipLaunchKernelGGL(weights_image_kernel, dim3((unsigned)((t.total + 255) / 256)), dim3(256), 0, st, t);
     }
@@ -1179,6 +1166,7 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scrat
     char name[56];
     snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
     KernelScope ks(name, 2.0 * (double)a.d.Q * a.K * a.Nn * taps_, 4.0 * (double)a.d.Q * (a.K + a.Nn), st);
+    if (cover) return launch_conv_cover(a, st);
     if (nb == 32) return ck == 8 ? launch_conv_t<32, 8>(a, st) : launch_conv_t<32, 16>(a, st);
     return ck == 8 ? launch_conv_t<64, 8>(a, st) : launch_conv_t<64, 16>(a, st);
 }

@@ -153,6 +153,27 @@ __device__ __forceinline__ ChunkIter chunk_next(ChunkIter x, int n_kc, int nck, 
     return x;
 }
 
+// Forward and data-gradient convolution on the fp32 matrix cores (prox.hip, prox_cover.hip).
+struct ConvArgs {
+    const float* in;        // [Q][K]
+    float* out;             // [Q][Nn]
+    const float* wt;        // weights re-laid as LDS images, see weights_image_kernel
+    const float* bias;      // [Nn] or null
+    const float* mask_ref;  // [Q][Nn] or null: ReLU mask source (value > 0 passes)
+    const float* add;       // [Q][Nn] or null: added to the result
+    const unsigned* bits_in;   // Winograd launches only, or null: sign words that stand in for mask_ref
+    unsigned* bits_out;        // Winograd launches only, or null: sign words of the output
+    int K, Nn;              // input / output channels of this GEMM
+    int flip;               // 1: data gradient (only used for naming)
+    int relu_in, relu_out, mask_acc, mask_add;
+    PixDims d;
+};
+
+// Direct convolution with every output channel in one workgroup (prox_cover.hip): output channels per weight image (Nn), 0
+// where the layer does not take it.
+int conv_cover_channels(const PixDims& d, int K, int Nn);
+hipError_t launch_conv_cover(const ConvArgs& a, hipStream_t stream);
+
 // 3x3 and 3x3x3 convolution with operands split into bfloat16 parts, float32 (prox_split.hip).  Same fused epilogue as the
 // direct kernels.
 struct SplitConvArgs {
