@@ -1,5 +1,6 @@
-"""The direct float32 kernels with every output channel in one workgroup (prox_cover.hip), which give the same bits as
-the kernels they stand in for: a batch large enough for them against its samples one by one."""
+"""The direct float32 kernels with every output channel in one workgroup (prox_cover.hip) and the weight gradient in blocks
+across the taps (wgrad_pipe_kernel<.., COVER>), which give the same bits as the kernels they stand in for: a batch large enough for
+them against its samples one by one, and the calls' 64-bit results."""
 import dataclasses
 
 import numpy as np
@@ -9,7 +10,7 @@ from paper_2207_08393_amd import binding as gb
 from paper_2207_08393_amd import synth
 from paper_2207_08393_amd.runner import ModuleRunner
 from tests.gpu_util import rel_l2
-from tests.test_gpu_parity import K2, K3, kernel_policy  # noqa: F401
+from tests.test_gpu_parity import K2, K3, check_module, kernel_policy  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,12 @@ def test_batch_and_its_samples_alike(chans, taps, kernel_policy):
     # the loss is a mean over the pixels; sums in float32 over other runs of pixels: 2e-7 seen, a lost or doubled term of one
     # pixel in 1e5 would be 1e-5
     assert rel_l2(grad, 0.5 * (parts[0] + parts[1])) <= 2e-6
+
+
+# rows and columns that leave blocks of 4 x 4 on both sides, on one, on none; up to sixteen waves of units and small blocks
+@pytest.mark.parametrize("ci,co", [(100, 100), (96, 96), (72, 72), (80, 68), (96, 100), (100, 68), (68, 104), (128, 68), (84, 84)])
+def test_weight_gradient_in_blocks_across_the_taps(ci, co, kernel_policy):
+    kernel_policy(gb.POLICY_NO_WINOGRAD)
+    print("case cover weights", ci, co, flush=True)
+    check_module(synth.make_custom(9, synth.Geom(1, 2, 2, 1, 1, 11, 46), synth.chain_prox([2, ci, co, 2], [K2] * 3), accel=2.0, centre=2,
+                                   bias_std=0.1, alpha=0.8))
