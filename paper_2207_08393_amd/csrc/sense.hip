@@ -18,11 +18,15 @@ namespace gleam {
 // Lines (rows or columns) per workgroup tile and threads per workgroup, by transform length: 16 lines on 256 threads, a thread
 // or two per butterfly, so that a tile is short from its first load to its last store and several workgroups share a CU (reducing rows of
 // 368 on 384 threads: 37 us instead of 31 for 2 x 15 x 640 of them); 8 lines of 640 points (one tile of 16 would fill half of
-// LDS), 64 lines where the whole transform is one butterfly.
-template <int N> constexpr int rows_lines() { return N > 384 ? 8 : N == 46 || N <= 24 ? 64 : 16; }
+// LDS), 64 lines where the whole transform is one butterfly, 128 of them for 8 to 12 points (4 x 16 x 8 x 640 x 8: the operator
+// 47.8 -> 34.6 us, with 12 points 70.8 -> 51.8; with 16 points the 400 frames of 16 x 16 pixels of 16 coils, which fill 128 lines
+// no better, 41.2 -> 47.7).  32 points are two butterflies a line: MANY takes 64 lines, 16 leave 224 of 256 threads without one
+// and are for calls that would have too few tiles (kManyTiles).
+template <int N> constexpr bool rows_have_many() { return N == 32; }
+template <int N, bool MANY = false> constexpr int rows_lines() { return N > 384 ? 8 : N >= 8 && N <= 12 ? 128 : N == 46 || N <= 24 || MANY ? 64 : 16; }
 template <int N> constexpr int reduce_threads() { return 256; }
 template <int N> constexpr int expand_threads() { return N == 320 ? 320 : N == 368 ? 384 : 256; }
-template <int N> constexpr int fused_lines() { return N == 32 ? 64 : N == 64 || N == 96 ? 32 : rows_lines<N>(); }
+template <int N> constexpr int fused_lines() { return N <= 32 ? 64 : N == 64 || N == 96 ? 32 : rows_lines<N>(); }
 // Waves per SIMD that the compiler is asked to leave registers for.
 template <int N> constexpr int rows_min_waves() { return N <= 256 && N != 46 ? 4 : 1; }
 // Columns: 64 bytes a row of 640 points, 128 bytes otherwise; 256 bytes (WIDE) for 96 .. 256 points where there are tiles enough
@@ -109,9 +113,9 @@ template <int R, int T> __device__ __forceinline__ void alternate(float2 (&u)[R]
 // workgroups, which are at about the same coil, keep all memory channels busy: the coils of a volume lie multiples of 1 MiB
 // apart, and with all of them in one tile, 8 x 256 x 160 x 160 took 196 us, 202 us with a workgroup per coil side by side, and
 // takes 175 us = 5.1 TB/s like this.
-template <int N>
+template <int N, bool MANY>
 __global__ __launch_bounds__(expand_threads<N>(), (rows_min_waves<N>())) void rows_expand_kernel(RowsArgs a) {
-    constexpr int L = rows_lines<N>(), NT = expand_threads<N>();
+    constexpr int L = rows_lines<N, MANY>(), NT = expand_threads<N>();
     __shared__ float2 buf[Tile<N, L, true>::kElems];
     // workgroups go to the eight XCDs in turn: those that share a tile to the same one, whose L2 holds its image rows
     const unsigned slot = blockIdx.x >> 3, id = a.first + slot / a.groups * 8 + (blockIdx.x & 7);
@@ -150,9 +154,9 @@ __global__ __launch_bounds__(expand_threads<N>(), (rows_min_waves<N>())) void ro
 // With: x <- r + beta x first (CgFusion).  A tile is lr image rows x all coils; every coil line forms the new values for
 // itself, and those of the first coil write them back behind the first exchange, when no line of the tile reads the old ones
 // any more.
-template <int N>
+template <int N, bool MANY>
 __global__ __launch_bounds__(expand_threads<N>(), (rows_min_waves<N>())) void rows_expand_update_kernel(RowsCgArgs a) {
-    constexpr int L = rows_lines<N>(), NT = expand_threads<N>();
+    constexpr int L = rows_lines<N, MANY>(), NT = expand_threads<N>();
     __shared__ float2 buf[Tile<N, L, true>::kElems];
     const RowTile tile(a, a.first + blockIdx.x);
     const long long at = (tile.frame * a.DH + tile.row0) * N;   // first image element of the tile
@@ -288,9 +292,9 @@ __device__ __forceinline__ float2 dc_value(const RowsArgs& a, float2 g, long lon
 }
 
 // DOT: every tile also writes its part of Re <x, out> (CgFusion), summed in double.
-template <int N, int PER, bool DOT>
+template <int N, bool MANY, int PER, bool DOT>
 __global__ __launch_bounds__(reduce_threads<N>(), (rows_min_waves<N>())) void rows_reduce_kernel(RowsArgsOf<DOT> a) {
-    constexpr int L = rows_lines<N>(), NT = reduce_threads<N>();
+    constexpr int L = rows_lines<N, MANY>(), NT = reduce_threads<N>();
     __shared__ float2 buf[Tile<N, L, true>::kElems];
     __shared__ double red[DOT ? NT / 64 : 1];
     const RowTile tile(a, blockIdx.x + a.first);
@@ -570,17 +574,22 @@ bool fft_size_supported(long long n) {
     }
 }
 
-static int rows_lines_of(long long N) {
-    switch (N) {
-#define X(NN) case NN: return rows_lines<NN>();
+// Whether the row sweeps take 64 lines of 32 points: from so many tiles of 16 on.  The operator, 16 lines / 64, us: 4 x 16 x 8 x
+// 640 x 32 (20480 tiles) 136 / 102, 2 x 20 x 8 x 256 x 32 (5120) 53.5 / 41.4, 16 x 400 x 16 x 32 (6400) 55.5 / 55.6, 16 x 20 x 64 x
+// 32 (1280) 18.3 / 20.6, 4 x 20 x 160 x 32 (800) 16.0 / 16.2, 8 x 64 x 32 (32) 10.4 / 12.4.
+constexpr long long kManyTiles = 2048;
+static bool rows_many(const gleam_geom& g) { return g.W == 32 && g.B * g.C * g.T * g.D * g.H >= 16 * kManyTiles; }
+static int rows_lines_of(const gleam_geom& g) {
+    switch (g.W) {
+#define X(NN) case NN: return rows_have_many<NN>() && rows_many(g) ? rows_lines<NN, true>() : rows_lines<NN>();
         GLEAM_FFT_SIZES(X)
 #undef X
         default: return 1;
     }
 }
-static int reduce_rows_of(long long N, long long C) {
-    switch (N) {
-#define X(NN) case NN: return reduce_rows_per_tile(NN, rows_lines<NN>(), reduce_threads<NN>(), C);
+static int reduce_rows_of(const gleam_geom& g) {
+    switch (g.W) {
+#define X(NN) case NN: return reduce_rows_per_tile(NN, rows_lines_of(g), reduce_threads<NN>(), g.C);
         GLEAM_FFT_SIZES(X)
 #undef X
         default: return 1;
@@ -612,18 +621,18 @@ static long long tile_rows(const gleam_geom& g, long long cg, long long rows, Ro
 }
 
 // Values per thread of a reducing sweep: 1, 2 or 4 (kRedAcc), as many as the tile's rows need.
-template <int N, int PER> static void launch_reduce_t(const RowsCgArgs& a, dim3 grid, hipStream_t st) {
-    if (a.cg_job.dot) hipLaunchKernelGGL((rows_reduce_kernel<N, PER, true>), grid, dim3(reduce_threads<N>()), 0, st, a);
-    else hipLaunchKernelGGL((rows_reduce_kernel<N, PER, false>), grid, dim3(reduce_threads<N>()), 0, st, (const RowsArgs&)a);
+template <int N, bool MANY, int PER> static void launch_reduce_t(const RowsCgArgs& a, dim3 grid, hipStream_t st) {
+    if (a.cg_job.dot) hipLaunchKernelGGL((rows_reduce_kernel<N, MANY, PER, true>), grid, dim3(reduce_threads<N>()), 0, st, a);
+    else hipLaunchKernelGGL((rows_reduce_kernel<N, MANY, PER, false>), grid, dim3(reduce_threads<N>()), 0, st, (const RowsArgs&)a);
 }
-template <int N> static void launch_rows_t(bool reduce, const RowsCgArgs& a, dim3 grid, hipStream_t st) {
+template <int N, bool MANY> static void launch_rows_t(bool reduce, const RowsCgArgs& a, dim3 grid, hipStream_t st) {
     const int per = ((int)a.lr * N + reduce_threads<N>() - 1) / reduce_threads<N>();
     if (!reduce) {
-        if (a.cg_job.r) hipLaunchKernelGGL((rows_expand_update_kernel<N>), grid, dim3(expand_threads<N>()), 0, st, a);
-        else hipLaunchKernelGGL((rows_expand_kernel<N>), grid, dim3(expand_threads<N>()), 0, st, (const RowsArgs&)a);
-    } else if (per <= 1) launch_reduce_t<N, 1>(a, grid, st);
-    else if (per <= 2) launch_reduce_t<N, 2>(a, grid, st);
-    else launch_reduce_t<N, 4>(a, grid, st);
+        if (a.cg_job.r) hipLaunchKernelGGL((rows_expand_update_kernel<N, MANY>), grid, dim3(expand_threads<N>()), 0, st, a);
+        else hipLaunchKernelGGL((rows_expand_kernel<N, MANY>), grid, dim3(expand_threads<N>()), 0, st, (const RowsArgs&)a);
+    } else if (per <= 1) launch_reduce_t<N, MANY, 1>(a, grid, st);
+    else if (per <= 2) launch_reduce_t<N, MANY, 2>(a, grid, st);
+    else launch_reduce_t<N, MANY, 4>(a, grid, st);
 }
 template <int N> static void launch_rows_fused_t(const gleam_geom& g, RowsArgs a, const float2* y, const unsigned char* M, hipStream_t st) {
     if constexpr (N < kFusedStaged) {
@@ -647,10 +656,10 @@ template <int N> static void launch_rows_fused_t(const gleam_geom& g, RowsArgs a
 }
 
 static hipError_t launch_rows(const gleam_geom& g, bool reduce, RowsCgArgs a, hipStream_t st) {
-    const int L = rows_lines_of(g.W);
+    const int L = rows_lines_of(g);
     const bool plain = !reduce && !a.cg_job.r;
     const long long cg = plain ? 1 : g.C < L ? g.C : L;
-    const long long n = tile_rows(g, cg, reduce ? reduce_rows_of(g.W, g.C) : L / cg, a);
+    const long long n = tile_rows(g, cg, reduce ? reduce_rows_of(g) : L / cg, a);
     if (plain) {   // as many coils in turn as leave kExpandGroups workgroups
         const long long turns = n * g.C / kExpandGroups;
         a.groups = (unsigned)(turns <= 1 ? g.C : turns >= g.C ? 1 : (g.C + turns - 1) / turns);
@@ -661,7 +670,13 @@ static hipError_t launch_rows(const gleam_geom& g, bool reduce, RowsCgArgs a, hi
         const long long m = n - first < most ? n - first : most;
         const dim3 grid((unsigned)(plain ? (m + 7) / 8 * 8 * a.groups : m));
         switch (g.W) {
-#define X(NN) case NN: launch_rows_t<NN>(reduce, a, grid, st); break;
+#define X(NN)                                                                         \
+    case NN:                                                                          \
+        if (rows_have_many<NN>() && L == rows_lines<NN, true>())                      \
+            launch_rows_t<NN, rows_have_many<NN>()>(reduce, a, grid, st);             \
+        else                                                                          \
+            launch_rows_t<NN, false>(reduce, a, grid, st);                            \
+        break;
             GLEAM_FFT_SIZES(X)
 #undef X
             default: return hipErrorInvalidValue;
@@ -797,11 +812,11 @@ hipError_t sense_cg(const gleam_geom& g, const float2* x, const float2* S, const
 }
 
 int cg_fused_dot_partials(const gleam_geom& g, int max_partials) {
-    const long long per = reduce_rows_of(g.W, g.C), n = g.T * ((g.D * g.H + per - 1) / per);
+    const long long per = reduce_rows_of(g), n = g.T * ((g.D * g.H + per - 1) / per);
     return g.ndim_fft == 1 || n > max_partials ? 0 : (int)n;
 }
 
-bool cg_fused_update(const gleam_geom& g) { return g.ndim_fft > 1 && g.C <= rows_lines_of(g.W); }
+bool cg_fused_update(const gleam_geom& g) { return g.ndim_fft > 1 && g.C <= rows_lines_of(g); }
 
 // Measured k-space to hybrid space: the inverse transform (centred when the geometry says so) along the outermost
 // transformed axis, in place: H for two transformed axes, D for three.

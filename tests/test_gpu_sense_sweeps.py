@@ -48,6 +48,14 @@ def test_rows_and_coils_that_do_not_fill_a_tile(W, coils):
         check(*inputs(nd, 1, coils, 2, 1, H, W, coils % 2, W + coils))
 
 
+# tiles of 128 short rows, and of 64 rows of 32 points, which calls of 32768 coil rows and more take: coils that fill one, leave it
+# ragged, need a second one; frames that end inside a tile
+@pytest.mark.parametrize("W,coils,D,H", [(8, 2, 1, 46), (8, 16, 1, 46), (10, 3, 1, 46), (12, 127, 1, 46), (12, 129, 1, 46), (8, 128, 1, 46),
+                                         (32, 2, 273, 10), (32, 2, 274, 10), (32, 63, 1, 128), (32, 64, 1, 96), (32, 65, 1, 96), (32, 129, 1, 46)])
+def test_short_rows_and_coils_that_do_not_fill_a_tile(W, coils, D, H):
+    check(*inputs(2, 2, coils, 3, D, H, W, coils % 2, W + coils))
+
+
 # every length along both strided axes; W = 20 and 46 leave the column tiles ragged, and the mask's rows unaligned
 @pytest.mark.parametrize("N", LENGTHS)
 def test_every_length_along_the_strided_axes(N):
@@ -74,3 +82,9 @@ def test_solver(B, C, H, W):
     aty = og.sense_adjoint(c.y.astype(np.complex128), c.S, c.M, 2)
     f = og.modl_module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, aty, 0.5, 4, c.theta, c.x_true)
     assert_image_close(x, f["x_out"], 4 * TOL, "MoDL x_out")   # four steps, each with an operator of its own in float32
+
+
+# ... with 64 rows of 32 points to a tile: coils of a row in one tile, and in two
+@pytest.mark.parametrize("coils", [52, 65])
+def test_solver_with_many_short_rows(coils):
+    test_solver(1, coils, 640, 32)
