@@ -18,12 +18,11 @@ namespace gleam {
 // Lines (rows or columns) per workgroup tile and threads per workgroup, by transform length: 16 lines on 256 threads, a thread
 // or two per butterfly, so that a tile is short from its first load to its last store and several workgroups share a CU (reducing rows of
 // 368 on 384 threads: 37 us instead of 31 for 2 x 15 x 640 of them); 8 lines of 640 points (one tile of 16 would fill half of
-// LDS), 64 lines where the whole transform is one butterfly, 128 of them for 8 to 12 points (4 x 16 x 8 x 640 x 8: the operator
-// 47.8 -> 34.6 us, with 12 points 70.8 -> 51.8; with 16 points the 400 frames of 16 x 16 pixels of 16 coils, which fill 128 lines
-// no better, 41.2 -> 47.7).  32 points are two butterflies a line: MANY takes 64 lines, 16 leave 224 of 256 threads without one
-// and are for calls that would have too few tiles (kManyTiles).
-template <int N> constexpr bool rows_have_many() { return N == 32; }
-template <int N, bool MANY = false> constexpr int rows_lines() { return N > 384 ? 8 : N >= 8 && N <= 12 ? 128 : N == 46 || N <= 24 || MANY ? 64 : 16; }
+// LDS), 64 lines where the whole transform is one butterfly.  MANY, for calls of many tiles (kManyTiles): 64 lines of 32 points, which
+// are two butterflies a line (16 lines leave 224 of 256 threads without one), and 128 lines of 8 to 12 points (64 leave most
+// threads idle in the coil sum).
+template <int N> constexpr bool rows_have_many() { return N == 32 || (N >= 8 && N <= 12); }
+template <int N, bool MANY = false> constexpr int rows_lines() { return N > 384 ? 8 : MANY ? (N == 32 ? 64 : 128) : N == 46 || N <= 24 ? 64 : 16; }
 template <int N> constexpr int reduce_threads() { return 256; }
 template <int N> constexpr int expand_threads() { return N == 320 ? 320 : N == 368 ? 384 : 256; }
 template <int N> constexpr int fused_lines() { return N <= 32 ? 64 : N == 64 || N == 96 ? 32 : rows_lines<N>(); }
@@ -574,14 +573,20 @@ bool fft_size_supported(long long n) {
     }
 }
 
-// Whether the row sweeps take 64 lines of 32 points: from so many tiles of 16 on.  The operator, 16 lines / 64, us: 4 x 16 x 8 x
-// 640 x 32 (20480 tiles) 136 / 102, 2 x 20 x 8 x 256 x 32 (5120) 53.5 / 41.4, 16 x 400 x 16 x 32 (6400) 55.5 / 55.6, 16 x 20 x 64 x
-// 32 (1280) 18.3 / 20.6, 4 x 20 x 160 x 32 (800) 16.0 / 16.2, 8 x 64 x 32 (32) 10.4 / 12.4.
+// Tiles from which the row sweeps take more lines to a tile (MANY).  The operator without / with, us: 4 x 16 x 8 x 640 x 32 (20480
+// tiles) 136 / 102, 2 x 20 x 8 x 256 x 32 (5120) 53.5 / 41.4, 16 x 400 x 16 x 32 (6400) 55.5 / 55.6, 16 x 20 x 64 x 32 (1280)
+// 18.3 / 20.6, 4 x 20 x 160 x 32 (800) 16.0 / 16.2, 8 x 64 x 32 (32) 10.4 / 12.4; 4 x 16 x 8 x 640 x 8 (5120) 47.6 / 34.5, 16 x
+// 400 x 16 x 10 (1600) 36.4 / 35.1, 16 x 20 x 64 x 8 (320) 11.8 / 12.0.
 constexpr long long kManyTiles = 2048;
-static bool rows_many(const gleam_geom& g) { return g.W == 32 && g.B * g.C * g.T * g.D * g.H >= 16 * kManyTiles; }
+template <int N> static int rows_lines_for(const gleam_geom& g) {
+    if constexpr (rows_have_many<N>()) {
+        if (g.B * g.C * g.T * g.D * g.H >= kManyTiles * rows_lines<N>()) return rows_lines<N, true>();
+    }
+    return rows_lines<N>();
+}
 static int rows_lines_of(const gleam_geom& g) {
     switch (g.W) {
-#define X(NN) case NN: return rows_have_many<NN>() && rows_many(g) ? rows_lines<NN, true>() : rows_lines<NN>();
+#define X(NN) case NN: return rows_lines_for<NN>(g);
         GLEAM_FFT_SIZES(X)
 #undef X
         default: return 1;
@@ -589,7 +594,7 @@ static int rows_lines_of(const gleam_geom& g) {
 }
 static int reduce_rows_of(const gleam_geom& g) {
     switch (g.W) {
-#define X(NN) case NN: return reduce_rows_per_tile(NN, rows_lines_of(g), reduce_threads<NN>(), g.C);
+#define X(NN) case NN: return reduce_rows_per_tile(NN, rows_lines_for<NN>(g), reduce_threads<NN>(), g.C);
         GLEAM_FFT_SIZES(X)
 #undef X
         default: return 1;
@@ -672,7 +677,7 @@ static hipError_t launch_rows(const gleam_geom& g, bool reduce, RowsCgArgs a, hi
         switch (g.W) {
 #define X(NN)                                                                         \
     case NN:                                                                          \
-        if (rows_have_many<NN>() && L == rows_lines<NN, true>())                      \
+        if (rows_have_many<NN>() && L != rows_lines<NN>())                            \
             launch_rows_t<NN, rows_have_many<NN>()>(reduce, a, grid, st);             \
         else                                                                          \
             launch_rows_t<NN, false>(reduce, a, grid, st);                            \

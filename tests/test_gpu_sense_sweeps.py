@@ -48,10 +48,11 @@ def test_rows_and_coils_that_do_not_fill_a_tile(W, coils):
         check(*inputs(nd, 1, coils, 2, 1, H, W, coils % 2, W + coils))
 
 
-# tiles of 128 short rows, and of 64 rows of 32 points, which calls of 32768 coil rows and more take: coils that fill one, leave it
-# ragged, need a second one; frames that end inside a tile
-@pytest.mark.parametrize("W,coils,D,H", [(8, 2, 1, 46), (8, 16, 1, 46), (10, 3, 1, 46), (12, 127, 1, 46), (12, 129, 1, 46), (8, 128, 1, 46),
-                                         (32, 2, 273, 10), (32, 2, 274, 10), (32, 63, 1, 128), (32, 64, 1, 96), (32, 65, 1, 96), (32, 129, 1, 46)])
+# Tiles of 128 rows of 8 to 12 points and of 64 rows of 32, which calls of 131072 and of 32768 coil rows and more take, on both sides
+# of these lines: coils that fill a tile, leave it ragged, need a second one; frames that end inside a tile
+@pytest.mark.parametrize("W,coils,D,H", [(8, 2, 1092, 10), (8, 2, 1093, 10), (8, 16, 137, 10), (10, 3, 729, 10), (12, 127, 4, 46),
+                                         (12, 128, 4, 46), (12, 129, 4, 46), (32, 2, 273, 10), (32, 2, 274, 10), (32, 63, 1, 128),
+                                         (32, 64, 1, 96), (32, 65, 1, 96), (32, 129, 1, 46)])
 def test_short_rows_and_coils_that_do_not_fill_a_tile(W, coils, D, H):
     check(*inputs(2, 2, coils, 3, D, H, W, coils % 2, W + coils))
 
@@ -84,7 +85,7 @@ def test_solver(B, C, H, W):
     assert_image_close(x, f["x_out"], 4 * TOL, "MoDL x_out")   # four steps, each with an operator of its own in float32
 
 
-# ... with 64 rows of 32 points to a tile: coils of a row in one tile, and in two
-@pytest.mark.parametrize("coils", [52, 65])
-def test_solver_with_many_short_rows(coils):
-    test_solver(1, coils, 640, 32)
+# ... with 64 rows of 32 points and 128 of 8 to a tile: coils of a row in one tile, and in two
+@pytest.mark.parametrize("B,coils,W", [(1, 52, 32), (1, 65, 32), (2, 103, 8), (2, 129, 8)])
+def test_solver_with_many_short_rows(B, coils, W):
+    test_solver(B, coils, 640, W)
