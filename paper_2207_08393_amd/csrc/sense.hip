@@ -225,17 +225,22 @@ __global__ __launch_bounds__(expand_threads<N>(), (rows_min_waves<N>())) void ro
 
 // Inverse transform along W and coil reduction.  A tile is lr image rows x cg coils transformed together; then
 // out = xs*x + gs * sum_c conj(S_c) * row_c is accumulated in registers, looping over coil groups when C > cg.  The per-coil
-// images never leave LDS.  lr is capped so that a thread owns at most kRedAcc output values.
+// images never leave LDS.  lr is capped so that a thread owns at most kRedAcc output values, twice as many where rows of 640 points
+// would leave half of the tile's eight lines or more without work (one row a tile, up to four coils: 2 x 32 x 256 x 640, the
+// sweep with one coil 179 us, 92 where it is staged through LDS; the operator 323 -> 220, with four coils 822 -> 746).
 constexpr int kRedAcc = 4;
+constexpr bool reduce_has_double(int N) { return N > 384; }
 static inline int reduce_rows_per_tile(int N, int L, int threads, long long C) {
-    const int lr = L / (C < L ? (int)C : L), most = kRedAcc * threads / N < 1 ? 1 : kRedAcc * threads / N;
+    const int cg = C < L ? (int)C : L, lr = L / cg;
+    int most = kRedAcc * threads / N < 1 ? 1 : kRedAcc * threads / N;
+    if (reduce_has_double(N) && 2 * most * cg <= L) most = 2 * kRedAcc * threads / N;
     return lr < most ? lr : most;
 }
 
 // The coil sum of one tile, PER values per thread.  The coil maps of the first kMaps coils of a group, as a rule all there
 // are, are requested ahead of its transform.
 template <int N, int L, int NT, int PER> struct CoilSum {
-    static constexpr int kMaps = (N > 384 ? 8 : 16) / PER;
+    static constexpr int kMaps = (N > 384 && PER <= 4 ? 8 : 16) / PER;
     using Lay = Tile<N, L, true>;
     float2 acc[PER], sv[PER][kMaps];
     const float2* sp[PER];   // coil map of the first coil at the thread's values
@@ -625,7 +630,7 @@ static long long tile_rows(const gleam_geom& g, long long cg, long long rows, Ro
     return n;
 }
 
-// Values per thread of a reducing sweep: 1, 2 or 4 (kRedAcc), as many as the tile's rows need.
+// Values per thread of a reducing sweep: 1, 2, 4 (kRedAcc) or 8, as many as the tile's rows need.
 template <int N, bool MANY, int PER> static void launch_reduce_t(const RowsCgArgs& a, dim3 grid, hipStream_t st) {
     if (a.cg_job.dot) hipLaunchKernelGGL((rows_reduce_kernel<N, MANY, PER, true>), grid, dim3(reduce_threads<N>()), 0, st, a);
     else hipLaunchKernelGGL((rows_reduce_kernel<N, MANY, PER, false>), grid, dim3(reduce_threads<N>()), 0, st, (const RowsArgs&)a);
@@ -637,7 +642,8 @@ template <int N, bool MANY> static void launch_rows_t(bool reduce, const RowsCgA
         else hipLaunchKernelGGL((rows_expand_kernel<N, MANY>), grid, dim3(expand_threads<N>()), 0, st, (const RowsArgs&)a);
     } else if (per <= 1) launch_reduce_t<N, MANY, 1>(a, grid, st);
     else if (per <= 2) launch_reduce_t<N, MANY, 2>(a, grid, st);
-    else launch_reduce_t<N, MANY, 4>(a, grid, st);
+    else if (per <= 4 || !reduce_has_double(N)) launch_reduce_t<N, MANY, 4>(a, grid, st);
+    else if constexpr (reduce_has_double(N)) launch_reduce_t<N, MANY, 8>(a, grid, st);
 }
 template <int N> static void launch_rows_fused_t(const gleam_geom& g, RowsArgs a, const float2* y, const unsigned char* M, hipStream_t st) {
     if constexpr (N < kFusedStaged) {

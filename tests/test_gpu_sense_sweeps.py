@@ -57,6 +57,14 @@ def test_short_rows_and_coils_that_do_not_fill_a_tile(W, coils, D, H):
     check(*inputs(2, 2, coils, 3, D, H, W, coils % 2, W + coils))
 
 
+# rows of 640 points with so few coils that a tile takes three rows of them, or two: rows that do not divide by that
+@pytest.mark.parametrize("coils", [1, 2, 3, 4, 5])
+def test_long_rows_of_few_coils(coils):
+    for nd, D, H in ((2, 1, 20), (3, 4, 10)):
+        check(*inputs(nd, 2, coils, 2, D, H, 640, coils % 2, coils))
+    test_solver(2, coils, 10, 640)
+
+
 # every length along both strided axes; W = 20 and 46 leave the column tiles ragged, and the mask's rows unaligned
 @pytest.mark.parametrize("N", LENGTHS)
 def test_every_length_along_the_strided_axes(N):
