@@ -30,13 +30,16 @@ template <int N> constexpr int fused_lines() { return N <= 32 ? 64 : N == 64 || 
 template <int N> constexpr int rows_min_waves() { return N <= 256 && N != 46 ? 4 : 1; }
 // Columns: 64 bytes a row of 640 points, 128 bytes otherwise; 256 bytes (WIDE) for 96 .. 256 points where there are tiles enough
 // (8 x 256 x 160 x 160: the sweep along 256 points 196 -> 179 us; 2 x 8 x 320 x 256, with 256 tiles of 16 columns: 11.8 -> 13.5).
-template <int N> constexpr bool cols_have_wide() { return N >= 96 && N <= 256; }
-template <int N, bool WIDE> constexpr int cols_lines() { return N > 384 ? 8 : N <= 24 || N == 46 ? 64 : WIDE && cols_have_wide<N>() ? 32 : 16; }
+// Not the sweep that reads y (MODE 3) along 256 points: 512 threads share a CU with others only if they keep to 128 registers, and y
+// makes it 141.  Three workgroups of 256 threads, nothing spilled, instead of two of 512 with 25 values spilled: the operator of
+// a step, 8 x 256 x 160 x 160, 1023 -> 923 us, 4 x 16 x 256 x 256 55.8 -> 48.6.
+template <int N, int MODE> constexpr bool cols_have_wide() { return N >= 96 && N <= 256 && !(N == 256 && MODE == 3); }
+template <int N, bool WIDE> constexpr int cols_lines() { return N > 384 ? 8 : N <= 24 || N == 46 ? 64 : WIDE ? 32 : 16; }
 template <int N, bool WIDE> constexpr int cols_threads() {
     return N <= 24 ? 64 : N == 46 ? 256 : N > 384 ? 256 : N == 320 ? 320 : N == 368 ? 384 : reduce_threads<N>() * cols_lines<N, WIDE>() / 16;
 }
-template <int N, bool WIDE> constexpr int cols_min_waves() {
-    return N == 256 ? 4 : N == 368 ? 3 : 1;
+template <int N, int MODE> constexpr int cols_min_waves() {
+    return N == 256 ? (MODE == 3 ? 3 : 4) : N == 368 ? 3 : 1;
 }
 
 struct RowsArgs {
@@ -482,7 +485,7 @@ template <int N, int L, int NT> struct MaskTile {
 // MODE 0: forward, 1: inverse, 2: forward -> (mask ? k : 0) -> inverse, 3: forward -> (mask ? k - y : 0) -> inverse
 // (a kernel of its own: with the y path merely compiled in, the sweep without y ran 20-30 % slower).
 template <int N, int MODE, bool WIDE>
-__global__ __launch_bounds__((cols_threads<N, WIDE>()), (cols_min_waves<N, WIDE>())) void cols_kernel(ColsArgs a) {
+__global__ __launch_bounds__((cols_threads<N, WIDE>()), (cols_min_waves<N, MODE>())) void cols_kernel(ColsArgs a) {
     constexpr int L = cols_lines<N, WIDE>(), NT = cols_threads<N, WIDE>();
     using Lay = Tile<N, L, false>;
     __shared__ float2 buf[Lay::kSingle ? 1 : Lay::kElems];
@@ -706,27 +709,30 @@ static hipError_t launch_rows_fused(const gleam_geom& g, const RowsArgs& a, cons
     return hipGetLastError();
 }
 
-template <int N, bool WIDE> static void launch_cols_t(int mode, long long outer, ColsArgs a, hipStream_t st) {
+template <int N, int MODE, bool WIDE> static void launch_cols_t(long long outer, ColsArgs a, hipStream_t st) {
     constexpr int L = cols_lines<N, WIDE>();
     a.tiles_per = (a.inner + L - 1) / L;
     const long long n = outer * a.tiles_per;
-    if constexpr (!WIDE && cols_have_wide<N>()) {
-        if (n >= 2 * kWideTiles) return launch_cols_t<N, true>(mode, outer, a, st);
+    if constexpr (!WIDE && cols_have_wide<N, MODE>()) {
+        if (n >= 2 * kWideTiles) return launch_cols_t<N, MODE, true>(outer, a, st);
     }
     a.n_tiles = (unsigned)n;
     for (long long first = 0; first < n; first += kLaunchTiles) {
         a.first = (unsigned)first;
         const long long m = n - first < kLaunchTiles ? n - first : kLaunchTiles;
         const dim3 grid((unsigned)((m + 7) / 8 * 8)), block(cols_threads<N, WIDE>());   // a multiple of 8 for the split over the XCDs
-        if (mode == 0) hipLaunchKernelGGL((cols_kernel<N, 0, WIDE>), grid, block, 0, st, a);
-        else if (mode == 1) hipLaunchKernelGGL((cols_kernel<N, 1, WIDE>), grid, block, 0, st, a);
-        else if (a.y == nullptr) hipLaunchKernelGGL((cols_kernel<N, 2, WIDE>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((cols_kernel<N, 3, WIDE>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((cols_kernel<N, MODE, WIDE>), grid, block, 0, st, a);
     }
+}
+template <int N> static void launch_cols_n(int mode, long long outer, const ColsArgs& a, hipStream_t st) {
+    if (mode == 0) launch_cols_t<N, 0, false>(outer, a, st);
+    else if (mode == 1) launch_cols_t<N, 1, false>(outer, a, st);
+    else if (a.y == nullptr) launch_cols_t<N, 2, false>(outer, a, st);
+    else launch_cols_t<N, 3, false>(outer, a, st);
 }
 static hipError_t launch_cols(int mode, int N, long long outer, const ColsArgs& a, hipStream_t st) {
     switch (N) {
-#define X(NN) case NN: launch_cols_t<NN, false>(mode, outer, a, st); break;
+#define X(NN) case NN: launch_cols_n<NN>(mode, outer, a, st); break;
         GLEAM_FFT_SIZES(X)
 #undef X
         default: return hipErrorInvalidValue;
