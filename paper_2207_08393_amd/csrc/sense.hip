@@ -614,10 +614,25 @@ constexpr long long kLaunchTiles = 1LL << 22;
 
 // Workgroups up to which the coils of a tile are spread over several.
 constexpr long long kExpandGroups = 2048;
-// Row length from which the single sweep of one transformed axis stays with the kernel staged through LDS: with everything in
-// registers between load and store it needs two to three times as many, and a CU holds one or two workgroups.  8 coils, 20 x 160
-// rows: 38 (staged) and 22 us at 256 points, 45 and 51 at 320, 59 and 65 at 368, 91 and 106 at 640.
+// Where the single sweep of one transformed axis stays with the kernel staged through LDS, which needs half the registers (a CU
+// holds four or five of its workgroups, of this one's one to three) and whose tiles go across frames (staged / here, us):
+//   - Rows of kFusedStaged points and more.  8 coils, 20 x 160 rows: 38 and 22 us at 256 points, 45 and 51 at 320, 59 and 65 at 368,
+//     91 and 106 at 640.
+//   - Frames that leave more than a fifth of their tiles' rows empty, from more than kFusedTiles tiles on (what the card holds at once):
+//     1600 frames of 1 x 160, 4 coils 10.0 / 17.5; of 20 x 24, 4 coils 17.8 / 26.7.  400 tiles: 400 frames of 8 x 24, 4 coils
+//     9.5 / 8.9.
+//   - Rows of 20 and 24 points, one butterfly, which one of four waves transforms while the others wait, from half as many tiles
+//     more on (with y, which takes the registers of the third workgroup, from kFusedTiles): 64 frames of 320 x 20, 2 coils
+//     0.80 of the time here; 8 frames of 320 x 24, 16 coils (640 tiles) 1.28, with y 0.84.  Shorter rows only with y or of one
+//     coil: 1600 frames of 64 x 16, 2 coils, with y 0.71; 1 coil 0.80; 16 coils 1.05.
+//   - The 23-point stage of 46 points with y, one workgroup to a CU: from a second round of them on (2 x 8 x 641 rows, 2 coils
+//     16.5 / 22.5; 320 rows of 8 coils, 40 tiles 15.3 / 12.7).
+//   - With y, tiles with few coils, which use no more than about half of their lines (the coil sum holds four values per thread):
+//     400 frames of 64 x 256, 1 coil 0.85; without y 1.03, 2 coils with y 0.93 to 1.1.
+// Over 1561 calls of 8 to 256 points, 1 to 16 coils, frames of 1 to 320 rows, 1 to 1600 of them, the calls are 1.23 (with y 1.16) times
+// as fast as with the staged kernel alone and 1.07 (1.10) times as with this one alone.
 constexpr int kFusedStaged = 320;
+constexpr long long kFusedTiles = 512;
 // Tiles from which the column sweeps take 32 columns instead of 16 (256 bytes a row).
 constexpr long long kWideTiles = 2048;
 
@@ -699,6 +714,26 @@ static hipError_t launch_rows(const gleam_geom& g, bool reduce, RowsCgArgs a, hi
     return hipGetLastError();
 }
 
+template <int N> static bool fused_staged_t(const gleam_geom& g, bool y) {
+    constexpr int L = fused_lines<N>();
+    const long long cg = g.C < L ? g.C : L, per = reduce_rows_per_tile(N, L, expand_threads<N>(), g.C);
+    const long long rows = g.D * g.H, of_frame = (rows + per - 1) / per, tiles = g.B * g.T * of_frame;
+    if (N >= kFusedStaged) return true;
+    if (N == 46 && y && tiles > kFusedTiles / 2) return true;
+    if (tiles <= kFusedTiles) return false;
+    if (5 * rows < 4 * of_frame * per) return true;
+    if (N <= 24 && tiles > kFusedTiles * 3 / 2) return y || N > 16 || g.C == 1;
+    return y && (N <= 24 ? N > 16 : 20 * per * cg < 11 * L);
+}
+static bool fused_staged(const gleam_geom& g, bool y) {
+    switch (g.W) {
+#define X(NN) case NN: return fused_staged_t<NN>(g, y);
+        GLEAM_FFT_SIZES(X)
+#undef X
+        default: return false;
+    }
+}
+
 static hipError_t launch_rows_fused(const gleam_geom& g, const RowsArgs& a, const float2* y, const unsigned char* M, hipStream_t st) {
     switch (g.W) {
 #define X(NN) case NN: launch_rows_fused_t<NN>(g, a, y, M, st); break;
@@ -765,7 +800,7 @@ static hipError_t sense_sweeps(const gleam_geom& g, const float2* x, const float
     const double S8 = E8 / (double)g.T, M1 = P8 / 8.0;
     hipError_t e;
     if (g.ndim_fft == 1) {   // one transformed axis: the whole operator in one sweep, no k-space buffer
-        if (g.W >= kFusedStaged) return sense_dc_staged(g, x, S, M, y, xs, gs, out, kbuf, st);
+        if (fused_staged(g, y != nullptr)) return sense_dc_staged(g, x, S, M, y, xs, gs, out, kbuf, st);
         KernelScope ks("sense_rows_fused", 0.0, S8 + P8 + (y ? E8 : 0.0) + M1 + P8 + (xs != 0.f ? P8 : 0.0), st);
         return launch_rows_fused(g, ra, y, M, st);
     }

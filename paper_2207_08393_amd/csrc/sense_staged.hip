@@ -1,6 +1,7 @@
 // The operator with every transform staged through LDS: the sweeps that sense.hip had before its transforms went through
 // registers.  They are slower but for one, and stay for two callers:
-//   - the single sweep of one transformed axis with rows of 320 points and more (see kFusedStaged in sense.hip);
+//   - the single sweep of one transformed axis where it is the faster one: rows of 320 points and more, many tiles that this
+//     kernel's layout fills better (see kFusedStaged in sense.hip);
 //   - the data-consistency step of calls whose results depend on its last bits, the greedy training iteration with float32
 //     layers (ProxPlan::staged).  Adam's first step moves a parameter by lr * sign(gradient), so any other order of rounding ahead
 //     of it, also one no further from 64 bits, moves the parameters whose gradient is near zero by 2 lr.  The sweeps of
@@ -666,7 +667,7 @@ hipError_t sense_dc_staged(const gleam_geom& g, const float2* x, const float2* S
     const double P8 = 8.0 * (double)(g.B * g.T * g.D * g.H * g.W);          // bytes of one image
     const double S8 = E8 / (double)g.T, M1 = P8 / 8.0;
     if (g.ndim_fft == 1) {
-        KernelScope ks("sense_rows_fused", 0.0, S8 + P8 + E8 + M1 + P8 + (xs != 0.f ? P8 : 0.0), st);
+        KernelScope ks("sense_rows_fused_staged", 0.0, S8 + P8 + (y ? E8 : 0.0) + M1 + P8 + (xs != 0.f ? P8 : 0.0), st);
         return staged::rows(2, g.W, ra, y, M, st);
     }
     hipError_t e;

@@ -65,6 +65,23 @@ def test_long_rows_of_few_coils(coils):
     test_solver(2, coils, 10, 640)
 
 
+# One transformed axis: the kernel in registers and the one staged through LDS, on both sides of the lines between them (without y and
+# with y): few tiles and many, short rows, frames of few rows, few coils, 46 points with y.
+@pytest.mark.parametrize("centred", [0, 1])
+@pytest.mark.parametrize("W,coils,B,T,H,staged", [
+    (24, 4, 2, 16, 16, (0, 0)), (24, 4, 2, 129, 20, (1, 1)), (24, 4, 5, 103, 16, (0, 1)), (24, 4, 7, 110, 16, (1, 1)), (20, 3, 1, 1, 641, (0, 0)),
+    (8, 16, 3, 257, 4, (0, 1)), (8, 16, 3, 256, 4, (0, 0)), (16, 1, 13, 60, 62, (1, 1)), (8, 16, 129, 4, 5, (1, 1)),
+    (160, 4, 1, 513, 1, (1, 1)), (160, 4, 1, 512, 1, (0, 0)), (64, 4, 2, 257, 7, (0, 0)), (64, 4, 2, 257, 6, (1, 1)),
+    (192, 1, 1, 103, 25, (0, 1)), (192, 2, 1, 103, 25, (0, 0)), (46, 2, 2, 8, 641, (0, 1)), (46, 8, 1, 1, 320, (0, 0)),
+    (46, 70, 1, 1, 257, (0, 1)), (32, 16, 4, 5, 97, (0, 0)), (4, 1, 5, 1, 7, (0, 0)), (320, 2, 1, 1, 9, (1, 1)), (256, 16, 1, 1, 640, (0, 0))])
+def test_one_axis_on_both_kernels(W, coils, B, T, H, staged, centred):
+    geom, *arrays = inputs(1, B, coils, T, 1, H, W, centred, W + coils + H)
+    gb.gleam_profile_begin()
+    check(geom, *arrays)
+    ran = [r[0] for r in gb.gleam_profile_end() if r[0].startswith("sense_rows_fused")]
+    assert [n.endswith("staged") for n in ran] == [bool(s) for s in staged]
+
+
 # every length along both strided axes; W = 20 and 46 leave the column tiles ragged, and the mask's rows unaligned
 @pytest.mark.parametrize("N", LENGTHS)
 def test_every_length_along_the_strided_axes(N):
