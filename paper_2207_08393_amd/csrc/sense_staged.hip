@@ -6,7 +6,7 @@
 //     layers (ProxPlan::staged).  Adam's first step moves a parameter by lr * sign(gradient), so any other order of rounding ahead
 //     of it, also one no further from 64 bits, moves the parameters whose gradient is near zero by 2 lr.  The sweeps of
 //     sense.hip round in another order (the inverse transform goes through its stages backwards, and the compiler contracts a
-//     complex product by its neighbourhood).  Of an iteration of 8 modules, 100 channels, 4 x 320 x 256 (81 ms) these are 0.54 ms,
+//     complex product by its neighbourhood).  Of an iteration of 8 modules, 100 channels, 4 x 320 x 256 (65 ms) these are 0.54 ms,
 //     and would be 0.4.
 //
 // The same 2d-1 sweeps: rows_expand, cols, rows_reduce (see sense.hip).
@@ -462,12 +462,11 @@ struct ColsArgs {
     long long outer, inner;  // inner is even (it is a product of transform lengths, all even)
     long long C, T, Dq;    // outer = ((b*C + c)*T + t)*Dq + dq ; mask row = (b*T + t)*Dq + dq
     float scale;           // N^-1/2, applied at the store (mid applies its forward N^-1/2 in LDS)
-    // Centred transform.  cen_y (mid sweep): the measured k-space enters as (sign) D y, where the parity of an
+    // Centred transform, cen_y (mid sweep): the measured k-space enters as (sign) D y, where the parity of an
     // element is p + (column / Wrow) + (column % Wrow) (the inner index is h*W + w when three axes are transformed,
     // w alone otherwise: then column / Wrow is 0) and ysign_bit is 1 when the product of (-1)^(n/2) over the
-    // transformed axes is -1.  cen_io (MODE 1 on its own, k-space to hybrid space): the centred inverse transform
-    // of this axis, (-1)^(N/2) D F^H D: input and output signs by the parity of p.
-    int cen_y, ysign_bit, cen_io;
+    // transformed axes is -1.
+    int cen_y, ysign_bit;
     long long Wrow;
     // Walk the tiles from the last to the first.  The k-space buffer of the 3D workload (419 MB) is larger than the
     // Infinity Cache (256 MB), which holds what the previous sweep wrote last: a sweep that starts where the previous
@@ -542,9 +541,6 @@ __global__ __launch_bounds__(cols_threads<N>(), (cols_min_waves<N, MODE>())) voi
                 const int l = 2 * (idx % L2), p = idx / L2;
                 float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (l < valid) v = *reinterpret_cast<const float4*>(a.k + base + (long long)p * a.inner + l);
-                if constexpr (MODE == 1) {
-                    if (a.cen_io && (p & 1)) v = make_float4(-v.x, -v.y, -v.z, -v.w);
-                }
                 *reinterpret_cast<float4*>(&buf[Lay::at(l, p)]) = v;
             }
         }
@@ -598,12 +594,8 @@ __global__ __launch_bounds__(cols_threads<N>(), (cols_min_waves<N, MODE>())) voi
                 const int l = 2 * (idx % L2), p = idx / L2;
                 if (l < valid) {
                     const float4 v = *reinterpret_cast<const float4*>(&buf[Lay::at(l, p)]);
-                    float sc = a.scale;
-                    if constexpr (MODE == 1) {
-                        if (a.cen_io && ((p + N / 2) & 1)) sc = -sc;
-                    }
                     *reinterpret_cast<float4*>(a.k + base + (long long)p * a.inner + l) =
-                        make_float4(v.x * sc, v.y * sc, v.z * sc, v.w * sc);
+                        make_float4(v.x * a.scale, v.y * a.scale, v.z * a.scale, v.w * a.scale);
                 }
             }
         }
@@ -672,7 +664,7 @@ hipError_t sense_dc_staged(const gleam_geom& g, const float2* x, const float2* S
     }
     hipError_t e;
     {
-        KernelScope ks("sense_rows_expand", 0.0, S8 + P8 + E8, st);
+        KernelScope ks("sense_rows_expand_staged", 0.0, S8 + P8 + E8, st);
         e = staged::rows(0, g.W, ra, nullptr, nullptr, st);
     }
     if (e != hipSuccess) return e;
@@ -686,7 +678,7 @@ hipError_t sense_dc_staged(const gleam_geom& g, const float2* x, const float2* S
     if (g.ndim_fft == 3) {
         ca.rev = 1;
         {
-            KernelScope ks("sense_cols_fwd", 0.0, 2.0 * E8, st);
+            KernelScope ks("sense_cols_fwd_staged", 0.0, 2.0 * E8, st);
             e = staged::cols(0, g.H, ca, st);
         }
         if (e != hipSuccess) return e;
@@ -694,16 +686,16 @@ hipError_t sense_dc_staged(const gleam_geom& g, const float2* x, const float2* S
         ma.scale = 1.0f / sqrtf((float)g.D);
     }
     {
-        KernelScope ks("sense_cols_mid", 0.0, 3.0 * E8 + M1, st);
+        KernelScope ks("sense_cols_mid_staged", 0.0, 3.0 * E8 + M1, st);
         e = staged::cols(3, g.ndim_fft == 3 ? g.D : g.H, ma, st);
     }
     if (e != hipSuccess) return e;
     if (g.ndim_fft == 3) {
-        KernelScope ks("sense_cols_inv", 0.0, 2.0 * E8, st);
+        KernelScope ks("sense_cols_inv_staged", 0.0, 2.0 * E8, st);
         e = staged::cols(1, g.H, ca, st);
         if (e != hipSuccess) return e;
     }
-    KernelScope ks("sense_rows_reduce", 0.0, E8 + S8 + P8 + (xs != 0.f ? P8 : 0.0), st);
+    KernelScope ks("sense_rows_reduce_staged", 0.0, E8 + S8 + P8 + (xs != 0.f ? P8 : 0.0), st);
     return staged::rows(1, g.W, ra, nullptr, nullptr, st);
 }
 

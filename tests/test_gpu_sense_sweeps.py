@@ -3,13 +3,17 @@
 A value passes 2 d transforms of at most two butterflies each; a butterfly of R <= 32 points is at most log2(R) + 2 roundings
 deep, its twiddles one more.  With roundings of 2^-24 / sqrt(3) that are independent of one another, three transformed axes give
 sqrt(6 * 2 * 8) * 3.4e-8 = 3.4e-7; the bound is three times that (measured 1.0e-7 to 1.8e-7)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
 from oracle import gleam_oracle as og
 from paper_2207_08393_amd import binding as gb
 from paper_2207_08393_amd import synth
+from paper_2207_08393_amd.runner import ModuleRunner
 from tests.gpu_util import assert_image_close, run_sense_normal
+from tests.test_gpu_parity import kernel_policy  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-6
@@ -87,6 +91,26 @@ def test_one_axis_on_both_kernels(W, coils, B, T, H, staged, centred):
 def test_every_length_along_the_strided_axes(N):
     for nd, D, H, W in ((2, 2, N, 20), (3, N, 4, 46), (3, 4, N, 16)):
         check(*inputs(nd, 1, 2, 1, D, H, W, N % 4 == 0, N + D))
+
+
+# The sweeps staged through LDS, which float32 layers with kernels on split operands take when those are switched off (and greedy
+# iterations): the data-consistency step alone, by a network whose weights are zero.  Every length along every axis, centred or not.
+@pytest.mark.parametrize("centred", [0, 1])
+@pytest.mark.parametrize("N", LENGTHS)
+def test_data_consistency_on_the_staged_sweeps(N, centred, kernel_policy):
+    kernel_policy(gb.POLICY_NO_WINOGRAD)
+    prox = synth.chain_prox([2, 4, 4, 2], [(1, 1, 3, 3)] * 3)
+    for nd, coils, D, H, W in ((2, 3, 2, N, 20), (2, 17, 1, 6, N), (3, 2, N, 4, 46), (3, 2, 4, N, 16), (1, 3, 1, 7, N)):
+        geom, x, S, M, y = inputs(nd, 2, coils, 2, D, H, W, centred, N + nd)
+        print("case staged", geom, flush=True)
+        c = synth.make_custom(3, geom, prox, alpha=0.8)
+        c = dataclasses.replace(c, x_in=x, S=S, M=M, y=y, theta=np.zeros_like(c.theta))
+        r = ModuleRunner(c)
+        gb.gleam_profile_begin()
+        r.fwd()
+        ran = [rec[0] for rec in gb.gleam_profile_end() if rec[0].startswith("sense_")]
+        assert len(ran) == 2 * nd - 1 and all(n.endswith("_staged") for n in ran), ran
+        assert_image_close(r.results()[0], og.dc_step(x, S, M, y, 0.8, nd, centred=bool(centred)), TOL, "DC")
 
 
 # so many tiles that the columns go 32 at a time and a workgroup of the first sweep takes several coils
