@@ -106,7 +106,10 @@ int gleam_theta_count(const gleam_prox_desc* prox, size_t* n_floats);
  * gleam_workspace_bytes must be asked under the policy the calls will run with.  Not synchronised with calls in
  * flight on other threads.  Unknown bits: GLEAM_E_DESC. */
 #define GLEAM_POLICY_NO_WINOGRAD      1u  /* 3x3 and 3x3x3 fp32 layers: direct fp32 MFMA kernels instead of the minimal-filtering
-                                          * ones (split bfloat16 operands; fp32 MFMA in MoDL modules and greedy iterations) */
+                                          * ones (split bfloat16 operands; fp32 MFMA in MoDL modules and greedy iterations).  The
+                                          * data-consistency step of networks with such layers (widths that are multiples of 4) then
+                                          * takes the transforms of the greedy iteration too, staged through LDS, so that a greedy
+                                          * iteration and the same calls by hand give the same bits */
 #define GLEAM_POLICY_NO_BF16_2D       2u  /* 3x3 bf16 layers: flattened-pixel kernel instead of the 2D-tile one        */
 #define GLEAM_POLICY_NO_THIN_MFMA     4u  /* 2-channel first / last layers: vector-ALU kernels instead of matrix-core   */
 #define GLEAM_POLICY_NO_WGRAD_BALANCE 8u  /* 27-tap weight gradient: nine 3-tap jobs instead of the balanced 8-wave split */
@@ -158,7 +161,10 @@ int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox,
 
 /* Backward pass of the same module: grad_theta = d loss / d theta (Alg. 1, gradient step), overwritten.
  * Consumes `saved` of the matching gleam_module_fwd call (same geom / prox / theta).  No gradient is
- * produced for x_in, S or y: modules are decoupled and the data-consistency step is not differentiated. */
+ * produced for x_in, S or y: modules are decoupled and the data-consistency step is not differentiated.
+ * Range: the weight gradient of float32 3x3 and 3x3x3 layers whose widths are multiples of 4 takes activations and output gradients
+ * of the same range as gleam_module_fwd; what they overflow and an infinity come out as infinity or NaN.  Output gradients
+ * below about 1e-28 (at activations of order one) lose bits, at 1e-31 about 1e-5 of the value. */
 int gleam_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, const float* theta,
                      const void* saved, size_t saved_bytes, float* grad_theta,
                      void* ws, size_t ws_bytes, void* stream);
@@ -269,7 +275,8 @@ int gleam_adam_step(const gleam_adam* hyper, int64_t t, size_t n, float* theta, 
  * architecture `prox`.  Other arguments as in gleam_module_fwd.
  * The iteration does what gleam_module_fwd, gleam_module_bwd and gleam_adam_step do in turn, to the same bits where a layer
  * has one kernel for both.  Float32 3x3 and 3x3x3 layers whose widths are multiples of 4 have two: the module calls and
- * gleam_unrolled_infer run them on split operands, this call (like a MoDL module) on the float32 matrix cores.  Outputs,
+ * gleam_unrolled_infer run them on split operands, this call (like a MoDL module) on the float32 matrix cores; its
+ * data-consistency steps then go through transforms of their own as well, of another order of rounding.  Outputs,
  * losses and first moments then differ by rounding (6e-7 over two modules of 64 channels); a parameter whose gradient is that
  * close to zero can differ by twice the learning rate after Adam's first step.  Under GLEAM_POLICY_NO_WINOGRAD all of it is
  * the same bit for bit, at the speed of the direct kernels. */

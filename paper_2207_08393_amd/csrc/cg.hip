@@ -194,17 +194,17 @@ hipError_t cg_solve(const gleam_geom& g, const float2* S, const unsigned char* M
     }
     // Where the tiles of the operator's row sweeps allow it, the inner product rides on the last sweep and the update of the
     // search direction on the first sweep of the next application: four launches per step instead of six, and p and q are not read
-    // again.  At 2 x 320 x 256 with 8 coils a step is bound by its launches (the module 1717 -> 1602 us; 1595 with the scalars
-    // summed by each wave for itself, the first elements in flight meanwhile).  The products are summed in double as before, in
-    // another order.
+    // again.  The products are summed in double as before, in another order.
     // Every tile of the first sweep sums the partials of its samples for itself, and every workgroup of the update those of the
     // inner product, so many of them cost more than the launches they save.  A module of 10 steps, all apart / by the rule below /
-    // with both limits at 512 (samples x coils x size: sums, partials of the inner product; us):
-    //     2 x 8 x 320 x 256         80,  160   1130 / 1036 / 1029     1 x 5 x 4 x 128 x 256    128, none    937 /  902 /  901
-    //     4 x 12 x 320 x 368       115,  320   2786 / 2792 / 2779     1 x 15 x 320 x 368       115,  320   1456 / 1415 / 1370
-    //     1 x 8 x 640 x 320        200,  320   1270 / 1271 / 1187     2 x 15 x 640 x 368       230,  640   2787 / 2787 / 2813
-    //     1 x 5 x 256 x 24 x 160   512, 1024   4245 / 4243 / 4279     1 x 8 x 20 x 192 x 160   512,  960   2114 / 2114 / 2147
-    // What the rule takes in has never cost more than 0.2 %; above it, it depends on how many tiles a workgroup has.
+    // with up to 512 partials of the inner product (samples x coils x size: sums, partials; us):
+    //     2 x 8 x 320 x 256         80,  160    982 /  934 /  926     1 x 5 x 4 x 128 x 256    128,  171    851 /  775 /  775
+    //     4 x 12 x 320 x 368       115,  320   2196 / 2299 / 2286     1 x 15 x 320 x 368       115,  320   1100 / 1126 / 1087
+    //     1 x 8 x 640 x 320        200,  320   1145 / 1145 / 1105     2 x 15 x 640 x 368       230,  640   2385 / 2393 / 2393
+    //     1 x 5 x 256 x 24 x 160   512, 2048   2162 / 2160 / 2155     1 x 8 x 20 x 192 x 160   512, 1920   1791 / 1788 / 1786
+    // The update inside the sweep, over 115 calls of 96 x 96 to 640 x 192, 2 to 16 coils, 1 to 4 samples: 3.2 % of the module gained in
+    // the geometric mean, up to 9 % where launches count, and up to 4 % lost by 12 coils, of which a tile of 16 lines holds one
+    // row with a quarter of its lines empty.
     constexpr int kFusedPartials = 256;
     static_assert(kFusedPartials <= kCgBlocksMax, "what sum_partials takes");
     const int room = 3 * kCgBlocksMax - 2 * nb, n_dot = cg_fused_dot_partials(g, room < kFusedPartials ? room : kFusedPartials);

@@ -76,16 +76,17 @@ hipError_t kspace_to_hybrid(const gleam_geom& g, float2* y, hipStream_t st);
 //           [G_1 .. G_{L-1} | split-K partials | loss partials] for backward
 struct ProxPlan {
     int L;
-    // Whether 3x3 and 3x3x3 float32 layers run on split bfloat16 operands (conv_split_applies, wgrad_split_applies).  The MoDL
-    // module and the greedy iteration keep the float32 matrix cores, so that their results stay what they were.  It is not for
-    // speed (100 -> 100 channels at 4 x 320 x 256: 713 us forward and 970 us weight gradient there, 280 and 340 us here) and not
-    // for accuracy (the split kernels are the nearer ones to 64 bits): any other order of rounding shows in them.  The first
-    // Adam step moves a parameter by lr * sign(g), so one whose gradient is near zero moves by 2 lr; the gradient of a MoDL
-    // module with the complex-l1 loss takes d / |d| of residuals that the solve drives to zero, and is 1e-6 .. 5e-4 from the
-    // 64-bit result by input, with either arithmetic.
+    // Whether 3x3 and 3x3x3 float32 layers run on split bfloat16 operands (conv_split_applies, wgrad_split_applies).  Not in the
+    // greedy iteration, so that its results stay what they were: the first Adam step moves a parameter by lr * sign(g), so one
+    // whose gradient is near zero moves by 2 lr with any other order of rounding.  It is not for speed (100 -> 100 channels at
+    // 4 x 320 x 256: 565 us forward and 738 us weight gradient there, 280 and 340 us here) and not for accuracy (the split kernels
+    // are the nearer ones to 64 bits).  Nor, as yet, in the MoDL module, whose gradient with the complex-l1 loss takes d / |d| of
+    // residuals that the solve drives to zero and is 1e-6 .. 5e-4 from the 64-bit result by input, with either arithmetic; its
+    // solver rounds in another order since its sweeps go through registers, so this is no promise about its bits.
     bool split;
     // Whether the data-consistency step takes the sweeps staged through LDS: where float32 layers that have split kernels are kept
-    // from them, and for the same reason.
+    // from them, in the greedy iteration for the same reason and under GLEAM_POLICY_NO_WINOGRAD so that the two stay the same
+    // bits.  (MoDL modules have no such step.)
     bool staged;
     long long Q;                      // pixels B*T*D*H*W
     size_t act_off[kMaxLayers + 1];   // t_l inside saved, l < L

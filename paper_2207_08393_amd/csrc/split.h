@@ -2,7 +2,8 @@
 // x = x1 + x2 + x3 exactly, with x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2 (8 + 8 + 8 significant bits; the method of
 // Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019).
 // Range: 2^-103 <= |x| <= 3.39e38, the largest bfloat16.  Below, parts are subnormal and x is kept to 2^-126; above, and for
-// infinity, x - x1 is NaN.  What is split are sums of two (transformed inputs) or three (weights) float32 numbers: an input is
+// infinity, x - x1 is NaN.  Partial products lose what lies below 2^-126 too: of numbers whose product is below about 2^-94, bits are
+// gone.  What is split are sums of two (transformed inputs) or three (weights) float32 numbers: an input is
 // good up to 1.69e38.
 #pragma once
 #include "prox_common.h"

@@ -1,5 +1,7 @@
 """The split-operand 3x3 / 3x3x3 kernels (prox_split.hip) where their blocks, chunks and channel groups end: module steps
 against the oracle at the float32 tolerance, per layer and per element (tests/test_gpu_parity.py check_module)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -229,3 +231,44 @@ def test_blocks_of_four_and_eight_rows_2d(H):
 def test_blocks_of_four_and_eight_rows_3d(D):
     check_module(synth.make_custom(52, synth.Geom(3, 1, 2, 1, D, 10, 20), synth.chain_prox([2, 20, 32, 20, 2], [K3] * 4), accel=2.0,
                                    centre=2, bias_std=0.1, alpha=0.8))
+
+
+@pytest.mark.parametrize("geom,k", [(synth.Geom(2, 1, 2, 1, 1, 20, 46), K2), (synth.Geom(3, 1, 2, 1, 8, 20, 46), K3)], ids=["2d", "3d"])
+def test_range_of_the_weight_gradient(geom, k):
+    """What lies below 2^-126 of an operand's parts and of their products is lost (csrc/split.h).  As in test_gpu_cover.py the gradient
+    of layer 2 is one product per value, so scaling the weights of layer 3 by a power of two scales it exactly, and the weight
+    gradient of layer 2 with it, but for that loss.  A product has six partial products of up to eight multiplied bits each whose
+    smallest are 2^-126 when it is 2^-102: 6 * 8 losses of 2^-126 against values of 2^a .. 2^(a + 2), activations of order one (44 to
+    56 seen where it is more than the rounding of the result).  Nothing down to 2^-94 = 5e-29.  An infinity shows."""
+    taps, n = int(np.prod(k)), 32
+    rng = np.random.default_rng(5)
+    shape = geom.image_shape
+    ref = (rng.uniform(1, 2, (2,) + shape) * rng.choice((-1.0, 1.0), (2,) + shape) * 2.0 ** 40).astype(np.float32)
+    w1, b1 = rng.standard_normal((n, taps, 2)), rng.standard_normal(n)
+    w2, b2 = rng.standard_normal((n, taps, n)) / np.sqrt(taps * n), rng.standard_normal(n)
+    c = synth.make_custom(19, geom, synth.chain_prox([2, n, n, 2], [k] * 3), alpha=0.0)
+    part = next(p for layer, kind, p in theta_slices(c.prox) if layer == 2 and kind == "W")
+    g_z = 2.0 ** 41 / (geom.B * geom.T * geom.D * geom.H * geom.W)     # of the smallest value of ref
+
+    def weight_gradient(a, x_in=c.x_in):
+        w3 = np.zeros((2, taps, n))
+        w3[np.arange(n) % 2, np.arange(n) * 5 % taps, np.arange(n)] = np.random.default_rng(6).uniform(1, 2, n)
+        w3 *= 2.0 ** (a - np.floor(np.log2(g_z)))
+        theta = np.concatenate([v.ravel() for v in (w1, b1, w2, b2, w3, np.zeros(2))]).astype(np.float32)
+        r = ModuleRunner(dataclasses.replace(c, x_true=ref[0] + 1j * ref[1], theta=theta, x_in=x_in))
+        gb.gleam_profile_begin()
+        r.step()
+        ran = wide_convolutions(gb.gleam_profile_end())
+        assert {v for name, v in ran.items() if "wgrad" in name} == {4.0}, ran
+        return r.grad.cpu().numpy()[part].astype(np.float64)
+
+    print("case range", k, flush=True)
+    base = weight_gradient(0)
+    assert np.all(np.isfinite(base)) and rel_l2(base, np.zeros_like(base) + base.mean()) > 0.1
+    for a in (-60, -94, -104, -112):
+        err = rel_l2(weight_gradient(a) * 2.0 ** -a, base)
+        print("smallest output gradient 2 ^", a, "apart", err, flush=True)
+        assert err <= (0 if a >= -94 else 64 * 2.0 ** (-126 - a))
+    x_in = c.x_in.copy()
+    x_in[..., 5, 7] = np.inf
+    assert not np.isfinite(weight_gradient(0, x_in)).all()
