@@ -40,7 +40,7 @@ MEASURED_TRAFFIC = {
     ("knee2d_640x368_c15_b2", "conv_fwd+dgrad_64to64_t9"): 1.792e5 * 1024 * 2.0 + 1.192e5 * 1024 * 1.0,
     ("knee2d_640x368_c15_b2", "conv_wgrad_64to64_t9"): 1.675e5 * 1024 * 2.0 + 1.846e4 * 1024 * 1.0,
     ("vol3d_256x160x160_c8_b1", "conv_fwd+dgrad_32to32_t27"): 9.49e5 * 1024 * 2.0 + 8.256e5 * 1024 * 1.0,
-    ("vol3d_256x160x160_c8_b1", "conv_wgrad_32to32_t27"): 8.663e5 * 1024 * 2.0 + 9.939e4 * 1024 * 1.0,
+    ("vol3d_256x160x160_c8_b1", "conv_wgrad_32to32_t27"): 2.112e6 * 1024 * 2.0 + 1.817e4 * 1024 * 1.0,
     ("cine2dt_20x192x160_c8_b1", "conv_fwd+dgrad_64to64_t9"): 2.233e5 * 1024 * 2.0 + 1.536e5 * 1024 * 1.0,
     ("cine2dt_20x192x160_c8_b1", "conv_wgrad_64to64_t9"): 2.175e5 * 1024 * 2.0 + 1.846e4 * 1024 * 1.0,
     ("brain2d_640x320_c16_b4_bf16", "conv_bf16_fwd+dgrad_128to128_t9"): 1.235e5 * 1024 * 2.0 + 2.0907e5 * 1024 * 1.0,
