@@ -2,11 +2,12 @@
 //     out = xs * x + gs * S^H F^H Omega (F S x - y)          (Eq. 1-3; A = Omega F S)
 // as 2d-1 sweeps over the coil k-space buffer for a d-dimensional transform:
 //   rows_expand  : coil multiply fused into the load of the transform along W (contiguous axis)
-//   cols_*       : strided axes, a tile of neighbouring columns per workgroup staged through LDS;
-//                  the middle sweep does forward transform, mask / residual and inverse transform of
-//                  its axis without leaving LDS
+//   cols_*       : strided axes, a tile of neighbouring columns per workgroup; the middle sweep does
+//                  forward transform, mask / residual (in registers) and inverse transform of its axis
+//                  in one go
 //   rows_reduce  : inverse transform along W with conj(S) multiply, coil sum and the DC update fused
 //                  into the store (the per-coil images are never written).
+// sense_staged.hip has the same sweeps with whole transforms in LDS, for the calls that take those.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
