@@ -106,7 +106,8 @@ int gleam_theta_count(const gleam_prox_desc* prox, size_t* n_floats);
  * gleam_workspace_bytes must be asked under the policy the calls will run with.  Not synchronised with calls in
  * flight on other threads.  Unknown bits: GLEAM_E_DESC. */
 #define GLEAM_POLICY_NO_WINOGRAD      1u  /* 3x3 and 3x3x3 fp32 layers: direct fp32 MFMA kernels instead of the minimal-filtering
-                                          * ones (split bfloat16 operands; fp32 MFMA in MoDL modules and greedy iterations).  The
+                                          * ones (split bfloat16 operands; fp32 MFMA in greedy iterations, in the forward pass
+                                          * of MoDL modules and in the backward pass of those of fewer than 4096 pixels).  The
                                           * data-consistency step of networks with such layers (widths that are multiples of 4) then
                                           * takes the transforms of the greedy iteration too, staged through LDS, so that a greedy
                                           * iteration and the same calls by hand give the same bits */
@@ -275,7 +276,7 @@ int gleam_adam_step(const gleam_adam* hyper, int64_t t, size_t n, float* theta, 
  * architecture `prox`.  Other arguments as in gleam_module_fwd.
  * The iteration does what gleam_module_fwd, gleam_module_bwd and gleam_adam_step do in turn, to the same bits where a layer
  * has one kernel for both.  Float32 3x3 and 3x3x3 layers whose widths are multiples of 4 have two: the module calls and
- * gleam_unrolled_infer run them on split operands, this call (like a MoDL module) on the float32 matrix cores; its
+ * gleam_unrolled_infer run them on split operands, this call (like a MoDL module's forward pass) on the float32 matrix cores; its
  * data-consistency steps then go through transforms of their own as well, of another order of rounding.  Outputs,
  * losses and first moments then differ by rounding (6e-7 over two modules of 64 channels); a parameter whose gradient is that
  * close to zero can differ by twice the learning rate after Adam's first step.  Under GLEAM_POLICY_NO_WINOGRAD all of it is

@@ -470,6 +470,20 @@ int gleam_mask_constant_along_outer_axis(const gleam_geom* geom, const uint8_t* 
     return GLEAM_OK;
 }
 
+// The plan of a MoDL module's backward pass.  The forward pass stays on the float32 kernels: a solve and a loss stand behind it,
+// and another rounding of the prox decides a ReLU near zero the other way, which moves the gradient by 5e-5 to 1.5e-4 (either side
+// is that far from 64 bits).  Behind the masks that the forward pass has fixed the gradients are sums of products, so they take the
+// split operands (csrc/prox_split.hip), like a plain module's: 1e-7 apart, nearer to 64 bits.  64 -> 64 channels at 2 x 320 x 256:
+// data gradient 68 us on the float32 matrix cores, 52 on split operands, weight gradient with its sums 84 and 55; 16 -> 16 at
+// 4 x 344 x 368: 58 and 33, 195 and 33.  The forward launches' sign words are in the float32 kernels' order, so the masks come from
+// the activations.  Calls of fewer than 4096 pixels stay on the float32 kernels, with which the tests compare them.
+static void plan_modl_backward(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
+    const bool split = n_pixels(g) >= 4096;
+    plan_prox(g, p, split, plan);
+    if (split && p.dtype == 0)
+        for (size_t& off : plan.sign_off) off = 0;
+}
+
 static int check_modl(const gleam_geom* geom, const gleam_prox_desc* prox, float mu, int n_cg) {
     int rc = check_geom(geom);
     if (rc) return rc;
@@ -538,7 +552,7 @@ int gleam_modl_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, c
     if (!aligned(ws) || ws_bytes < ws_need) return GLEAM_E_WORKSPACE;
     if (!aligned(saved) || saved_bytes < saved_need) return GLEAM_E_WORKSPACE;
     ProxPlan plan;
-    plan_prox(*geom, *prox, false, plan);
+    plan_modl_backward(*geom, *prox, plan);
     hipStream_t st = (hipStream_t)stream;
     unsigned char* scratch = (unsigned char*)ws + (ws_need - cg_scratch_bytes(*geom));
     // dL/dz = mu Q^-1 dL/dx_out, solved in place: the solve is linear in its right-hand side, so the factor mu

@@ -80,9 +80,9 @@ struct ProxPlan {
     // greedy iteration, so that its results stay what they were: the first Adam step moves a parameter by lr * sign(g), so one
     // whose gradient is near zero moves by 2 lr with any other order of rounding.  It is not for speed (100 -> 100 channels at
     // 4 x 320 x 256: 565 us forward and 738 us weight gradient there, 280 and 340 us here) and not for accuracy (the split kernels
-    // are the nearer ones to 64 bits).  Nor, as yet, in the MoDL module, whose gradient with the complex-l1 loss takes d / |d| of
-    // residuals that the solve drives to zero and is 1e-6 .. 5e-4 from the 64-bit result by input, with either arithmetic; its
-    // solver rounds in another order since its sweeps go through registers, so this is no promise about its bits.
+    // are the nearer ones to 64 bits).  Nor in the MoDL module's forward pass, where
+    // another rounding decides a ReLU near zero the other way and moves the gradient by 5e-5 to 1.5e-4; its backward pass takes them
+    // (plan_modl_backward in gleam_api.hip).
     bool split;
     // Whether the data-consistency step takes the sweeps staged through LDS: where float32 layers that have split kernels are kept
     // from them, in the greedy iteration for the same reason and under GLEAM_POLICY_NO_WINOGRAD so that the two stay the same

@@ -312,7 +312,7 @@ bool wgrad_split_applies(const PixDims& d, int Ci, int Co) {
     // between the other launches of a step, under the power limit, it is not: 1.56 - 1.66 ms there, 1.43 here, with the sums of
     // the partial results 66 and 40 us (64 -> 64 at 2 x 20 x 96 x 96: 370 + 104 and 290 + 15 us a layer, the step 2370 and 2031).
     // Under 160 row segments the step takes 166 - 178 us here and 179 - 195 there; such volumes stay there, so that the kernel,
-    // which MoDL modules and greedy iterations run, has plain modules to be compared with.
+    // which greedy iterations run, has plain modules to be compared with.
     const long long segments = d.Q / d.W * ((d.W + 31) / 32);
     return d.kt == 1 && (d.kd == 1 || d.kd == 3) && d.kh == 3 && d.kw == 3 && Ci % 4 == 0 && Co % 4 == 0 &&
            (d.kd == 1 || Ci % 32 != 0 || Co % 32 != 0 || segments >= 160) &&

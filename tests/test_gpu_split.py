@@ -167,6 +167,33 @@ def test_float32_matrix_core_kernels_of_greedy_and_modl_calls(name, geom, prox, 
     assert {v for n, v in ran.items() if "wgrad" in n} == {0.444 if prox.layers[1].kd == 3 else 4.0}, ran
 
 
+# 4096 pixels are the least with a backward pass on split operands; channels that the forward kernels take by Winograd, whose sign words
+# the backward launches must not read, and directly; skips and a mask behind the sum
+@pytest.mark.parametrize("geom,prox", [(synth.Geom(2, 2, 2, 1, 1, 64, 32), synth.chain_prox([2, 64, 128, 64, 2], [K2] * 4, loss_kind=1)),
+                                       (synth.Geom(2, 1, 2, 1, 2, 46, 46), synth.resblock_prox(36, 1)),
+                                       (synth.Geom(2, 1, 2, 1, 1, 96, 46), synth.resblock_prox(64, 1)),
+                                       (synth.Geom(3, 1, 2, 1, 8, 20, 32), synth.chain_prox([2, 32, 64, 32, 2], [K3] * 4))],
+                         ids=["words_4096", "res36", "res64", "volume"])
+def test_modl_backward_on_split_operands(geom, prox):
+    """The backward pass of a MoDL module on split operands behind a forward pass on the float32 matrix cores."""
+    from paper_2207_08393_amd.runner import ModlRunner
+    assert geom.B * geom.D * geom.H * geom.W >= 4096
+    c = synth.make_custom(32, geom, prox, accel=2.0, centre=2, bias_std=0.1)
+    mu, n_cg = 0.5, 2
+    print("case modl backward", [l.cout for l in prox.layers], flush=True)
+    r = ModlRunner(c, mu, n_cg)
+    gb.gleam_profile_begin()
+    r.step()
+    ran = wide_convolutions(gb.gleam_profile_end())
+    assert {v for n, v in ran.items() if "fwd" in n} <= {0.444, 1.0} and len(ran) >= 3, ran
+    assert {v for n, v in ran.items() if "fwd" not in n} == {4.0}, ran
+    x, loss, grad, aty = r.results()
+    f = og.modl_module_fwd(c.geom, c.prox, c.x_in, c.S, c.M, aty.astype(np.complex128), mu, n_cg, c.theta, c.x_true)
+    g = og.modl_module_bwd(c.geom, c.prox, c.S, c.M, mu, n_cg, c.theta, f)
+    assert_image_close(x, f["x_out"], TOL)
+    assert rel_l2(grad, g) <= TOL
+
+
 def modules_by_hand(c, thetas, lr):
     """What gleam_greedy_iteration does, call by call: x, losses, theta, m, v."""
     from paper_2207_08393_amd.runner import GreedyRunner
