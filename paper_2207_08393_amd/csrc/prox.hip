@@ -870,36 +870,6 @@ __global__ __launch_bounds__(256) void conv_thin_out_kernel(ConvThinOutArgs a, c
     }
 }
 
-// Re-lays one layer's weights as the LDS images conv_mfma_kernel<NB, CK> copies verbatim.  Image
-// (rt, kc, nb) holds row-tap rt, input-channel chunk kc and output-channel block nb as
-// [kw][CK/8][2][NB][4]: element (dw, k = 8g + 4h + s, n) at (((dw*G + g)*2 + h)*NB + n)*4 + s, zero
-// where k or n runs past the layer.  Source element (n, tap, k) is w[n*sn + tapidx*st + k*sk] with
-// tapidx = flip ? taps-1-tap : tap, which covers the forward pass (n = cout, k = cin) and the data
-// gradient (n = cin, k = cout, taps mirrored).
-struct WimgArgs {
-    const float* w;
-    float* wt;
-    long long sn, st, sk;
-    int K, Nn, flip, taps, kw, CK, NB, n_kc, n_nb;
-    long long total;
-};
-__global__ void weights_image_kernel(WimgArgs a) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.total) return;
-    const int img_elems = a.kw * a.CK * a.NB;
-    const long long img = i / img_elems;
-    const int e = (int)(i % img_elems);
-    const int s = e & 3, n = (e >> 2) % a.NB, hg = (e >> 2) / a.NB;   // hg = (dw*G + g)*2 + h
-    const int h = hg & 1, g = (hg >> 1) % (a.CK / 8), dw = (hg >> 1) / (a.CK / 8);
-    const int nb = (int)(img % a.n_nb), kc = (int)((img / a.n_nb) % a.n_kc), rt = (int)(img / ((long long)a.n_nb * a.n_kc));
-    const int k = kc * a.CK + 8 * g + 4 * h + s, nn = nb * a.NB + n;
-    const int tap = rt * a.kw + dw;
-    const int tapidx = a.flip ? a.taps - 1 - tap : tap;
-    float v = 0.f;
-    if (k < a.K && nn < a.Nn) v = a.w[nn * a.sn + tapidx * a.st + k * a.sk];
-    a.wt[i] = v;
-}
-
 static int conv_grid_x(long long n_tiles) {
     const long long cap = 256LL * 2;   // persistent: two workgroups per CU fit (LDS), each loops over tiles
     return (int)(n_tiles < cap ? n_tiles : cap);
@@ -1042,24 +1012,10 @@ static void launch_conv_thin_out_t(const ConvThinOutArgs& t, const float* w, boo
     launch_conv_thin_out_k<KT, KD, KH, KW, 16>(t, w, bf, st);
 }
 
-// wt[n][tap][k] = w[n*sn + tapidx*st + k*sk] (tapidx mirrored when flip), n < 2: the layout the
-// two-channel-output kernel reads, for the data gradient of a layer whose INPUT is the 2-channel image.
-// round_bf: the values are rounded to bfloat16 (kept as float32), for the kernels that multiply bfloat16 data
-// with float32 arithmetic: weights that meet bfloat16 data are bfloat16 values in every kernel.
-__global__ void thin_out_weights_kernel(const float* __restrict__ w, long long sn, long long st_, long long sk, int flip,
-                                        int taps, int K, int round_bf, float* __restrict__ wt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 2 * taps * K) return;
-    const int k = i % K, tap = (i / K) % taps, n = i / (K * taps);
-    const int tapidx = flip ? taps - 1 - tap : tap;
-    const float v = w[n * sn + tapidx * st_ + k * sk];
-    wt[i] = round_bf ? bf16_to_f32(f32_to_bf16(v)) : v;
-}
-
 // Launches the two-channel-output kernel when the layer fits it; *hit tells whether it did.  The forward
 // pass reads theta's own layout; other weight layouts (the data gradient into the image) are re-laid into
-// wt_scratch first.  `in` is bfloat16 when bf.
-static hipError_t launch_conv_thin_out(const ConvArgs& a, const ConvWeights& cw, bool bf, float* wt_scratch, bool* hit,
+// wt first.  `in` is bfloat16 when bf.
+static hipError_t launch_conv_thin_out(const ConvArgs& a, const ConvWeights& cw, bool bf, float* wt, WeightBatch* collect, bool* hit,
                                        hipStream_t st) {
     *hit = false;
     const PixDims& d = a.d;
@@ -1070,7 +1026,6 @@ static hipError_t launch_conv_thin_out(const ConvArgs& a, const ConvWeights& cw,
     // in float32 and gets a rounded copy, so that the result does not depend on which of the two runs
     const bool round_copy = bf && !conv_thin_out_mfma_applies(a.d, a.K, bf);
     const bool direct = in_place && !round_copy;
-    if (!direct && wt_scratch == nullptr) return hipSuccess;
     const bool k2 = d.kt == 1 && d.kd == 1 && d.kh == 3 && d.kw == 3, k3 = d.kt == 1 && d.kd == 3 && d.kh == 3 && d.kw == 3;
     const bool kt3 = d.kt == 3 && d.kd == 1 && d.kh == 1 && d.kw == 1;
     if (!k2 && !k3 && !kt3) return hipSuccess;
@@ -1080,13 +1035,13 @@ static hipError_t launch_conv_thin_out(const ConvArgs& a, const ConvWeights& cw,
     ConvThinOutArgs t{};
     t.in = a.in; t.bias = a.bias; t.add = a.add; t.out = a.out;
     t.K = a.K; t.KC = kc; t.relu_in = a.relu_in; t.relu_out = a.relu_out; t.d = d;
-    const float* wts = cw.w;
-    if (!direct) {
-        const int n = 2 * taps_ * a.K;
-        hipLaunchKernelGGL(thin_out_weights_kernel, dim3((n + 255) / 256), dim3(256), 0, st, cw.w, cw.sn, cw.st, cw.sk, a.flip,
-                           taps_, a.K, round_copy ? 1 : 0, wt_scratch);
-        wts = wt_scratch;
+    if (collect) {
+        if (!direct)
+            collect->job[collect->n++] = WeightJob{cw.w, wt, cw.sn, cw.st, cw.sk, kWeightsThinOut, a.flip, a.K, a.Nn, taps_, d.kw, 0, 0, round_copy ? 1 : 0, 0};
+        *hit = true;
+        return hipSuccess;
     }
+    const float* wts = direct ? cw.w : wt;
     char name[56];
     snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
     KernelScope ks(name, 2.0 * (double)d.Q * a.K * a.Nn * taps_, (bf ? 2.0 : 4.0) * (double)d.Q * a.K + 8.0 * (double)d.Q, st);
@@ -1101,47 +1056,58 @@ static hipError_t launch_conv_thin_out(const ConvArgs& a, const ConvWeights& cw,
     return hipGetLastError();
 }
 
-static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scratch, hipStream_t st, const float* wino_u, const float* split_u) {
+// wt: where this layer's re-laid or transformed weights are, or, with `collect`, are to be made.  split: layers that have kernels on
+// split operands take them.
+static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt, bool split, WeightBatch* collect, hipStream_t st) {
     const int taps_ = a.d.kt * a.d.kd * a.d.kh * a.d.kw;
     {   // two input channels and a wide output: HBM-bound kernels (matrix cores for 3x3x3 taps, vector ALUs otherwise)
+        if (collect && conv_thin_in_applies(a.d, a.K, a.Nn)) return hipSuccess;   // reads theta itself
         bool hit = false;
         const hipError_t e = launch_conv_thin_in(a, cw, false, &hit, st);
         if (hit || e != hipSuccess) return e;
     }
     {   // two output channels and a wide input (forward): HBM-bound kernels (prox_thin.hip where it has the shape)
         bool hit = false;
-        const hipError_t e = launch_conv_thin_out(a, cw, false, wt_scratch, &hit, st);
+        const hipError_t e = launch_conv_thin_out(a, cw, false, wt, collect, &hit, st);
         if (hit || e != hipSuccess) return e;
     }
-    if (split_u) {   // 3x3 and 3x3x3: F(2, 3) on split operands
+    auto enter = [&](int form, int ck, int nb) {
+        collect->job[collect->n++] = WeightJob{cw.w, wt, cw.sn, cw.st, cw.sk, form, a.flip, a.K, a.Nn, taps_, a.d.kw, ck, nb, 0, 0};
+        return hipSuccess;
+    };
+    if (split && wino_enabled() && conv_split_applies(a.d, a.K, a.Nn)) {   // 3x3 and 3x3x3: F(2, 3) on split operands
+        if (collect) return enter(kWeightsSplit, 0, 0);
         SplitConvArgs sa{};
         sa.in = a.in; sa.out = a.out; sa.bias = a.bias; sa.mask_ref = a.mask_ref; sa.add = a.add;
-        sa.bits_in = a.bits_in; sa.bits_out = a.bits_out; sa.u = split_u;
+        sa.bits_in = a.bits_in; sa.bits_out = a.bits_out; sa.u = wt;
         sa.K = a.K; sa.Nn = a.Nn; sa.relu_out = a.relu_out; sa.mask_acc = a.mask_acc; sa.mask_add = a.mask_add;
         char name[56];
         snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
         return launch_conv_split(sa, a.d, a.relu_in, name, st);
     }
     if (wino_enabled() && conv_wino_applies(a.d, a.K, a.Nn)) {   // 3x3 in the plane: Winograd F(2x2, 3x3)
+        if (collect) return enter(kWeightsWino, 0, 0);
         WinoArgs wa{};
-        wa.in = a.in; wa.out = a.out; wa.bias = a.bias; wa.mask_ref = a.mask_ref; wa.add = a.add;
+        wa.in = a.in; wa.out = a.out; wa.u = wt; wa.bias = a.bias; wa.mask_ref = a.mask_ref; wa.add = a.add;
         wa.bits_in = a.bits_in; wa.bits_out = a.bits_out;
         wa.K = a.K; wa.Nn = a.Nn; wa.relu_out = a.relu_out; wa.mask_acc = a.mask_acc; wa.mask_add = a.mask_add;
         wa.H = a.d.H; wa.W = a.d.W; wa.NI = a.d.Q / ((long long)a.d.H * a.d.W);
         char name[56];
         snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
-        return launch_conv_wino(wa, cw.w, cw.sn, cw.st, cw.sk, a.flip, a.relu_in, wt_scratch, wino_u, name, st);
+        return launch_conv_wino(wa, a.relu_in, name, st);
     }
     if (wino_enabled() && conv_wino3_applies(a.d, a.K, a.Nn)) {   // 3x3x3: Winograd in the slice, depth taps summed
+        if (collect) return enter(kWeightsWino3, 0, 0);
         WinoArgs wa{};
-        wa.in = a.in; wa.out = a.out; wa.bias = a.bias; wa.mask_ref = a.mask_ref; wa.add = a.add;
+        wa.in = a.in; wa.out = a.out; wa.u = wt; wa.bias = a.bias; wa.mask_ref = a.mask_ref; wa.add = a.add;
         wa.K = a.K; wa.Nn = a.Nn; wa.relu_out = a.relu_out; wa.mask_acc = a.mask_acc; wa.mask_add = a.mask_add;
         wa.H = a.d.H; wa.W = a.d.W; wa.D = a.d.D; wa.NI = a.d.Q / ((long long)a.d.H * a.d.W);
         char name[56];
         snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
-        return launch_conv_wino3(wa, cw.w, cw.sn, cw.st, cw.sk, a.flip, a.relu_in, wt_scratch, name, st);
+        return launch_conv_wino3(wa, a.relu_in, name, st);
     }
     if (!(kernel_policy() & GLEAM_POLICY_NO_FRAME_WALK) && conv_time_applies(a.d, a.K, a.Nn)) {   // temporal 3x1x1: walk along the frames
+        if (collect) return hipSuccess;   // reads theta itself
         TimeConvArgs t{};
         t.in = a.in; t.out = a.out; t.bias = a.bias; t.mask_ref = a.mask_ref; t.add = a.add;
         t.w = cw.w; t.sn = cw.sn; t.st = cw.st; t.sk = cw.sk; t.flip = a.flip;
@@ -1153,16 +1119,8 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt_scrat
     }
     const int cover = conv_cover_channels(a.d, a.K, a.Nn);
     const int ck = conv_ck(a.K), nb = cover ? cover : conv_nb(a.Nn);
-    {
-        WimgArgs t{};
-        t.w = cw.w; t.wt = wt_scratch; t.sn = cw.sn; t.st = cw.st; t.sk = cw.sk;
-        t.K = a.K; t.Nn = a.Nn; t.flip = a.flip; t.taps = taps_; t.kw = a.d.kw; t.CK = ck; t.NB = nb;
-        t.n_kc = (a.K + ck - 1) / ck; t.n_nb = (a.Nn + nb - 1) / nb;
-        t.total = (long long)taps_ * t.n_kc * ck * t.n_nb * nb;
-        KernelScope ks("weights_image", 0.0, 8.0 * (double)t.total, st);
-        hipLaunchKernelGGL(weights_image_kernel, dim3((unsigned)((t.total + 255) / 256)), dim3(256), 0, st, t);
-    }
-    a.wt = wt_scratch;
+    if (collect) return enter(kWeightsImage, ck, nb);
+    a.wt = wt;
     char name[56];
     snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
     KernelScope ks(name, 2.0 * (double)a.d.Q * a.K * a.Nn * taps_, 4.0 * (double)a.d.Q * (a.K + a.Nn), st);
@@ -2097,45 +2055,26 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
     w += plan.partial_bytes;
     plan.bias_partial_off = w;
     w += align256((size_t)kThinSplit * kMaxChannels * sizeof(float));
-    size_t max_img = 0;
+    // the weights of every layer as its kernel of this pass reads them, whichever that is
+    size_t img_bytes = 0;
     for (int l = 0; l < L; ++l) {
         const gleam_conv& c = p.layers[l];
         const int taps = c.kt * c.kd * c.kh * c.kw;
-        const size_t f = conv_wimg_floats(c.cin, c.cout, taps), b = conv_wimg_floats(c.cout, c.cin, taps);
-        max_img = f > max_img ? f : max_img;
-        max_img = b > max_img ? b : max_img;
-        if (taps == 9) {      // transformed weights of the Winograd path (16 values per channel pair)
-            const size_t wn = conv_wino_weight_floats(c.cin, c.cout);
-            max_img = wn > max_img ? wn : max_img;
+        size_t floats = 0;
+        auto room = [&](size_t n) { floats = n > floats ? n : floats; };
+        room(conv_wimg_floats(c.cin, c.cout, taps));
+        room(conv_wimg_floats(c.cout, c.cin, taps));
+        if (taps == 9) room(conv_wino_weight_floats(c.cin, c.cout));      // 16 values per channel pair
+        if (taps == 27) room(conv_wino3_weight_floats(c.cin, c.cout));    // ... and depth tap
+        if (p.dtype == 1) {   // half the bytes per element, but chunked by 32 channels
+            room((conv_bf16_wimg_elems(c.cin, c.cout, taps) + 1) / 2);
+            room((conv_bf16_wimg_elems(c.cout, c.cin, taps) + 1) / 2);
         }
-        if (taps == 27) {     // ... and of its 3x3x3 form (16 values per depth tap)
-            const size_t wn = conv_wino3_weight_floats(c.cin, c.cout);
-            max_img = wn > max_img ? wn : max_img;
-        }
-        if (p.dtype == 1) {   // bf16 images are half the bytes per element, but chunked by 32 channels
-            const size_t fb = (conv_bf16_wimg_elems(c.cin, c.cout, taps) + 1) / 2, bb = (conv_bf16_wimg_elems(c.cout, c.cin, taps) + 1) / 2;
-            max_img = fb > max_img ? fb : max_img;
-            max_img = bb > max_img ? bb : max_img;
-        }
+        if (p.dtype == 0 && split && conv_split_applies(pix_dims(g, c), c.cin, c.cout)) room(conv_split_weight_floats(c.cin, c.cout, c.kd));
+        if (p.dtype == 0 && split && conv_split_applies(pix_dims(g, c), c.cout, c.cin)) room(conv_split_weight_floats(c.cout, c.cin, c.kd));
+        plan.wimg_layer[l] = img_bytes;
+        img_bytes += align256(floats * sizeof(float));
     }
-    // behind the per-layer scratch: the transformed weights of all Winograd and of all split-operand layers of one pass, each
-    // made in one launch
-    size_t wino_floats = 0, split_floats = 0;
-    if (p.dtype == 0)
-        for (int l = 0; l < L; ++l) {
-            const gleam_conv& c = p.layers[l];
-            PixDims dd{};
-            dd.T = (int)g.T; dd.D = (int)g.D; dd.H = (int)g.H; dd.W = (int)g.W;
-            dd.kt = c.kt; dd.kd = c.kd; dd.kh = c.kh; dd.kw = c.kw;
-            if (conv_wino_applies(dd, c.cin, c.cout) || conv_wino_applies(dd, c.cout, c.cin))
-                wino_floats += (conv_wino_weight_floats(c.cin, c.cout) + 63) / 64 * 64;
-            const size_t f = split && conv_split_applies(dd, c.cin, c.cout) ? conv_split_weight_floats(c.cin, c.cout, c.kd) : 0;
-            const size_t b = split && conv_split_applies(dd, c.cout, c.cin) ? conv_split_weight_floats(c.cout, c.cin, c.kd) : 0;
-            split_floats += ((f > b ? f : b) + 63) / 64 * 64;
-        }
-    plan.wino_u_off = align256(max_img * sizeof(float));
-    plan.split_u_off = plan.wino_u_off + align256(wino_floats * sizeof(float));
-    const size_t img_bytes = plan.split_u_off + align256(split_floats * sizeof(float));
     plan.wimg_off_bwd = w;
     w += img_bytes;
     const size_t bwd_ws = w;
@@ -2165,36 +2104,7 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
                         unsigned char* act_base, const float2* x_ref, float2* x_out, float* loss, void* ws,
                         hipStream_t st) {
     const int L = p.n_layers;
-    const float* wino_u[kMaxLayers] = {};
-    if (p.dtype == 0 && wino_enabled()) {   // transformed weights of every Winograd layer, one launch
-        WinoWeightBatch wb{};
-        float* up = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.wino_u_off);
-        for (int l = 0; l < L; ++l) {
-            const gleam_conv& c = p.layers[l];
-            if ((plan.split && conv_split_applies(pix_dims(g, c), c.cin, c.cout)) || !conv_wino_applies(pix_dims(g, c), c.cin, c.cout)) continue;
-            wb.job[wb.n++] = WinoWeightJob{theta + plan.w_off[l], (long long)(9 * c.cin), (long long)c.cin, 1, 0, c.cin, c.cout, up};
-            wino_u[l] = up;
-            up += (conv_wino_weight_floats(c.cin, c.cout) + 63) / 64 * 64;
-        }
-        const hipError_t e = wino_weights_batch(wb, st);
-        if (e != hipSuccess) return e;
-    }
-    const float* split_u[kMaxLayers] = {};
-    if (p.dtype == 0 && plan.split && wino_enabled()) {   // the same for the split-operand layers
-        SplitWeightBatch wb{};
-        float* up = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.split_u_off);
-        for (int l = 0; l < L; ++l) {
-            const gleam_conv& c = p.layers[l];
-            if (!conv_split_applies(pix_dims(g, c), c.cin, c.cout)) continue;
-            wb.job[wb.n++] = SplitWeightJob{theta + plan.w_off[l], (long long)(9 * c.kd * c.cin), (long long)c.cin, 1, 0, c.cin, c.cout, c.kd,
-                                            reinterpret_cast<unsigned short*>(up)};
-            split_u[l] = up;
-            up += (conv_split_weight_floats(c.cin, c.cout, c.kd) + 63) / 64 * 64;
-        }
-        const hipError_t e = split_weights_batch(wb, st);
-        if (e != hipSuccess) return e;
-    }
-    for (int l = 0; l < L; ++l) {
+    auto layer = [&](int l, WeightBatch* collect) -> hipError_t {   // runs layer l, or enters its weights
         const gleam_conv& c = p.layers[l];
         const size_t taps = (size_t)c.kt * c.kd * c.kh * c.kw;
         ConvArgs a{};
@@ -2204,13 +2114,15 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
         a.bias = c.has_bias ? theta + plan.b_off[l] : nullptr;
         a.add = c.skip_src >= 0 ? reinterpret_cast<const float*>(act_base + plan.act_off[c.skip_src]) : nullptr;
         a.K = c.cin; a.Nn = c.cout;
-        if ((wino_u[l] || split_u[l]) && l + 1 < L && plan.sign_off[l + 1]) a.bits_out = reinterpret_cast<unsigned*>(act_base + plan.sign_off[l + 1]);
+        if (p.dtype == 0 && wino_enabled() && l + 1 < L && plan.sign_off[l + 1]) a.bits_out = reinterpret_cast<unsigned*>(act_base + plan.sign_off[l + 1]);
         a.relu_in = (c.relu_in && !plan.post_relu[l]) ? 1 : 0;
         a.relu_out = (c.relu_out || (l + 1 < L && plan.post_relu[l + 1])) ? 1 : 0;
         a.d = pix_dims(g, c);
+        float* const wt = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.wimg_layer[l]);
         hipError_t e;
         if (p.dtype == 1) {
             if (l == 0) {           // float32 image in, bfloat16 features out
+                if (collect) return hipSuccess;   // reads theta itself
                 bool hit = false;
                 e = launch_conv_thin_in(a, cw, true, &hit, st);
                 // cannot miss: prox_bf16_supported (checked before any launch) admits exactly the first-layer
@@ -2219,9 +2131,8 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
             } else {                // bfloat16 in; the last layer writes the float32 image
                 if (l == L - 1) {
                     bool hit = false;
-                    e = launch_conv_thin_out(a, cw, true, reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd), &hit, st);
-                    if (e != hipSuccess) return e;
-                    if (hit) continue;
+                    e = launch_conv_thin_out(a, cw, true, wt, collect, &hit, st);
+                    if (hit || e != hipSuccess) return e;
                 }
                 ConvBf16Args b{};
                 b.in = reinterpret_cast<const unsigned short*>(a.in);
@@ -2233,12 +2144,24 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
                 b.relu_in = a.relu_in; b.relu_out = a.relu_out;
                 b.d = a.d;
                 if (l + 1 < L && plan.sign_off[l + 1]) b.bits_out = reinterpret_cast<unsigned*>(act_base + plan.sign_off[l + 1]);
-                e = launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 0,
-                                     reinterpret_cast<unsigned short*>((unsigned char*)ws + plan.wimg_off_fwd), st);
+                e = launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 0, reinterpret_cast<unsigned short*>(wt), collect, st);
             }
         } else {
-            e = launch_conv(a, cw, reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd), st, wino_u[l], split_u[l]);
+            e = launch_conv(a, cw, wt, plan.split, collect, st);
         }
+        return e;
+    };
+    WeightBatch wb{};
+    for (int l = 0; l < L; ++l) {
+        const hipError_t e = layer(l, &wb);
+        if (e != hipSuccess) return e;
+    }
+    {
+        const hipError_t e = prepare_weights(wb, st);
+        if (e != hipSuccess) return e;
+    }
+    for (int l = 0; l < L; ++l) {
+        const hipError_t e = layer(l, nullptr);
         if (e != hipSuccess) return e;
     }
     if (x_ref) {
@@ -2444,34 +2367,69 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
     // pending[s]: layer (1-based) whose output gradient also flows into t_s through its skip, or 0
     int pending[kMaxLayers + 1] = {0};
 
-    const float* wino_u[kMaxLayers] = {};   // transformed (mirrored, transposed) weights of the data gradients, one launch
-    if (p.dtype == 0 && wino_enabled()) {
-        WinoWeightBatch wb{};
-        float* up = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.wino_u_off);
-        for (int l = 2; l <= L; ++l) {   // the data gradient of layer l maps cout -> cin channels
-            const gleam_conv& c = p.layers[l - 1];
-            if ((plan.split && conv_split_applies(pix_dims(g, c), c.cout, c.cin)) || !conv_wino_applies(pix_dims(g, c), c.cout, c.cin)) continue;
-            wb.job[wb.n++] = WinoWeightJob{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(9 * c.cin), 1, c.cout, c.cin, up};
-            wino_u[l - 1] = up;
-            up += (conv_wino_weight_floats(c.cout, c.cin) + 63) / 64 * 64;
+    // gradient into t_{l-1} (the module's input for l = 1), or, with `collect`, its weights
+    auto data_gradient = [&](int l, WeightBatch* collect) -> hipError_t {
+        const gleam_conv& c = p.layers[l - 1];
+        const size_t taps = (size_t)c.kt * c.kd * c.kh * c.kw;
+        const PixDims d = pix_dims(g, c);
+        float* const wt = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.wimg_layer[l - 1]);
+        ConvArgs a{};
+        a.in = G(l);
+        const ConvWeights cw{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(taps * c.cin)};
+        a.flip = 1;
+        a.K = c.cout; a.Nn = c.cin;
+        a.d = d;
+        if (l == 1) {
+            // a module of several unrolled iterations: gradient with respect to this iteration's input u,
+            // dL/du = conv_1^T(G_1) + (gradient of a skip taken from u), float32 2 channels
+            a.out = reinterpret_cast<float*>(g_in);
+            a.add = skip_from_input ? G(skip_from_input) : nullptr;
+            if (p.dtype == 0) return launch_conv(a, cw, wt, false, collect, st);
+            bool hit = false;
+            const hipError_t e = launch_conv_thin_out(a, cw, true, wt, collect, &hit, st);
+            if (hit || e != hipSuccess) return e;
+            ConvBf16Args b{};
+            b.in = reinterpret_cast<const unsigned short*>(a.in);
+            b.out = a.out; b.add = a.add; b.out_f32 = 1;
+            b.K = a.K; b.Nn = a.Nn; b.d = d;
+            return launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 1, reinterpret_cast<unsigned short*>(wt), collect, st);
         }
-        const hipError_t e = wino_weights_batch(wb, st);
+        // fused with the ReLU masks and the pending skip gradient
+        const gleam_conv& below = p.layers[l - 2];  // layer that produced t_{l-1}
+        a.out = G(l - 1);
+        a.mask_acc = (c.relu_in || below.relu_out) ? 1 : 0;
+        a.mask_add = below.relu_out ? 1 : 0;
+        a.mask_ref = (a.mask_acc || a.mask_add) ? act(l - 1) : nullptr;
+        a.add = pending[l - 1] ? G(pending[l - 1]) : nullptr;
+        if (p.dtype == 0) {
+            if (wino_enabled() && a.mask_ref && plan.sign_off[l - 1])   // then the forward pass wrote them
+                a.bits_in = reinterpret_cast<const unsigned*>(saved + plan.sign_off[l - 1]);
+            return launch_conv(a, cw, wt, plan.split, collect, st);
+        }
+        if (l == L) {           // float32 loss gradient in, bfloat16 gradient out
+            if (collect) return hipSuccess;   // reads theta itself
+            bool hit = false;
+            const hipError_t e = launch_conv_thin_in(a, cw, true, &hit, st);
+            return e == hipSuccess && !hit ? hipErrorInvalidValue : e;
+        }
+        ConvBf16Args b{};
+        b.in = reinterpret_cast<const unsigned short*>(a.in);
+        b.out = a.out;
+        b.mask_ref = reinterpret_cast<const unsigned short*>(a.mask_ref);
+        b.add = a.add;
+        b.K = a.K; b.Nn = a.Nn;
+        b.mask_acc = a.mask_acc; b.mask_add = a.mask_add;
+        b.d = d;
+        if (a.mask_ref && plan.sign_off[l - 1]) b.bits_in = reinterpret_cast<const unsigned*>(saved + plan.sign_off[l - 1]);
+        return launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 1, reinterpret_cast<unsigned short*>(wt), collect, st);
+    };
+    WeightBatch weights{};
+    for (int l = g_in ? 1 : 2; l <= L; ++l) {
+        const hipError_t e = data_gradient(l, &weights);
         if (e != hipSuccess) return e;
     }
-
-    const float* split_u[kMaxLayers] = {};
-    if (p.dtype == 0 && plan.split && wino_enabled()) {
-        SplitWeightBatch wb{};
-        float* up = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.split_u_off);
-        for (int l = 2; l <= L; ++l) {
-            const gleam_conv& c = p.layers[l - 1];
-            if (!conv_split_applies(pix_dims(g, c), c.cout, c.cin)) continue;
-            wb.job[wb.n++] = SplitWeightJob{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(9 * c.kd * c.cin), 1, c.cout, c.cin, c.kd,
-                                            reinterpret_cast<unsigned short*>(up)};
-            split_u[l - 1] = up;
-            up += (conv_split_weight_floats(c.cout, c.cin, c.kd) + 63) / 64 * 64;
-        }
-        const hipError_t e = split_weights_batch(wb, st);
+    {
+        const hipError_t e = prepare_weights(weights, st);
         if (e != hipSuccess) return e;
     }
 
@@ -2614,68 +2572,8 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
         }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (l == 1) {
-            if (!g_in) break;   // nothing flows into t_0 = u: the module input is detached
-            // a module of several unrolled iterations: gradient with respect to this iteration's input u,
-            // dL/du = conv_1^T(G_1) + (gradient of a skip taken from u), float32 2 channels
-            ConvArgs a{};
-            a.in = G(1); a.out = reinterpret_cast<float*>(g_in);
-            const ConvWeights cw{theta + plan.w_off[0], 1, (long long)c.cin, (long long)(taps * c.cin)};
-            a.flip = 1;
-            a.K = c.cout; a.Nn = c.cin;
-            a.add = skip_from_input ? G(skip_from_input) : nullptr;
-            a.d = d;
-            float* scratch = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd);
-            if (p.dtype == 1) {
-                bool hit = false;
-                e = launch_conv_thin_out(a, cw, true, scratch, &hit, st);
-                if (e == hipSuccess && !hit) {
-                    ConvBf16Args b{};
-                    b.in = reinterpret_cast<const unsigned short*>(a.in);
-                    b.out = a.out; b.add = a.add; b.out_f32 = 1;
-                    b.K = a.K; b.Nn = a.Nn; b.d = d;
-                    e = launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 1, reinterpret_cast<unsigned short*>(scratch), st);
-                }
-            } else {
-                e = launch_conv(a, cw, scratch, st, nullptr, nullptr);   // two output channels: neither kernel takes it
-            }
-            if (e != hipSuccess) return e;
-            break;
-        }
-        // data gradient into t_{l-1}, fused with the ReLU masks and the pending skip gradient
-        const gleam_conv& below = p.layers[l - 2];  // layer that produced t_{l-1}
-        ConvArgs a{};
-        a.in = G(l); a.out = G(l - 1);
-        const ConvWeights cw{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(taps * c.cin)};
-        a.flip = 1;
-        a.K = c.cout; a.Nn = c.cin;
-        a.mask_acc = (c.relu_in || below.relu_out) ? 1 : 0;
-        a.mask_add = below.relu_out ? 1 : 0;
-        a.mask_ref = (a.mask_acc || a.mask_add) ? act(l - 1) : nullptr;
-        a.add = pending[l - 1] ? G(pending[l - 1]) : nullptr;
-        if (p.dtype == 0 && wino_enabled() && a.mask_ref && plan.sign_off[l - 1])   // then the forward pass wrote them
-            a.bits_in = reinterpret_cast<const unsigned*>(saved + plan.sign_off[l - 1]);
-        a.d = d;
-        if (p.dtype == 1) {
-            if (l == L) {           // float32 loss gradient in, bfloat16 gradient out
-                bool hit = false;
-                e = launch_conv_thin_in(a, cw, true, &hit, st);
-                if (e == hipSuccess && !hit) e = hipErrorInvalidValue;
-            } else {
-                ConvBf16Args b{};
-                b.in = reinterpret_cast<const unsigned short*>(a.in);
-                b.out = a.out;
-                b.mask_ref = reinterpret_cast<const unsigned short*>(a.mask_ref);
-                b.add = a.add;
-                b.K = a.K; b.Nn = a.Nn;
-                b.mask_acc = a.mask_acc; b.mask_add = a.mask_add;
-                b.d = d;
-                if (a.mask_ref && plan.sign_off[l - 1]) b.bits_in = reinterpret_cast<const unsigned*>(saved + plan.sign_off[l - 1]);
-                e = launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 1, reinterpret_cast<unsigned short*>(wsb + plan.wimg_off_bwd), st);
-            }
-        } else {
-            e = launch_conv(a, cw, reinterpret_cast<float*>(wsb + plan.wimg_off_bwd), st, wino_u[l - 1], split_u[l - 1]);
-        }
+        if (l == 1 && !g_in) break;   // nothing flows into t_0 = u: the module input is detached
+        e = data_gradient(l, nullptr);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

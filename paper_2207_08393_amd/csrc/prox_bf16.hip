@@ -24,34 +24,6 @@ namespace gleam {
 
 constexpr int kBfCK = 32;   // input channels per staged chunk of the forward / data-gradient kernel
 
-// ------------------------------------------------------------------ weights -> bf16 LDS images
-// Image (rt, kc, nb) = [kw][kBfCK/16][2][NB][8]: element (dw, k = 16g + 8h + s, n) at
-// ((((dw*G + g)*2 + h)*NB + n)*8 + s, zero past the layer; source (n, tap, k) at w[n*sn + tapidx*st + k*sk].
-struct WimgBf16Args {
-    const float* w;
-    unsigned short* wt;
-    long long sn, st, sk;
-    int K, Nn, flip, taps, kw, NB, n_kc, n_nb;
-    long long total;
-};
-__global__ void weights_image_bf16_kernel(WimgBf16Args a) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.total) return;
-    constexpr int G = kBfCK / 16;
-    const int img_elems = a.kw * kBfCK * a.NB;
-    const long long img = i / img_elems;
-    const int e = (int)(i % img_elems);
-    const int s = e & 7, n = (e >> 3) % a.NB, hg = (e >> 3) / a.NB;
-    const int h = hg & 1, g = (hg >> 1) % G, dw = (hg >> 1) / G;
-    const int nb = (int)(img % a.n_nb), kc = (int)((img / a.n_nb) % a.n_kc), rt = (int)(img / ((long long)a.n_nb * a.n_kc));
-    const int k = kc * kBfCK + 16 * g + 8 * h + s, nn = nb * a.NB + n;
-    const int tap = rt * a.kw + dw;
-    const int tapidx = a.flip ? a.taps - 1 - tap : tap;
-    float v = 0.f;
-    if (k < a.K && nn < a.Nn) v = a.w[nn * a.sn + tapidx * a.st + k * a.sk];
-    a.wt[i] = f32_to_bf16(v);
-}
-
 static inline int bf_nb(int Nn) { return Nn <= 32 ? 32 : 64; }
 size_t conv_bf16_wimg_elems(int K, int Nn, int taps) {
     const int nb = bf_nb(Nn);
@@ -344,24 +316,6 @@ constexpr int kB2StageStride = 34;    // floats per staged output pixel: 32 chan
 constexpr int kB2RegLoads = (kB2RegQuads + 255) / 256;   // direct-load slots per lane: region
 constexpr int kB2WLoads = (kB2WQuads + 255) / 256;       // and weights
 
-// weights as LDS images: wt[((((ny*n_kc + kc)*9 + tap)*2 + hq)*64 + nn)*8 + kk], k = 16*kc + 8*hq + kk, n = 64*ny + nn;
-// one zero quad follows.  Source (n, tap, k) at w[n*sn + tapidx*st + k*sk], taps mirrored for the data gradient.
-__global__ __launch_bounds__(256) void weights_image_bf16_2d_kernel(const float* __restrict__ w, long long sn, long long st_, long long sk,
-                                                                    int flip, int K, int Nn, unsigned short* __restrict__ wt) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long total = 9LL * K * Nn;
-    if (i < 8) wt[total + i] = 0;
-    if (i >= total) return;
-    const int kk = (int)(i & 7), nn = (int)((i >> 3) & 63), hq = (int)((i >> 9) & 1);
-    const long long rest = i >> 10;
-    const int tap = (int)(rest % 9);
-    const long long ck = rest / 9;
-    const int n_kc = K / 16;
-    const int kc = (int)(ck % n_kc), ny = (int)(ck / n_kc);
-    const int k = 16 * kc + 8 * hq + kk, n = 64 * ny + nn;
-    wt[i] = f32_to_bf16(w[n * sn + (flip ? 8 - tap : tap) * st_ + k * sk]);
-}
-
 template <bool RELU>
 __global__ __launch_bounds__(256, 2) void conv_bf16_2d_kernel(ConvBf16Args a, int bx_n, int by_n, long long n_blocks) {
     // Two chunk buffers as two arrays, and the chunk loop written out for both: the compiler orders a direct load's
@@ -617,26 +571,6 @@ template <int NKC> struct RwGeom {
     static constexpr int LOADS = (QUADS + 63) / 64;      // wave-wide direct loads per region
     static constexpr int PER_LANE = (LOADS + 3) / 4;
 };
-
-// weights as A operands: wt[((((ny*4 + wave)*9 + tap)*NKC + kc)*64 + lane)*8 + s] = W[n = 128*ny + 32*wave + (lane & 31)]
-// [tap][k = 16*kc + 8*(lane >> 5) + s]; one zero quad follows.  Source (n, tap, k) at w[n*sn + tapidx*st + k*sk].
-__global__ __launch_bounds__(256) void weights_image_bf16_rw_kernel(const float* __restrict__ w, long long sn, long long st_, long long sk,
-                                                                    int flip, int K, int Nn, unsigned short* __restrict__ wt) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long total = 9LL * K * Nn;
-    if (i < 8) wt[total + i] = 0;
-    if (i >= total) return;
-    const int nkc = K / 16;
-    const int s = (int)(i & 7), lane = (int)((i >> 3) & 63);
-    long long rest = i >> 9;
-    const int kc = (int)(rest % nkc);
-    rest /= nkc;
-    const int tap = (int)(rest % 9);
-    rest /= 9;
-    const int wave = (int)(rest & 3), ny = (int)(rest >> 2);
-    const int n = 128 * ny + 32 * wave + (lane & 31), k = 16 * kc + 8 * (lane >> 5) + s;
-    wt[i] = f32_to_bf16(w[n * sn + (flip ? 8 - tap : tap) * st_ + k * sk]);
-}
 
 // VAR: 0 forward; 1 forward that leaves the ReLU mask of its output as lane masks; 2 data gradient with the ReLU mask
 // taken from the activation; 3 data gradient with the mask taken from lane masks.
@@ -945,15 +879,7 @@ static bool conv_bf16_rw_applies(const ConvBf16Args& a) {
            12.0 * a.d.W * a.K < 2.0e9 && 2.0 * (double)a.d.Q * a.Nn < 4.0e9;
 }
 
-static hipError_t launch_conv_bf16_rw(ConvBf16Args a, const float* w, long long sn, long long st_, long long sk, int flip,
-                                      unsigned short* wt_scratch, hipStream_t st) {
-    {
-        const long long total = 9LL * a.K * a.Nn;
-        KernelScope ks("weights_image_bf16", 0.0, 6.0 * (double)total, st);
-        hipLaunchKernelGGL(weights_image_bf16_rw_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w, sn, st_, sk, flip,
-                           a.K, a.Nn, wt_scratch);
-    }
-    a.wt = wt_scratch;
+static hipError_t launch_conv_bf16_rw(const ConvBf16Args& a, int flip, hipStream_t st) {
     const int bx_n = (a.d.W + 31) / 32, by_n = (a.d.H + 3) / 4;
     const long long n_img = a.d.Q / ((long long)a.d.H * a.d.W);
     const long long n_blocks = n_img * bx_n * by_n;
@@ -1004,15 +930,7 @@ size_t conv_bf16_sign_words(const PixDims& d, int Nn, int variant) {
     return n_img * ((d.W + 31) / 32) * ((d.H + kB2TileRows - 1) / kB2TileRows) * 256 * 4 * (size_t)(Nn / 64);
 }
 
-static hipError_t launch_conv_bf16_2d(ConvBf16Args a, const float* w, long long sn, long long st_, long long sk, int flip,
-                                      unsigned short* wt_scratch, hipStream_t st) {
-    {
-        const long long total = 9LL * a.K * a.Nn;
-        KernelScope ks("weights_image_bf16", 0.0, 6.0 * (double)total, st);
-        hipLaunchKernelGGL(weights_image_bf16_2d_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w, sn, st_, sk, flip,
-                           a.K, a.Nn, wt_scratch);
-    }
-    a.wt = wt_scratch;
+static hipError_t launch_conv_bf16_2d(const ConvBf16Args& a, int flip, hipStream_t st) {
     const int bx_n = (a.d.W + 31) / 32, by_n = (a.d.H + kB2TileRows - 1) / kB2TileRows;
     const long long n_img = a.d.Q / ((long long)a.d.H * a.d.W);
     const long long n_blocks = n_img * bx_n * by_n;
@@ -1028,22 +946,19 @@ static hipError_t launch_conv_bf16_2d(ConvBf16Args a, const float* w, long long 
 }
 
 hipError_t launch_conv_bf16(const ConvBf16Args& a_in, const float* w, long long sn, long long st_, long long sk, int flip,
-                            unsigned short* wt_scratch, hipStream_t stream) {
+                            unsigned short* wt, WeightBatch* collect, hipStream_t stream) {
     ConvBf16Args a = a_in;
-    if (bf16_2d_enabled() && conv_bf16_rw_applies(a)) return launch_conv_bf16_rw(a, w, sn, st_, sk, flip, wt_scratch, stream);
-    if (bf16_2d_enabled() && conv_bf16_2d_applies(a)) return launch_conv_bf16_2d(a, w, sn, st_, sk, flip, wt_scratch, stream);
+    a.wt = wt;
     const int taps = a.d.kt * a.d.kd * a.d.kh * a.d.kw;
     const int nb = bf_nb(a.Nn);
-    {
-        WimgBf16Args t{};
-        t.w = w; t.wt = wt_scratch; t.sn = sn; t.st = st_; t.sk = sk;
-        t.K = a.K; t.Nn = a.Nn; t.flip = flip; t.taps = taps; t.kw = a.d.kw; t.NB = nb;
-        t.n_kc = (a.K + kBfCK - 1) / kBfCK; t.n_nb = (a.Nn + nb - 1) / nb;
-        t.total = (long long)conv_bf16_wimg_elems(a.K, a.Nn, taps);
-        KernelScope ks("weights_image_bf16", 0.0, 6.0 * (double)t.total, stream);
-        hipLaunchKernelGGL(weights_image_bf16_kernel, dim3((unsigned)((t.total + 255) / 256)), dim3(256), 0, stream, t);
+    const bool rw = bf16_2d_enabled() && conv_bf16_rw_applies(a), tile = !rw && bf16_2d_enabled() && conv_bf16_2d_applies(a);
+    if (collect) {
+        collect->job[collect->n++] = WeightJob{w, wt, sn, st_, sk, rw ? kWeightsBf16Resident : tile ? kWeightsBf16Tile : kWeightsImageBf16, flip,
+                                               a.K, a.Nn, taps, a.d.kw, kBfCK, nb, 0, 0};
+        return hipSuccess;
     }
-    a.wt = wt_scratch;
+    if (rw) return launch_conv_bf16_rw(a, flip, stream);
+    if (tile) return launch_conv_bf16_2d(a, flip, stream);
     char name[56];
     snprintf(name, sizeof(name), "conv_bf16_%s_%dto%d_t%d", flip ? "dgrad" : "fwd", a.K, a.Nn, taps);
     KernelScope ks(name, 2.0 * (double)a.d.Q * a.K * a.Nn * taps, 2.0 * (double)a.d.Q * (a.K + a.Nn), stream);

@@ -153,11 +153,31 @@ __device__ __forceinline__ ChunkIter chunk_next(ChunkIter x, int n_kc, int nck, 
     return x;
 }
 
+// One layer's weights, re-laid or transformed into what its kernel reads (weights.hip has the forms).  Element (output n, tap t,
+// input k) of the source is w[n*sn + t*st + k*sk]; flip: taps mirrored (data gradient: n counts its outputs, the layer's inputs).
+enum WeightForm { kWeightsImage, kWeightsImageBf16, kWeightsBf16Tile, kWeightsBf16Resident, kWeightsThinOut, kWeightsSplit, kWeightsWino, kWeightsWino3 };
+struct WeightJob {
+    const float* w;
+    void* out;
+    long long sn, st, sk;
+    int form, flip, K, Nn, taps;
+    int kw, CK, NB;        // images: taps along W, input channels per chunk, output channels per image
+    int round_bf;          // kWeightsThinOut: values rounded to bfloat16
+    long long threads;     // set by prepare_weights
+};
+// The jobs of a pass, all made in one launch (a launch costs more than the work of one layer).  The launchers below take a batch:
+// not null, they enter the job that the launch will need, if any, and launch nothing; null, they launch and rely on it being done.
+struct WeightBatch {
+    int n;
+    WeightJob job[kMaxLayers];
+};
+hipError_t prepare_weights(WeightBatch& b, hipStream_t stream);
+
 // Forward and data-gradient convolution on the fp32 matrix cores (prox.hip, prox_cover.hip).
 struct ConvArgs {
     const float* in;        // [Q][K]
     float* out;             // [Q][Nn]
-    const float* wt;        // weights re-laid as LDS images, see weights_image_kernel
+    const float* wt;        // weights re-laid as LDS images, see weights.hip
     const float* bias;      // [Nn] or null
     const float* mask_ref;  // [Q][Nn] or null: ReLU mask source (value > 0 passes)
     const float* add;       // [Q][Nn] or null: added to the result
@@ -179,7 +199,7 @@ hipError_t launch_conv_cover(const ConvArgs& a, hipStream_t stream);
 struct SplitConvArgs {
     const float* in;        // [slices][H][W][K]
     float* out;             // [slices][H][W][Nn]
-    const void* u;          // transformed and split weights made by split_weights_batch
+    const void* u;          // transformed and split weights (kWeightsSplit)
     const float* bias;      // [Nn] or null
     const float* mask_ref;  // [Q][Nn] or null: ReLU mask source (value > 0 passes)
     const float* add;       // [Q][Nn] or null
@@ -194,23 +214,11 @@ size_t conv_split_weight_floats(int K, int Nn, int kd);
 // 32-bit words of the sign-bit image of a [pixels][Nn] tensor as the kernel's threads write and read it
 size_t conv_split_sign_words(const PixDims& d, int Nn);
 hipError_t launch_conv_split(SplitConvArgs a, const PixDims& d, int relu_in, const char* name, hipStream_t stream);
-// Transformed weights of several layers in one launch (a launch costs more than the transform of one layer).
-struct SplitWeightJob {
-    const float* w;    // element (output n, tap t, input k) at w[n*sn + t*st + k*sk]; flip: taps mirrored
-    long long sn, st, sk;
-    int flip, K, Nn, kd;
-    unsigned short* u;   // conv_split_weight_floats(K, Nn, kd) floats
-};
-struct SplitWeightBatch {
-    int n;
-    SplitWeightJob job[kMaxLayers];
-};
-hipError_t split_weights_batch(const SplitWeightBatch& b, hipStream_t stream);
 // Winograd F(2x2, 3x3) convolution, float32 (prox_wino.hip).  Same fused epilogue as the direct kernels.
 struct WinoArgs {
     const float* in;        // [NI][H][W][K]
     float* out;             // [NI][H][W][Nn]
-    const float* u;         // transformed weights (set by the launcher)
+    const float* u;         // transformed weights (kWeightsWino, kWeightsWino3)
     const float* zero;      // one quad of zeros in global memory (set by the launcher)
     const float* bias;      // [Nn] or null
     const float* mask_ref;  // [Q][Nn] or null: ReLU mask source (value > 0 passes)
@@ -227,16 +235,11 @@ bool conv_wino_applies(const PixDims& d, int K, int Nn);
 size_t conv_wino_weight_floats(int K, int Nn);
 // 32-bit words of the sign-bit image of a [pixels][Nn] tensor as the Winograd kernel's threads write and read it
 size_t conv_wino_sign_words(const PixDims& d, int Nn);
-// u_ready: transformed weights made earlier by wino_weights_batch (then w and the strides are not used);
-// otherwise they are made now, into u_scratch.
-hipError_t launch_conv_wino(WinoArgs a, const float* w, long long sn, long long st, long long sk, int flip, int relu_in,
-                            float* u_scratch, const float* u_ready, const char* name, hipStream_t stream);
-// 3x3x3 layers: Winograd inside every slice, plain sum over the three depth taps (prox_wino3.hip).  The transformed
-// weights (conv_wino3_weight_floats(K, Nn) floats) are made at launch into u_scratch.
+hipError_t launch_conv_wino(WinoArgs a, int relu_in, const char* name, hipStream_t stream);
+// 3x3x3 layers: Winograd inside every slice, plain sum over the three depth taps (prox_wino3.hip).
 bool conv_wino3_applies(const PixDims& d, int K, int Nn);
 size_t conv_wino3_weight_floats(int K, int Nn);
-hipError_t launch_conv_wino3(WinoArgs a, const float* w, long long sn, long long st, long long sk, int flip, int relu_in,
-                             float* u_scratch, const char* name, hipStream_t stream);
+hipError_t launch_conv_wino3(WinoArgs a, int relu_in, const char* name, hipStream_t stream);
 // Weight gradient of a 3x3x3 layer by the same scheme (prox_wino3.hip): partial sums of the 3 x 16 transformed products
 // per workgroup, then reduce_partials_kernel and wgrad_wino3_finish.
 struct Wino3WgradArgs {
@@ -284,19 +287,6 @@ struct TimeConvArgs {
 };
 bool conv_time_applies(const PixDims& d, int K, int Nn);
 hipError_t launch_conv_time(TimeConvArgs a, const PixDims& d, hipStream_t stream);
-// Transformed weights of several layers in one launch (a launch costs more than the transform of one layer).
-struct WinoWeightJob {
-    const float* w;
-    long long sn, st, sk;
-    int flip, K, Nn;
-    float* u;          // conv_wino_weight_floats(K, Nn) floats
-};
-struct WinoWeightBatch {
-    int n;
-    WinoWeightJob job[kMaxLayers];
-};
-hipError_t wino_weights_batch(const WinoWeightBatch& b, hipStream_t stream);
-
 // Winograd weight gradient of a 3x3 layer, float32 (prox_wino.hip): partial sums of the 16 transformed
 // products per workgroup, then a fixed-order reduction and the back-transform to the nine taps.
 struct WinoWgradArgs {
@@ -389,7 +379,7 @@ struct ConvBf16Args {
 int conv_bf16_takes_sign_words(const PixDims& d, int K, int Nn);
 size_t conv_bf16_sign_words(const PixDims& d, int Nn, int variant);
 hipError_t launch_conv_bf16(const ConvBf16Args& a, const float* w, long long sn, long long st, long long sk, int flip,
-                            unsigned short* wt_scratch, hipStream_t stream);
+                            unsigned short* wt, WeightBatch* collect, hipStream_t stream);
 size_t conv_bf16_wimg_elems(int K, int Nn, int taps);
 
 // Weight gradient with bf16 operands: g [Q][Co], a [Q][Ci] bfloat16; partial sums float32.

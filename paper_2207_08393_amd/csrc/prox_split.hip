@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
         load_lds(s.rs, dst + (nu + 4 * k) * 256, o, s.off);
     };
 
-    // weight operands of this wave: [channel block][chunk][row tap][position][part][lane]
+    // weight operands of this wave (weights.hip): [channel block][chunk][row tap][position][part][lane]
     const bf16x8* const ubase = reinterpret_cast<const bf16x8*>(a.u) + ((size_t)blockIdx.y * n_ch * 12 + nu) * 3 * 64;
     bf16x8 u[3][3];
     auto load_u = [&](int ch, int ky) {
@@ -398,42 +398,6 @@ __global__ __launch_bounds__(256, 2) void conv_split_kernel(SplitConvArgs a) {
     }
 }
 
-// Transformed and split weights, one thread per (output channel, input channel) padded to 32 and 16:
-// u[block of 32 outputs][chunk = kd * n_kc + kc][ky][position][part][lane = 32 * (k / 8 % 2) + n % 32][k % 8]
-__global__ __launch_bounds__(256) void split_weights_kernel(SplitWeightBatch b) {
-    const SplitWeightJob& jb = b.job[blockIdx.y];
-    const int n_kc = (jb.K + kChunk - 1) / kChunk, Kp = n_kc * kChunk, Np = (jb.Nn + 31) / 32 * 32;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= Kp * Np) return;
-    const int k = idx % Kp, n = idx / Kp;
-    const bool in = k < jb.K && n < jb.Nn;
-    const int taps = 9 * jb.kd;
-    for (int kd = 0; kd < jb.kd; ++kd) {
-        unsigned short* dst = jb.u + ((size_t)(n / 32) * (jb.kd * n_kc) + kd * n_kc + k / kChunk) * (36 * kOperand) +
-                              (32 * ((k % kChunk) / 8) + n % 32) * 8 + k % 8;
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-            float g[3];
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx) {
-                const int t = (kd * 3 + ky) * 3 + kx;
-                g[kx] = in ? jb.w[n * jb.sn + (jb.flip ? taps - 1 - t : t) * jb.st + k * jb.sk] : 0.f;
-            }
-            const float uu[4] = {g[0], 0.5f * (g[0] + g[1] + g[2]), 0.5f * (g[0] - g[1] + g[2]), g[2]};
-#pragma unroll
-            for (int nu = 0; nu < 4; ++nu) {
-                float r = uu[nu];
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    const unsigned short s = (unsigned short)pack_bf16x2(r, 0.f);   // (keeps every NaN, unlike f32_to_bf16)
-                    dst[((ky * 4 + nu) * 3 + p) * kOperand] = s;
-                    r -= bf16_to_f32(s);
-                }
-            }
-        }
-    }
-}
-
 bool conv_split_applies(const PixDims& d, int K, int Nn) {
     return d.kt == 1 && (d.kd == 1 || d.kd == 3) && d.kh == 3 && d.kw == 3 && K % 4 == 0 && Nn % 4 == 0 &&
            4.0 * d.H * d.W * (K > Nn ? K : Nn) < 2.0e9;   // byte offsets inside a slice stay below the out-of-image marker
@@ -455,21 +419,6 @@ static int split_rows(const PixDims& d, int Nn) { return split_blocks(d, 8) * ((
 
 size_t conv_split_sign_words(const PixDims& d, int Nn) {   // one word per thread, block and group of 32 channels
     return (size_t)split_blocks(d, split_rows(d, Nn)) * 256 * (size_t)((Nn + 31) / 32);
-}
-
-hipError_t split_weights_batch(const SplitWeightBatch& b, hipStream_t st) {
-    if (b.n < 1) return hipSuccess;
-    int most = 0;
-    double bytes = 0.0;
-    for (int i = 0; i < b.n; ++i) {
-        const SplitWeightJob& j = b.job[i];
-        const int kn = (j.K + kChunk - 1) / kChunk * kChunk * ((j.Nn + 31) / 32 * 32);
-        most = kn > most ? kn : most;
-        bytes += (36.0 + 72.0) * j.kd * kn;
-    }
-    KernelScope ks("weights_image", 0.0, bytes, st);
-    hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)b.n), dim3(256), 0, st, b);
-    return hipGetLastError();
 }
 
 template <int KD, int G>

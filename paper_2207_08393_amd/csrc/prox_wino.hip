@@ -319,43 +319,6 @@ __global__ __launch_bounds__(256, 2) void conv_wino_kernel(WinoArgs a) {
     }
 }
 
-// U = G g G^T for every (output channel n, input channel k), laid out as the kernel's LDS image:
-// u[((((ny*n_kc + kc)*16 + pos)*2 + hq)*64 + nn)*4 + kk], n = 64*ny + nn, k = 8*kc + 4*hq + kk, pos = 4*xi + nu; one zero
-// quad follows.  Source weight (n, tap, k) at w[n*sn + tapidx*st + k*sk], taps mirrored for the data gradient.
-__global__ __launch_bounds__(256) void wino_weights_kernel(WinoWeightBatch b) {
-    const WinoWeightJob& jb = b.job[blockIdx.y];
-    const float* __restrict__ w = jb.w;
-    float* __restrict__ u = jb.u;
-    const long long sn = jb.sn, st_ = jb.st, sk = jb.sk;
-    const int flip = jb.flip, K = jb.K, Nn = jb.Nn;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx == 0) {
-        float* z = u + (size_t)16 * K * Nn;
-        z[0] = z[1] = z[2] = z[3] = 0.f;
-    }
-    if (idx >= K * Nn) return;
-    const int k = idx % K, n = idx / K;
-    float g[3][3];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) g[t / 3][t % 3] = w[n * sn + (flip ? 8 - t : t) * st_ + k * sk];
-    float gg[4][3];   // G g
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-        gg[0][b] = g[0][b];
-        gg[1][b] = 0.5f * (g[0][b] + g[1][b] + g[2][b]);
-        gg[2][b] = 0.5f * (g[0][b] - g[1][b] + g[2][b]);
-        gg[3][b] = g[2][b];
-    }
-    const int ny = n / 64, nn = n % 64, kc = k / 8, hq = (k % 8) / 4, kk = k % 4, n_kc = K / 8;
-    float* dst = u + ((((size_t)(ny * n_kc + kc) * 16) * 2 + hq) * 64 + nn) * 4 + kk;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const float uu[4] = {gg[x][0], 0.5f * (gg[x][0] + gg[x][1] + gg[x][2]), 0.5f * (gg[x][0] - gg[x][1] + gg[x][2]), gg[x][2]};
-#pragma unroll
-        for (int nu = 0; nu < 4; ++nu) dst[(size_t)(4 * x + nu) * 2 * 64 * 4] = uu[nu];
-    }
-}
-
 // ------------------------------------------------------------------ weight gradient
 // dL/dg = G^T [ sum over tiles of (A dY A^T) .* (B^T d B) ] G: per position of the 4x4 grid a
 // [cout x tiles] . [tiles x cin] matrix product.  A workgroup of 8 waves keeps all 16 products of a 64 x 64
@@ -639,32 +602,8 @@ size_t conv_wino_sign_words(const PixDims& d, int Nn) {   // one word per thread
     return n_img * ((d.W + 31) / 32) * ((d.H + 3) / 4) * 256 * (size_t)(Nn / 64);
 }
 
-hipError_t wino_weights_batch(const WinoWeightBatch& b, hipStream_t st) {
-    if (b.n < 1) return hipSuccess;
-    int most = 0;
-    double bytes = 0.0;
-    for (int i = 0; i < b.n; ++i) {
-        const int kn = b.job[i].K * b.job[i].Nn;
-        most = kn > most ? kn : most;
-        bytes += 4.0 * (9 + 16) * kn;
-    }
-    KernelScope ks("weights_image", 0.0, bytes, st);
-    hipLaunchKernelGGL(wino_weights_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)b.n), dim3(256), 0, st, b);
-    return hipGetLastError();
-}
-
-hipError_t launch_conv_wino(WinoArgs a, const float* w, long long sn, long long st_, long long sk, int flip, int relu_in,
-                            float* u_scratch, const float* u_ready, const char* name, hipStream_t st) {
-    if (!u_ready) {
-        WinoWeightBatch one{};
-        one.n = 1;
-        one.job[0] = WinoWeightJob{w, sn, st_, sk, flip, a.K, a.Nn, u_scratch};
-        const hipError_t e = wino_weights_batch(one, st);
-        if (e != hipSuccess) return e;
-        u_ready = u_scratch;
-    }
-    a.u = u_ready;
-    a.zero = u_ready + (size_t)16 * a.K * a.Nn;
+hipError_t launch_conv_wino(WinoArgs a, int relu_in, const char* name, hipStream_t st) {
+    a.zero = a.u + (size_t)16 * a.K * a.Nn;
     a.bx_n = (a.W + 31) / 32;
     a.by_n = (a.H + 3) / 4;
     a.n_blocks = a.NI * (long long)a.bx_n * a.by_n;

@@ -345,45 +345,6 @@ __global__ __launch_bounds__(256, 2) void conv_wino3_kernel(WinoArgs a) {
     }
 }
 
-// U = G g G^T for every (depth tap, output channel n, input channel k), laid out as the kernel's LDS images:
-// u[(((((ny*3 + kd)*n_kc + kc)*16 + pos)*2 + hq)*32 + nn)*4 + kk], n = 32*ny + nn, k = 8*kc + 4*hq + kk, pos = 4*xi + nu;
-// one zero quad follows.  Source weight (n, tap, k) at w[n*sn + tapidx*st + k*sk], tap = (kd*3 + kh)*3 + kw, taps
-// mirrored for the data gradient.
-__global__ __launch_bounds__(256) void wino3_weights_kernel(const float* __restrict__ w, long long sn, long long st_, long long sk,
-                                                            int flip, int K, int Nn, float* __restrict__ u) {
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx == 0) {
-        float* z = u + (size_t)48 * K * Nn;
-        z[0] = z[1] = z[2] = z[3] = 0.f;
-    }
-    if (idx >= K * Nn) return;
-    const int k = idx % K, n = idx / K;
-    const int ny = n / 32, nn = n % 32, kc = k / 8, hq = (k % 8) / 4, kk = k % 4, n_kc = K / 8;
-    for (int kd = 0; kd < 3; ++kd) {
-        float g[3][3];
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int tap = kd * 9 + t;
-            g[t / 3][t % 3] = w[n * sn + (flip ? 26 - tap : tap) * st_ + k * sk];
-        }
-        float gg[4][3];   // G g
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            gg[0][b] = g[0][b];
-            gg[1][b] = 0.5f * (g[0][b] + g[1][b] + g[2][b]);
-            gg[2][b] = 0.5f * (g[0][b] - g[1][b] + g[2][b]);
-            gg[3][b] = g[2][b];
-        }
-        float* dst = u + (((((size_t)(ny * 3 + kd) * n_kc + kc) * 16) * 2 + hq) * 32 + nn) * 4 + kk;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const float uu[4] = {gg[x][0], 0.5f * (gg[x][0] + gg[x][1] + gg[x][2]), 0.5f * (gg[x][0] - gg[x][1] + gg[x][2]), gg[x][2]};
-#pragma unroll
-            for (int nu = 0; nu < 4; ++nu) dst[(size_t)(4 * x + nu) * 2 * 32 * 4] = uu[nu];
-        }
-    }
-}
-
 // ------------------------------------------------------------------ weight gradient
 // dL/dg_kd = G^T [ sum over slices d and tiles of (A dY(d) A^T) .* (B^T x(d + kd - 1) B) ] G: per depth tap and position
 // of the 4x4 grid a [cout x tiles] . [tiles x cin] matrix product, 16 multiplications per tile, depth tap and channel
@@ -713,17 +674,8 @@ bool conv_wino3_applies(const PixDims& d, int K, int Nn) {
 
 size_t conv_wino3_weight_floats(int K, int Nn) { return (size_t)48 * K * Nn + 4; }
 
-hipError_t launch_conv_wino3(WinoArgs a, const float* w, long long sn, long long st_, long long sk, int flip, int relu_in,
-                             float* u_scratch, const char* name, hipStream_t st) {
-    {
-        KernelScope ks("weights_image", 0.0, 4.0 * (27 + 48) * a.K * a.Nn, st);
-        hipLaunchKernelGGL(wino3_weights_kernel, dim3((unsigned)((a.K * a.Nn + 255) / 256)), dim3(256), 0, st, w, sn, st_, sk, flip,
-                           a.K, a.Nn, u_scratch);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    a.u = u_scratch;
-    a.zero = u_scratch + (size_t)48 * a.K * a.Nn;
+hipError_t launch_conv_wino3(WinoArgs a, int relu_in, const char* name, hipStream_t st) {
+    a.zero = a.u + (size_t)48 * a.K * a.Nn;
     a.bx_n = (a.W + 31) / 32;
     a.by_n = (a.H + 7) / 8;
     a.n_blocks = a.NI * (long long)a.bx_n * a.by_n;
