@@ -94,7 +94,7 @@ struct ProxPlan {
     size_t sign_off[kMaxLayers + 1];  // sign words of t_l inside saved, or 0 when there are none (see plan_prox)
     size_t saved_bytes;
     size_t grad_off[kMaxLayers + 1];  // G_l inside ws, 1 <= l < L
-    size_t partial_off, partial_bytes;
+    size_t partial_off, partial_bytes, wait_bytes;   // wait_bytes for sums not yet added up, then partial_bytes for any layer's
     size_t bias_partial_off;          // [n_split][kMaxChannels] floats
     size_t wimg_off_fwd, wimg_off_bwd;  // the weights of a pass as its kernels read them (inside ws) ...
     size_t wimg_layer[kMaxLayers];      // ... of each layer, behind either of them

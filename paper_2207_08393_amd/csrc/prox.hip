@@ -1747,50 +1747,71 @@ __global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a) {
     }
 }
 
-// out[i] = sum_s partial[s][i] in a fixed order (run-to-run identical bits).  Two segments in one launch:
-// the weight-gradient partials (n elements, blocks [0, nbw)) and, when n2 > 0, the bias-gradient partials.
+// out[i] = sum_s partial[s][i] in a fixed order (run-to-run identical bits), for the layers of a batch in one launch, each with
+// two segments: the weight-gradient partials (n elements, nbw blocks) and, when n2 > 0, the bias-gradient partials.
 // A block of 256 threads is 16 split groups x 16 lanes: group g sums its contiguous sixteenth of the
 // partials (several loads in flight per thread), the 16 group sums are then added in ascending order.
-// VEC = 4 (weights only, when n % 4 == 0 and `out` is 16-byte aligned) moves float4 per lane.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partial, int n_split, long long n,
-                                                              float* __restrict__ out, int vec, int nbw,
-                                                              const float* __restrict__ partial2, long long n2,
-                                                              float* __restrict__ out2) {
+// vec (weights only, when n % 4 == 0 and `out` is 16-byte aligned) moves float4 per lane.
+// What bounds it: for the partial sums of a small or a two-channel layer the launch (4 - 5 us for 0.1 - 5 MB), which is why they
+// wait for each other (prox_backward has the limit); above, memory.
+struct ReduceJob {
+    const float* partial;
+    float* out;
+    const float* partial2;
+    float* out2;
+    long long n, n2;
+    int n_split, vec, nbw;
+};
+constexpr int kMaxReduce = 16;
+struct ReduceBatch {
+    int n;
+    int end[kMaxReduce];   // blocks up to and including each job's
+    ReduceJob job[kMaxReduce];
+};
+__global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceBatch b) {
     __shared__ float4 red[16][16];
+    int which = 0;
+#pragma unroll
+    for (int k = 0; k < kMaxReduce; ++k) which += k < b.n && (int)blockIdx.x >= b.end[k] ? 1 : 0;
+    const ReduceJob& jb = b.job[which];
+    const int blk = (int)blockIdx.x - (which ? b.end[which - 1] : 0);
+    const int n_split = jb.n_split;
     const int lane = threadIdx.x & 15, sg = threadIdx.x >> 4;
     const int per = (n_split + 15) / 16;
     const int k0 = sg * per, k1 = k0 + per < n_split ? k0 + per : n_split;
-    const bool first = (int)blockIdx.x < nbw;
-    const float* src = first ? partial : partial2;
-    float* dst = first ? out : out2;
-    const long long stride = first ? n : n2;
-    const int width = (first && vec) ? 4 : 1;
-    const long long i = ((long long)(first ? blockIdx.x : blockIdx.x - nbw) * 16 + lane) * width;
+    const bool first = blk < jb.nbw;
+    const float* __restrict__ src = first ? jb.partial : jb.partial2;
+    float* __restrict__ dst = first ? jb.out : jb.out2;
+    const long long stride = first ? jb.n : jb.n2;
+    const int width = (first && jb.vec) ? 4 : 1;
+    const long long i = ((long long)(first ? blk : blk - jb.nbw) * 16 + lane) * width;
     const bool ok = i < stride;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int U = 8;   // loads in flight
     if (ok) {
+        int k = k0;
         if (width == 4) {
-            int k = k0;
-            for (; k + 4 <= k1; k += 4) {
-                float4 v[4];
+            for (; k + U <= k1; k += U) {
+                float4 v[U];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(src + (size_t)(k + u) * stride + i);
+                for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(src + (size_t)(k + u) * stride + i);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
+                for (int u = 0; u < U; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
             }
+#pragma unroll 2
             for (; k < k1; ++k) {
                 const float4 v = *reinterpret_cast<const float4*>(src + (size_t)k * stride + i);
                 s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
             }
         } else {
-            int k = k0;
-            for (; k + 4 <= k1; k += 4) {
-                float v[4];
+            for (; k + U <= k1; k += U) {
+                float v[U];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = src[(size_t)(k + u) * stride + i];
+                for (int u = 0; u < U; ++u) v[u] = src[(size_t)(k + u) * stride + i];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) s.x += v[u];
+                for (int u = 0; u < U; ++u) s.x += v[u];
             }
+#pragma unroll 2
             for (; k < k1; ++k) s.x += src[(size_t)k * stride + i];
         }
     }
@@ -1893,6 +1914,7 @@ __global__ __launch_bounds__(256) void real_dot_kernel(const float2* __restrict_
 // ------------------------------------------------------------------ host side
 static inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr int kLossBlocks = kLossPartials;
+constexpr size_t kWaitBytes = 8u << 20, kBiasWaitBytes = 1u << 20;
 
 hipError_t loss_and_grad(const float2* x, const float2* x_ref, float2* g, long long n, int loss_kind, int relu_mask,
                          double* part, float* loss, hipStream_t st) {
@@ -2052,9 +2074,12 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }
     }
-    w += plan.partial_bytes;
+    // Partial sums of up to 8 MB wait for the next layer's: more would have left the L2s by the time they are added up, and
+    // one launch in four or five no longer shows (64 -> 64 channels at 2 x 640 x 368: 19 MB, 5 of 150 us a layer).
+    plan.wait_bytes = plan.partial_bytes * L < kWaitBytes ? plan.partial_bytes * L : kWaitBytes;
+    w += plan.wait_bytes + plan.partial_bytes;
     plan.bias_partial_off = w;
-    w += align256((size_t)kThinSplit * kMaxChannels * sizeof(float));
+    w += kBiasWaitBytes + align256((size_t)kThinSplit * kMaxChannels * sizeof(float));
     // the weights of every layer as its kernel of this pass reads them, whichever that is
     size_t img_bytes = 0;
     for (int l = 0; l < L; ++l) {
@@ -2357,7 +2382,33 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
     const int L = p.n_layers;
     int skip_from_input = 0;   // layer (1-based) whose output gradient also flows into t_0 = u through its skip
     unsigned char* wsb = (unsigned char*)ws;
-    float* partial = reinterpret_cast<float*>(wsb + plan.partial_off);
+    // Partial sums wait until those of several layers are added up in one launch: behind the wait_bytes there is room for those of
+    // any layer.
+    float* const partial0 = reinterpret_cast<float*>(wsb + plan.partial_off);
+    float* const bpart0 = reinterpret_cast<float*>(wsb + plan.bias_partial_off);
+    size_t waiting = 0, bias_waiting = 0;   // floats
+    ReduceBatch sums{};
+    double sum_bytes = 0.0;
+    auto add_up = [&]() -> hipError_t {
+        if (sums.n < 1) return hipSuccess;
+        KernelScope ks("wgrad_reduce", 0.0, sum_bytes, st);
+        hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)sums.end[sums.n - 1]), dim3(256), 0, st, sums);
+        sums.n = 0;
+        sum_bytes = 0.0;
+        waiting = bias_waiting = 0;
+        return hipGetLastError();
+    };
+    // n_split partial sums of n weights and of n2 biases
+    auto queue = [&](const float* partial, int n_split, long long n, float* out, const float* bpart, long long n2, float* out2) {
+        const int vec = n % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0 ? 1 : 0;
+        const int nbw = (int)((n + 16 * (vec ? 4 : 1) - 1) / (16 * (vec ? 4 : 1))), nbb = (int)((n2 + 15) / 16);
+        sums.job[sums.n] = ReduceJob{partial, out, bpart, out2, n, n2, n_split, vec, nbw};
+        sums.end[sums.n] = (sums.n ? sums.end[sums.n - 1] : 0) + nbw + nbb;
+        ++sums.n;
+        waiting += ((size_t)n_split * n + 63) / 64 * 64;
+        bias_waiting += ((size_t)n_split * n2 + 63) / 64 * 64;
+        sum_bytes += 4.0 * (double)(n + n2) * (n_split + 1);
+    };
     // Gradient buffer of tensor t_l (1 <= l <= L); G_L is g_z.
     auto G = [&](int l) -> float* {
         return l == L ? reinterpret_cast<float*>(const_cast<unsigned char*>(saved) + plan.gz_off)
@@ -2446,10 +2497,11 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
             skip_from_input = l;
         }
         // weight gradient (+ bias gradient)
+        float* const partial = partial0 + waiting;
         WgradArgs wa{};
         wa.g = G(l); wa.a = act(l - 1); wa.partial = partial;
         wa.Co = c.cout; wa.Ci = c.cin; wa.relu_in = (c.relu_in && !plan.post_relu[l - 1]) ? 1 : 0; wa.d = d;
-        float* bpart = reinterpret_cast<float*>(wsb + plan.bias_partial_off);
+        float* const bpart = bpart0 + bias_waiting;
         bool bias_done = false, wino_wgrad_done = false;
         int used_split = plan.n_split;
         hipError_t e;
@@ -2504,11 +2556,9 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
             }
             float* psum = partial + (size_t)plan.n_split * np;
             {
-                KernelScope ks("wgrad_reduce", 0.0, 4.0 * (double)(np + nb) * (plan.n_split + 1), st);
-                const int nbw = (int)((np + 63) / 64), nbb = (int)((nb + 15) / 16);
-                hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)(nbw + nbb)), dim3(256), 0, st, (const float*)partial,
-                                   plan.n_split, np, psum, 1, nbw, (const float*)bpart, nb,
-                                   c.has_bias ? grad_theta + plan.b_off[l - 1] : nullptr);
+                queue(partial, plan.n_split, np, psum, bpart, nb, c.has_bias ? grad_theta + plan.b_off[l - 1] : nullptr);
+                e = add_up();
+                if (e != hipSuccess) return e;
                 e = wgrad_wino_finish(psum, c.cout, c.cin, grad_theta + plan.w_off[l - 1], st);
                 if (e != hipSuccess) return e;
             }
@@ -2530,11 +2580,9 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
             }
             float* psum = partial + (size_t)n3 * np;
             {
-                KernelScope ks("wgrad_reduce", 0.0, 4.0 * (double)(np + nb) * (n3 + 1), st);
-                const int nbw = (int)((np + 63) / 64), nbb = (int)((nb + 15) / 16);
-                hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)(nbw + nbb)), dim3(256), 0, st, (const float*)partial,
-                                   n3, np, psum, 1, nbw, (const float*)bpart, nb,
-                                   c.has_bias ? grad_theta + plan.b_off[l - 1] : nullptr);
+                queue(partial, n3, np, psum, bpart, nb, c.has_bias ? grad_theta + plan.b_off[l - 1] : nullptr);
+                e = add_up();
+                if (e != hipSuccess) return e;
                 e = wgrad_wino3_finish(psum, c.cout, c.cin, grad_theta + plan.w_off[l - 1], st);
                 if (e != hipSuccess) return e;
             }
@@ -2562,13 +2610,11 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
         }
         if (!wino_wgrad_done) {
             const long long nb = c.has_bias ? c.cout : 0;
-            KernelScope ks("wgrad_reduce", 0.0, 4.0 * (double)(nw + nb) * (used_split + 1), st);
-            float* gw = grad_theta + plan.w_off[l - 1];
-            const int vec = (nw % 4 == 0 && (reinterpret_cast<uintptr_t>(gw) & 15) == 0) ? 1 : 0;
-            const int nbw = (int)((nw + 16 * (vec ? 4 : 1) - 1) / (16 * (vec ? 4 : 1))), nbb = (int)((nb + 15) / 16);
-            hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)(nbw + nbb)), dim3(256), 0, st,
-                               (const float*)partial, used_split, nw, gw, vec, nbw,
-                               (const float*)bpart, nb, c.has_bias ? grad_theta + plan.b_off[l - 1] : nullptr);
+            queue(partial, used_split, nw, grad_theta + plan.w_off[l - 1], bpart, nb, c.has_bias ? grad_theta + plan.b_off[l - 1] : nullptr);
+            if (waiting * sizeof(float) > plan.wait_bytes || bias_waiting * sizeof(float) > kBiasWaitBytes || sums.n == kMaxReduce || l == 1) {
+                e = add_up();
+                if (e != hipSuccess) return e;
+            }
         }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
