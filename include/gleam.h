@@ -105,7 +105,8 @@ int gleam_theta_count(const gleam_prox_desc* prox, size_t* n_floats);
  * under the same policy (the Winograd and 2D-tile bf16 kernels hand ReLU masks over as sign words), and
  * gleam_workspace_bytes must be asked under the policy the calls will run with.  Not synchronised with calls in
  * flight on other threads.  Unknown bits: GLEAM_E_DESC. */
-#define GLEAM_POLICY_NO_WINOGRAD      1u  /* 3x3 and 3x3x3 fp32 layers: direct fp32 MFMA kernels instead of the minimal-filtering
+#define GLEAM_POLICY_NO_WINOGRAD      1u  /* 3x3, 3x3x3 and 3x1x1 fp32 layers: fp32 MFMA kernels instead of those on split operands,
+                                          * 3x3 and 3x3x3 ones direct fp32 MFMA kernels instead of the minimal-filtering
                                           * ones (split bfloat16 operands; fp32 MFMA in greedy iterations, in the forward pass
                                           * of MoDL modules and in the backward pass of those of fewer than 4096 pixels).  The
                                           * data-consistency step of networks with such layers (widths that are multiples of 4) then

@@ -1106,6 +1106,17 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt, bool
         snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
         return launch_conv_wino3(wa, a.relu_in, name, st);
     }
+    if (split && wino_enabled() && !(kernel_policy() & GLEAM_POLICY_NO_FRAME_WALK) && conv_time_split_applies(a.d, a.K, a.Nn)) {   // temporal 3x1x1
+        if (collect) return enter(kWeightsTimeSplit, conv_time_split_chunks(a.K), 0);
+        TimeSplitArgs t{};
+        t.in = a.in; t.out = a.out; t.u = wt; t.bias = a.bias; t.mask_ref = a.mask_ref; t.add = a.add;
+        t.K = a.K; t.Nn = a.Nn; t.relu_in = a.relu_in; t.relu_out = a.relu_out; t.mask_acc = a.mask_acc; t.mask_add = a.mask_add;
+        char name[56];
+        snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
+        const double direct = 2.0 * (double)a.d.Q * a.K * a.Nn * taps_;   // six bfloat16 products per multiplication
+        KernelScope ks(name, direct, 4.0 * (double)a.d.Q * (a.K + a.Nn), st, direct * 6.0);
+        return launch_conv_time_split(t, a.d, st);
+    }
     if (!(kernel_policy() & GLEAM_POLICY_NO_FRAME_WALK) && conv_time_applies(a.d, a.K, a.Nn)) {   // temporal 3x1x1: walk along the frames
         if (collect) return hipSuccess;   // reads theta itself
         TimeConvArgs t{};
@@ -2061,6 +2072,10 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
             const size_t need = align256(wgrad_split_partial_floats(dd, c.cin, c.cout) * sizeof(float));
             if (need > plan.partial_bytes) plan.partial_bytes = need;
         }
+        if (p.dtype == 0 && split && wgrad_time_split_applies(dd, c.cin, c.cout)) {
+            const size_t need = align256(wgrad_time_split_partial_floats(dd, c.cin, c.cout) * sizeof(float));
+            if (need > plan.partial_bytes) plan.partial_bytes = need;
+        }
         if (p.dtype == 0 && wgrad_time_applies(dd, c.cin, c.cout)) {
             const size_t need = align256(wgrad_time_partial_floats(dd, c.cin, c.cout) * sizeof(float));
             if (need > plan.partial_bytes) plan.partial_bytes = need;
@@ -2097,6 +2112,10 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
         }
         if (p.dtype == 0 && split && conv_split_applies(pix_dims(g, c), c.cin, c.cout)) room(conv_split_weight_floats(c.cin, c.cout, c.kd));
         if (p.dtype == 0 && split && conv_split_applies(pix_dims(g, c), c.cout, c.cin)) room(conv_split_weight_floats(c.cout, c.cin, c.kd));
+        if (p.dtype == 0 && split && conv_time_split_applies(pix_dims(g, c), c.cin, c.cout)) {
+            room(conv_time_split_weight_floats(c.cin, c.cout));
+            room(conv_time_split_weight_floats(c.cout, c.cin));
+        }
         plan.wimg_layer[l] = img_bytes;
         img_bytes += align256(floats * sizeof(float));
     }
@@ -2587,16 +2606,18 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
                 if (e != hipSuccess) return e;
             }
             wino_wgrad_done = true;
-        } else if (!(kernel_policy() & GLEAM_POLICY_NO_FRAME_WALK) && wgrad_time_applies(d, c.cin, c.cout)) {
+        } else if (const bool on_split = plan.split && wino_enabled() && c.cin > 2 && c.cout > 2 && wgrad_time_split_applies(d, c.cin, c.cout);
+                   !(kernel_policy() & GLEAM_POLICY_NO_FRAME_WALK) && (on_split || wgrad_time_applies(d, c.cin, c.cout))) {
             // temporal 3x1x1: walk along the frames, every input and gradient read once
             TimeWgradArgs tw{};
             tw.g = wa.g; tw.a = wa.a; tw.partial = partial; tw.bias_partial = c.has_bias ? bpart : nullptr;
             tw.Co = c.cout; tw.Ci = c.cin;
             char name[56];
             snprintf(name, sizeof(name), "conv_wgrad_%dto%d_t%d", c.cin, c.cout, taps);
-            KernelScope ks(name, 2.0 * (double)d.Q * c.cin * c.cout * taps, 4.0 * (double)d.Q * (c.cin + c.cout), st);
-            e = launch_wgrad_time(tw, d, wa.relu_in, st);
-            used_split = wgrad_time_splits(d);
+            const double direct = 2.0 * (double)d.Q * c.cin * c.cout * taps;   // six bfloat16 products per multiplication on split operands
+            KernelScope ks(name, direct, 4.0 * (double)d.Q * (c.cin + c.cout), st, direct * (on_split ? 6.0 : 1.0));
+            e = on_split ? launch_wgrad_time_split(tw, d, wa.relu_in, st) : launch_wgrad_time(tw, d, wa.relu_in, st);
+            used_split = on_split ? wgrad_time_split_splits(d, c.cin, c.cout) : wgrad_time_splits(d);
             bias_done = c.has_bias;
         } else {
             e = launch_wgrad(wa, c.has_bias ? bpart : nullptr, &bias_done, plan.n_split,

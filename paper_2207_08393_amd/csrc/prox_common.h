@@ -155,7 +155,7 @@ __device__ __forceinline__ ChunkIter chunk_next(ChunkIter x, int n_kc, int nck, 
 
 // One layer's weights, re-laid or transformed into what its kernel reads (weights.hip has the forms).  Element (output n, tap t,
 // input k) of the source is w[n*sn + t*st + k*sk]; flip: taps mirrored (data gradient: n counts its outputs, the layer's inputs).
-enum WeightForm { kWeightsImage, kWeightsImageBf16, kWeightsBf16Tile, kWeightsBf16Resident, kWeightsThinOut, kWeightsSplit, kWeightsWino, kWeightsWino3 };
+enum WeightForm { kWeightsImage, kWeightsImageBf16, kWeightsBf16Tile, kWeightsBf16Resident, kWeightsThinOut, kWeightsSplit, kWeightsWino, kWeightsWino3, kWeightsTimeSplit };
 struct WeightJob {
     const float* w;
     void* out;
@@ -287,6 +287,27 @@ struct TimeConvArgs {
 };
 bool conv_time_applies(const PixDims& d, int K, int Nn);
 hipError_t launch_conv_time(TimeConvArgs a, const PixDims& d, hipStream_t stream);
+// Forward / data gradient of a temporal 3x1x1 layer with operands split into bfloat16 parts (prox_time_split.hip).
+struct TimeSplitArgs {
+    const float* in;        // [samples][T][P][K]
+    float* out;             // [samples][T][P][Nn]
+    const void* u;          // split weights (kWeightsTimeSplit)
+    const float* bias;      // [Nn] or null
+    const float* mask_ref;  // [..][Nn] or null: ReLU mask source (value > 0 passes)
+    const float* add;       // [..][Nn] or null
+    int K, Nn, relu_in, relu_out, mask_acc, mask_add;
+    int T, NB, seg_px, run, runs;   // set by the launcher: frames, 32-channel blocks per workgroup, pixels per segment, frames per run
+    long long P, segs, n_items;     // pixels per frame, segments per frame, segments of all runs
+};
+bool conv_time_split_applies(const PixDims& d, int K, int Nn);
+size_t conv_time_split_weight_floats(int K, int Nn);
+int conv_time_split_chunks(int K);   // 16-channel chunks of its weights
+bool wgrad_time_split_applies(const PixDims& d, int Ci, int Co);
+int wgrad_time_split_splits(const PixDims& d, int Ci, int Co);   // workgroups along x = partial sums written
+size_t wgrad_time_split_partial_floats(const PixDims& d, int Ci, int Co);
+hipError_t launch_wgrad_time_split(TimeWgradArgs a, const PixDims& d, int relu_in, hipStream_t stream);
+hipError_t launch_conv_time_split(TimeSplitArgs a, const PixDims& d, hipStream_t stream);
+
 // Winograd weight gradient of a 3x3 layer, float32 (prox_wino.hip): partial sums of the 16 transformed
 // products per workgroup, then a fixed-order reduction and the back-transform to the nine taps.
 struct WinoWgradArgs {

@@ -96,6 +96,25 @@ __device__ __forceinline__ void split_form(const WeightJob& j, int i) {
     }
 }
 
+// conv_time_split_kernel, split, one thread per (output channel, input channel) padded to 32 and to whole chunks:
+// u[block of 32 outputs][tap][chunk][part][lane = 32 * (k / 8 % 2) + n % 32][k % 8]
+__device__ __forceinline__ void time_split_form(const WeightJob& j, int i) {
+    const int k = i % (16 * j.CK), n = i / (16 * j.CK);   // CK: chunks
+    const bool in = k < j.K && n < j.Nn;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        unsigned short* dst = static_cast<unsigned short*>(j.out) + (((size_t)(n / 32) * 3 + t) * j.CK + k / 16) * (3 * 64 * 8) +
+                              (32 * ((k % 16) / 8) + n % 32) * 8 + k % 8;
+        float r = in ? weight_at(j, n, t, k) : 0.f;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const unsigned short s = (unsigned short)pack_bf16x2(r, 0.f);
+            dst[p * (64 * 8)] = s;
+            r -= bf16_to_f32(s);
+        }
+    }
+}
+
 // U = G g G^T for every (depth tap, output channel n, input channel k) as the LDS images of conv_wino_kernel (NBLK 64, one depth
 // tap) and conv_wino3_kernel (NBLK 32, three):
 // u[(((((ny*KD + kd)*n_kc + kc)*16 + pos)*2 + hq)*NBLK + nn)*4 + kk], n = NBLK*ny + nn, k = 8*kc + 4*hq + kk, pos = 4*xi + nu; one
@@ -143,6 +162,7 @@ __global__ __launch_bounds__(256) void prepare_weights_kernel(WeightBatch b) {
         case kWeightsBf16Resident: bf16_resident(j, i); break;
         case kWeightsThinOut: thin_out(j, i); break;
         case kWeightsSplit: split_form(j, i); break;
+        case kWeightsTimeSplit: time_split_form(j, i); break;
         case kWeightsWino: wino_form<1, 64>(j, i); break;
         default: wino_form<3, 32>(j, i); break;
     }
@@ -162,11 +182,12 @@ hipError_t prepare_weights(WeightBatch& b, hipStream_t st) {
             case kWeightsBf16Tile:
             case kWeightsBf16Resident: j.threads = 9 * kn; break;
             case kWeightsThinOut: j.threads = j.taps * kn; break;
+            case kWeightsTimeSplit: j.threads = 16 * j.CK * up(j.Nn, 32); break;
             case kWeightsSplit: j.threads = up(j.K, 16) * up(j.Nn, 32); break;
             default: j.threads = kn; break;
         }
         most = j.threads > most ? j.threads : most;
-        const double per = j.form == kWeightsImage ? 4 : j.form == kWeightsSplit ? 72.0 * j.taps / 9 : j.form == kWeightsWino ? 64 :
+        const double per = j.form == kWeightsImage ? 4 : j.form == kWeightsSplit ? 72.0 * j.taps / 9 : j.form == kWeightsTimeSplit ? 18 : j.form == kWeightsWino ? 64 :
                            j.form == kWeightsWino3 ? 192 : j.form == kWeightsThinOut ? 4 : 2;   // written per thread
         bytes += 4.0 * j.taps * (double)kn + per * (double)j.threads;
     }
