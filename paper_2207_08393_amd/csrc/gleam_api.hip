@@ -258,7 +258,7 @@ int gleam_sense_normal_static(const gleam_geom* geom, const gleam_c64* x, const 
 static int module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, bool split, const gleam_c64* x_in,
                      const gleam_c64* S, const uint8_t* M, const gleam_c64* y, float alpha, const float* theta,
                      const gleam_c64* x_ref, gleam_c64* x_out, float* loss, void* saved, size_t saved_bytes,
-                     void* ws, size_t ws_bytes, void* stream) {
+                     void* ws, size_t ws_bytes, const PassWeights& weights, void* stream) {
     int rc = check_geom(geom);
     if (rc) return rc;
     rc = check_prox(prox);
@@ -276,7 +276,7 @@ static int module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, bool 
     hipError_t e = (plan.staged ? sense_dc_staged : sense_dc)(*geom, (const float2*)x_in, (const float2*)S, M, (const float2*)y,
                                                               1.f, -alpha, u, (float2*)ws, st);
     if (e != hipSuccess) return GLEAM_E_LAUNCH;
-    e = prox_forward(*geom, *prox, plan, theta, act_base, (const float2*)x_ref, (float2*)x_out, loss, ws, st);
+    e = prox_forward(*geom, *prox, plan, theta, act_base, (const float2*)x_ref, (float2*)x_out, loss, ws, weights, st);
     return e == hipSuccess ? GLEAM_OK : GLEAM_E_LAUNCH;
 }
 
@@ -284,11 +284,11 @@ int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, const 
                      const gleam_c64* S, const uint8_t* M, const gleam_c64* y, float alpha, const float* theta,
                      const gleam_c64* x_ref, gleam_c64* x_out, float* loss, void* saved, size_t saved_bytes,
                      void* ws, size_t ws_bytes, void* stream) {
-    return module_fwd(geom, prox, true, x_in, S, M, y, alpha, theta, x_ref, x_out, loss, saved, saved_bytes, ws, ws_bytes, stream);
+    return module_fwd(geom, prox, true, x_in, S, M, y, alpha, theta, x_ref, x_out, loss, saved, saved_bytes, ws, ws_bytes, {}, stream);
 }
 
 static int module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, bool split, const float* theta, const void* saved,
-                     size_t saved_bytes, float* grad_theta, void* ws, size_t ws_bytes, void* stream) {
+                     size_t saved_bytes, float* grad_theta, void* ws, size_t ws_bytes, const PassWeights& weights, void* stream) {
     int rc = check_geom(geom);
     if (rc) return rc;
     rc = check_prox(prox);
@@ -298,14 +298,14 @@ static int module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, bool 
     plan_prox(*geom, *prox, split, plan);
     if (!aligned(ws) || ws_bytes < plan.ws_bytes) return GLEAM_E_WORKSPACE;
     if (!aligned(saved) || saved_bytes < plan.saved_bytes) return GLEAM_E_WORKSPACE;
-    hipError_t e = prox_backward(*geom, *prox, plan, theta, (const unsigned char*)saved, grad_theta, nullptr, ws,
+    hipError_t e = prox_backward(*geom, *prox, plan, theta, (const unsigned char*)saved, grad_theta, nullptr, ws, weights,
                                  (hipStream_t)stream);
     return e == hipSuccess ? GLEAM_OK : GLEAM_E_LAUNCH;
 }
 
 int gleam_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, const float* theta, const void* saved,
                      size_t saved_bytes, float* grad_theta, void* ws, size_t ws_bytes, void* stream) {
-    return module_bwd(geom, prox, true, theta, saved, saved_bytes, grad_theta, ws, ws_bytes, stream);
+    return module_bwd(geom, prox, true, theta, saved, saved_bytes, grad_theta, ws, ws_bytes, {}, stream);
 }
 
 static int check_deep(const gleam_prox_desc* prox, int n_iter);
@@ -326,7 +326,7 @@ int gleam_module_bwd_alpha(const gleam_geom* geom, const gleam_prox_desc* prox, 
     if (!aligned(saved) || saved_bytes < plan.saved_bytes) return GLEAM_E_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     float2* g_u = (float2*)((unsigned char*)saved + plan.act_off[0]);   // dL/du replaces u, which is dead by then
-    hipError_t e = prox_backward(*geom, *prox, plan, theta, (const unsigned char*)saved, grad_theta, g_u, ws, st);
+    hipError_t e = prox_backward(*geom, *prox, plan, theta, (const unsigned char*)saved, grad_theta, g_u, ws, {}, st);
     if (e != hipSuccess) return GLEAM_E_LAUNCH;
     // r = A^H (A x_in - y) into the image slot behind the k-space buffer, then dL/dalpha = -<dL/du, r>
     float2* r = (float2*)((unsigned char*)ws + plan.k_bytes);
@@ -404,7 +404,7 @@ int gleam_deep_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, i
         // dL/du_j overwrites u_j = t_0 of this iteration, which is dead once its first layer's weight gradient is done
         float2* g_u = j > 0 ? (float2*)(sj + plan.act_off[0]) : nullptr;
         hipError_t e = prox_backward(*geom, *prox, plan, theta + (size_t)j * n_theta, sj, grad_theta + (size_t)j * n_theta, g_u,
-                                     ws, st);
+                                     ws, {}, st);
         if (e != hipSuccess) return GLEAM_E_LAUNCH;
         if (j > 0) {
             // through the data-consistency step: dL/dx_{j-1} = g_u - alpha A^H A g_u, the incoming gradient of iteration j-1
@@ -528,7 +528,7 @@ int gleam_modl_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox, c
     // z lands in the solver's third vector, which the first operator application overwrites only after the
     // right-hand side aty + mu z has been formed
     float2* z = (float2*)(scratch + 2 * align_up(img));
-    hipError_t e = prox_forward(*geom, *prox, plan, theta, act_base, nullptr, z, nullptr, ws, st);
+    hipError_t e = prox_forward(*geom, *prox, plan, theta, act_base, nullptr, z, nullptr, ws, {}, st);
     if (e != hipSuccess) return GLEAM_E_LAUNCH;
     e = cg_solve(*geom, (const float2*)S, M, mu, n_cg, (const float2*)aty, z, 1.f, mu, (float2*)x_out, (float2*)ws, scratch, st);
     if (e != hipSuccess) return GLEAM_E_LAUNCH;
@@ -560,7 +560,7 @@ int gleam_modl_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, c
     float2* g = (float2*)((unsigned char*)saved + plan.gz_off);
     hipError_t e = cg_solve(*geom, (const float2*)S, M, mu, n_cg, g, nullptr, mu, 0.f, g, (float2*)ws, scratch, st);
     if (e != hipSuccess) return GLEAM_E_LAUNCH;
-    e = prox_backward(*geom, *prox, plan, theta, (const unsigned char*)saved, grad_theta, nullptr, ws, st);
+    e = prox_backward(*geom, *prox, plan, theta, (const unsigned char*)saved, grad_theta, nullptr, ws, {}, st);
     return e == hipSuccess ? GLEAM_OK : GLEAM_E_LAUNCH;
 }
 
@@ -589,15 +589,27 @@ int gleam_greedy_iteration(const gleam_geom* geom, const gleam_prox_desc* prox, 
     size_t n_theta = 0;
     rc = gleam_theta_count(prox, &n_theta);
     if (rc) return rc;
+    ProxPlan plan;
+    plan_prox(*geom, *prox, false, plan);
+    const int many = plan.wimg_many / 2;   // modules whose weights of both passes are made at once: a module's theta changes behind its own
     const gleam_c64* x_in = x0;
     for (int i = 0; i < n_modules; ++i) {
+        PassWeights fwd, bwd;
+        if (many > 1) {
+            const int left = n_modules - i;
+            if (i % many == 0 && prox_prepare(*geom, *prox, plan, theta + (size_t)i * n_theta, n_theta, left < many ? left : many, true, ws,
+                                              (hipStream_t)stream) != hipSuccess)
+                return GLEAM_E_LAUNCH;
+            fwd.at = (unsigned char*)ws + plan.wimg_many_off + (size_t)(i % many) * 2 * plan.wimg_bytes;
+            bwd.at = fwd.at + plan.wimg_bytes;
+        }
         // alternate the two image buffers so that the last module writes x_out
         gleam_c64* xo = ((n_modules - 1 - i) % 2 == 0) ? x_out : x_tmp;
         float* th = theta + (size_t)i * n_theta;
         rc = module_fwd(geom, prox, false, x_in, S, M, y, alpha, th, x_ref, xo, losses + i, saved, saved_bytes, ws, ws_bytes,
-                              stream);
+                        fwd, stream);
         if (rc) return rc;
-        rc = module_bwd(geom, prox, false, th, saved, saved_bytes, grad, ws, ws_bytes, stream);
+        rc = module_bwd(geom, prox, false, th, saved, saved_bytes, grad, ws, ws_bytes, bwd, stream);
         if (rc) return rc;
         rc = gleam_adam_step(hyper, t, n_theta, th, grad, adam_m + (size_t)i * n_theta, adam_v + (size_t)i * n_theta, stream);
         if (rc) return rc;
@@ -617,11 +629,22 @@ int gleam_unrolled_infer(const gleam_geom* geom, const gleam_prox_desc* prox, in
     size_t n_theta = 0;
     rc = gleam_theta_count(prox, &n_theta);
     if (rc) return rc;
+    ProxPlan plan;
+    plan_prox(*geom, *prox, true, plan);
+    const int many = plan.wimg_many;   // modules whose weights are made at once
     const gleam_c64* x_in = x0;
     for (int i = 0; i < n_modules; ++i) {
+        PassWeights weights;
+        if (many > 1) {
+            const int left = n_modules - i;
+            if (i % many == 0 && prox_prepare(*geom, *prox, plan, theta + (size_t)i * n_theta, n_theta, left < many ? left : many, false, ws,
+                                              (hipStream_t)stream) != hipSuccess)
+                return GLEAM_E_LAUNCH;
+            weights.at = (unsigned char*)ws + plan.wimg_many_off + (size_t)(i % many) * plan.wimg_bytes;
+        }
         gleam_c64* xo = ((n_modules - 1 - i) % 2 == 0) ? x_out : x_tmp;
-        rc = gleam_module_fwd(geom, prox, x_in, S, M, y, alpha, theta + (size_t)i * n_theta, nullptr, xo, nullptr, nullptr, 0,
-                              ws, ws_bytes, stream);
+        rc = module_fwd(geom, prox, true, x_in, S, M, y, alpha, theta + (size_t)i * n_theta, nullptr, xo, nullptr, nullptr, 0, ws, ws_bytes,
+                        weights, stream);
         if (rc) return rc;
         x_in = xo;
     }

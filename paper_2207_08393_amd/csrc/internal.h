@@ -98,6 +98,8 @@ struct ProxPlan {
     size_t bias_partial_off;          // [n_split][kMaxChannels] floats
     size_t wimg_off_fwd, wimg_off_bwd;  // the weights of a pass as its kernels read them (inside ws) ...
     size_t wimg_layer[kMaxLayers];      // ... of each layer, behind either of them
+    size_t wimg_bytes, wimg_many_off;   // of all layers; where calls of several modules keep those of wimg_many passes
+    int wimg_many;
     size_t red_off;                   // loss partial sums (doubles)
     size_t k_bytes;                   // coil k-space buffer at the head of ws (forward)
     size_t ws_bytes;
@@ -117,18 +119,29 @@ bool prox_bf16_supported(const gleam_prox_desc& p);
 
 void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, bool split, ProxPlan& plan);
 
+// The weights a pass reads: made by it (at null), or made before, at `at`; with `collect` they are only entered there.
+struct WeightBatch;
+struct PassWeights {
+    unsigned char* at = nullptr;
+    WeightBatch* collect = nullptr;
+};
+// Makes the weights of n modules (theta n_theta floats apart), forward or both passes, one pass behind the other, at
+// ws + wimg_many_off; n passes of the plan's wimg_many.
+hipError_t prox_prepare(const gleam_geom& g, const gleam_prox_desc& p, const ProxPlan& plan, const float* theta, size_t n_theta, int n,
+                        bool backward, void* ws, hipStream_t st);
+
 // z = f_theta(u) with u = t_0 already stored at act_base + act_off[0]; writes t_1..t_{L-1} next to it
 // and z to x_out.  With x_ref: loss (device scalar) and g_z are produced as well.
 hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const ProxPlan& plan, const float* theta,
                         unsigned char* act_base, const float2* x_ref, float2* x_out, float* loss, void* ws,
-                        hipStream_t st);
+                        const PassWeights& weights, hipStream_t st);
 
 // grad_theta = dL/dtheta from the activations and g_z left by prox_forward.  g_in (may be null): receives
 // dL/du, the gradient with respect to the prox input, float32 2 channels; it may alias t_0 inside `saved`
 // (t_0 is dead once the first layer's weight gradient is done).  Requires layers[0].relu_in == 0 and at
 // most one layer taking its skip from t_0.
 hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const ProxPlan& plan, const float* theta,
-                         const unsigned char* saved, float* grad_theta, float2* g_in, void* ws, hipStream_t st);
+                         const unsigned char* saved, float* grad_theta, float2* g_in, void* ws, const PassWeights& weights, hipStream_t st);
 
 // loss (device scalar) of x against x_ref and g = dL/dx (2 real channels); `part` holds kLossPartials doubles.
 // relu_mask: zero the gradient where x <= 0 (x is the output of a layer that ends in a ReLU).

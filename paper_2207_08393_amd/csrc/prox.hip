@@ -1925,6 +1925,10 @@ __global__ __launch_bounds__(256) void real_dot_kernel(const float2* __restrict_
 // ------------------------------------------------------------------ host side
 static inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr int kLossBlocks = kLossPartials;
+// Weights of several modules at once: up to 4 MB of them, sixteen modules' forward (or eight's of both passes).  Reconstruction of
+// 8 x 160 x 128 through ten modules of 32 channels: 422 -> 386 us.  Larger networks would keep them no longer in an L2
+// and their launches do not notice.
+constexpr size_t kManyBytes = 4u << 20;
 constexpr size_t kWaitBytes = 8u << 20, kBiasWaitBytes = 1u << 20;
 
 hipError_t loss_and_grad(const float2* x, const float2* x_ref, float2* g, long long n, int loss_kind, int relu_mask,
@@ -2129,7 +2133,11 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
     plan.k_bytes = kbytes;
     plan.wimg_off_fwd = kbytes + plan.saved_bytes;
     const size_t fwd_ws = kbytes + plan.saved_bytes + img_bytes;  // activations live here when no saved buffer is given
-    plan.ws_bytes = fwd_ws > bwd_ws ? fwd_ws : bwd_ws;
+    plan.wimg_bytes = img_bytes;
+    plan.wimg_many_off = align256(fwd_ws > bwd_ws ? fwd_ws : bwd_ws);
+    const size_t many = kManyBytes / img_bytes;
+    plan.wimg_many = many < 2 ? 0 : many > 16 ? 16 : (int)many;
+    plan.ws_bytes = plan.wimg_many_off + plan.wimg_many * img_bytes;
 }
 
 void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, bool split, ProxPlan& plan) {
@@ -2146,7 +2154,7 @@ void plan_prox(const gleam_geom& g, const gleam_prox_desc& p, bool split, ProxPl
 
 hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const ProxPlan& plan, const float* theta,
                         unsigned char* act_base, const float2* x_ref, float2* x_out, float* loss, void* ws,
-                        hipStream_t st) {
+                        const PassWeights& weights, hipStream_t st) {
     const int L = p.n_layers;
     auto layer = [&](int l, WeightBatch* collect) -> hipError_t {   // runs layer l, or enters its weights
         const gleam_conv& c = p.layers[l];
@@ -2162,7 +2170,7 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
         a.relu_in = (c.relu_in && !plan.post_relu[l]) ? 1 : 0;
         a.relu_out = (c.relu_out || (l + 1 < L && plan.post_relu[l + 1])) ? 1 : 0;
         a.d = pix_dims(g, c);
-        float* const wt = reinterpret_cast<float*>((unsigned char*)ws + plan.wimg_off_fwd + plan.wimg_layer[l]);
+        float* const wt = reinterpret_cast<float*>((weights.at ? weights.at : (unsigned char*)ws + plan.wimg_off_fwd) + plan.wimg_layer[l]);
         hipError_t e;
         if (p.dtype == 1) {
             if (l == 0) {           // float32 image in, bfloat16 features out
@@ -2195,12 +2203,14 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
         }
         return e;
     };
-    WeightBatch wb{};
-    for (int l = 0; l < L; ++l) {
-        const hipError_t e = layer(l, &wb);
-        if (e != hipSuccess) return e;
-    }
-    {
+    if (!weights.at || weights.collect) {
+        WeightBatch own{};
+        WeightBatch& wb = weights.collect ? *weights.collect : own;
+        for (int l = 0; l < L; ++l) {
+            const hipError_t e = layer(l, &wb);
+            if (e != hipSuccess) return e;
+        }
+        if (weights.collect) return hipSuccess;
         const hipError_t e = prepare_weights(wb, st);
         if (e != hipSuccess) return e;
     }
@@ -2397,7 +2407,7 @@ size_t wgrad_lds_bytes(const gleam_conv& c) {
 }
 
 hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const ProxPlan& plan, const float* theta,
-                         const unsigned char* saved, float* grad_theta, float2* g_in, void* ws, hipStream_t st) {
+                         const unsigned char* saved, float* grad_theta, float2* g_in, void* ws, const PassWeights& weights, hipStream_t st) {
     const int L = p.n_layers;
     int skip_from_input = 0;   // layer (1-based) whose output gradient also flows into t_0 = u through its skip
     unsigned char* wsb = (unsigned char*)ws;
@@ -2442,7 +2452,7 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
         const gleam_conv& c = p.layers[l - 1];
         const size_t taps = (size_t)c.kt * c.kd * c.kh * c.kw;
         const PixDims d = pix_dims(g, c);
-        float* const wt = reinterpret_cast<float*>(wsb + plan.wimg_off_bwd + plan.wimg_layer[l - 1]);
+        float* const wt = reinterpret_cast<float*>((weights.at ? weights.at : wsb + plan.wimg_off_bwd) + plan.wimg_layer[l - 1]);
         ConvArgs a{};
         a.in = G(l);
         const ConvWeights cw{theta + plan.w_off[l - 1], 1, (long long)c.cin, (long long)(taps * c.cin)};
@@ -2493,13 +2503,15 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
         if (a.mask_ref && plan.sign_off[l - 1]) b.bits_in = reinterpret_cast<const unsigned*>(saved + plan.sign_off[l - 1]);
         return launch_conv_bf16(b, cw.w, cw.sn, cw.st, cw.sk, 1, reinterpret_cast<unsigned short*>(wt), collect, st);
     };
-    WeightBatch weights{};
-    for (int l = g_in ? 1 : 2; l <= L; ++l) {
-        const hipError_t e = data_gradient(l, &weights);
-        if (e != hipSuccess) return e;
-    }
-    {
-        const hipError_t e = prepare_weights(weights, st);
+    if (!weights.at || weights.collect) {
+        WeightBatch own{};
+        WeightBatch& wb = weights.collect ? *weights.collect : own;
+        for (int l = g_in ? 1 : 2; l <= L; ++l) {
+            const hipError_t e = data_gradient(l, &wb);
+            if (e != hipSuccess) return e;
+        }
+        if (weights.collect) return hipSuccess;
+        const hipError_t e = prepare_weights(wb, st);
         if (e != hipSuccess) return e;
     }
 
@@ -2644,6 +2656,27 @@ hipError_t prox_backward(const gleam_geom& g, const gleam_prox_desc& p, const Pr
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t prox_prepare(const gleam_geom& g, const gleam_prox_desc& p, const ProxPlan& plan, const float* theta, size_t n_theta, int n,
+                        bool backward, void* ws, hipStream_t st) {
+    unsigned char* const at = (unsigned char*)ws + plan.wimg_many_off;
+    WeightBatch b{};
+    hipError_t e = prox_forward(g, p, plan, theta, at, nullptr, nullptr, nullptr, ws, PassWeights{at, &b}, st);
+    if (e != hipSuccess) return e;
+    b.more = n - 1;
+    b.w_step = (long long)n_theta;
+    b.out_step = (long long)plan.wimg_bytes * (backward ? 2 : 1);
+    if (backward) {
+        if (2 * p.n_layers > kMaxLayers) {   // the jobs of both passes do not fit a batch
+            e = prepare_weights(b, st);
+            if (e != hipSuccess) return e;
+            b.n = 0;
+        }
+        e = prox_backward(g, p, plan, theta, at, nullptr, nullptr, ws, PassWeights{at + plan.wimg_bytes, &b}, st);
+        if (e != hipSuccess) return e;
+    }
+    return prepare_weights(b, st);
 }
 
 // ------------------------------------------------------------------ Adam ("Update Parameters", Alg. 1)

@@ -169,6 +169,8 @@ struct WeightJob {
 // not null, they enter the job that the launch will need, if any, and launch nothing; null, they launch and rely on it being done.
 struct WeightBatch {
     int n;
+    int more;              // modules behind the first, whose weights lie w_step floats and their results out_step bytes further
+    long long w_step, out_step;
     WeightJob job[kMaxLayers];
 };
 hipError_t prepare_weights(WeightBatch& b, hipStream_t stream);

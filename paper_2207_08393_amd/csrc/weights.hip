@@ -3,7 +3,7 @@
 // What bounds it: the launch.  A dependent launch takes 4.2 - 4.8 us here whatever it does, and the largest of these jobs
 // (128 x 128 channels, 3x3) moves 1 MB.  With a launch of its own per layer the eight that a training step of the 128-channel
 // bfloat16 chain or of a 100-channel residual network makes were 38 us; the two that are left, one before the forward and one
-// before the data-gradient launches, are 10.  A thread makes one element of an image or what one (output, input) channel pair
+// before the data-gradient launches, are 10.  Calls of several modules make those of up to sixteen modules at once.  A thread makes one element of an image or what one (output, input) channel pair
 // becomes; reads of neighbouring threads are neighbouring where the form allows it, and all of it stays in L2.
 #include "prox_common.h"
 
@@ -152,7 +152,9 @@ template <int KD, int NBLK> __device__ __forceinline__ void wino_form(const Weig
 }  // namespace
 
 __global__ __launch_bounds__(256) void prepare_weights_kernel(WeightBatch b) {
-    const WeightJob& j = b.job[blockIdx.y];
+    WeightJob j = b.job[blockIdx.y];
+    j.w += blockIdx.z * b.w_step;
+    j.out = static_cast<char*>(j.out) + blockIdx.z * b.out_step;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= j.threads) return;
     switch (j.form) {   // uniform for the workgroup
@@ -191,8 +193,8 @@ hipError_t prepare_weights(WeightBatch& b, hipStream_t st) {
                            j.form == kWeightsWino3 ? 192 : j.form == kWeightsThinOut ? 4 : 2;   // written per thread
         bytes += 4.0 * j.taps * (double)kn + per * (double)j.threads;
     }
-    KernelScope ks("weights_image", 0.0, bytes, st);
-    hipLaunchKernelGGL(prepare_weights_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)b.n), dim3(256), 0, st, b);
+    KernelScope ks("weights_image", 0.0, bytes * (1 + b.more), st);
+    hipLaunchKernelGGL(prepare_weights_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)b.n, (unsigned)(1 + b.more)), dim3(256), 0, st, b);
     return hipGetLastError();
 }
 
