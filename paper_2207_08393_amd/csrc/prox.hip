@@ -1859,36 +1859,54 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ g
 }
 
 // ------------------------------------------------------------------ loss
-// part[blk] = sum over this workgroup's pixels of |z-x|^2 (kind 0) or |z-x| (kind 1); gz = dL/dz.
-__global__ __launch_bounds__(256) void loss_kernel(const float2* __restrict__ z, const float2* __restrict__ xr, float2* __restrict__ gz,
-                                                   long long n, int kind, float inv_n, int relu_mask, double* __restrict__ part) {
-    __shared__ double red[256];
+// A pixel's dL/dz, its loss added to s: |z-x|^2 (kind 0) or |z-x| (kind 1).
+__device__ __forceinline__ float2 loss_at(float2 zv, float2 xv, int kind, float inv_n, int relu_mask, double& s) {
+    const float dx = zv.x - xv.x, dy = zv.y - xv.y;
+    float2 g;
+    if (kind == 0) {
+        s += (double)dx * dx + (double)dy * dy;
+        g = make_float2(2.f * dx * inv_n, 2.f * dy * inv_n);
+    } else {
+        const float mag = sqrtf(dx * dx + dy * dy);
+        s += (double)mag;
+        g = mag > 0.f ? make_float2(dx / mag * inv_n, dy / mag * inv_n) : make_float2(0.f, 0.f);
+    }
+    if (relu_mask) {  // last layer ended in a ReLU: gradient passes where its output is positive
+        g.x = zv.x > 0.f ? g.x : 0.f;
+        g.y = zv.y > 0.f ? g.y : 0.f;
+    }
+    return g;
+}
+
+// part[blk] = sum over this workgroup's pixels; gz = dL/dz.  One workgroup of 1024 threads with a loss writes that instead: the second
+// launch of a small call costs more than its pixels (4096 pixels: 6.5 - 9 us in two launches, 4.1 in one).
+__global__ __launch_bounds__(1024) void loss_kernel(const float2* __restrict__ z, const float2* __restrict__ xr, float2* __restrict__ gz,
+                                                    long long n, int kind, float inv_n, int relu_mask, double* __restrict__ part,
+                                                    float* __restrict__ loss, double mean) {
+    __shared__ double red[16];
     double s = 0.0;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const float2 zv = z[i], xv = xr[i];
-        const float dx = zv.x - xv.x, dy = zv.y - xv.y;
-        float2 g;
-        if (kind == 0) {
-            s += (double)dx * dx + (double)dy * dy;
-            g = make_float2(2.f * dx * inv_n, 2.f * dy * inv_n);
-        } else {
-            const float mag = sqrtf(dx * dx + dy * dy);
-            s += (double)mag;
-            g = mag > 0.f ? make_float2(dx / mag * inv_n, dy / mag * inv_n) : make_float2(0.f, 0.f);
+    const long long step = (long long)gridDim.x * blockDim.x;
+    long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    for (; i + 3 * step < n; i += 4 * step) {   // four pixels in flight
+        float2 zv[4], xv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            zv[u] = z[i + u * step];
+            xv[u] = xr[i + u * step];
         }
-        if (relu_mask) {  // last layer ended in a ReLU: gradient passes where its output is positive
-            g.x = zv.x > 0.f ? g.x : 0.f;
-            g.y = zv.y > 0.f ? g.y : 0.f;
-        }
-        gz[i] = g;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) gz[i + u * step] = loss_at(zv[u], xv[u], kind, inv_n, relu_mask, s);
     }
-    red[threadIdx.x] = s;
+    for (; i < n; i += step) gz[i] = loss_at(z[i], xr[i], kind, inv_n, relu_mask, s);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        for (unsigned w = 1; w < blockDim.x / 64; ++w) s += red[w];
+        if (loss) *loss = (float)(s * mean);
+        else part[blockIdx.x] = s;
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
 __global__ void loss_final_kernel(const double* __restrict__ part, int n_part, double inv_n, float* __restrict__ loss) {
@@ -1925,6 +1943,7 @@ __global__ __launch_bounds__(256) void real_dot_kernel(const float2* __restrict_
 // ------------------------------------------------------------------ host side
 static inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr int kLossBlocks = kLossPartials;
+constexpr long long kLossOneGroup = 16384;   // pixels up to which one workgroup makes the loss
 // Weights of several modules at once: up to 4 MB of them, sixteen modules' forward (or eight's of both passes).  Reconstruction of
 // 8 x 160 x 128 through ten modules of 32 channels: 422 -> 386 us.  Larger networks would keep them no longer in an L2
 // and their launches do not notice.
@@ -1934,8 +1953,13 @@ constexpr size_t kWaitBytes = 8u << 20, kBiasWaitBytes = 1u << 20;
 hipError_t loss_and_grad(const float2* x, const float2* x_ref, float2* g, long long n, int loss_kind, int relu_mask,
                          double* part, float* loss, hipStream_t st) {
     KernelScope ks("loss", 0.0, 24.0 * (double)n, st);
-    hipLaunchKernelGGL(loss_kernel, dim3(kLossBlocks), dim3(256), 0, st, x, x_ref, g, n, loss_kind, (float)(1.0 / (double)n),
-                       relu_mask, part);
+    const float inv_n = (float)(1.0 / (double)n);
+    if (n <= kLossOneGroup) {
+        hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(1024), 0, st, x, x_ref, g, n, loss_kind, inv_n, relu_mask, part, loss, 1.0 / (double)n);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(loss_kernel, dim3(kLossBlocks), dim3(256), 0, st, x, x_ref, g, n, loss_kind, inv_n, relu_mask, part, (float*)nullptr,
+                       0.0);
     hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(64), 0, st, (const double*)part, kLossBlocks, 1.0 / (double)n, loss);
     return hipGetLastError();
 }
