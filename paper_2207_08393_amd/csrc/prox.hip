@@ -1594,7 +1594,7 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         if (tid < a.Co) {
             const int c4 = tid / 4, e = tid % 4;
             float t = 0.f;
-            for (int v = c4; v < PG * NT; v += Co4) {
+            for (int v = c4; v < n_g4; v += Co4) {   // (the slots behind n_g4 are empty)
                 const float4 x = red[v];
                 t += e == 0 ? x.x : (e == 1 ? x.y : (e == 2 ? x.z : x.w));
             }
@@ -1629,7 +1629,6 @@ __global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a) {
     const PixDims d = a.d;
     const int WS = (d.W + PX - 1) / PX * PX + 2 * NC4 - PX;   // slab columns: image columns -KW/2 .., zero past the row
     float* slab = smem;                     // [RT][WS][TH]
-    float* red = smem + RT * WS * TH;       // [256]
     const int WCr = a.WC <= 32 ? 32 : (a.WC <= 64 ? 64 : (a.WC <= 128 ? 128 : 256));
     const int groups = 256 / WCr;
     const int c = threadIdx.x % WCr;
@@ -1720,40 +1719,40 @@ __global__ __launch_bounds__(256) void wgrad_thin_kernel(WgradThinArgs a) {
             }
         }
     }
-    // fold the pixel groups of this workgroup, then write the partial in dw layout
+    // Fold the pixel groups of this workgroup, each sum in the order of the groups, and write the partial in dw layout.  The sums of
+    // nine taps go through LDS together (one after the other, between two barriers each, they took 5 of the 8 us of a call on 64 x 64
+    // pixels).
+    constexpr int NB = THIN_IN ? 1 : TH;   // bias sums
+    constexpr int ROUND = TAPS < 9 ? TAPS : 9;
+    static_assert(TAPS % ROUND == 0, "whole rounds of taps");
+    float* const red = smem;               // [ROUND * TH + NB][256]
     const int Co = THIN_IN ? a.WC : TH, Ci = THIN_IN ? TH : a.WC;
     float* dst = a.partial + (size_t)blockIdx.x * Co * TAPS * Ci;
 #pragma unroll
-    for (int t = 0; t < TAPS; ++t)
+    for (int t0 = 0; t0 < TAPS; t0 += ROUND) {
+        __syncthreads();
 #pragma unroll
-        for (int e = 0; e < TH; ++e) {
-            __syncthreads();
-            red[threadIdx.x] = acc[t][e];
-            __syncthreads();
-            if (pg == 0 && c_ok) {
-                float sum = 0.f;
-                for (int g2 = 0; g2 < groups; ++g2) sum += red[g2 * WCr + c];
-                const size_t o = THIN_IN ? ((size_t)c * TAPS + t) * Ci + e : ((size_t)e * TAPS + t) * Ci + c;
-                dst[o] = sum;
-            }
+        for (int t = 0; t < ROUND; ++t)
+#pragma unroll
+            for (int e = 0; e < TH; ++e) red[(t * TH + e) * 256 + threadIdx.x] = acc[t0 + t][e];
+        if (t0 == 0) {
+#pragma unroll
+            for (int e = 0; e < NB; ++e) red[(ROUND * TH + e) * 256 + threadIdx.x] = bs[e];
         }
-    if (a.bias_partial != nullptr) {
-#pragma unroll
-        for (int e = 0; e < (THIN_IN ? 1 : TH); ++e) {
-            __syncthreads();
-            red[threadIdx.x] = bs[e];
-            __syncthreads();
-            if (THIN_IN) {
-                if (pg == 0 && c_ok) {
-                    float sum = 0.f;
-                    for (int g2 = 0; g2 < groups; ++g2) sum += red[g2 * WCr + c];
-                    a.bias_partial[(size_t)blockIdx.x * Co + c] = sum;
-                }
-            } else if (threadIdx.x == 0) {
-                float sum = 0.f;
-                for (int g2 = 0; g2 < groups; ++g2) sum += red[g2 * WCr];
-                a.bias_partial[(size_t)blockIdx.x * Co + e] = sum;
-            }
+        __syncthreads();
+        for (int i = threadIdx.x; i < ROUND * TH * WCr; i += 256) {
+            const int k = i / WCr, c2 = i % WCr;   // (WCr is a power of two and divides 256)
+            if (c2 >= a.WC) continue;
+            float sum = 0.f;
+            for (int g2 = 0; g2 < groups; ++g2) sum += red[k * 256 + g2 * WCr + c2];
+            const int t = t0 + k / TH, e = k % TH;
+            dst[THIN_IN ? ((size_t)c2 * TAPS + t) * Ci + e : ((size_t)e * TAPS + t) * Ci + c2] = sum;
+        }
+        if (t0 == 0 && a.bias_partial != nullptr && threadIdx.x < (THIN_IN ? a.WC : TH)) {
+            float sum = 0.f;   // of a channel, or of the first lane of every group
+            for (int g2 = 0; g2 < groups; ++g2)
+                sum += THIN_IN ? red[ROUND * TH * 256 + g2 * WCr + threadIdx.x] : red[(ROUND * TH + threadIdx.x) * 256 + g2 * WCr];
+            a.bias_partial[(size_t)blockIdx.x * Co + threadIdx.x] = sum;
         }
     }
 }
@@ -2267,7 +2266,10 @@ static void launch_wgrad_thin_t(const WgradArgs& a, float* bias_partial, int n_s
     WgradThinArgs t{};
     t.partial = a.partial; t.bias_partial = bias_partial; t.relu_in = a.relu_in; t.d = a.d;
     constexpr int PX = 4, NC4 = (PX + KW - 1 + 1) / 2;
-    const size_t lds = ((size_t)KT * KD * KH * ((a.d.W + PX - 1) / PX * PX + 2 * NC4 - PX) * 2 + 256) * sizeof(float);
+    constexpr int TAPS = KT * KD * KH * KW;
+    const size_t slab = (size_t)KT * KD * KH * ((a.d.W + PX - 1) / PX * PX + 2 * NC4 - PX) * 2;
+    constexpr size_t fold = ((TAPS < 9 ? TAPS : 9) * 2 + 2) * 256;   // the slab's memory, once it is done with
+    const size_t lds = (slab > fold ? slab : fold) * sizeof(float);
     const dim3 grid(n_split), blk(256);
     if (a.Ci == 2) {   // thin input a (float32), wide output gradient g
         t.wide = a.g; t.thin = a.a; t.WC = a.Co;
