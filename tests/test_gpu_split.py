@@ -260,6 +260,17 @@ def test_blocks_of_four_and_eight_rows_3d(D):
                                    centre=2, bias_std=0.1, alpha=0.8))
 
 
+# blocks of eight rows whose input lies inside the image, between such that reach over its border: offsets from a table; several blocks
+# per workgroup, of several images; sign words between two launches, a mask with a tensor to add, a ReLU on the input
+@pytest.mark.parametrize("geom,prox", [(synth.Geom(1, 1, 2, 1, 4, 180, 96), synth.chain_prox([2, 20, 32, 64, 2], [K2] * 4)),
+                                       (synth.Geom(2, 2, 2, 1, 2, 192, 160), synth.resblock_prox(36, 1)),
+                                       (synth.Geom(3, 1, 2, 1, 8, 46, 96), synth.chain_prox([2, 32, 32, 20, 2], [K3] * 4))],
+                         ids=["words", "residual", "volume"])
+def test_blocks_inside_the_image(geom, prox):
+    print("case inside", [l.cout for l in prox.layers], flush=True)
+    check_module(synth.make_custom(53, geom, prox, accel=2.0, centre=2, bias_std=0.1, alpha=0.8))
+
+
 @pytest.mark.parametrize("geom,k", [(synth.Geom(2, 1, 2, 1, 1, 20, 46), K2), (synth.Geom(3, 1, 2, 1, 8, 20, 46), K3)], ids=["2d", "3d"])
 def test_range_of_the_weight_gradient(geom, k):
     """What lies below 2^-126 of an operand's parts and of their products is lost (csrc/split.h).  As in test_gpu_cover.py the gradient
