@@ -142,7 +142,8 @@ def _nbytes(t) -> int:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        # the handle itself: building a Stream object around it took 2.8 of the 14 us of a small operator call, this takes 0.3
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
