@@ -1128,6 +1128,14 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt, bool
         KernelScope ks(name, 2.0 * (double)a.d.Q * a.K * a.Nn * taps_, 4.0 * (double)a.d.Q * (a.K + a.Nn), st);
         return launch_conv_time(t, a.d, st);
     }
+    if (conv_pair_applies(a.d, a.K, a.Nn) && !a.mask_ref) {   // two output channels: the bits of the kernel below
+        if (collect) return enter(kWeightsPair, conv_ck(a.K), 0);
+        a.wt = wt;
+        char name[56];
+        snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
+        KernelScope ks(name, 2.0 * (double)a.d.Q * a.K * a.Nn * taps_, 4.0 * (double)a.d.Q * (a.K + a.Nn), st);
+        return launch_conv_pair(a, st);
+    }
     const int cover = conv_cover_channels(a.d, a.K, a.Nn);
     const int ck = conv_ck(a.K), nb = cover ? cover : conv_nb(a.Nn);
     if (collect) return enter(kWeightsImage, ck, nb);
@@ -2130,7 +2138,7 @@ static void plan_one(const gleam_geom& g, const gleam_prox_desc& p, bool split, 
         size_t floats = 0;
         auto room = [&](size_t n) { floats = n > floats ? n : floats; };
         room(conv_wimg_floats(c.cin, c.cout, taps));
-        room(conv_wimg_floats(c.cout, c.cin, taps));
+        room(conv_wimg_floats(c.cout, c.cin, taps));   // (conv_pair_weight_floats is a sixteenth of it)
         if (taps == 9) room(conv_wino_weight_floats(c.cin, c.cout));      // 16 values per channel pair
         if (taps == 27) room(conv_wino3_weight_floats(c.cin, c.cout));    // ... and depth tap
         if (p.dtype == 1) {   // half the bytes per element, but chunked by 32 channels

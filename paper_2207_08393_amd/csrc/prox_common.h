@@ -155,7 +155,7 @@ __device__ __forceinline__ ChunkIter chunk_next(ChunkIter x, int n_kc, int nck, 
 
 // One layer's weights, re-laid or transformed into what its kernel reads (weights.hip has the forms).  Element (output n, tap t,
 // input k) of the source is w[n*sn + t*st + k*sk]; flip: taps mirrored (data gradient: n counts its outputs, the layer's inputs).
-enum WeightForm { kWeightsImage, kWeightsImageBf16, kWeightsBf16Tile, kWeightsBf16Resident, kWeightsThinOut, kWeightsSplit, kWeightsWino, kWeightsWino3, kWeightsTimeSplit };
+enum WeightForm { kWeightsImage, kWeightsImageBf16, kWeightsBf16Tile, kWeightsBf16Resident, kWeightsThinOut, kWeightsSplit, kWeightsWino, kWeightsWino3, kWeightsTimeSplit, kWeightsPair };
 struct WeightJob {
     const float* w;
     void* out;
@@ -190,6 +190,11 @@ struct ConvArgs {
     int relu_in, relu_out, mask_acc, mask_add;
     PixDims d;
 };
+
+// Direct convolution with two output channels (prox_pair.hip).
+bool conv_pair_applies(const PixDims& d, int K, int Nn);
+size_t conv_pair_weight_floats(int K, int taps);
+hipError_t launch_conv_pair(const ConvArgs& a, hipStream_t stream);
 
 // Direct convolution with every output channel in one workgroup (prox_cover.hip): output channels per weight image (Nn), 0
 // where the layer does not take it.

@@ -59,6 +59,20 @@ __device__ __forceinline__ void bf16_resident(const WeightJob& j, int i) {
     wt[i] = f32_to_bf16(weight_at(j, 32 * block + (lane & 31), tap, 16 * kc + 8 * (lane >> 5) + s));
 }
 
+// conv_pair_kernel, in the order of use: [row tap][chunk of CK input channels][tap along W][group of 8][e][half][n], n < 2, of input
+// channel 8 * group + 4 * half + e of the chunk
+__device__ __forceinline__ void pair_form(const WeightJob& j, int i) {
+    const int n = i & 1, half = (i >> 1) & 1, e = (i >> 2) & 3, G = j.CK / 8;
+    int rest = i >> 4;
+    const int g = rest % G;
+    rest /= G;
+    const int dw = rest % j.kw;
+    rest /= j.kw;
+    const int n_kc = (j.K + j.CK - 1) / j.CK, kc = rest % n_kc, rt = rest / n_kc;
+    const int k = kc * j.CK + 8 * g + 4 * half + e;
+    static_cast<float*>(j.out)[i] = k < j.K ? weight_at(j, n, rt * j.kw + dw, k) : 0.f;
+}
+
 // two-channel-output kernels: [n][tap][k], n < 2.  round_bf: the values are rounded to bfloat16 (kept as float32), for the kernels
 // that multiply bfloat16 data with float32 arithmetic: weights that meet bfloat16 data are bfloat16 values in every kernel.
 __device__ __forceinline__ void thin_out(const WeightJob& j, int i) {
@@ -164,6 +178,7 @@ __global__ __launch_bounds__(256) void prepare_weights_kernel(WeightBatch b) {
         case kWeightsBf16Resident: bf16_resident(j, i); break;
         case kWeightsThinOut: thin_out(j, i); break;
         case kWeightsSplit: split_form(j, i); break;
+        case kWeightsPair: pair_form(j, i); break;
         case kWeightsTimeSplit: time_split_form(j, i); break;
         case kWeightsWino: wino_form<1, 64>(j, i); break;
         default: wino_form<3, 32>(j, i); break;
@@ -184,13 +199,14 @@ hipError_t prepare_weights(WeightBatch& b, hipStream_t st) {
             case kWeightsBf16Tile:
             case kWeightsBf16Resident: j.threads = 9 * kn; break;
             case kWeightsThinOut: j.threads = j.taps * kn; break;
+            case kWeightsPair: j.threads = j.taps * up(j.K, j.CK) * 2; break;
             case kWeightsTimeSplit: j.threads = 16 * j.CK * up(j.Nn, 32); break;
             case kWeightsSplit: j.threads = up(j.K, 16) * up(j.Nn, 32); break;
             default: j.threads = kn; break;
         }
         most = j.threads > most ? j.threads : most;
         const double per = j.form == kWeightsImage ? 4 : j.form == kWeightsSplit ? 72.0 * j.taps / 9 : j.form == kWeightsTimeSplit ? 18 : j.form == kWeightsWino ? 64 :
-                           j.form == kWeightsWino3 ? 192 : j.form == kWeightsThinOut ? 4 : 2;   // written per thread
+                           j.form == kWeightsWino3 ? 192 : j.form == kWeightsThinOut || j.form == kWeightsPair ? 4 : 2;   // written per thread
         bytes += 4.0 * j.taps * (double)kn + per * (double)j.threads;
     }
     KernelScope ks("weights_image", 0.0, bytes * (1 + b.more), st);
