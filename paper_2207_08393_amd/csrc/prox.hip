@@ -1149,14 +1149,6 @@ static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt, bool
 }
 
 // ------------------------------------------------------------------ weight gradient
-struct WgradArgs {
-    const float* g;    // [Q][Co]  gradient at the conv output (already ReLU-masked)
-    const float* a;    // [Q][Ci]  conv input before its optional ReLU
-    float* partial;    // [n_split][Co][taps][Ci]
-    int Co, Ci, relu_in;
-    PixDims d;
-};
-
 constexpr int kWgTM = 32;  // pixels per staged chunk
 constexpr int kThinSplit = 1024;  // most partial sums the thin weight-gradient kernel writes
 
@@ -1259,25 +1251,7 @@ struct WgradPipeArgs {
 // BAL (one 32x32 channel block, more taps than waves): the taps are dealt to all NW waves in runs whose lengths
 // differ by at most one, longest first, so that the waves sharing a SIMD (w and w + 4) carry nearly the same
 // number of MFMAs; JT is then the longest run.
-//
-// COVER (2 or 3: whole blocks of 32 output channels): the gradient is a matrix of Co rows and taps * Ci columns.  A wave takes
-// its COVER blocks of 32 rows in JT / COVER blocks of 32 columns, across the borders of the taps, and so reads COVER + JT / COVER
-// operands for JT matrix instructions; what is left of rows and columns goes by 4 x 4 blocks, sixteen to a
-// v_mfma_f32_4x4x1_f32 (as many multiply-adds a cycle), kCoverQuads of those to a wave.  100 -> 100 channels, nine taps: 84 blocks
-// in 14 waves and 249 small ones in two, instead of 16 jobs of one channel block x nine taps, of which seven carried four
-// channels: 968 -> 738 us at 4 x 320 x 256 (865 us with an operand read for each factor of each product), 80 TFLOP/s.  What bounds
-// it: matrix cores half of the time, the LDS reads and the staging between two barriers the rest.  Both instructions add their products with fused multiply-adds in the order of the pixels: the sums are the
-// same bits as without COVER.
-constexpr int kCoverUnits = 6, kCoverQuads = 8;
-struct CoverSplit {
-    int F, ncol, quads;   // blocks of 32 rows, columns, blocks of 4 x 4
-    __host__ __device__ CoverSplit(int Co, int ncol_)
-        : F(Co / 32), ncol(ncol_), quads(Co % 32 / 4 * (ncol_ / 4) + Co / 32 * 8 * (ncol_ % 32 / 4)) {}
-    __host__ __device__ int unit_waves() const { return (ncol / 32 + kCoverUnits / F - 1) / (kCoverUnits / F); }
-    __host__ __device__ int waves() const { return unit_waves() + (quads + 16 * kCoverQuads - 1) / (16 * kCoverQuads); }
-};
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-template <int JT, int PG, int PA, int NW, bool BAL = false, int COVER = 0>
+template <int JT, int PG, int PA, int NW, bool BAL = false>
 __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
     constexpr int NT = NW * 64;
     extern __shared__ __attribute__((aligned(16))) float smem[];
@@ -1292,10 +1266,8 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, m = lane & 31, h = lane >> 5;
     const int ncb = (a.Co + 31) / 32, nib = (a.Ci + 31) / 32, tapgroups = (taps + JT - 1) / JT;
-    const CoverSplit cover(a.Co, taps * a.Ci);
-    const int job = COVER ? wave * gridDim.y + blockIdx.y : blockIdx.y * NW + wave;
-    const bool active = BAL || job < (COVER ? cover.unit_waves() : ncb * nib * tapgroups);
-    const bool quads = COVER && job >= cover.unit_waves() && job < cover.waves();
+    const int job = blockIdx.y * NW + wave;
+    const bool active = BAL || job < ncb * nib * tapgroups;
     const int tg = job % tapgroups, pair = job / tapgroups;
     const int cb = BAL ? 0 : pair / nib, ib = BAL ? 0 : pair % nib;
     const int bal_base = taps / NW, bal_extra = taps % NW;
@@ -1308,7 +1280,7 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
     // Row tap and pixel offset of a slot: apart, or as one word (row tap << 8 | pixel offset + 128, row tap 31: none) in the
     // eight waves of nine taps, which have no registers for two.  (One word everywhere: two more instructions per slot and
     // chunk; 16 -> 16 channels 59.7 -> 60.4 us at 555 x 256, 96 -> 96 230.1 -> 232.3 us at 3 x 128 x 160.)
-    constexpr bool kOneWord = (JT == 9 && NW == 8) || COVER > 0;
+    constexpr bool kOneWord = JT == 9 && NW == 8;
     int a_lds[PA], a_c[PA], a_px[PA];
     unsigned a_rt[PA];
 #pragma unroll
@@ -1429,42 +1401,6 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         b_off[j] = (rt * n_pa + dw + h) * RSa + ci_c;
     }
     const int a_off = h * RSg + co_c;
-    // COVER: LDS offsets of a wave's column blocks (rows: u_row), or of the rows and columns of its 4 x 4 blocks (lane 4 * block +
-    // row, + column)
-    constexpr int CU = COVER ? JT / COVER : 1;
-    int ca_off[COVER ? kCoverQuads : 1], cb_off[COVER ? kCoverQuads : 1];
-    const int ncol = taps * a.Ci, u_row = h * RSg + m;
-    auto column = [&](int n) {   // of its pixel 0
-        const int tap = n / a.Ci;
-        return (tap / d.kw * n_pa + tap % d.kw) * RSa + n % a.Ci;
-    };
-    auto quad_block = [&](int j, int& row, int& col) {   // first row and column; false: there is none
-        const int t = ((job - cover.unit_waves()) * kCoverQuads + j) * 16 + (lane >> 2);
-        const int n_rows = a.Co % 32 / 4 * (ncol / 4), rem = ncol % 32 / 4;
-        row = col = 0;
-        if (!quads || t >= cover.quads) return false;
-        row = t < n_rows ? a.Co / 32 * 32 + t / (ncol / 4) * 4 : (t - n_rows) / rem * 4;
-        col = t < n_rows ? t % (ncol / 4) * 4 : ncol / 32 * 32 + (t - n_rows) % rem * 4;
-        return true;
-    };
-    if constexpr (COVER > 0) {
-        if (active) {
-#pragma unroll
-            for (int j = 0; j < CU; ++j) {
-                const int c = job * CU + j;
-                cb_off[j] = column((c < ncol / 32 ? c * 32 : 0) + m) + h * RSa;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kCoverQuads; ++j) {
-                int row, col;
-                (void)quad_block(j, row, col);
-                ca_off[j] = row + (lane & 3);
-                cb_off[j] = column(col + (lane & 3));
-            }
-        }
-    }
-
     const long long n_chunks = (d.Q / d.W) * segs;
     const XcdRange xr = xcd_range(n_chunks);
     long long chunk = xr.first;
@@ -1480,58 +1416,7 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
     for (; chunk < xr.end; chunk += xr.stride) {
         const long long next = chunk + xr.stride;
         if (next < xr.end) fetch();
-        if constexpr (COVER > 0) {
-            if (active) {
-                const float* gr = gs + u_row;
-                float av[COVER], bv[CU];
-#pragma unroll
-                for (int r = 0; r < COVER; ++r) av[r] = gr[32 * r];
-#pragma unroll
-                for (int j = 0; j < CU; ++j) bv[j] = as[cb_off[j]];
-#pragma unroll 2
-                for (int s = 0; s < kWgTM / 2; ++s) {
-                    const int sn = s + 1 < kWgTM / 2 ? s + 1 : s;
-                    float av_n[COVER], bv_n[CU];
-#pragma unroll
-                    for (int r = 0; r < COVER; ++r) av_n[r] = gr[2 * sn * RSg + 32 * r];
-#pragma unroll
-                    for (int j = 0; j < CU; ++j) bv_n[j] = as[cb_off[j] + 2 * sn * RSa];
-#pragma unroll
-                    for (int j = 0; j < CU; ++j)
-#pragma unroll
-                        for (int r = 0; r < COVER; ++r)
-                            acc[j * COVER + r] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[r], bv[j], acc[j * COVER + r], 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < COVER; ++r) av[r] = av_n[r];
-#pragma unroll
-                    for (int j = 0; j < CU; ++j) bv[j] = bv_n[j];
-                }
-            } else if (quads) {
-                floatx4 accq[kCoverQuads];   // (lie in acc between the chunks)
-#pragma unroll
-                for (int j = 0; j < kCoverQuads; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) accq[j][r] = acc[j / 4][4 * (j % 4) + r];
-                float av[kCoverQuads], bv[kCoverQuads];
-#pragma unroll
-                for (int j = 0; j < kCoverQuads; ++j) { av[j] = gs[ca_off[j]]; bv[j] = as[cb_off[j]]; }
-#pragma unroll 2
-                for (int s = 0; s < kWgTM; ++s) {
-                    const int sn = s + 1 < kWgTM ? s + 1 : s;
-                    float av_n[kCoverQuads], bv_n[kCoverQuads];
-#pragma unroll
-                    for (int j = 0; j < kCoverQuads; ++j) { av_n[j] = gs[ca_off[j] + sn * RSg]; bv_n[j] = as[cb_off[j] + sn * RSa]; }
-#pragma unroll
-                    for (int j = 0; j < kCoverQuads; ++j) accq[j] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[j], bv[j], accq[j], 0, 0, 0);
-#pragma unroll
-                    for (int j = 0; j < kCoverQuads; ++j) { av[j] = av_n[j]; bv[j] = bv_n[j]; }
-                }
-#pragma unroll
-                for (int j = 0; j < kCoverQuads; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[j / 4][4 * (j % 4) + r] = accq[j][r];
-            }
-        } else if (active) {
+        if (active) {
             // software pipeline over the 2-pixel K-steps: operands of step s+1 are read from LDS
             // before the MFMAs of step s are issued
             float av = gs[a_off];
@@ -1557,29 +1442,7 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         if (next < xr.end) stash();
         __syncthreads();
     }
-    if constexpr (COVER > 0) {
-        float* dst = a.partial + (size_t)blockIdx.x * a.Co * ncol;
-        if (active) {
-#pragma unroll
-            for (int j = 0; j < CU; ++j) {
-                const int c = job * CU + j;
-                if (c >= ncol / 32) continue;
-#pragma unroll
-                for (int b = 0; b < COVER; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        dst[(32 * b + 8 * (r / 4) + 4 * h + r % 4) * ncol + 32 * c + m] = acc[j * COVER + b][r];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kCoverQuads; ++j) {
-                int row, col;
-                if (!quad_block(j, row, col)) continue;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dst[(row + r) * ncol + col + (lane & 3)] = acc[j / 4][4 * (j % 4) + r];
-            }
-        }
-    } else if (active) {
+    if (active) {
         float* dst = a.partial + (size_t)blockIdx.x * a.Co * taps * a.Ci;
 #pragma unroll
         for (int j = 0; j < JT; ++j) {
@@ -2258,15 +2121,15 @@ hipError_t prox_forward(const gleam_geom& g, const gleam_prox_desc& p, const Pro
     return hipSuccess;
 }
 
-template <int JT, int PG, int PA, int NW, bool BAL = false, int COVER = 0>
+template <int JT, int PG, int PA, int NW, bool BAL = false>
 static void launch_wgrad_pipe_t(const WgradPipeArgs& pa, dim3 grid, size_t lds, hipStream_t st) {
     static bool once = false;
     if (!once) {
-        (void)hipFuncSetAttribute((const void*)wgrad_pipe_kernel<JT, PG, PA, NW, BAL, COVER>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        (void)hipFuncSetAttribute((const void*)wgrad_pipe_kernel<JT, PG, PA, NW, BAL>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         once = true;
     }
     if (lds < (size_t)PG * NW * 64 * sizeof(float4)) lds = (size_t)PG * NW * 64 * sizeof(float4);
-    hipLaunchKernelGGL((wgrad_pipe_kernel<JT, PG, PA, NW, BAL, COVER>), grid, dim3(NW * 64), lds, st, pa);
+    hipLaunchKernelGGL((wgrad_pipe_kernel<JT, PG, PA, NW, BAL>), grid, dim3(NW * 64), lds, st, pa);
 }
 
 template <int KT, int KD, int KH, int KW>
@@ -2349,8 +2212,14 @@ static hipError_t launch_wgrad(const WgradArgs& a, float* bias_partial, bool* bi
             return hipSuccess;
         }
     }
-    // (2) channel counts that are multiples of 4: register-prefetch pipelined MFMA kernel
+    // (2) more than eight channel blocks: two workgroups of eight waves either way, with six matrix instructions a wave and pixel pair
+    // instead of nine
     const double max_off = (double)(d.kt / 2 + 1) * d.D * d.H * d.W * (a.Ci > a.Co ? a.Ci : a.Co);   // 32-bit slot offsets
+    if (wgrad_cover_applies(d, a.Co, a.Ci) && max_off < 2147483648.0) {
+        *bias_done = bias_partial != nullptr;
+        return launch_wgrad_cover(a, bias_partial, n_split, st);
+    }
+    // (3) channel counts that are multiples of 4: register-prefetch pipelined MFMA kernel
     if (a.Co % 4 == 0 && a.Ci % 4 == 0 && max_off < 2147483648.0) {
         const int n_pa = kWgTM + d.kw - 1;
         const int need_pg = (kWgTM * (a.Co / 4) + kConvThreads - 1) / kConvThreads;
@@ -2380,14 +2249,6 @@ static hipError_t launch_wgrad(const WgradArgs& a, float* bias_partial, bool* bi
                 hit_none = false;
             } else if (jobs1 >= 7 && jobs1 <= 12 && pg12 <= 1 && pa12 <= 3) {
                 launch_wgrad_pipe_t<1, 1, 3, 12>(pa, g12, lds, st);
-                hit_none = false;
-            } else if (taps == 9 && (a.Co / 32 == 2 || a.Co / 32 == 3) && blocks > 8 && blocks <= 16 &&
-                       CoverSplit(a.Co, taps * a.Ci).waves() <= 16 && pg8b <= 2 && pa8b <= 5) {
-                // nine to sixteen channel blocks: two workgroups of eight waves either way, with six matrix instructions a wave and
-                // pixel pair instead of nine
-                const dim3 g2(n_split, 2);
-                if (a.Co / 32 == 2) launch_wgrad_pipe_t<kCoverUnits, 2, 5, 8, false, 2>(pa, g2, lds, st);
-                else launch_wgrad_pipe_t<kCoverUnits, 2, 5, 8, false, 3>(pa, g2, lds, st);
                 hit_none = false;
             } else if (taps == 9 && blocks > 4 && (blocks + 7) / 8 * 8 <= (blocks + 3) / 4 * 4 && pg8b <= 2 && pa8b <= 5) {
                 // more than 64 channels on a side: eight waves of nine taps share one staged chunk, two per SIMD (four waves with
@@ -2419,7 +2280,7 @@ static hipError_t launch_wgrad(const WgradArgs& a, float* bias_partial, bool* bi
         }
         if (hit) return hipErrorInvalidValue;  // cannot happen: the plan bounds LDS use
     }
-    // (3) generic fallback
+    // (4) generic fallback
     const int RSg = (a.Co + 3) / 4 * 4 + 1, RSa = (a.Ci + 3) / 4 * 4 + 1;
     const size_t lds = ((size_t)kWgTM * RSg + (size_t)rowtaps * (kWgTM + d.kw - 1) * RSa + kWgTM) * sizeof(float);
     if (jt == 9) {

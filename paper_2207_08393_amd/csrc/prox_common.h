@@ -196,6 +196,18 @@ bool conv_pair_applies(const PixDims& d, int K, int Nn);
 size_t conv_pair_weight_floats(int K, int taps);
 hipError_t launch_conv_pair(const ConvArgs& a, hipStream_t stream);
 
+struct WgradArgs {
+    const float* g;    // [Q][Co]  gradient at the conv output (already ReLU-masked)
+    const float* a;    // [Q][Ci]  conv input before its optional ReLU
+    float* partial;    // [n_split][Co][taps][Ci]
+    int Co, Ci, relu_in;
+    PixDims d;
+};
+
+// Weight gradient of 68 to 124 x 68 to 100 channels, nine taps (prox_coverw.hip).
+bool wgrad_cover_applies(const PixDims& d, int Co, int Ci);
+hipError_t launch_wgrad_cover(const WgradArgs& a, float* bias_partial, int n_split, hipStream_t stream);
+
 // Direct convolution with every output channel in one workgroup (prox_cover.hip): output channels per weight image (Nn), 0
 // where the layer does not take it.
 int conv_cover_channels(const PixDims& d, int K, int Nn);

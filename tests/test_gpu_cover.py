@@ -1,5 +1,5 @@
 """The direct float32 kernels with every output channel in one workgroup (prox_cover.hip) and the weight gradient in blocks
-across the taps (wgrad_pipe_kernel<.., COVER>), which give the same bits as the kernels they stand in for: a batch large enough for
+across the taps (prox_coverw.hip), which give the same bits as the kernels they stand in for: a batch large enough for
 them against its samples one by one, and the calls' 64-bit results."""
 import dataclasses
 
