@@ -9,7 +9,7 @@
 // image are stored as 0, so the matrix instructions need no masks.  Two chunks lie in LDS: while one is multiplied the next is
 // fetched, slot by slot in the first half of the multiplications, and stored in the second, between one barrier and the next.  Rows
 // of fixed length make every LDS address a register and a constant, and the operands of a step are read during the one before.
-// 100 -> 100 channels at 4 x 320 x 256: 544 us, 108 TFLOP/s; 750 us with one chunk in LDS between two barriers, operands read
+// 100 -> 100 channels at 4 x 320 x 256: 536 us, 110 TFLOP/s; 750 us with one chunk in LDS between two barriers, operands read
 // where they were needed (the compiler had moved the reads back) and the LDS addresses of every step computed.  What bounds it: the
 // matrix cores, 0.75 of the time.
 //
@@ -78,10 +78,21 @@ __global__ __launch_bounds__(512) void wgrad_cover_kernel(WgradArgs a, float* bi
     const XcdRange xr = xcd_range((d.Q / d.W) * segs);
     PixDims cd = d;
     cd.W = segs;
-    PixCoord cc = pix_coord(xr.first, cd);   // segment, row, slice, frame of the chunk to fetch
-    const PixCoord cstep = pix_coord(xr.stride, cd);
-    long long crow = xr.first / segs;        // its image row
-    const long long rstep = xr.stride / segs;
+    // (there are fewer than 2^31 chunks: 64 channels of as many pixels have no room)
+    auto coord = [&](int q) {
+        PixCoord c;
+        c.w = q % segs;
+        q /= segs;
+        c.h = q % d.H;
+        q /= d.H;
+        c.dd = q % d.D;
+        c.t = q / d.D % d.T;
+        return c;
+    };
+    PixCoord cc = coord((int)xr.first);   // segment, row, slice, frame of the chunk to fetch
+    const PixCoord cstep = coord((int)xr.stride);
+    int crow = (int)xr.first / segs;      // its image row
+    const int rstep = (int)xr.stride / segs;
     const float *gbase = a.g, *abase = a.a;
     int w0 = 0, w_end = 0;
     unsigned rows_ok = 0u, ok = 0u;
@@ -92,7 +103,7 @@ __global__ __launch_bounds__(512) void wgrad_cover_kernel(WgradArgs a, float* bi
             const int at = d.kt == 3 ? cc.t : d.kd == 3 ? cc.dd : cc.h, n = d.kt == 3 ? d.T : d.kd == 3 ? d.D : d.H;
             rows_ok = (at > 0 ? 1u : 0u) | 2u | (at + 1 < n ? 4u : 0u);
             w0 = cc.w * kPx;
-            const long long q0 = crow * d.W + w0;
+            const long long q0 = (long long)crow * d.W + w0;
             gbase = a.g + q0 * a.Co;
             abase = a.a + q0 * a.Ci;
             crow += rstep + (cc.w + cstep.w >= segs ? 1 : 0);
@@ -142,8 +153,8 @@ __global__ __launch_bounds__(512) void wgrad_cover_kernel(WgradArgs a, float* bi
         }
         __syncthreads();
         int at = 0;
+        next(xr.first + xr.stride < xr.end);
         for (long long chunk = xr.first; chunk < xr.end; chunk += xr.stride) {
-            next(chunk + xr.stride < xr.end);
             float* const buf = smem + at;
             at = kSlab - at;
             float* const other = smem + at;
@@ -152,8 +163,9 @@ __global__ __launch_bounds__(512) void wgrad_cover_kernel(WgradArgs a, float* bi
             for (int s = 0; s < kPx / 2; ++s) {
                 step(buf, s);
                 if (s < kSlotsG + kSlotsA) fetch(s);
-                stash(other, s - (kPx / 2 - kSlotsG - kSlotsA));
+                stash(other, s - kPx / 4);
             }
+            next(chunk + 2 * xr.stride < xr.end);   // (under the last matrix instructions)
             __syncthreads();
         }
     };
