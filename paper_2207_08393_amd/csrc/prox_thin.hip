@@ -549,17 +549,23 @@ hipError_t launch_conv_thin_out_mfma(const void* in, const float* wts, const flo
 // 32-pixel column segments on its own.  The kernel it replaces for these shapes computes on the vector ALUs,
 // 2*taps multiply-adds per output.
 
-template <int KD, int NB, int NH, bool BF, bool EPI>   // EPI: the call has a ReLU mask source or an add operand
+//
+// ANY: Nn channels, a multiple of 4 up to 32 * NB * NH; those behind it are computed with channel 0's weights and not stored.  The
+// sums are the bits of conv_thin_in_kernel: they begin at the bias and take the taps in their order. 2 -> 20 channels, 3x3x3, 1507328
+// pixels: 246 us on the vector ALUs, which issued twice the instructions of the products alone; what bounds it now: a row's loads and
+// stores, one after the other in a wave (2 -> 100 channels at 4 x 320 x 256: 131 MB in 59 us, as before).
+template <int KD, int NB, int NH, bool BF, bool EPI, bool ANY>   // EPI: the call has a ReLU mask source or an add operand
 __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a, int runs, int run_len) {
     // NH passes of NB blocks of 32 output channels each: Nn = 32 * NB * NH
     static_assert(KD == 1 || KD == 3, "the walk keeps KD slices of three rows");
-    constexpr int TAPS = 9 * KD, NP = 32 * NB, NN = NP * NH, SS = NP + 4;   // SS: floats per pixel row of the wave's LDS rows
+    constexpr int TAPS = 9 * KD, NP = 32 * NB, SS = NP + 4;   // SS: floats per pixel row of the wave's LDS rows
     __shared__ __attribute__((aligned(16))) float stage_all[4 * 32 * SS];
     const PixDims d = a.d;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 31, h = lane >> 5;
     float* stage = stage_all + wave * 32 * SS;
+    const int NN = ANY ? a.Nn : NP * NH;
     float wreg[NH][NB][TAPS];
 #pragma unroll
     for (int hb = 0; hb < NH; ++hb)
@@ -567,7 +573,7 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int t = 0; t < TAPS; ++t)
-                wreg[hb][nb][t] = a.w[(NP * hb + 32 * nb + m) * a.sn + (a.flip ? TAPS - 1 - t : t) * a.st + h * a.sk];
+                wreg[hb][nb][t] = a.w[(!ANY || NP * hb + 32 * nb + m < NN ? NP * hb + 32 * nb + m : 0) * a.sn + (a.flip ? TAPS - 1 - t : t) * a.st + h * a.sk];
     // A wave walks down the rows of one 32-pixel column segment of one slice: of the 9 KD input values a row needs (KD
     // slices x three rows x three columns) those of the two upper rows are the previous row's, so a row costs 3 KD loads,
     // and all of its addresses are a wave-uniform row pointer plus a lane constant.  Item = (slice of an image, segment,
@@ -611,8 +617,8 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
     };
     const int in_floor_i = a.relu_in ? 0 : (int)0x80000000;
     const float out_floor = a.relu_out ? 0.f : -__builtin_huge_valf();
-    __shared__ __attribute__((aligned(16))) float bias_s[NN];
-    if ((int)threadIdx.x < NN) bias_s[threadIdx.x] = a.bias ? a.bias[threadIdx.x] : 0.f;
+    __shared__ __attribute__((aligned(16))) float bias_s[NP * NH];
+    if ((int)threadIdx.x < NP * NH) bias_s[threadIdx.x] = a.bias && (int)threadIdx.x < NN ? a.bias[threadIdx.x] : 0.f;
     __syncthreads();
     for (long long item = first; item < n_items; item += step) {
         // segments fastest: the four waves of a workgroup walk down neighbouring segments of the same rows
@@ -660,7 +666,8 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
                     const unsigned f = __builtin_amdgcn_raw_buffer_load_b32(r_in, col_off[ix], row, 0);
                     // (ReLU as a signed-integer maximum: negative floats are negative integers)
                     const int fi = (int)(f & (row_mask & col_ok[ix]));
-                    v[iz][slot][ix] = __int_as_float(fi > in_floor_i ? fi : in_floor_i);
+                    if constexpr (ANY) v[iz][slot][ix] = a.relu_in ? fmaxf(__int_as_float(fi), 0.f) : __int_as_float(fi);   // (no NaN is kept)
+                    else v[iz][slot][ix] = __int_as_float(fi > in_floor_i ? fi : in_floor_i);
                 }
             }
         };
@@ -684,14 +691,23 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
                         addq[u] = load_piece(r_add, oo_item[u], rb);
                     }
                 }
+                if constexpr (ANY) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const float4 b = *reinterpret_cast<const float4*>(bias_s + NP * hb + 32 * nb + 8 * g + 4 * h);
+                            acc[nb][4 * g] = b.x; acc[nb][4 * g + 1] = b.y; acc[nb][4 * g + 2] = b.z; acc[nb][4 * g + 3] = b.w;
+                        }
+                }
                 // row taps in the order upper, middle, lower: the lower row's values are the ones just requested
 #pragma unroll
                 for (int k = 0; k < TAPS; ++k) {
-                    const int iy = k / (3 * KD), iz = (k / 3) % KD, ix = k % 3, t = 9 * iz + 3 * iy + ix;
+                    const int iy = ANY ? k / 3 % 3 : k / (3 * KD), iz = ANY ? k / 9 : (k / 3) % KD, ix = k % 3, t = 9 * iz + 3 * iy + ix;
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         floatx16 c;
-                        if (k == 0) {
+                        if (!ANY && k == 0) {
 #pragma unroll
                             for (int r = 0; r < 16; ++r) c[r] = 0.f;
                         } else {
@@ -721,7 +737,7 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
                     for (int u = 0; u < UN; ++u) {
                         const int j = (p0 + u) * 64 + lane;
                         const int px = j / (NP / 4), cq = j - px * (NP / 4);
-                        okk[u] = okk_item[p0 + u];
+                        okk[u] = okk_item[p0 + u] && (!ANY || NP * hb + 4 * cq < NN);
                         oo[u] = oo_item[p0 + u];
                         accv[u] = *reinterpret_cast<const float4*>(stage + px * SS + 4 * cq);
                         refv[u] = make_float4(1.f, 1.f, 1.f, 1.f);
@@ -737,13 +753,15 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
                     for (int u = 0; u < UN; ++u) {
                         const int j = (p0 + u) * 64 + lane;
                         const int co = NP * hb + 4 * (j % (NP / 4));
-                        const float4 bv = *reinterpret_cast<const float4*>(bias_s + co);
-                        float xv[4] = {accv[u].x + bv.x, accv[u].y + bv.y, accv[u].z + bv.z, accv[u].w + bv.w};
+                        const float4 bv = ANY ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4*>(bias_s + co);
+                        float xv[4] = {accv[u].x, accv[u].y, accv[u].z, accv[u].w};
+                        if constexpr (!ANY) { xv[0] += bv.x; xv[1] += bv.y; xv[2] += bv.z; xv[3] += bv.w; }
                         const float rr[4] = {refv[u].x, refv[u].y, refv[u].z, refv[u].w};
                         const float aa[4] = {addv[u].x, addv[u].y, addv[u].z, addv[u].w};
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            xv[e] = fmaxf(xv[e], out_floor);
+                            if constexpr (ANY) xv[e] = a.relu_out ? fmaxf(xv[e], 0.f) : xv[e];
+                            else xv[e] = fmaxf(xv[e], out_floor);
                             if constexpr (EPI) {
                                 if (a.mask_acc) xv[e] = rr[e] > 0.f ? xv[e] : 0.f;
                                 xv[e] += (a.mask_add && !(rr[e] > 0.f)) ? 0.f : aa[e];
@@ -757,6 +775,8 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
                                 typedef float f32x4 __attribute__((ext_vector_type(4)));
                                 const f32x4 pk = {xv[0], xv[1], xv[2], xv[3]};
                                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned, pk), r_out, oo[u], row_byte, 0);
+                                // (the data registers of a store of 16 bytes with a scalar offset stay in use for one instruction more)
+                                asm volatile("s_nop 0" : : "v"(pk) : "memory");
                             }
                         }
                     }
@@ -776,11 +796,11 @@ __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a
     }
 }
 
-template <int KD, int NB, int NH, bool BF, bool EPI>
+template <int KD, int NB, int NH, bool BF, bool EPI, bool ANY>
 static void launch_thin_in_mfma_e(const ThinInMfmaArgs& a, hipStream_t st) {
     static const int per_cu = [] {   // persistent waves: what the instantiation's registers allow, at most four workgroups
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, conv_thin_in_mfma_kernel<KD, NB, NH, BF, EPI>, 256, 0) != hipSuccess) n = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, conv_thin_in_mfma_kernel<KD, NB, NH, BF, EPI, ANY>, 256, 0) != hipSuccess) n = 1;
         return n < 1 ? 1 : (n > 4 ? 4 : n);
     }();
     // runs of rows per (slice, segment) column: the split that minimises (columns per wave) x (run length + the two rows a
@@ -797,22 +817,24 @@ static void launch_thin_in_mfma_e(const ThinInMfmaArgs& a, hipStream_t st) {
     }
     const long long n_items = cols * runs;
     const long long want = (n_items + 3) / 4, cap = 256LL * per_cu;
-    hipLaunchKernelGGL((conv_thin_in_mfma_kernel<KD, NB, NH, BF, EPI>), dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0, st, a, runs, run_len);
+    hipLaunchKernelGGL((conv_thin_in_mfma_kernel<KD, NB, NH, BF, EPI, ANY>), dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0, st, a, runs, run_len);
 }
 
-template <int KD, int NB, int NH, bool BF>
+template <int KD, int NB, int NH, bool BF, bool ANY>
 static void launch_thin_in_mfma_t(const ThinInMfmaArgs& a, hipStream_t st) {
-    if (a.mask_ref || a.add) launch_thin_in_mfma_e<KD, NB, NH, BF, true>(a, st);
-    else launch_thin_in_mfma_e<KD, NB, NH, BF, false>(a, st);
+    if (a.mask_ref || a.add) launch_thin_in_mfma_e<KD, NB, NH, BF, true, ANY>(a, st);
+    else launch_thin_in_mfma_e<KD, NB, NH, BF, false, ANY>(a, st);
 }
 
 template <int KD, bool BF>
 static void launch_thin_in_mfma_n(const ThinInMfmaArgs& a, hipStream_t st) {
-    switch (a.Nn / 32) {
-        case 1: launch_thin_in_mfma_t<KD, 1, 1, BF>(a, st); break;
-        case 2: launch_thin_in_mfma_t<KD, 2, 1, BF>(a, st); break;
-        default: launch_thin_in_mfma_t<KD, 2, 2, BF>(a, st); break;
-    }
+    if (a.Nn == 32) launch_thin_in_mfma_t<KD, 1, 1, BF, false>(a, st);
+    else if (a.Nn == 64) launch_thin_in_mfma_t<KD, 2, 1, BF, false>(a, st);
+    else if (a.Nn == 128) launch_thin_in_mfma_t<KD, 2, 2, BF, false>(a, st);
+    else if (a.Nn < 32) launch_thin_in_mfma_t<KD, 1, 1, BF, true>(a, st);
+    else if (a.Nn < 64) launch_thin_in_mfma_t<KD, 2, 1, BF, true>(a, st);
+    else if (a.Nn <= 96) launch_thin_in_mfma_t<KD, 1, 3, BF, true>(a, st);
+    else launch_thin_in_mfma_t<KD, 2, 2, BF, true>(a, st);
 }
 
 bool conv_thin_in_mfma_applies(const PixDims& d, int Nn) {
@@ -820,7 +842,12 @@ bool conv_thin_in_mfma_applies(const PixDims& d, int Nn) {
     if (!on || !(d.kt == 1 && (d.kd == 3 || d.kd == 1) && d.kh == 3 && d.kw == 3)) return false;
     // byte offsets into the input and the output are 32 bits in the kernel
     if ((double)d.Q * 8.0 >= 4.0e9 || (double)d.Q * Nn * 4.0 >= 4.0e9) return false;
-    return Nn == 32 || Nn == 64 || Nn == 128;
+    if (Nn == 32 || Nn == 64 || Nn == 128) return true;
+    // Fewer pixels: the row after row of a wave takes longer than the vector kernel (a training step of 8, 36, 48 and 96 channels, us, vector /
+    // here: 480 pixels 92.4 / 92.8, 110.7 / 112.0, 104.7 / 106.7, 132.9 / 137.7; 4096 93.9 / 93.8, 118.4 / 119.6, 112.8 / 114.9,
+    // 163.0 / 161.8; 20480 110.6 / 107.9, 169.4 / 164.9, 167.3 / 161.7, 255.6 / 237.7; 122880 155.9 / 152.0, 338.7 / 334.7,
+    // 362.4 / 356.0, 716.6 / 697.3).
+    return d.Q >= 8192 && Nn % 4 == 0 && Nn >= 8 && Nn <= 128;
 }
 
 hipError_t launch_conv_thin_in_mfma(const ThinInMfmaArgs& a, bool bf, hipStream_t st) {
