@@ -1060,7 +1060,7 @@ static hipError_t launch_conv_thin_out(const ConvArgs& a, const ConvWeights& cw,
 // split operands take them.
 static hipError_t launch_conv(ConvArgs a, const ConvWeights& cw, float* wt, bool split, WeightBatch* collect, hipStream_t st) {
     const int taps_ = a.d.kt * a.d.kd * a.d.kh * a.d.kw;
-    {   // two input channels and a wide output: HBM-bound kernels (matrix cores for 3x3x3 taps, vector ALUs otherwise)
+    {   // two input channels and a wide output: HBM-bound kernels (matrix cores or vector ALUs)
         if (collect && conv_thin_in_applies(a.d, a.K, a.Nn)) return hipSuccess;   // reads theta itself
         bool hit = false;
         const hipError_t e = launch_conv_thin_in(a, cw, false, &hit, st);
@@ -1417,25 +1417,56 @@ __global__ __launch_bounds__(NW * 64) void wgrad_pipe_kernel(WgradPipeArgs pa) {
         const long long next = chunk + xr.stride;
         if (next < xr.end) fetch();
         if (active) {
-            // software pipeline over the 2-pixel K-steps: operands of step s+1 are read from LDS
-            // before the MFMAs of step s are issued
-            float av = gs[a_off];
-            float bv[JT];
+            // software pipeline over the 2-pixel K-steps: operands are read from LDS before the MFMAs of the steps ahead of them
+            // are issued
+            if constexpr (!BAL && JT < 9) {
+                // AH steps at a time (the scheduler, left alone, moves the reads back to where they are needed; 12 -> 12 channels,
+                // nine jobs of one tap: five greedy modules at 122880 pixels 1316 -> 1269 us)
+                constexpr int AH = JT == 1 ? 4 : JT <= 3 ? 2 : 1, GROUPS = kWgTM / 2 / AH;
+                float av[2][AH], bv[2][AH][JT];
+                auto read = [&](int set, int g) {
 #pragma unroll
-            for (int j = 0; j < JT; ++j) bv[j] = as[b_off[j]];
+                    for (int e = 0; e < AH; ++e) {
+                        av[set][e] = gs[a_off + 2 * (g * AH + e) * RSg];
+#pragma unroll
+                        for (int j = 0; j < JT; ++j) bv[set][e][j] = as[b_off[j] + 2 * (g * AH + e) * RSa];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                auto multiply = [&](int set) {
+#pragma unroll
+                    for (int e = 0; e < AH; ++e)
+#pragma unroll
+                        for (int j = 0; j < JT; ++j)
+                            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[set][e], bv[set][e][j], acc[j], 0, 0, 0);
+                };
+                read(0, 0);
+#pragma unroll 1
+                for (int g = 0; g < GROUPS; g += 2) {
+                    read(1, g + 1);
+                    multiply(0);
+                    read(0, g + 2 < GROUPS ? g + 2 : g);
+                    multiply(1);
+                }
+            } else {   // nine taps have no registers for that, balanced runs were 1 % slower with it
+                float av = gs[a_off];
+                float bv[JT];
+#pragma unroll
+                for (int j = 0; j < JT; ++j) bv[j] = as[b_off[j]];
 #pragma unroll 2
-            for (int s = 0; s < kWgTM / 2; ++s) {
-                const int sn = s + 1 < kWgTM / 2 ? s + 1 : s;
-                const float av_n = gs[a_off + 2 * sn * RSg];
-                float bv_n[JT];
+                for (int s = 0; s < kWgTM / 2; ++s) {
+                    const int sn = s + 1 < kWgTM / 2 ? s + 1 : s;
+                    const float av_n = gs[a_off + 2 * sn * RSg];
+                    float bv_n[JT];
 #pragma unroll
-                for (int j = 0; j < JT; ++j) bv_n[j] = as[b_off[j] + 2 * sn * RSa];
+                    for (int j = 0; j < JT; ++j) bv_n[j] = as[b_off[j] + 2 * sn * RSa];
 #pragma unroll
-                for (int j = 0; j < JT; ++j)
-                    if (!BAL || j < JT - 1 || n_my == JT) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv[j], acc[j], 0, 0, 0);
-                av = av_n;
+                    for (int j = 0; j < JT; ++j)
+                        if (!BAL || j < JT - 1 || n_my == JT) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv[j], acc[j], 0, 0, 0);
+                    av = av_n;
 #pragma unroll
-                for (int j = 0; j < JT; ++j) bv[j] = bv_n[j];
+                    for (int j = 0; j < JT; ++j) bv[j] = bv_n[j];
+                }
             }
         }
         __syncthreads();

@@ -11,7 +11,7 @@
 // of fixed length make every LDS address a register and a constant, and the operands of a step are read during the one before.
 // 100 -> 100 channels at 4 x 320 x 256: 536 us, 110 TFLOP/s; 750 us with one chunk in LDS between two barriers, operands read
 // where they were needed (the compiler had moved the reads back) and the LDS addresses of every step computed.  What bounds it: the
-// matrix cores, 0.75 of the time.
+// matrix cores, 0.70 of the time.
 //
 // Both instructions add their products with fused multiply-adds in the order of the pixels: the sums are the same bits as
 // those of wgrad_pipe_kernel with as many workgroups.
