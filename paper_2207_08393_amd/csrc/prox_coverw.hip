@@ -3,7 +3,7 @@
 // The gradient is a matrix of Co rows and 9 * Ci columns.  Two workgroups of eight waves share it: a wave takes the F = Co / 32 whole
 // blocks of 32 rows in 6 / F blocks of 32 columns, across the borders of the taps, and so reads F + 6 / F operands for six matrix
 // instructions; what is left of rows and columns goes by 4 x 4 blocks, sixteen to a v_mfma_f32_4x4x1_f32 (as many multiply-adds a
-// cycle), kCoverQuads of those to a wave.  100 -> 100 channels: 84 blocks in 14 waves and 249 small ones in two.
+// cycle), kQuads of those to a wave.  100 -> 100 channels: 84 blocks in 14 waves and 249 small ones in two.
 //
 // A chunk is a segment of 32 pixels of an image row, staged as float4; pixels past the end of the row get g = 0, and taps outside the
 // image are stored as 0, so the matrix instructions need no masks.  Two chunks lie in LDS: while one is multiplied the next is
@@ -287,15 +287,18 @@ bool wgrad_cover_applies(const PixDims& d, int Co, int Ci) {
            CoverSplit(Co, 9 * Ci).waves() <= 16 && Co <= 128 && 3 * (kPx + 2) * (Ci / 4) <= 512 * kSlotsA;
 }
 
-hipError_t launch_wgrad_cover(const WgradArgs& a, float* bias_partial, int n_split, hipStream_t st) {
+// (a function per kernel: each has to be allowed its LDS)
+template <int F>
+static hipError_t launch_wgrad_cover_t(const WgradArgs& a, float* bias_partial, int n_split, hipStream_t st) {
     constexpr size_t lds = 2 * kSlab * sizeof(float);   // 118656 bytes: a workgroup per CU
-    auto go = [&](auto kern) {
-        static const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(n_split, 2), dim3(512), lds, st, a, bias_partial);
-        return hipGetLastError();
-    };
-    return a.Co / 32 == 2 ? go(wgrad_cover_kernel<2>) : go(wgrad_cover_kernel<3>);
+    static const hipError_t e = hipFuncSetAttribute((const void*)wgrad_cover_kernel<F>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(wgrad_cover_kernel<F>, dim3(n_split, 2), dim3(512), lds, st, a, bias_partial);
+    return hipGetLastError();
+}
+
+hipError_t launch_wgrad_cover(const WgradArgs& a, float* bias_partial, int n_split, hipStream_t st) {
+    return a.Co / 32 == 2 ? launch_wgrad_cover_t<2>(a, bias_partial, n_split, st) : launch_wgrad_cover_t<3>(a, bias_partial, n_split, st);
 }
 
 }  // namespace gleam

@@ -208,10 +208,18 @@ bool conv_time_split_applies(const PixDims& d, int K, int Nn) {
 size_t conv_time_split_weight_floats(int K, int Nn) { return (size_t)((Nn + 31) / 32) * 9 * time_split_chunks(K) * 64 * 4; }
 int conv_time_split_chunks(int K) { return time_split_chunks(K); }
 
+// (a function per kernel: each has to be allowed more than 64 KB of LDS)
+template <int NKC, bool EPI>
+static hipError_t launch_conv_time_split_e(const TimeSplitArgs& a, dim3 grid, size_t lds, hipStream_t st) {
+    static const hipError_t e = hipFuncSetAttribute((const void*)conv_time_split_kernel<NKC, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((conv_time_split_kernel<NKC, EPI>), grid, dim3(256), lds, st, a);
+    return hipGetLastError();
+}
+
 template <int NKC>
-static void launch_conv_time_split_t(const TimeSplitArgs& a, dim3 grid, size_t lds, hipStream_t st) {
-    if (a.mask_ref || a.add) hipLaunchKernelGGL((conv_time_split_kernel<NKC, true>), grid, dim3(256), lds, st, a);
-    else hipLaunchKernelGGL((conv_time_split_kernel<NKC, false>), grid, dim3(256), lds, st, a);
+static hipError_t launch_conv_time_split_t(const TimeSplitArgs& a, dim3 grid, size_t lds, hipStream_t st) {
+    return a.mask_ref || a.add ? launch_conv_time_split_e<NKC, true>(a, grid, lds, st) : launch_conv_time_split_e<NKC, false>(a, grid, lds, st);
 }
 
 hipError_t launch_conv_time_split(TimeSplitArgs a, const PixDims& d, hipStream_t st) {
@@ -230,14 +238,13 @@ hipError_t launch_conv_time_split(TimeSplitArgs a, const PixDims& d, hipStream_t
     const size_t lds = (size_t)a.NB * 9 * nkc * 1024;
     const dim3 grid((unsigned)(a.n_items < cap ? a.n_items : cap), (unsigned)ny);
     switch (nkc) {
-        case 1: launch_conv_time_split_t<1>(a, grid, lds, st); break;
-        case 2: launch_conv_time_split_t<2>(a, grid, lds, st); break;
-        case 3: launch_conv_time_split_t<3>(a, grid, lds, st); break;
-        case 4: launch_conv_time_split_t<4>(a, grid, lds, st); break;
-        case 6: launch_conv_time_split_t<6>(a, grid, lds, st); break;
-        default: launch_conv_time_split_t<8>(a, grid, lds, st); break;
+        case 1: return launch_conv_time_split_t<1>(a, grid, lds, st);
+        case 2: return launch_conv_time_split_t<2>(a, grid, lds, st);
+        case 3: return launch_conv_time_split_t<3>(a, grid, lds, st);
+        case 4: return launch_conv_time_split_t<4>(a, grid, lds, st);
+        case 6: return launch_conv_time_split_t<6>(a, grid, lds, st);
+        default: return launch_conv_time_split_t<8>(a, grid, lds, st);
     }
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------------------------
