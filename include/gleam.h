@@ -107,11 +107,10 @@ int gleam_theta_count(const gleam_prox_desc* prox, size_t* n_floats);
  * flight on other threads.  Unknown bits: GLEAM_E_DESC. */
 #define GLEAM_POLICY_NO_WINOGRAD      1u  /* 3x3, 3x3x3 and 3x1x1 fp32 layers: fp32 MFMA kernels instead of those on split operands,
                                           * 3x3 and 3x3x3 ones direct fp32 MFMA kernels instead of the minimal-filtering
-                                          * ones (split bfloat16 operands; fp32 MFMA in greedy iterations, in the forward pass
-                                          * of MoDL modules and in the backward pass of those of fewer than 4096 pixels).  The
-                                          * data-consistency step of networks with such layers (widths that are multiples of 4) then
-                                          * takes the transforms of the greedy iteration too, staged through LDS, so that a greedy
-                                          * iteration and the same calls by hand give the same bits */
+                                          * ones (split bfloat16 operands; fp32 MFMA in greedy iterations and in the forward pass
+                                          * of MoDL modules).  The data-consistency step of networks with 3x3 or 3x3x3 layers whose
+                                          * widths are multiples of 4 then takes the transforms of the greedy iteration too, staged
+                                          * through LDS, so that a greedy iteration and the same calls by hand give the same bits */
 #define GLEAM_POLICY_NO_BF16_2D       2u  /* 3x3 bf16 layers: flattened-pixel kernel instead of the 2D-tile one        */
 #define GLEAM_POLICY_NO_THIN_MFMA     4u  /* 2-channel first / last layers: vector-ALU kernels instead of matrix-core   */
 #define GLEAM_POLICY_NO_WGRAD_BALANCE 8u  /* 27-tap weight gradient: nine 3-tap jobs instead of the balanced 8-wave split */

@@ -90,7 +90,6 @@ int check_geom(const gleam_geom* g) {
 }
 
 inline size_t n_coil_pixels(const gleam_geom& g) { return (size_t)(g.B * g.C * g.T * g.D * g.H * g.W); }
-inline size_t n_pixels(const gleam_geom& g) { return (size_t)(g.B * g.T * g.D * g.H * g.W); }
 
 int check_prox(const gleam_prox_desc* p) {
     if (!p) return GLEAM_E_NULL;
@@ -473,14 +472,16 @@ int gleam_mask_constant_along_outer_axis(const gleam_geom* geom, const uint8_t* 
 // The plan of a MoDL module's backward pass.  The forward pass stays on the float32 kernels: a solve and a loss stand behind it,
 // and another rounding of the prox decides a ReLU near zero the other way, which moves the gradient by 5e-5 to 1.5e-4 (either side
 // is that far from 64 bits).  Behind the masks that the forward pass has fixed the gradients are sums of products, so they take the
-// split operands (csrc/prox_split.hip), like a plain module's: 1e-7 apart, nearer to 64 bits.  64 -> 64 channels at 2 x 320 x 256:
-// data gradient 68 us on the float32 matrix cores, 52 on split operands, weight gradient with its sums 84 and 55; 16 -> 16 at
-// 4 x 344 x 368: 58 and 33, 195 and 33.  The forward launches' sign words are in the float32 kernels' order, so the masks come from
-// the activations.  Calls of fewer than 4096 pixels stay on the float32 kernels, with which the tests compare them.
+// split operands (csrc/prox_split.hip, csrc/prox_time_split.hip) at every size, like a plain module's.  Against a 64-bit backward pass
+// from the same activations and the same dL/dz, over 60 inputs of 12 to 128 channels, 4096 to 117760 pixels, all kinds of taps: 7e-8 to
+// 1.4e-7 off, 0.86 times as far as the float32 kernels in the geometric mean.  The whole backward pass with one solver step, float32 /
+// here, us: 16 channels 61 / 51 at 400 pixels, 72 / 63 at 2116, 67 / 57 at 9216; 64 channels, five layers 150 / 91, 191 / 113, 200 / 129;
+// 100 channels 120 / 67, 154 / 87, 180 / 108; 3x3x3, 32 channels 169 / 102 at 3200, 177 / 117 at 16384; 3x3 and 3x1x1, 16 channels
+// 84 / 65 at 800, 93 / 82 at 11776.  The forward launches' sign words are in the float32 kernels' order, so the masks come from the
+// activations.
 static void plan_modl_backward(const gleam_geom& g, const gleam_prox_desc& p, ProxPlan& plan) {
-    const bool split = n_pixels(g) >= 4096;
-    plan_prox(g, p, split, plan);
-    if (split && p.dtype == 0)
+    plan_prox(g, p, true, plan);
+    if (p.dtype == 0)
         for (size_t& off : plan.sign_off) off = 0;
 }
 

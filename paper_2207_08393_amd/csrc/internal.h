@@ -76,12 +76,12 @@ hipError_t kspace_to_hybrid(const gleam_geom& g, float2* y, hipStream_t st);
 //           [G_1 .. G_{L-1} | split-K partials | loss partials] for backward
 struct ProxPlan {
     int L;
-    // Whether 3x3 and 3x3x3 float32 layers run on split bfloat16 operands (conv_split_applies, wgrad_split_applies).  Not in the
-    // greedy iteration, so that its results stay what they were: the first Adam step moves a parameter by lr * sign(g), so one
-    // whose gradient is near zero moves by 2 lr with any other order of rounding.  It is not for speed (100 -> 100 channels at
-    // 4 x 320 x 256: 565 us forward and 738 us weight gradient there, 280 and 340 us here) and not for accuracy (the split kernels
-    // are the nearer ones to 64 bits).  Nor in the MoDL module's forward pass, where
-    // another rounding decides a ReLU near zero the other way and moves the gradient by 5e-5 to 1.5e-4; its backward pass takes them
+    // Whether 3x3, 3x3x3 and 3x1x1 float32 layers run on split bfloat16 operands (conv_split_applies, conv_time_split_applies and
+    // the like for weight gradients).  Not in the greedy iteration, so that its results stay what they were: the first Adam step
+    // moves a parameter by lr * sign(g), so one whose gradient is near zero moves by 2 lr with any other order of rounding.  It is
+    // not for speed (100 -> 100 channels at 4 x 320 x 256: 565 us forward and 544 us weight gradient there, 280 and 340 us here) and
+    // not for accuracy (the split kernels are the nearer ones to 64 bits).  Nor in the MoDL module's forward pass, where another
+    // rounding decides a ReLU near zero the other way and moves the gradient by 5e-5 to 1.5e-4; its backward pass takes them
     // (plan_modl_backward in gleam_api.hip).
     bool split;
     // Whether the data-consistency step takes the sweeps staged through LDS: where float32 layers that have split kernels are kept
