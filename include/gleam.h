@@ -151,9 +151,11 @@ int gleam_sense_normal_static(const gleam_geom* geom, const gleam_c64* x, const 
  *   loss   : device float32 scalar, overwritten with L(x_out, x_ref) (Eq. 10).
  *   x_out  : image, overwritten; must not alias x_in.  Passing it as the next module's x_in is the
  *            detached hand-off between modules.
- * Range: float32 3x3 and 3x3x3 layers whose widths are multiples of 4 take inputs of up to 1.69e38, half the float32 range.
- * What overflows there, and an infinity that gets through the layer's own ReLU, comes out as infinity or NaN (also in the pixel
- * beside the ones it reaches) and passes the ReLUs behind it. */
+ * Range: float32 3x3 and 3x3x3 layers whose widths are multiples of 4 take inputs of up to 1.69e38, half the float32 range, and
+ * 3x1x1 layers of such widths with up to 128 input channels inputs of up to 3.39e38, all but its top.  What overflows there, and an
+ * infinity that gets through the layer's own ReLU, comes out as infinity or NaN (3x3 and 3x3x3: also in the pixel beside the ones it
+ * reaches) and passes the ReLUs behind it.  Inputs or weights below about 1e-31 are kept to 1e-38, and products of the two below about
+ * 5e-29 lose bits. */
 int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox,
                      const gleam_c64* x_in, const gleam_c64* S, const uint8_t* M, const gleam_c64* y,
                      float alpha, const float* theta, const gleam_c64* x_ref,
@@ -163,9 +165,9 @@ int gleam_module_fwd(const gleam_geom* geom, const gleam_prox_desc* prox,
 /* Backward pass of the same module: grad_theta = d loss / d theta (Alg. 1, gradient step), overwritten.
  * Consumes `saved` of the matching gleam_module_fwd call (same geom / prox / theta).  No gradient is
  * produced for x_in, S or y: modules are decoupled and the data-consistency step is not differentiated.
- * Range: the weight gradient of float32 3x3 and 3x3x3 layers whose widths are multiples of 4 takes activations and output gradients
- * of the same range as gleam_module_fwd; what they overflow and an infinity come out as infinity or NaN.  Output gradients
- * below about 1e-28 (at activations of order one) lose bits, at 1e-31 about 1e-5 of the value. */
+ * Range: float32 3x3, 3x3x3 and 3x1x1 layers whose widths are multiples of 4 take activations and output gradients of the same range
+ * as gleam_module_fwd; what they overflow and an infinity come out as infinity or NaN.  Output gradients below about 1e-28 (at
+ * activations or weights of order one) lose bits, at 1e-31 about 1e-5 of the value. */
 int gleam_module_bwd(const gleam_geom* geom, const gleam_prox_desc* prox, const float* theta,
                      const void* saved, size_t saved_bytes, float* grad_theta,
                      void* ws, size_t ws_bytes, void* stream);
@@ -232,7 +234,8 @@ int gleam_mask_constant_along_outer_axis(const gleam_geom* geom, const uint8_t* 
  * recurrence stay on the device; a sample whose residual is exactly zero stops moving).  With x_ref the local
  * loss (device scalar) is produced and `saved` keeps what the backward pass needs.
  * gleam_modl_module_bwd: dL/dtheta; dL/dz = mu (A^H A + mu I)^-1 dL/dx_out is formed by the same n_cg-step
- * solve, then the prox is swept backwards; nothing is propagated to x_in.
+ * solve, then the prox is swept backwards; nothing is propagated to x_in.  Its convolution kernels, and
+ * so the range of its gradients, are those of gleam_module_bwd.
  *   mu >= 0, n_cg >= 1 (else GLEAM_E_DIMS).  The last prox layer must not end in a ReLU (GLEAM_E_DESC).
  *   saved : as gleam_workspace_bytes reports (written by the backward pass as well).
  *   ws    : gleam_modl_workspace_bytes; x_out must not alias x_in, aty or x_ref. */
@@ -275,12 +278,12 @@ int gleam_adam_step(const gleam_adam* hyper, int64_t t, size_t n, float* theta, 
  * Every module's output is computed with its parameters BEFORE the update.  All modules share the
  * architecture `prox`.  Other arguments as in gleam_module_fwd.
  * The iteration does what gleam_module_fwd, gleam_module_bwd and gleam_adam_step do in turn, to the same bits where a layer
- * has one kernel for both.  Float32 3x3 and 3x3x3 layers whose widths are multiples of 4 have two: the module calls and
- * gleam_unrolled_infer run them on split operands, this call (like a MoDL module's forward pass) on the float32 matrix cores; its
- * data-consistency steps then go through transforms of their own as well, of another order of rounding.  Outputs,
- * losses and first moments then differ by rounding (6e-7 over two modules of 64 channels); a parameter whose gradient is that
- * close to zero can differ by twice the learning rate after Adam's first step.  Under GLEAM_POLICY_NO_WINOGRAD all of it is
- * the same bit for bit, at the speed of the direct kernels. */
+ * has one kernel for both.  Float32 3x3, 3x3x3 and 3x1x1 layers whose widths are multiples of 4 have two: the module calls and
+ * gleam_unrolled_infer run them on split operands, this call (like a MoDL module's forward pass) on the float32 matrix cores; with
+ * 3x3 or 3x3x3 ones its data-consistency steps then go through transforms of their own as well, of another order of rounding.
+ * Outputs, losses and first moments then differ by rounding (two modules of 64 channels: 7e-7 with 3x3 layers, 5e-7 with a 3x1x1 layer
+ * among them or, of 36 channels, throughout); a parameter whose gradient is that close to zero can differ by twice the learning rate
+ * after Adam's first step.  Under GLEAM_POLICY_NO_WINOGRAD all of it is the same bit for bit, at the speed of the direct kernels. */
 int gleam_greedy_iteration(const gleam_geom* geom, const gleam_prox_desc* prox, int n_modules,
                            const gleam_c64* x0, const gleam_c64* S, const uint8_t* M, const gleam_c64* y,
                            float alpha, float* theta, float* adam_m, float* adam_v, const gleam_adam* hyper,
@@ -302,8 +305,8 @@ int gleam_unrolled_infer(const gleam_geom* geom, const gleam_prox_desc* prox, in
  * *n_records receives the number of launches seen.  `flops` / `bytes` are the algorithmic work of the launch
  * (padding and re-reads not counted; a convolution counts 2 * taps * cin * cout per pixel whatever the kernel);
  * `mfma_flops` is what the launch issues on the matrix cores: equal to `flops` for the direct kernels, 4/9 of it
- * for the Winograd F(2x2,3x3) kernels, 4 times it for the split-operand kernels (2/3 of the multiplications, six bfloat16
- * products each).  mfma_flops / time never exceeds the peak of the matrix cores it is issued on: the bfloat16 ones for the
+ * for the Winograd F(2x2,3x3) kernels, 4 times it for the split-operand kernels of 3x3 and 3x3x3 layers (2/3 of the multiplications,
+ * six bfloat16 products each) and 6 times it for those of 3x1x1 layers.  mfma_flops / time never exceeds the peak of the matrix cores it is issued on: the bfloat16 ones for the
  * split-operand kernels and for dtype 1, the float32 ones for the others.
  * Not thread-safe; leave it off in production. */
 typedef struct {

@@ -62,12 +62,13 @@ def test_weights_of_several_modules_at_once(prox):
 
 
 @pytest.mark.parametrize("prox", [synth.resblock_prox(36, 1), synth.chain_prox([2, 9, 7, 2], [K2] * 3), synth.chain_prox([2, 16, 16, 2], [K3] * 3, dtype=1),
-                                  synth.chain_prox([2] + [12] * 17 + [2], [K2] * 18)], ids=["res36", "odd", "bf16_volume", "eighteen_layers"])
+                                  synth.chain_prox([2] + [12] * 17 + [2], [K2] * 18), synth.chain_prox([2, 64, 36, 2], [KS, KT, KS])],
+                         ids=["res36", "odd", "bf16_volume", "eighteen_layers", "time64"])
 def test_greedy_iteration_of_many_modules_and_the_same_calls_by_hand(prox, kernel_policy):
     """Ten modules, more than the eight whose weights of both passes are made at once; eighteen layers, whose two passes take a launch
     each.  Bit for bit the modules one by one, whose weights are made call by call."""
     kernel_policy(gb.POLICY_NO_WINOGRAD)
-    geom = synth.Geom(3, 1, 2, 1, 8, 10, 12) if prox.layers[0].kd == 3 else synth.Geom(2, 1, 2, 1, 1, 20, 46)
+    geom = synth.Geom(3, 1, 2, 1, 8, 10, 12) if prox.layers[0].kd == 3 else synth.Geom(2, 1, 2, 4 if prox.layers[1].kt == 3 else 1, 1, 20, 46)
     c = synth.make_custom(74, geom, prox, accel=2.0, centre=2, bias_std=0.1, alpha=0.5)
     thetas = [(c.theta * np.float32(0.5 + 0.04 * i)).astype(np.float32) for i in range(10)]
     print("case greedy many", [l.cout for l in prox.layers], flush=True)

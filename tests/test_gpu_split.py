@@ -9,7 +9,7 @@ from oracle import gleam_oracle as og
 from paper_2207_08393_amd import binding as gb
 from paper_2207_08393_amd import synth
 from tests.gpu_util import ModuleRunner, assert_grad_close, assert_image_close, rel_l2, theta_slices
-from tests.test_gpu_parity import K2, K3, TOL, check_module, kernel_policy  # noqa: F401
+from tests.test_gpu_parity import K2, K3, KT, TOL, check_module, kernel_policy  # noqa: F401
 from tests.test_split_arithmetic import BOUND
 
 pytestmark = pytest.mark.gpu
@@ -222,22 +222,28 @@ def modules_by_hand(c, thetas, lr):
     return r.results()
 
 
-@pytest.mark.parametrize("nf", [64, 36, 6])
-def test_greedy_iteration_and_the_same_calls_by_hand(nf, kernel_policy):
+@pytest.mark.parametrize("geom,prox,one_kernel", [(synth.Geom(2, 2, 3, 1, 1, 12, 46), synth.resblock_prox(64, 1), False),
+                                                  (synth.Geom(2, 2, 3, 1, 1, 12, 46), synth.resblock_prox(36, 1), False),
+                                                  (synth.Geom(2, 2, 3, 1, 1, 12, 46), synth.resblock_prox(6, 1), True),
+                                                  (synth.Geom(2, 1, 3, 6, 1, 12, 20), time_layers(synth.resblock_prox(64, 1), 2), False),
+                                                  (synth.Geom(2, 1, 3, 6, 1, 12, 20), synth.resblock_prox(36, 1, KT), False),
+                                                  (synth.Geom(2, 1, 3, 6, 1, 12, 20), synth.resblock_prox(6, 1, KT), True)],
+                         ids=["64", "36", "6", "mixed64", "time36", "time6"])
+def test_greedy_iteration_and_the_same_calls_by_hand(geom, prox, one_kernel, kernel_policy):
     """Bit for bit the same where a layer has one kernel for both (6 channels, or GLEAM_POLICY_NO_WINOGRAD).  Otherwise the
     modules by hand run on split operands and the iteration does not: each is within 1e-6 of the 64-bit results in its first
     module (test above, and TOL for the iteration), a second module starts from an input that differs by that much; no further
     apart than 1e-5 in the outputs and the first moments, where no ReLU of these networks is decided the other way."""
     from paper_2207_08393_amd.runner import GreedyRunner
-    c = synth.make_custom(21, synth.Geom(2, 2, 3, 1, 1, 12, 46), synth.resblock_prox(nf, 1), accel=2.0, centre=2, bias_std=0.1, alpha=0.8)
+    c = synth.make_custom(21, geom, prox, accel=2.0, centre=2, bias_std=0.1, alpha=0.8)
     thetas = [c.theta, c.theta + np.float32(0.03) * np.random.default_rng(2).standard_normal(c.theta.size).astype(np.float32)]
     for policy in (0, gb.POLICY_NO_WINOGRAD):
         kernel_policy(policy)
-        print("case greedy by hand", nf, policy, flush=True)
+        print("case greedy by hand", [(l.cout, l.kt) for l in prox.layers], policy, flush=True)
         r = GreedyRunner(c, thetas, 1e-3)
         r.iteration(1)
         whole, parts = r.results(), modules_by_hand(c, thetas, 1e-3)
-        if policy or nf == 6:
+        if policy or one_kernel:
             assert all(np.array_equal(a, b) for a, b in zip(whole, parts))
             continue
         x, losses, _, m, _ = whole
@@ -285,13 +291,17 @@ def test_blocks_inside_the_image(geom, prox):
     check_module(synth.make_custom(53, geom, prox, accel=2.0, centre=2, bias_std=0.1, alpha=0.8))
 
 
-@pytest.mark.parametrize("geom,k", [(synth.Geom(2, 1, 2, 1, 1, 20, 46), K2), (synth.Geom(3, 1, 2, 1, 8, 20, 46), K3)], ids=["2d", "3d"])
-def test_range_of_the_weight_gradient(geom, k):
+@pytest.mark.parametrize("geom,k,modl", [(synth.Geom(2, 1, 2, 1, 1, 20, 46), K2, False), (synth.Geom(3, 1, 2, 1, 8, 20, 46), K3, False),
+                                         (synth.Geom(2, 1, 2, 6, 1, 10, 20), KT, False), (synth.Geom(2, 1, 2, 1, 1, 20, 46), K2, True),
+                                         (synth.Geom(2, 1, 2, 6, 1, 10, 20), KT, True)], ids=["2d", "3d", "time", "modl_2d", "modl_time"])
+def test_range_of_the_weight_gradient(geom, k, modl):
     """What lies below 2^-126 of an operand's parts and of their products is lost (csrc/split.h).  As in test_gpu_cover.py the gradient
     of layer 2 is one product per value, so scaling the weights of layer 3 by a power of two scales it exactly, and the weight
     gradient of layer 2 with it, but for that loss.  A product has six partial products of up to eight multiplied bits each whose
     smallest are 2^-126 when it is 2^-102: 6 * 8 losses of 2^-126 against values of 2^a .. 2^(a + 2), activations of order one (44 to
-    56 seen where it is more than the rounding of the result).  Nothing down to 2^-94 = 5e-29.  An infinity shows."""
+    56 seen where it is more than the rounding of the result).  Nothing down to 2^-94 = 5e-29.  An infinity shows.
+    In a MoDL module dL/dz is that of the loss divided by 1 + (A^H A) / mu, here within a tenth of one: half the values at most."""
+    from paper_2207_08393_amd.runner import ModlRunner
     taps, n = int(np.prod(k)), 32
     rng = np.random.default_rng(5)
     shape = geom.image_shape
@@ -307,20 +317,21 @@ def test_range_of_the_weight_gradient(geom, k):
         w3[np.arange(n) % 2, np.arange(n) * 5 % taps, np.arange(n)] = np.random.default_rng(6).uniform(1, 2, n)
         w3 *= 2.0 ** (a - np.floor(np.log2(g_z)))
         theta = np.concatenate([v.ravel() for v in (w1, b1, w2, b2, w3, np.zeros(2))]).astype(np.float32)
-        r = ModuleRunner(dataclasses.replace(c, x_true=ref[0] + 1j * ref[1], theta=theta, x_in=x_in))
+        case = dataclasses.replace(c, x_true=ref[0] + 1j * ref[1], theta=theta, x_in=x_in)
+        r = ModlRunner(case, 64.0, 2) if modl else ModuleRunner(case)
         gb.gleam_profile_begin()
         r.step()
         ran = wide_convolutions(gb.gleam_profile_end())
-        assert {v for name, v in ran.items() if "wgrad" in name} == {4.0}, ran
+        assert {v for name, v in ran.items() if "wgrad" in name} == {6.0 if k == KT else 4.0}, ran
         return r.grad.cpu().numpy()[part].astype(np.float64)
 
-    print("case range", k, flush=True)
+    print("case range", k, modl, flush=True)
     base = weight_gradient(0)
     assert np.all(np.isfinite(base)) and rel_l2(base, np.zeros_like(base) + base.mean()) > 0.1
     for a in (-60, -94, -104, -112):
         err = rel_l2(weight_gradient(a) * 2.0 ** -a, base)
         print("smallest output gradient 2 ^", a, "apart", err, flush=True)
-        assert err <= (0 if a >= -94 else 64 * 2.0 ** (-126 - a))
+        assert err <= (0 if a >= -94 else (128 if modl else 64) * 2.0 ** (-126 - a))
     x_in = c.x_in.copy()
     x_in[..., 5, 7] = np.inf
     assert not np.isfinite(weight_gradient(0, x_in)).all()
