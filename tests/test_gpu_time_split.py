@@ -8,7 +8,7 @@ from paper_2207_08393_amd import binding as gb
 from paper_2207_08393_amd import synth
 from paper_2207_08393_amd.runner import ModuleRunner
 from tests.gpu_util import rel_l2, theta_slices
-from tests.test_gpu_parity import KS, KT, check_module
+from tests.test_gpu_parity import KS, KT, TOL, check_module
 from tests.test_gpu_split import linear_prox
 from tests.test_split_arithmetic import BOUND
 
@@ -39,7 +39,9 @@ def test_time_layers_on_split_operands_match_oracle(name, geom, prox):
     gb.gleam_profile_begin()
     r.step()
     ran = {n: round(m / f, 3) for n, f, _, _, m in gb.gleam_profile_end() if n.endswith("_t3") and "_2to" not in n and "to2_" not in n}
-    assert ran and {v for n, v in ran.items() if "132" not in n} <= {6.0}, ran
+    # more than 128 input channels: the forward launch by the kernels on the float32 matrix cores
+    assert ran and ran == {n: 1.0 if n.startswith("conv_fwd_132to") else 6.0 for n in ran}, ran
+    assert name != "wider_than_the_kernel" or set(ran) == {"conv_fwd_132to36_t3", "conv_dgrad_36to132_t3", "conv_wgrad_132to36_t3"}
     check_module(c)
 
 
@@ -64,7 +66,7 @@ def test_time_layers_keep_the_precision_of_float32(chans):
 @pytest.mark.parametrize("nf", [36, 64])
 def test_an_overflow_stays_visible_through_time_layers(nf):
     """A spot of 1e30 and weights of 1e10: pixels whose exact value is beyond float32 leave as infinity or NaN through the ReLUs."""
-    geom = synth.Geom(2, 1, 2, 6, 1, 8, 16)
+    geom = synth.Geom(2, 1, 2, 10, 1, 8, 16)
     for prox in (synth.chain_prox([2, nf, nf, 2], [KS, KT, KS]), synth.resblock_prox(nf, 1, KT)):
         c = synth.make_custom(82, geom, prox, accel=2.0, centre=2, bias_std=0.1, alpha=0.0)
         c.theta = np.abs(c.theta)
@@ -74,10 +76,10 @@ def test_an_overflow_stays_visible_through_time_layers(nf):
         c.x_in[:, 2, :, 4:6, 5:8] = 1e30
         z = og.prox_fwd(prox.layers, c.theta.astype(np.float64), c.x_in.astype(np.complex128))[0][-1]
         over = (np.abs(z) > np.finfo(np.float32).max).any(-1)
-        assert over.any() and not over.all()
+        assert over.any() and not over[:, 7:].any()   # four temporal layers carry the spot of frame 2 to frame 6
         print("case time overflow", nf, flush=True)
         r = ModuleRunner(c)
         r.fwd()
         x_out, loss, _ = r.results()
         assert not np.isfinite(x_out[over]).any() and not np.isfinite(loss)
-        assert rel_l2(x_out[:, 5], og.channels_to_complex(z)[:, 5]) <= 1e-4 or over[:, 5].any()
+        assert rel_l2(x_out[:, 7:], og.channels_to_complex(z)[:, 7:]) <= TOL
