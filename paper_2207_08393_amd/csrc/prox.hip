@@ -1844,7 +1844,10 @@ __global__ __launch_bounds__(256) void real_dot_kernel(const float2* __restrict_
 // ------------------------------------------------------------------ host side
 static inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr int kLossBlocks = kLossPartials;
-constexpr long long kLossOneGroup = 16384;   // pixels up to which one workgroup makes the loss
+// Pixels up to which one workgroup makes the loss (forward pass of a small module, us, in two launches / in one, squares: 400 pixels
+// 38.4 / 35.8, 4096 37.2 / 35.8, 8192 37.5 / 37.0, 10240 38.0 / 38.6, 16384 38.3 / 40.8; moduli: 36.8 / 33.9, 37.4 / 36.2, 38.1 / 37.9,
+// 38.3 / 39.5, 38.2 / 42.0).
+constexpr long long kLossOneGroup = 8192;
 // Weights of several modules at once: up to 4 MB of them, sixteen modules' forward (or eight's of both passes).  Reconstruction of
 // 8 x 160 x 128 through ten modules of 32 channels: 422 -> 386 us.  Larger networks would keep them no longer in an L2
 // and their launches do not notice.

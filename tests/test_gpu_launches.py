@@ -34,9 +34,9 @@ def test_partial_sums_of_several_layers(prox, launches):
     check_module(c)
 
 
-@pytest.mark.parametrize("W,H,loss_kind", [(64, 256, 0), (64, 256, 1), (64, 257, 0), (20, 20, 1), (64, 33, 0)])
+@pytest.mark.parametrize("W,H,loss_kind", [(64, 256, 0), (64, 256, 1), (64, 257, 0), (20, 20, 1), (64, 33, 0), (64, 128, 0), (64, 128, 1), (64, 129, 1)])
 def test_loss_in_one_workgroup_and_in_many(W, H, loss_kind):
-    """16384 pixels are the most of one workgroup; sizes that its 1024 threads with four pixels each divide and such that they do not."""
+    """8192 pixels are the most of one workgroup; sizes that its 1024 threads with four pixels each divide and such that they do not."""
     prox = synth.chain_prox([2, 8, 2], [K2] * 2, loss_kind=loss_kind)
     c = synth.make_custom(72, synth.Geom(1, 1, 2, 1, 1, H, W), prox, accel=2.0, centre=2, bias_std=0.1, alpha=0.5)
     print("case loss", W, H, loss_kind, flush=True)
