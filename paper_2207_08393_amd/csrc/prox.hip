@@ -976,7 +976,7 @@ static hipError_t launch_conv_thin_in(const ConvArgs& a, const ConvWeights& cw, 
     char name[56];
     snprintf(name, sizeof(name), "conv_%s_%dto%d_t%d", a.flip ? "dgrad" : "fwd", a.K, a.Nn, taps_);
     KernelScope ks(name, 2.0 * (double)a.d.Q * a.K * a.Nn * taps_, (bf ? 2.0 : 4.0) * (double)a.d.Q * a.Nn + 8.0 * (double)a.d.Q, st);
-    if (conv_thin_in_mfma_applies(d, a.Nn)) {   // one MFMA of depth two per tap and 32 output channels
+    if (conv_thin_in_mfma_applies(d, a.Nn, bf, a.mask_ref || a.add)) {   // one MFMA of depth two per tap and 32 output channels
         ThinInMfmaArgs t{};
         t.in = a.in; t.out = a.out; t.bias = a.bias; t.mask_ref = a.mask_ref; t.add = a.add;
         t.w = cw.w; t.sn = cw.sn; t.st = cw.st; t.sk = cw.sk;

@@ -366,7 +366,7 @@ struct ThinInMfmaArgs {
     int Nn, flip, relu_in, relu_out, mask_acc, mask_add;
     PixDims d;
 };
-bool conv_thin_in_mfma_applies(const PixDims& d, int Nn);
+bool conv_thin_in_mfma_applies(const PixDims& d, int Nn, bool bf, bool epi);
 
 // Weight gradient of a layer with the 2-channel image on one side, 3x3 or 3x3x3 taps, on the matrix cores (prox_thin.hip)
 struct WgradThinWalkArgs {

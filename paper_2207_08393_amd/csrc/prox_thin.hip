@@ -548,12 +548,12 @@ hipError_t launch_conv_thin_out_mfma(const void* in, const float* wts, const flo
 // (bfloat16) stores after a turn through the wave's own LDS rows.  No barriers in the loop: every wave walks down
 // 32-pixel column segments on its own.  The kernel it replaces for these shapes computes on the vector ALUs,
 // 2*taps multiply-adds per output.
-
 //
-// ANY: Nn channels, a multiple of 4 up to 32 * NB * NH; those behind it are computed with channel 0's weights and not stored.  The
-// sums are the bits of conv_thin_in_kernel: they begin at the bias and take the taps in their order. 2 -> 20 channels, 3x3x3, 1507328
-// pixels: 246 us on the vector ALUs, which issued twice the instructions of the products alone; what bounds it now: a row's loads and
-// stores, one after the other in a wave (2 -> 100 channels at 4 x 320 x 256: 131 MB in 59 us, as before).
+// Nn = 32 * NB * NH channels, or, with ANY: Nn channels, a multiple of 4 up to 32 * NB * NH; those behind it are computed with channel 0's weights and not stored.  The
+// sums are the bits of conv_thin_in_kernel: they begin at the bias and take the taps in their order.  2 -> 20 channels, 3x3x3, 1507328
+// pixels: 130 us on the vector ALUs, which issue twice the instructions of the products alone, 66 - 74 us here, as a masked data gradient
+// 135 and 76 - 83; 2 -> 100 channels at 4 x 320 x 256: 52 and 39 us.  What bounds it now: a row's loads and stores, one after the other in
+// a wave.
 template <int KD, int NB, int NH, bool BF, bool EPI, bool ANY>   // EPI: the call has a ReLU mask source or an add operand
 __global__ __launch_bounds__(256) void conv_thin_in_mfma_kernel(ThinInMfmaArgs a, int runs, int run_len) {
     // NH passes of NB blocks of 32 output channels each: Nn = 32 * NB * NH
@@ -847,7 +847,8 @@ static void launch_thin_in_mfma_n(const ThinInMfmaArgs& a, hipStream_t st) {
     else launch_thin_in_mfma_any<KD, 4, BF>(a, st);
 }
 
-bool conv_thin_in_mfma_applies(const PixDims& d, int Nn) {
+// epi: the call has a ReLU mask source or an add operand
+bool conv_thin_in_mfma_applies(const PixDims& d, int Nn, bool bf, bool epi) {
     const bool on = !(kernel_policy() & GLEAM_POLICY_NO_THIN_MFMA);   // else the vector-ALU kernel
     if (!on || !(d.kt == 1 && (d.kd == 3 || d.kd == 1) && d.kh == 3 && d.kw == 3)) return false;
     // byte offsets into the input and the output are 32 bits in the kernel
@@ -857,11 +858,20 @@ bool conv_thin_in_mfma_applies(const PixDims& d, int Nn) {
     // here: 480 pixels 92.4 / 92.8, 110.7 / 112.0, 104.7 / 106.7, 132.9 / 137.7; 4096 93.9 / 93.8, 118.4 / 119.6, 112.8 / 114.9,
     // 163.0 / 161.8; 20480 110.6 / 107.9, 169.4 / 164.9, 167.3 / 161.7, 255.6 / 237.7; 122880 155.9 / 152.0, 338.7 / 334.7,
     // 362.4 / 356.0, 716.6 / 697.3).
-    return d.Q >= 8192 && Nn % 4 == 0 && Nn >= 8 && Nn <= 128;
+    if (Nn % 4 != 0 || Nn < 8 || Nn > 128 || d.Q < 8192) return false;
+    // With 27 taps a row of a mask and an addition, or a third block of channels, takes longer still (us, vector / here: data gradient of
+    // 36, 60 and 100 channels at 16384 pixels 10.0 / 11.2, 9.6 / 11.2, 11.8 / 15.6, at 23552 13.0 / 11.4, 13.4 / 11.4, 18.2 / 16.1;
+    // forward of 36, 68 and 100 at 9216 12.9 / 11.8, 13.5 / 14.7, 15.4 / 18.0, at 23552 17.6 / 12.6, 20.3 / 15.0, 22.2 / 18.3).
+    if (d.kd == 3 && (epi || Nn > 64) && d.Q < 20480) return false;
+    // Float32 rows that begin in the middle of 32 bytes, with a mask: from 48 MB on the vector kernel writes them faster where they
+    // end in a second or a fourth block (60 channels 14.2 / 12.0 at 61440 pixels, 23.0 / 23.6 at 163840, 39.8 / 46.8 at 327680; 100
+    // 23.4 / 18.4, 36.7 / 43.7, 82.7 / 88.4; but 44 13.5 / 10.9, 21.9 / 18.3, 37.5 / 36.4, 84
+    // 23.2 / 15.8, 36.6 / 34.7, 72.7 / 71.2, and 112 23.7 / 16.5, 38.1 / 38.0, 80.8 / 77.5).
+    return !(epi && !bf && d.kd == 1 && Nn % 8 == 4 && ((Nn > 48 && Nn < 64) || Nn > 96) && d.Q * Nn >= 12000000);
 }
 
 hipError_t launch_conv_thin_in_mfma(const ThinInMfmaArgs& a, bool bf, hipStream_t st) {
-    if (!conv_thin_in_mfma_applies(a.d, a.Nn)) return hipErrorInvalidValue;
+    if (!conv_thin_in_mfma_applies(a.d, a.Nn, bf, a.mask_ref || a.add)) return hipErrorInvalidValue;
     if (a.d.kd == 3) {
         if (bf) launch_thin_in_mfma_n<3, true>(a, st);
         else launch_thin_in_mfma_n<3, false>(a, st);
