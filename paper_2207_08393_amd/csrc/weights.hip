@@ -3,8 +3,9 @@
 // What bounds it: the launch.  A dependent launch takes 4.2 - 4.8 us here whatever it does, and the largest of these jobs
 // (128 x 128 channels, 3x3) moves 1 MB.  With a launch of its own per layer the eight that a training step of the 128-channel
 // bfloat16 chain or of a 100-channel residual network makes were 38 us; the two that are left, one before the forward and one
-// before the data-gradient launches, are 10.  Calls of several modules make those of up to sixteen modules at once.  A thread makes one element of an image or what one (output, input) channel pair
-// becomes; reads of neighbouring threads are neighbouring where the form allows it, and all of it stays in L2.
+// before the data-gradient launches, are 10.  Calls of several modules make those of up to sixteen modules at once.  A thread makes
+// one element of an image or what one (output, input) channel pair becomes; reads of neighbouring threads are neighbouring where the
+// form allows it, and all of it stays in L2.
 #include "prox_common.h"
 
 namespace gleam {

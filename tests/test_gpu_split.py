@@ -280,7 +280,7 @@ def test_blocks_of_four_and_eight_rows_3d(D):
                                    centre=2, bias_std=0.1, alpha=0.8))
 
 
-# blocks of eight rows whose input lies inside the image, between such that reach over its border: offsets from a table; several blocks
+# blocks of eight rows whose input lies inside the image, between such that reach over its border; several blocks
 # per workgroup, of several images; sign words between two launches, a mask with a tensor to add, a ReLU on the input
 @pytest.mark.parametrize("geom,prox", [(synth.Geom(1, 1, 2, 1, 4, 180, 96), synth.chain_prox([2, 20, 32, 64, 2], [K2] * 4)),
                                        (synth.Geom(2, 2, 2, 1, 2, 192, 160), synth.resblock_prox(36, 1)),
